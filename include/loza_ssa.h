@@ -70,7 +70,9 @@ typedef enum {
  * bf16, rounded once (relative error 2^-9 each) or, where that is not good enough, as two bf16
  * terms (2^-17): for tiles that start within the first 128 positions, for patterns that leave every
  * row fewer than 128 live keys, and for every tile in which the one-term pass produced a result of
- * magnitude >= 1.97 (the tile is then computed again inside the same launch). Error of a result:
+ * magnitude >= 1.97 (the tile is then computed again inside the same launch). Calls of few query rows
+ * (at most 512 groups of 16 rows per key head, over all key heads and sequences) take two terms
+ * throughout. Error of a result:
  *     |out - exact| <= half an ulp of bf16 at |out|  +  w * D  +  about 1e-6 * |out|,
  * D = the softmax-weighted mean of |v_j - out| over the live keys (never more than their largest
  * distance from out), w = 2^-9 for one-term rows and 2^-17 for two-term rows. One-term rows have
@@ -109,9 +111,10 @@ int loza_ssa_prefill_f32(const float *q, const float *k, const float *v, float *
  * Supported (d_qk, d_v) and scale: as loza_ssa_prefill. Cache rows at or beyond seqlens[b] are
  * never read. The split count depends on the sizes only (and on LOZA_DECODE_SPLITS, see above), and
  * the merge adds the splits in a fixed order: the result is deterministic.
- * Numerics: as loza_ssa_prefill with one-term weights, except that a query with fewer than 128
- * live keys, and a query whose merged result reaches magnitude 1.97 in some column, is computed
- * from the cache rows directly in fp32 (weights not rounded at all; a rare, slower path: one
+ * Numerics: as loza_ssa_prefill with two-term weights; calls with many sequences and long windows on
+ * key heads of more than 32 query heads take one-term weights, except that a query with fewer than
+ * 128 live keys, and a query whose merged result reaches magnitude 1.97 in some column, is then
+ * computed from the cache rows directly in fp32 (weights not rounded at all; a rare, slower path: one
  * workgroup walks all live keys of that query).
  */
 int loza_ssa_decode(const void *q, const void *kcache, const void *vcache, const int32_t *seqlens,
@@ -142,7 +145,8 @@ int loza_ssa_decode_static(const void *q, const void *kcache, const void *vcache
 size_t loza_ssa_decode_workspace_bytes(int B, int Hq, int Hkv, int64_t S_max, int d_v,
                                        int64_t n_sink, int64_t window);
 
-/* Host-only (ours). Number of key splits loza_ssa_decode uses for these sizes (0 on invalid sizes). */
+/* Host-only (ours). Number of key splits the workspace of loza_ssa_decode is sized for at these sizes; the
+ * call uses as many or fewer (0 on invalid sizes). */
 int loza_ssa_decode_num_splits(int B, int Hq, int Hkv, int64_t S_max, int64_t n_sink, int64_t window);
 
 /*
@@ -199,8 +203,7 @@ int loza_ssa_decode_blocks(const void *q, const void *kcache, const void *vcache
  *           S_max is cut to it. Queries whose position would be negative (seqlens[b] < q_len)
  *           give out = 0, lse = -inf.
  *   out     [B, q_len, Hq, d_v] bf16       lse [B, Hq, q_len] fp32
- * 1 <= q_len <= S_max (else LOZA_ERR_SHAPE). No workspace: the prefill kernel runs over the q_len
- * positions (no split over keys), so it suits q_len * Hq / Hkv of a few hundred rows and more.
+ * 1 <= q_len <= S_max (else LOZA_ERR_SHAPE). No workspace (no split of a query's keys over workgroups).
  * Supported shapes, numerics, errors: as loza_ssa_prefill / loza_ssa_prefill_blocks.
  */
 int loza_ssa_extend(const void *q, const void *kcache, const void *vcache, const int32_t *seqlens, void *out, float *lse,

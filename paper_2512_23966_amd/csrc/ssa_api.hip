@@ -55,6 +55,15 @@ int check_common(int B, int Hq, int Hkv, int64_t S, int d_qk, int d_v, int64_t n
     return LOZA_OK;
 }
 
+// LOZA_DECODE_SPLITS (documented in the header): another split count, for tests and experiments; 0: none given
+int forced_splits()
+{
+    const char *env = getenv("LOZA_DECODE_SPLITS");
+    const long v = env ? strtol(env, nullptr, 10) : 0;
+    return v >= 1 && v <= kMaxSplits ? (int)v : 0;
+}
+
+// The split count a workspace is sized for. A call uses as many or fewer (decode_plan).
 int decode_splits(int B, int Hq, int Hkv, int64_t S_max, int64_t n_sink, int64_t window)
 {
     const int G = Hq / Hkv;
@@ -65,15 +74,43 @@ int decode_splits(int B, int Hq, int Hkv, int64_t S_max, int64_t n_sink, int64_t
     if (live > S_max) live = S_max;
     const int64_t tiles = (live + 63) / 64 + 2;
     int64_t n = (kComputeUnits + base - 1) / base;  // one workgroup per compute unit at least
-    // LOZA_DECODE_SPLITS (documented in the header): another split count, for tests and experiments
-    if (const char *env = getenv("LOZA_DECODE_SPLITS")) {
-        const long v = strtol(env, nullptr, 10);
-        if (v >= 1 && v <= kMaxSplits) n = v;
-    }
+    if (const int v = forced_splits()) n = v;
     if (n > tiles) n = tiles;
     if (n > kMaxSplits) n = kMaxSplits;
     if (n < 1) n = 1;
     return (int)n;
+}
+
+// Which of the two decode kernels takes a call, and in how many splits (at most `most`, which the
+// workspace is sized for). Both counts give every compute unit one workgroup and no compute unit two (a
+// workgroup fills the LDS: 43 sequences in 6 splits are 258 workgroups, two rounds, 60 us against 33 in 5).
+// Up to two groups of 16 query heads per key head the row kernel is always the faster (d = 128, 8 query
+// heads per group of 4, 16 sequences, window 4096: 56 against 74 us; 128 sequences on one key head of 32: 108
+// against 128). With more groups (absorbed MLA: four) it reads the keys once per group, from L2, where the
+// tile kernel reads them once but leaves fp32 partial results of every split; it wins until the live keys
+// per split outweigh that. The line is a time model of either, in tenths of a microsecond, fitted to the
+// measured times of both (MLA, row against tile kernel: window 8192, 8 sequences 36 against 50 us, 16: 59
+// against 56, 64: 190 against 130; the paper's 1,024 keys, 64 sequences: 32 against 44).
+struct DecodePlan {
+    bool rows;
+    int n_splits;
+};
+
+DecodePlan decode_plan(int B, int Hkv, int G, int64_t live, int d_qk, int most)
+{
+    const int64_t groups = (G + 15) / 16, rows_base = (int64_t)B * Hkv * groups;
+    const int64_t tile_base = (int64_t)B * Hkv * ((G + loza::decode_rows_per_tile() - 1) / loza::decode_rows_per_tile());
+    auto cut = [&](int64_t base) { const int64_t n = kComputeUnits / base; return (int)(n < 1 ? 1 : n < most ? n : most); };
+    int n_rows = cut(rows_base), n_tile = cut(tile_base);
+    if (forced_splits()) n_rows = n_tile = most;
+    if (groups <= 2) return {true, n_rows};
+    const bool wide = d_qk > 128;
+    const int64_t keys = (live + 63) / 64 * 64;
+    auto rounds = [&](int64_t wgs) { return (wgs + kComputeUnits - 1) / kComputeUnits; };
+    const int64_t rows_tiles = (keys / 64 + n_rows) / n_rows, tile_tiles = (keys / 32 + n_tile) / n_tile;
+    const int64_t t_rows = rounds(rows_base * n_rows) * (rows_tiles * (wide ? 13 : 7) + (wide ? 80 : 60)) + (n_rows > 1 ? 50 : 0);
+    const int64_t t_tile = rounds(tile_base * n_tile) * (tile_tiles * (wide ? 13 : 8) + (wide ? 250 : 180)) + 80;
+    return {t_rows <= t_tile, t_rows <= t_tile ? n_rows : n_tile};
 }
 
 // The pattern as the kernels take it: sink in tokens, window in blocks of `block` tokens, both cut
@@ -248,14 +285,17 @@ static int prefill_bf16(const void *q, const void *k, const void *v, void *out, 
     p.scale_log2 = scale * 1.44269504088896340736f;
     p.row_tiles = (int)row_tiles; p.n_splits = 1;
     set_rescale_policy(p);
+    const bool few_rows = loza::few_rows_bf16(B, Hkv, (extend ? q_len : S) * G);
     if (extend) {
         p.seqlens = seqlens; p.q_len = (int)q_len;
         if (paging) {
             p.block_table = paging->block_table;
             p.page_shift = page_shift; p.max_pages = paging->max_pages; p.num_pages = (int)paging->num_pages;
         }
+        if (few_rows) return loza::launch_rows_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
         return loza::launch_extend_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
     }
+    if (few_rows) return loza::launch_rows_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
     return loza::launch_prefill_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
 }
 
@@ -652,9 +692,12 @@ static int decode_bf16(const void *q, const void *kcache, const void *vcache, co
         return LOZA_ERR_ALIGN;
     const int G = Hq / Hkv;
     const int rows = loza::decode_rows_per_tile();
-    const int n_splits = decode_splits(B, Hq, Hkv, S_max, n_sink, window);
+    int64_t live = (n_sink < S_max ? n_sink : S_max) + (window < S_max ? window : S_max);
+    if (live > S_max) live = S_max;
+    const DecodePlan plan = decode_plan(B, Hkv, G, live, d_qk, decode_splits(B, Hq, Hkv, S_max, n_sink, window));
+    const int n_splits = plan.n_splits;
     const int64_t row_tiles = (G + rows - 1) / rows;
-    if (row_tiles * Hkv * B * n_splits > 2147483647LL) return LOZA_ERR_SHAPE;
+    if (row_tiles * Hkv * B * decode_splits(B, Hq, Hkv, S_max, n_sink, window) > 2147483647LL) return LOZA_ERR_SHAPE;
 
     loza::FwdParams p{};
     p.q = (const uint16_t *)q; p.k = (const uint16_t *)kcache; p.v = (const uint16_t *)vcache;
@@ -672,6 +715,10 @@ static int decode_bf16(const void *q, const void *kcache, const void *vcache, co
     p.scale_log2 = scale * 1.44269504088896340736f;
     p.row_tiles = (int)row_tiles; p.n_splits = n_splits;
     set_rescale_policy(p);
+    if (plan.rows) {
+        p.q_len = 1;
+        return loza::launch_rows_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
+    }
     return loza::launch_decode_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
 }
 

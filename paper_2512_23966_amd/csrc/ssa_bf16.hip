@@ -1114,20 +1114,6 @@ static bool pattern_needs_precise(const FwdParams &p)
     return live_at(kPrecisePositions - 1) < kPrecisePositions || (i0 < p.S && live_at(i0) < kPrecisePositions);
 }
 
-// The tile kernels use more dynamic LDS than the default limit: raised once per kernel and device.
-template <auto KERN>
-static hipError_t allow_lds(int bytes)
-{
-    static bool done[64] = {};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev >= 0 && dev < 64 && done[dev]) return hipSuccess;
-    e = hipFuncSetAttribute((const void *)KERN, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess && dev >= 0 && dev < 64) done[dev] = true;
-    return e;
-}
-
 template <int DQK, int DV, bool ALIAS, bool OUTF32, bool EXT>
 static hipError_t launch_prefill_kernel(FwdParams p, hipStream_t stream)
 {

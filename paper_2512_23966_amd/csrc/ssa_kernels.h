@@ -38,12 +38,34 @@ struct FwdParams {
     float lazy_log2;   // afterwards it moves only when exceeded by this much (log2 units)
 };
 
+// The tile kernels use more dynamic LDS than the default limit: raised once per kernel and device.
+template <auto KERN>
+static hipError_t allow_lds(int bytes)
+{
+    static bool done[64] = {};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev >= 0 && dev < 64 && done[dev]) return hipSuccess;
+    e = hipFuncSetAttribute((const void *)KERN, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess && dev >= 0 && dev < 64) done[dev] = true;
+    return e;
+}
+
 bool bf16_shape_supported(int d_qk, int d_v, bool alias);
 int prefill_rows_per_tile();
 int decode_rows_per_tile();
 hipError_t launch_prefill_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
 hipError_t launch_extend_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
 hipError_t launch_decode_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
+// Few query rows (ssa_rows.hip): prefill (seqlens null), extend or decode (q_len = 1; n_splits key splits
+// and a merge).
+hipError_t launch_rows_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
+// A prefill or extend of `rows` query rows per (batch, key head) is few rows when its groups of 16 rows make
+// at most two rounds of the 256 compute units. A round of the row kernel and one of the tile kernel (128 rows
+// a workgroup) cost, at window 8192 of the wide shape, 165 and 405 us (d = 128, window 4096: 51 and 152):
+// 512 groups 331 against 407 us (102 against 153), 1024 groups 638 against 412 (200 against 155).
+inline bool few_rows_bf16(int B, int Hkv, int64_t rows) { return (rows + 15) / 16 * Hkv * B <= 512; }
 hipError_t launch_blend_bf16(const float *o_full, const float *o_sparse, float alpha, uint16_t *out,
                              uint16_t *out_full, uint16_t *out_sparse, int64_t n, hipStream_t stream);
 // d(alpha) of the blend: sum of dout * (O - O') over n bf16 elements (n a multiple of 8); `partial`

@@ -1,0 +1,75 @@
+"""The few-rows kernel (decode, short extends and prompts) where it can go wrong: lengths around its 16-key
+tiles, sink and window edges inside a tile, fewer tiles than waves, groups of 16 rows that straddle positions
+or are partly empty, row counts on both sides of the line to the tile kernel, one split and many."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_23966_amd as loza
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _rand(shape, seed, device):
+    g = torch.Generator(device=device).manual_seed(seed)
+    return torch.randn(shape, generator=g, device=device, dtype=torch.float32).to(torch.bfloat16)
+
+
+LENS = [1, 15, 16, 17, 31, 33, 64, 65, 0, 127, 128, 129, 300, 511]
+
+
+@pytest.mark.parametrize("splits", [None, "1", "7"])
+@pytest.mark.parametrize("Hq,Hkv,d_qk,d_v,alias", [(64, 1, 576, 512, True), (20, 1, 576, 512, True), (8, 2, 128, 128, False),
+                                                   (64, 1, 128, 128, True), (6, 6, 128, 128, False)])
+@pytest.mark.parametrize("ns,win,block", [(5, 40, None), (128, 300, None), (0, 1, None), (1, 2, 48), (16, None, None)])
+def test_decode_lengths_around_the_tile(gpu_device, monkeypatch, splits, Hq, Hkv, d_qk, d_v, alias, ns, win, block):
+    if splits:
+        monkeypatch.setenv("LOZA_DECODE_SPLITS", splits)
+    B, S_max, scale = len(LENS), 511, d_qk ** -0.5
+    q, kc = _rand((B, Hq, d_qk), 1, gpu_device), _rand((B, S_max, Hkv, d_qk), 2, gpu_device)
+    vc = kc if alias else _rand((B, S_max, Hkv, d_v), 3, gpu_device)
+    for b, L in enumerate(LENS):
+        kc[b, L:] = float("nan")   # rows at or beyond the length must never be read
+        vc[b, L:] = float("nan")
+    lens = torch.tensor(LENS, dtype=torch.int32, device=gpu_device)
+    out, lse = H.run_decode(q, kc, vc, lens, ns, win, scale, d_v=d_v, block=block)
+    z = LENS.index(0)
+    assert bool((out[z] == 0).all()) and bool(torch.isneginf(lse[z]).all())
+    live = [b for b in range(B) if LENS[b]]
+    rb, rh = np.repeat(np.asarray(live, dtype=np.int64), Hq), np.tile(np.arange(Hq, dtype=np.int64), len(live))
+    H.compare_decode(q, kc, vc, lens, out, lse, rb, rh, ns, win, scale, f"rows decode {Hq}/{Hkv} d{d_qk} {ns},{win},{block}", block)
+
+
+# groups of 16 rows: 512 take the row kernel, 513 and more the tile kernel
+@pytest.mark.parametrize("B,q_len,Hq,Hkv,d,alias", [(1, 128, 64, 1, 576, True), (1, 129, 64, 1, 576, True), (3, 7, 12, 1, 576, True),
+                                                    (2, 5, 3, 1, 128, False), (1, 64, 32, 8, 128, False)])
+def test_extend_row_groups(gpu_device, B, q_len, Hq, Hkv, d, alias):
+    S_max, ns, win, scale = 400, 20, 90, d ** -0.5
+    d_v = 512 if d == 576 else 128
+    lens_h = [S_max - 37 * b for b in range(B)]
+    lens_h[-1] = max(1, min(lens_h[-1], q_len - 1))   # some queries of the last sequence lie before its start
+    q, kc = _rand((B, q_len, Hq, d), 4, gpu_device), _rand((B, S_max, Hkv, d), 5, gpu_device)
+    vc = kc if alias else _rand((B, S_max, Hkv, d_v), 6, gpu_device)
+    lens = torch.tensor(lens_h, dtype=torch.int32, device=gpu_device)
+    out = torch.full((B, q_len, Hq, d_v), float("nan"), dtype=torch.bfloat16, device=gpu_device)
+    lse = torch.full((B, Hq, q_len), float("nan"), dtype=torch.float32, device=gpu_device)
+    loza.loza_ssa_extend(q, kc, vc, lens, out, lse, ns, win, scale)
+    torch.cuda.synchronize()
+    for b, L in enumerate(lens_h):
+        for r in range(q_len):
+            i = L - q_len + r
+            if i < 0:
+                assert bool((out[b, r] == 0).all()) and bool(torch.isneginf(lse[b, :, r]).all())
+        first = max(0, q_len - L)
+        rows = np.asarray([(h, r) for h in range(Hq) for r in range(first, q_len)], dtype=np.int64)
+        rh, rr = rows[:, 0].copy(), rows[:, 1].copy()
+        zero = np.zeros_like(rh)
+        qf = torch.zeros(1, L, Hq, d, dtype=torch.bfloat16, device=gpu_device)
+        of = torch.zeros(1, L, Hq, d_v, dtype=torch.bfloat16, device=gpu_device)
+        lf = torch.zeros(1, Hq, L, dtype=torch.float32, device=gpu_device)
+        n = q_len - first
+        qf[0, L - n:], of[0, L - n:], lf[0, :, L - n:] = q[b, first:], out[b, first:], lse[b, :, first:]
+        kb = kc[b:b + 1, :L].contiguous()
+        vb = kb if alias else vc[b:b + 1, :L].contiguous()
+        H.compare_prefill(qf, kb, vb, of, lf, zero, rh, rr + L - q_len, ns, win, scale, f"rows extend q{q_len} {Hq}/{Hkv} d{d} L{L}")
