@@ -89,7 +89,7 @@ int loza_ssa_prefill(const void *q, const void *k, const void *v, void *out, flo
 /*
  * fp32 twin of loza_ssa_prefill (fp32 in, fp32 arithmetic, fp32 out), same layouts with float
  * elements. Any d_qk, d_v in [1, 256]; v may alias k with d_v <= d_qk; scale finite, any sign.
- * Plain vector arithmetic (no matrix cores): the small-shape check of the method, not a fast path.
+ * The small-shape check of the method (fp32 matrix instructions, a few rows per workgroup), not a fast path.
  */
 int loza_ssa_prefill_f32(const float *q, const float *k, const float *v, float *out, float *lse,
                          int B, int Hq, int Hkv, int64_t S, int d_qk, int d_v,
@@ -337,7 +337,7 @@ int loza_ssa_backward_blocks(const void *q, const void *k, const void *v, const 
  * sits at position seqlens[b] - 1 of its cache; Architecture section, Eq. 2 / Eq. 4): fp32 in, fp32
  * arithmetic, fp32 out, the layouts of the bf16 calls with float elements. Any d_qk, d_v in [1, 256];
  * vcache may alias kcache with d_v <= d_qk; a length beyond S_max is cut to it; an empty cache gives
- * out = 0 and lse = -inf. No workspace (one wavefront per query walks all of its live keys).
+ * out = 0 and lse = -inf. No workspace (one workgroup per 16 query heads walks all of their live keys).
  */
 int loza_ssa_decode_f32(const float *q, const float *kcache, const float *vcache, const int32_t *seqlens, float *out, float *lse,
                         int B, int Hq, int Hkv, int64_t S_max, int d_qk, int d_v,

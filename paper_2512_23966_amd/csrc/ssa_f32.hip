@@ -1,10 +1,8 @@
-// fp32 streaming sparse attention prefill for gfx950: fp32 in, fp32 arithmetic, fp32 out.
+// fp32 streaming sparse attention for gfx950: fp32 in, fp32 arithmetic, fp32 out.
 //
 // O* = softmax(scale * Q K*^T) V* over live(i) = { j <= i : j < n_sink or i - j < window }
 // (paper: Architecture section, Eq. 2 / Eq. 4).  This is the small, exact-arithmetic twin of the
-// bf16 MFMA kernels: one wavefront owns one query row, walks that row's live keys (sink range,
-// then window range, enumerated in closed form) in chunks of 64, one key per lane for the scores
-// and one output column per lane for the weighted sum, with an online softmax across chunks.
+// bf16 kernels, forward (prefill and decode) and backward.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -16,104 +14,235 @@ namespace loza {
 constexpr int F32_MAX_D = 256;
 constexpr int F32_WAVES = 4;
 
-__global__ __launch_bounds__(64 * F32_WAVES) void ssa_prefill_f32_kernel(const F32Params p)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Forward. A workgroup owns 16 query rows (position, head) of one key/value head; its NW waves share the
+// keys in tiles of 16 (tile number mod NW), each with its own softmax state and accumulators, and the
+// partial results meet in LDS once. Both products run on the fp32 matrix instruction (16x16x4, full fp32):
+// S^T[16 keys][16 rows] = K Q^T leaves lane (j, n) with row n's scores of keys 4j .. 4j + 3, and step i of
+// O^T += V^T P^T contracts keys 4j + i over j, so the probabilities are used where they are. The order of a
+// contraction and of the output columns is free, so every global load is 16 bytes a lane: feature
+// 16 kk + 4 j + e takes part in step e, column 64 d + 4 m + e is row m of block e.
+// What bounds it at these sizes is latency (1024 rows of 320 keys of width 64 are 64 workgroups of three
+// tiles a wave): one wave per row, one key per lane with strided 4-byte loads and a serial sum over the keys
+// took 80 us, this 9.
+// The online softmax takes each row's own running maximum in every tile, and a tile without a live key of a
+// row leaves that row's state exactly as it was: a row's result does not depend on the rows it shares a
+// workgroup with, and a decode gives the bits of the prefill's last row.
+// ND: blocks of 64 features and columns (the widths are cut to d_qk and d_v inside). VEC: widths that are
+// multiples of 4 (rows 16-byte aligned); otherwise the 16-byte loads are four guarded scalar ones.
+template <int ND>
+struct F32RowsCfg {
+    static constexpr int NW = ND <= 2 ? 8 : 4;         // (wider rows need the registers)
+    static constexpr int OROW = ND * 64 + 4;           // floats per row of a wave's partial output
+    static constexpr int LDS_BYTES = (NW * 16 * OROW + NW * 16 * 2) * 4;
+    static_assert(LDS_BYTES <= 160 * 1024, "does not fit the 160 KB LDS");
+};
+
+template <int ND, bool VEC>
+__global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(const F32Params p, const int row_tiles)
 {
-    __shared__ float s_q[F32_WAVES][F32_MAX_D];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    using C = F32RowsCfg<ND>;
+    constexpr int NW = C::NW, N = 16, OROW = C::OROW;
+    extern __shared__ __attribute__((aligned(16))) float smem_f[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, n16 = lane & 15, j4 = lane >> 4;
+    int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (id >= (int64_t)row_tiles * p.Hkv * p.B) return;
+    const int rt = (int)(id % row_tiles);
+    id /= row_tiles;
+    const int g = (int)(id % p.Hkv), b = (int)(id / p.Hkv), G = p.Hq / p.Hkv;
     const bool decode = p.seqlens != nullptr;
-    const int64_t n_rows = decode ? (int64_t)p.B * p.Hq : (int64_t)p.B * p.S * p.Hq;
-    const int64_t r = (int64_t)blockIdx.x * F32_WAVES + wave;
-    if (r >= n_rows) return;  // whole wavefront leaves together; no block-wide barrier is used
-    const int h = (int)(r % p.Hq);
-    const int64_t bi = r / p.Hq;
-    int i;
-    int64_t b;
-    if (decode) {
-        b = bi;
-        const int64_t L = (int64_t)p.seqlens[b] < p.S ? (int64_t)p.seqlens[b] : p.S;  // a length beyond the cache is cut to it
-        if (L <= 0) {  // empty cache: out = 0, lse = -inf
-            for (int c = lane; c < p.d_v; c += 64) p.out[r * p.d_v + c] = 0.f;
-            if (lane == 0) p.lse[r] = -INFINITY;
-            return;
+    // valid keys (a length beyond the cache is cut to it); queries are its last (decode) or all positions
+    const int64_t L = decode ? ((int64_t)p.seqlens[b] < p.S ? (int64_t)p.seqlens[b] : p.S) : p.S;
+    const int64_t Sq = decode ? 1 : p.S, pos0 = L - Sq, R = Sq * G, r0 = (int64_t)rt * 16;
+    const int n_sink = p.n_sink, block = p.block;
+    auto window_begin = [&](int i) {
+        const int qblk = i / block;
+        return p.window > qblk ? 0 : (qblk - p.window + 1) * block;
+    };
+    const int i_min = (int)(pos0 + r0 / G), i_max = (int)(pos0 + ((r0 + 15 < R ? r0 + 15 : R - 1) / G));
+
+    auto load4 = [&](const float *row, int c, int d) -> f32x4 {
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (VEC) {
+            if (c < d) x = *(const f32x4 *)(row + c);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (c + e < d) x[e] = row[c + e];
         }
-        i = (int)(L - 1);
-    } else {
-        i = (int)(bi % p.S);
-        b = bi / p.S;
-    }
-    const int g = h / (p.Hq / p.Hkv);
+        return x;
+    };
 
-    const float *q = p.q + r * p.d_qk;
-    for (int c = lane; c < p.d_qk; c += 64) s_q[wave][c] = q[c];
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    // this lane's query row (its matrix-core operand), and the row's window
+    const int64_t my_row = r0 + n16, row_c = my_row < R ? my_row : R - 1, qi = row_c / G;
+    const int i_row = (int)(pos0 + qi), w_lo_row = window_begin(i_row < 0 ? 0 : i_row);
+    const int64_t q_row = ((int64_t)b * Sq + qi) * p.Hq + (int64_t)g * G + (row_c - qi * G);
+    f32x4 qf[ND * 4];
+#pragma unroll
+    for (int kk = 0; kk < ND * 4; ++kk) qf[kk] = load4(p.q + q_row * p.d_qk, kk * 16 + j4 * 4, p.d_qk);
 
-    // live keys: [0, se) then [wb, i], disjoint and ordered
-    const int se = p.n_sink < i + 1 ? p.n_sink : i + 1;
-    const int qblk = i / p.block;
-    int wb = p.window > qblk ? 0 : (qblk - p.window + 1) * p.block;
-    if (wb < se) wb = se;
-    const int n_live = se + (i - wb + 1);
-
+    // live key tiles: [0, nA) and [wt0, wt1]; this wave takes those whose number is `wave` mod NW
+    const int win_begin = window_begin(i_min < 0 ? 0 : i_min);
+    const int sink_end = n_sink < i_max + 1 ? n_sink : i_max + 1;
+    int nA = (sink_end + N - 1) / N;
+    int wt0 = win_begin / N;
+    const int wt1 = i_max < 0 ? -1 : i_max / N;                 // (an empty cache has no tile)
+    if (i_max < 0) nA = 0;
+    if (wt0 < nA) wt0 = nA;
+    auto next_tile = [&](int t) {                               // first tile of this wave at or after t
+        t += (wave - t % NW + NW) % NW;
+        if (t >= nA && t < wt0) { t = wt0; t += (wave - t % NW + NW) % NW; }
+        return t;
+    };
     const float *kb = p.k + ((int64_t)b * p.S * p.Hkv + g) * p.k_row;
     const float *vb = p.v + ((int64_t)b * p.S * p.Hkv + g) * p.v_row;
     const int64_t kstep = (int64_t)p.Hkv * p.k_row, vstep = (int64_t)p.Hkv * p.v_row;
+    // a key that no row of this group sees is never read: a live one is loaded in its place (and masked)
+    auto live_key = [&](int j) {
+        if (j >= n_sink && j < win_begin) j = win_begin;
+        return j < i_max ? j : i_max;
+    };
+    f32x4 kf[ND * 4];
+    auto load_keys = [&](int t) {
+        const float *kr = kb + (int64_t)live_key(t * N + n16) * kstep;
+#pragma unroll
+        for (int kk = 0; kk < ND * 4; ++kk) kf[kk] = load4(kr, kk * 16 + j4 * 4, p.d_qk);
+    };
 
+    f32x4 o[ND][4];
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[d][e] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;
-    float acc[F32_MAX_D / 64];
+    int t = next_tile(0);
+    if (t <= wt1) load_keys(t);
+    while (t <= wt1) {
+        f32x4 vf[4][ND];                                        // values of keys 4 j4 + i
 #pragma unroll
-    for (int c = 0; c < F32_MAX_D / 64; ++c) acc[c] = 0.f;
-
-    for (int u0 = 0; u0 < n_live; u0 += 64) {
-        const int u = u0 + lane;
-        const bool have = u < n_live;
-        const int j = have ? (u < se ? u : wb + (u - se)) : 0;
-        float s = -INFINITY;
-        if (have) {
-            const float *kr = kb + (int64_t)j * kstep;
-            float dot = 0.f;
-            for (int c = 0; c < p.d_qk; ++c) dot = fmaf(s_q[wave][c], kr[c], dot);
-            s = dot * p.scale;
+        for (int i = 0; i < 4; ++i) {
+            const float *vr = vb + (int64_t)live_key(t * N + 4 * j4 + i) * vstep;
+#pragma unroll
+            for (int d = 0; d < ND; ++d) vf[i][d] = load4(vr, d * 64 + n16 * 4, p.d_v);
         }
-        float cm = s;
-        for (int off = 32; off > 0; off >>= 1) cm = fmaxf(cm, __shfl_xor(cm, off, 64));
-        const float m_new = fmaxf(m, cm);  // finite: every chunk holds at least one live key
-        const float alpha = expf(m - m_new);
-        const float pj = have ? expf(s - m_new) : 0.f;
-        float ps = pj;
-        for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off, 64);
-        l = l * alpha + ps;
+        f32x4 s4[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s4[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < ND * 4; ++kk)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s4[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kk][e], qf[kk][e], s4[e], 0, 0, 0);
+        const int t_next = next_tile(t + 1);
+        if (t_next <= wt1) load_keys(t_next);
+        f32x4 s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+        float cm = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = t * N + 4 * j4 + i;
+            const bool ok = (j <= i_row) & ((j < n_sink) | (j >= w_lo_row));
+            s[i] = ok ? s[i] * p.scale : -INFINITY;
+            cm = fmaxf(cm, s[i]);
+        }
+        cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
+        cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
+        const float m_new = fmaxf(m, cm);
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;   // a row without a live key so far
+        const float alpha = cm > m ? expf(m - m_use) : 1.f;
         m = m_new;
+        float ps = 0.f;
 #pragma unroll
-        for (int c = 0; c < F32_MAX_D / 64; ++c) acc[c] *= alpha;
-        const int cnt = n_live - u0 < 64 ? n_live - u0 : 64;
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float w = __shfl(pj, jj, 64);
-            const int jk = __shfl(j, jj, 64);
-            const float *vr = vb + (int64_t)jk * vstep;
-#pragma unroll
-            for (int c = 0; c < F32_MAX_D / 64; ++c) {
-                const int col = c * 64 + lane;
-                if (col < p.d_v) acc[c] = fmaf(w, vr[col], acc[c]);
-            }
+        for (int i = 0; i < 4; ++i) {
+            s[i] = s[i] == -INFINITY ? 0.f : expf(s[i] - m_use);
+            ps += s[i];
         }
-    }
-    const float inv = 1.0f / l;
-    float *o = p.out + r * p.d_v;
+        l = l * alpha + ps;
 #pragma unroll
-    for (int c = 0; c < F32_MAX_D / 64; ++c) {
-        const int col = c * 64 + lane;
-        if (col < p.d_v) o[col] = acc[c] * inv;
+        for (int d = 0; d < ND; ++d)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                o[d][e] *= alpha;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[d][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][d][e], s[i], o[d][e], 0, 0, 0);
+            }
+        t = t_next;
     }
-    if (lane == 0) p.lse[decode ? r : ((int64_t)b * p.Hq + h) * p.S + i] = m + logf(l);
+
+    // ---- the waves' partial results meet in LDS ---------------------------------------------------------
+    float *ml = smem_f + NW * 16 * OROW;
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    if (j4 == 0) {
+        ml[(wave * 16 + n16) * 2] = m;
+        ml[(wave * 16 + n16) * 2 + 1] = l;
+    }
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // lane (j4, n16): columns d * 64 + 16 j4 + 4 i + e of row n16
+            const f32x4 w = {o[d][0][i], o[d][1][i], o[d][2][i], o[d][3][i]};
+            *(f32x4 *)(smem_f + (wave * 16 + n16) * OROW + d * 64 + j4 * 16 + i * 4) = w;
+        }
+    __syncthreads();
+    for (int x = threadIdx.x; x < 16 * ND * 16; x += 64 * NW) {
+        const int rr = x / (ND * 16), c = (x % (ND * 16)) * 4;
+        const int64_t row = r0 + rr;
+        if (row >= R || c >= p.d_v) continue;
+        float m_all = -INFINITY, l_all = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, ml[(w * 16 + rr) * 2]);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float mw = ml[(w * 16 + rr) * 2], a = mw == -INFINITY ? 0.f : expf(mw - m_all);
+            l_all += a * ml[(w * 16 + rr) * 2 + 1];
+            acc += a * *(const f32x4 *)(smem_f + (w * 16 + rr) * OROW + c);
+        }
+        const float inv = l_all > 0.f ? 1.0f / l_all : 0.f;      // an empty cache gives 0
+        const int64_t i = row / G;
+        const int64_t h = (int64_t)g * G + (row - i * G);
+        float *op = p.out + (((int64_t)b * Sq + i) * p.Hq + h) * p.d_v + c;
+        if constexpr (VEC) {
+            *(f32x4 *)op = acc * inv;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (c + e < p.d_v) op[e] = acc[e] * inv;
+        }
+        if (c == 0) p.lse[((int64_t)b * p.Hq + h) * Sq + i] = m_all + logf(l_all);
+    }
+}
+
+template <int ND, bool VEC>
+static hipError_t launch_rows_f32_t(const F32Params &p, hipStream_t stream)
+{
+    using C = F32RowsCfg<ND>;
+    constexpr auto kern = ssa_rows_f32_kernel<ND, VEC>;
+    hipError_t e = allow_lds<kern>(C::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    const int64_t rows = (p.seqlens ? 1 : p.S) * (p.Hq / p.Hkv), row_tiles = (rows + 15) / 16;
+    // (a grid row holds fewer than 2^32 threads)
+    const int64_t blocks = row_tiles * p.Hkv * p.B, gx = blocks < (1 << 22) ? blocks : (1 << 22), gy = (blocks + gx - 1) / gx;
+    hipLaunchKernelGGL(kern, dim3((unsigned)gx, (unsigned)gy), dim3(64 * C::NW), C::LDS_BYTES, stream, p, (int)row_tiles);
+    return hipGetLastError();
+}
+
+template <bool VEC>
+static hipError_t launch_rows_f32(const F32Params &p, hipStream_t stream)
+{
+    const int d = p.d_qk > p.d_v ? p.d_qk : p.d_v;
+    if (d <= 64) return launch_rows_f32_t<1, VEC>(p, stream);
+    if (d <= 128) return launch_rows_f32_t<2, VEC>(p, stream);
+    if (d <= 192) return launch_rows_f32_t<3, VEC>(p, stream);
+    return launch_rows_f32_t<4, VEC>(p, stream);
 }
 
 hipError_t launch_prefill_f32(const F32Params &p, hipStream_t stream)
 {
-    const int64_t n_rows = p.seqlens ? (int64_t)p.B * p.Hq : (int64_t)p.B * p.S * p.Hq;
-    const int64_t blocks = (n_rows + F32_WAVES - 1) / F32_WAVES;
-    hipLaunchKernelGGL(ssa_prefill_f32_kernel, dim3((unsigned)blocks), dim3(64 * F32_WAVES), 0, stream, p);
-    return hipGetLastError();
+    // (base pointers are 16-byte aligned; rows of a multiple of four floats then are, too)
+    const bool vec = p.d_qk % 4 == 0 && p.d_v % 4 == 0;
+    return vec ? launch_rows_f32<true>(p, stream) : launch_rows_f32<false>(p, stream);
 }
 
 // ---- fp32 backward (the small, exact-arithmetic twin of ssa_bwd.hip) --------------------------------

@@ -73,3 +73,15 @@ def test_extend_row_groups(gpu_device, B, q_len, Hq, Hkv, d, alias):
         kb = kc[b:b + 1, :L].contiguous()
         vb = kb if alias else vc[b:b + 1, :L].contiguous()
         H.compare_prefill(qf, kb, vb, of, lf, zero, rh, rr + L - q_len, ns, win, scale, f"rows extend q{q_len} {Hq}/{Hkv} d{d} L{L}")
+
+
+# fp32 twin: its blocks of 64 features and columns, widths that are no multiple of 4 (guarded scalar loads)
+@pytest.mark.parametrize("d_qk,d_v", [(1, 1), (3, 66), (63, 64), (64, 65), (128, 4), (129, 130), (192, 192), (193, 7), (256, 255), (256, 256)])
+@pytest.mark.parametrize("S,Hq,Hkv,ns,win", [(17, 1, 1, 2, 3), (50, 6, 2, 20, 16)])
+def test_prefill_f32_widths(gpu_device, d_qk, d_v, S, Hq, Hkv, ns, win):
+    g = torch.Generator(device=gpu_device).manual_seed(7)
+    q, k, v = (torch.randn(2, S, h, d, generator=g, device=gpu_device) for h, d in ((Hq, d_qk), (Hkv, d_qk), (Hkv, d_v)))
+    scale = d_qk ** -0.5
+    out, lse = H.run_prefill(q, k, v, ns, win, scale)
+    rb, rh, ri = H.all_rows(2, Hq, S)
+    H.compare_prefill(q, k, v, out, lse, rb, rh, ri, ns, win, scale, f"f32 widths {d_qk},{d_v} S{S}")
