@@ -317,7 +317,8 @@ size_t loza_ssa_calibration_alpha_grad_workspace_bytes(int64_t n);
  * Supported: the (d_qk, d_v) pairs of loza_ssa_prefill, scale > 0, and Hq / Hkv a power of two up to
  * 32 or a multiple of 32 (else LOZA_ERR_UNSUPPORTED). Arithmetic: bf16 matrix-core operands (q, k,
  * v, dout, and p and ds rounded to bf16), fp32 accumulation, one rounding of each result to bf16.
- * Sums run in a fixed order: the result is deterministic. No output aliases an input.
+ * Sums run in a fixed order: the result is deterministic. No output aliases an input; dq may hold partial
+ * sums of dk and dv while the call runs.
  */
 int loza_ssa_backward(const void *q, const void *k, const void *v, const void *out, const float *lse,
                       const void *dout, void *dq, void *dk, void *dv,

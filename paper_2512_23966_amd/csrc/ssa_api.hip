@@ -506,6 +506,44 @@ static void backward_plan(loza::BwdParams &p)
     p.max_chunks = p.n_sink_kt > 0 ? (int)((hi - lo + 1 + ct - 1) / ct) : 1;
 }
 
+// The key-stationary kernel's work items (key tiles, chunks of sink tiles) take about the same time each,
+// and one workgroup fills a compute unit: what is left over after the last full round of 256 is cut into
+// chunks that fill the chip (16,384 tokens of 1 + 7 blocks of 128, absorbed MLA: 286 items ran two rounds,
+// 9.0 ms; 256 whole ones and 30 in 8 chunks each: 5.3). The chunks leave fp32 partial sums in `dq`, which
+// is free until the row-stationary kernel writes it (the workspace is sized without them); where that does
+// not hold them, the plan stays as it is.
+static void backward_balance(loza::BwdParams &p, int d_qk, int d_v, bool alias)
+{
+    const int64_t n_kt = (p.S + 63) / 64, BH = (int64_t)p.B * p.Hkv, cus = kComputeUnits;
+    const int64_t cols = alias ? d_qk : d_qk + d_v, room = (int64_t)p.B * p.S * p.Hq * d_qk * 2 / (64 * cols * 4);
+    const int64_t kt0 = p.split_kt0(), total = (kt0 * p.max_chunks + n_kt - kt0) * BH, rest = total % cus;
+    int lo, hi;
+    loza::bwd_key_tile_rows(p, (int)(kt0 < n_kt ? kt0 : n_kt - 1), lo, hi);
+    const int64_t len = hi - lo + 1;                                  // row tiles of the first tile to be split
+    int64_t n_split = (rest + BH - 1) / BH;
+    if (n_split > n_kt - kt0) n_split = n_kt - kt0;
+    if (n_split < 1) return;
+    // time of the last rounds in units of a whole item, each chunk costing about a hundredth more
+    int64_t best_k = 1, best = INT64_MAX;
+    for (int64_t k = 1; k <= 16 && len / k >= 32; ++k) {
+        const int64_t t = ((n_split * BH * k + cus - 1) / cus) * 1000 / k + 10 * k;
+        if (t < best) { best = t; best_k = k; }
+    }
+    if (best_k == 1) return;
+    loza::BwdParams q = p;
+    q.n_split_kt = (int)n_split;
+    q.split_chunks = (int)best_k;
+    if (total < cus && q.max_chunks > 1) {                            // no full round: the sink tiles' chunks too
+        q.chunk_tiles = (int)((p.chunk_tiles + best_k - 1) / best_k);
+        loza::bwd_key_tile_rows(p, 0, lo, hi);
+        q.max_chunks = (hi - lo + q.chunk_tiles) / q.chunk_tiles;
+    }
+    const int64_t slots = BH * ((q.max_chunks > 1 ? (int64_t)q.n_sink_kt * q.max_chunks : 0) + n_split * best_k);
+    if (slots > room) return;
+    q.part = (float *)p.dq;
+    p = q;
+}
+
 static int backward_fill(loza::BwdParams &p, int B, int Hq, int Hkv, int64_t S, int d_qk, int d_v,
                          int64_t sink, int64_t local, int64_t block, bool blocks, float scale, bool alias)
 {
@@ -571,6 +609,7 @@ static int backward_bf16(const void *q, const void *k, const void *v, const void
     p.dq = (uint16_t *)dq; p.dk = (uint16_t *)dk; p.dv = alias ? nullptr : (uint16_t *)dv;
     p.rowstat = (float2 *)workspace;
     p.part = (float *)((char *)workspace + part_offset);
+    backward_balance(p, d_qk, d_v, alias);
     return loza::launch_backward_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
 }
 

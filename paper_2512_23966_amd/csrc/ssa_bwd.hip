@@ -172,6 +172,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
     const int n_kt = (int)((S + 63) / 64);  // key tiles of 64 keys
     int b, g, xt, chunk = 0;
     bool partial = false;  // KEYS: leave an fp32 partial sum for the reduce kernel
+    bool is_split = false; // KEYS: a chunk of a key tile that is split for balance
     if (!KEYS) {
         const int x_tiles = (int)((R + 63) / 64);
         int id = blockIdx.x;
@@ -180,25 +181,40 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
         g = id % p.Hkv;
         b = id / p.Hkv;
     } else {
-        const int items = p.n_sink_kt * p.max_chunks + (n_kt - p.n_sink_kt);
+        const int kt0 = p.max_chunks > 1 ? p.n_sink_kt : 0;               // key tiles before it run in chunks
+        const int items = kt0 * p.max_chunks + (n_kt - kt0 - p.n_split_kt), BH = p.B * p.Hkv;
         // Workgroups go to the eight XCDs round-robin and every XCD has an L2 of its own. Handing every
         // XCD one contiguous eighth of the items makes the workgroups that share an L2 neighbouring key
-        // tiles, whose row ranges overlap almost completely (see the rotation below).
+        // tiles, whose row ranges overlap almost completely (see the rotation below). The chunks of split
+        // tiles come last, dealt out the same way among themselves.
+        auto per_xcd = [](int id, int total) {
+            const int eighth = total / 8;
+            return id < eighth * 8 ? (id % 8) * eighth + id / 8 : id;
+        };
         int id = blockIdx.x;
-        {
-            const int total = gridDim.x, eighth = total / 8;
-            if (id < eighth * 8) id = (id % 8) * eighth + id / 8;
+        is_split = id >= items * BH;
+        int it, per;
+        if (!is_split) {
+            id = per_xcd(id, items * BH);
+            per = items;
+        } else {
+            per = p.n_split_kt * p.split_chunks;
+            id = per_xcd(id - items * BH, per * BH);
         }
-        const int it = id % items;
-        id /= items;
+        it = id % per;
+        id /= per;
         g = id % p.Hkv;
         b = id / p.Hkv;
-        if (it < p.n_sink_kt * p.max_chunks) {
+        if (is_split) {
+            xt = kt0 + it / p.split_chunks;
+            chunk = it % p.split_chunks;
+            partial = true;
+        } else if (it < kt0 * p.max_chunks) {
             xt = it / p.max_chunks;
             chunk = it % p.max_chunks;
-            partial = p.max_chunks > 1;
+            partial = true;
         } else {
-            xt = p.n_sink_kt + (it - p.n_sink_kt * p.max_chunks);
+            xt = kt0 + p.n_split_kt + (it - kt0 * p.max_chunks);
         }
     }
 
@@ -225,9 +241,10 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
         bwd_key_tile_rows(p, xt, yt_lo, yt_hi);
         yt_begin = yt_lo;
         int yt_end = yt_hi + 1;
-        if (xt < p.n_sink_kt) {
-            yt_begin = yt_lo + chunk * p.chunk_tiles;
-            if (yt_begin + p.chunk_tiles < yt_end) yt_end = yt_begin + p.chunk_tiles;
+        if (partial) {
+            const int ct = is_split ? (yt_end - yt_lo + p.split_chunks - 1) / p.split_chunks : p.chunk_tiles;
+            yt_begin = yt_lo + chunk * ct;
+            if (yt_begin + ct < yt_end) yt_end = yt_begin + ct;
         }
         nt = yt_end - yt_begin;
         if (nt <= 0) return;  // a chunk beyond the rows of this key tile (the reduce kernel knows)
@@ -239,8 +256,9 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
         // own range: they then ask for the same row tile at about the same time, and one fetch into
         // the shared L2 serves all of them.
         yt_start = yt_begin;
-        if (xt >= p.n_sink_kt) {
-            const int last = p.n_sink_kt + ((xt - p.n_sink_kt) / 32) * 32 + 31;
+        if (xt >= p.n_sink_kt && !is_split) {
+            const int k0 = p.max_chunks > 1 || p.n_split_kt > p.n_sink_kt ? p.split_kt0() + p.n_split_kt : p.n_sink_kt;
+            const int last = k0 + ((xt - k0) / 32) * 32 + 31;
             int a_lo, a_hi;
             bwd_key_tile_rows(p, last < n_kt - 1 ? last : n_kt - 1, a_lo, a_hi);
             if (a_lo >= yt_begin && a_lo < yt_end) yt_start = a_lo;
@@ -684,8 +702,11 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
         } else if (partial) {
             // row [dK (d_qk) | dV (d_v, separate values only)] of fp32 partial sums
             constexpr int COLS = C::SPLIT_KV ? DQK + DV : DQK;
-            float *op = p.part + ((((int64_t)b * p.Hkv + g) * p.n_sink_kt + xt) * p.max_chunks + chunk) * 64 * COLS +
-                        (int64_t)(x2 * 32 + ln) * COLS + ((C::SPLIT_KV && ROLE == 1) ? DQK : 0) + 4 * lh;
+            const int64_t bg = (int64_t)b * p.Hkv + g;
+            const int64_t slot = is_split ? (p.max_chunks > 1 ? (int64_t)p.B * p.Hkv * p.n_sink_kt * p.max_chunks : 0) +
+                                                (bg * p.n_split_kt + (xt - p.split_kt0())) * p.split_chunks + chunk
+                                          : (bg * p.n_sink_kt + xt) * p.max_chunks + chunk;
+            float *op = p.part + slot * 64 * COLS + (int64_t)(x2 * 32 + ln) * COLS + ((C::SPLIT_KV && ROLE == 1) ? DQK : 0) + 4 * lh;
 #pragma unroll
             for (int a = 0; a < ND; ++a)
 #pragma unroll
@@ -713,31 +734,34 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
     else run(std::integral_constant<int, 1>{});
 }
 
-// Sum of the chunk partials of the key tiles that hold sink keys, in chunk order, rounded once.
-// One thread per four columns of one key.
-template <int DQK, int DV, bool ALIAS>
+// Sum of the chunk partials of a run of key tiles, in chunk order, rounded once: the tiles that hold sink
+// keys (SPLIT = false) or those split for balance. One thread per four columns of one key.
+template <int DQK, int DV, bool ALIAS, bool SPLIT>
 __global__ __launch_bounds__(256) void ssa_bwd_reduce_kernel(const BwdParams p)
 {
     constexpr int COLS = ALIAS ? DQK : DQK + DV;
     constexpr int TPK = COLS / 4;  // threads per key
+    const int kt0 = SPLIT ? p.split_kt0() : 0, n_tiles = SPLIT ? p.n_split_kt : p.n_sink_kt, n_chunks = SPLIT ? p.split_chunks : p.max_chunks;
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t n_keys = (int64_t)p.B * p.Hkv * p.n_sink_kt * 64;
+    const int64_t n_keys = (int64_t)p.B * p.Hkv * n_tiles * 64;
     if (t >= n_keys * TPK) return;
     const int c = (int)(t % TPK) * 4;
     const int64_t key = t / TPK;
     const int x = (int)(key % 64);
-    const int64_t tile = key / 64;  // flat (b, g, kt)
-    const int kt = (int)(tile % p.n_sink_kt);
-    const int64_t bg = tile / p.n_sink_kt;
+    const int64_t tile = key / 64;  // flat (b, g, tile of the run)
+    const int kt = kt0 + (int)(tile % n_tiles);
+    const int64_t bg = tile / n_tiles;
     const int g = (int)(bg % p.Hkv);
     const int64_t b = bg / p.Hkv;
     const int64_t j = (int64_t)kt * 64 + x;
     if (j >= p.S) return;
     int yt_lo, yt_hi;
     bwd_key_tile_rows(p, kt, yt_lo, yt_hi);
-    const int chunks = (yt_hi - yt_lo + 1 + p.chunk_tiles - 1) / p.chunk_tiles;
+    const int len = yt_hi - yt_lo + 1, ct = SPLIT ? (len + n_chunks - 1) / n_chunks : p.chunk_tiles;
+    const int chunks = (len + ct - 1) / ct;
     float4 s = {0.f, 0.f, 0.f, 0.f};
-    const float *pp = p.part + (tile * p.max_chunks * 64 + x) * COLS + c;
+    const int64_t first = (SPLIT && p.max_chunks > 1) ? (int64_t)p.B * p.Hkv * p.n_sink_kt * p.max_chunks : 0;
+    const float *pp = p.part + ((first + tile * n_chunks) * 64 + x) * COLS + c;
     for (int ch = 0; ch < chunks; ++ch) {
         const float4 v = *(const float4 *)(pp + (int64_t)ch * 64 * COLS);
         s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
@@ -758,28 +782,32 @@ static hipError_t launch_backward_t(const BwdParams &p, hipStream_t stream)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     {
+        using C = BwdCfg<DQK, DV, ALIAS, true>;
+        auto kern = ssa_bwd_kernel<DQK, DV, ALIAS, true>;
+        e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
+        if (e != hipSuccess) return e;
+        const int64_t n_kt = (p.S + 63) / 64;
+        const int64_t kt0 = p.split_kt0();
+        const int64_t blocks = (kt0 * p.max_chunks + (n_kt - kt0 - p.n_split_kt) + (int64_t)p.n_split_kt * p.split_chunks) * p.Hkv * p.B;
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), C::LDS_BYTES, stream, p);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    // (the partial results may lie in dq, which the row-stationary kernel writes after they have been added)
+    auto reduce = [&](auto kern, int64_t tiles) {
+        constexpr int COLS = ALIAS ? DQK : DQK + DV;
+        const int64_t threads = (int64_t)p.B * p.Hkv * tiles * 64 * (COLS / 4);
+        hipLaunchKernelGGL(kern, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, p);
+        return hipGetLastError();
+    };
+    if (p.max_chunks > 1 && (e = reduce(ssa_bwd_reduce_kernel<DQK, DV, ALIAS, false>, p.n_sink_kt)) != hipSuccess) return e;
+    if (p.n_split_kt > 0 && (e = reduce(ssa_bwd_reduce_kernel<DQK, DV, ALIAS, true>, p.n_split_kt)) != hipSuccess) return e;
+    {
         using C = BwdCfg<DQK, DV, ALIAS, false>;
         auto kern = ssa_bwd_kernel<DQK, DV, ALIAS, false>;
         e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
         if (e != hipSuccess) return e;
         const int64_t blocks = ((p.S * p.G + 63) / 64) * p.Hkv * p.B;
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), C::LDS_BYTES, stream, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    {
-        using C = BwdCfg<DQK, DV, ALIAS, true>;
-        auto kern = ssa_bwd_kernel<DQK, DV, ALIAS, true>;
-        e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
-        if (e != hipSuccess) return e;
-        const int64_t n_kt = (p.S + 63) / 64;
-        const int64_t blocks = ((int64_t)p.n_sink_kt * p.max_chunks + (n_kt - p.n_sink_kt)) * p.Hkv * p.B;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), C::LDS_BYTES, stream, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (p.n_sink_kt > 0 && p.max_chunks > 1) {
-        constexpr int COLS = ALIAS ? DQK : DQK + DV;
-        const int64_t threads = (int64_t)p.B * p.Hkv * p.n_sink_kt * 64 * (COLS / 4);
-        hipLaunchKernelGGL((ssa_bwd_reduce_kernel<DQK, DV, ALIAS>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

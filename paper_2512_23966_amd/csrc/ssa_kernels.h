@@ -80,7 +80,9 @@ struct BwdParams {
     const float *lse;
     uint16_t *dq, *dk, *dv;   // dv is unused when v aliases k (dk then holds the gradient of the shared tensor)
     float2 *rowstat;          // workspace: [B, Hkv, r_pad] (lse * log2(e), dO . O), row index i * G + head-in-group
-    float *part;              // workspace: [B, Hkv, n_sink_kt, max_chunks, 64, columns] fp32 partial dK | dV
+    // fp32 partial dK | dV: [B, Hkv, n_sink_kt, max_chunks, 64, columns] of the key tiles that hold sink keys,
+    // then [B, Hkv, n_split_kt, split_chunks, 64, columns] of the key tiles that are split for balance
+    float *part;
     int B, Hq, Hkv, G;
     int64_t S;
     int64_t r_pad;            // S * G rounded up to a multiple of 32
@@ -89,6 +91,11 @@ struct BwdParams {
     int n_sink_kt;            // key tiles (of 64 keys) that hold at least one sink key
     int chunk_tiles;          // row tiles (of 32 rows) per chunk of such a key tile
     int max_chunks;           // chunks of the first key tile (the one with most rows)
+    // Key tiles [n_sink_kt, n_sink_kt + n_split_kt) (where max_chunks == 1: [0, n_split_kt)) are cut into
+    // split_chunks equal chunks of their rows, work items of their own, so that the last round of workgroups
+    // does not leave most compute units idle (0: none).
+    int n_split_kt, split_chunks;
+    __host__ __device__ int split_kt0() const { return max_chunks > 1 ? n_sink_kt : 0; }
 };
 
 // Row tiles (32 rows each, row = position * G + head-in-group) that can see a key of key tile kt
