@@ -109,6 +109,10 @@ struct TileCfg {
     static constexpr int SPEC_JOBS = 30;
     static constexpr bool SPEC_SOFTMAX = !DECODE && (N / 16) * DVB * RB >= SPEC_JOBS;
     static_assert(LDS_BYTES <= 160 * 1024, "tile does not fit the 160 KB LDS");
+    // prefill / extend epilogue: the finished tile, rounded to bf16, on its way from the accumulators' layout
+    // to whole rows
+    static constexpr int OUTROW = DV * 2 + 16;
+    static_assert(DECODE || M * OUTROW <= OFF_ALPHA, "the output tile must fit the stages and P");
 };
 
 // One pass over one workgroup tile. PRECISE: P goes to the value phase as two bf16 terms. Returns
@@ -833,12 +837,40 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
     }
     lds_barrier();
 
-    if (!DECODE && !PRECISE) {
-        // A result of magnitude 2 or more leaves the error budget little beyond its own rounding to
-        // bf16 (half an ulp is 2^-7 there), and it can only come from a row whose weight sits on a few
-        // keys, where the rounding of P to bf16 shows most. A tile with such a row is not written: it
-        // is computed again with two-term P (the caller runs the PRECISE pass when this one says so).
-        bool big = false;
+    // A result of magnitude 2 or more leaves the error budget little beyond its own rounding to bf16
+    // (half an ulp is 2^-7 there), and it can only come from a row whose weight sits on a few keys, where
+    // the rounding of P to bf16 shows most. A tile with such a row is not written: it is computed again
+    // with two-term P (the caller runs the PRECISE pass when this one says so).
+    bool big = false;
+    if constexpr (!DECODE && !OUTF32) {
+        // Every lane holds 4 of the 512 (128) columns of 32 rows at a time: stored from here, every store
+        // instruction touches 32 rows (check and stores of a wide tile: 19.1 thousand cycles). Through LDS a
+        // wave stores whole rows, past the L2's keys (14.0 thousand; prefill with 1 + 7 blocks 1.7 % faster).
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const float rsum = s_lpart[M + rb * 32 + ln];
+            const float inv = rsum > 0.f ? 1.0f / rsum : 0.f;  // a row without a live key gives 0
+            char *op = smem + (rb * 32 + ln) * C::OUTROW + (vw * C::DVW + 4 * lh) * 2;
+            float mx = 0.f;
+#pragma unroll
+            for (int db = 0; db < C::DVB; ++db)
+#pragma unroll
+                for (int qd = 0; qd < 4; ++qd) {
+                    float x[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = o[db][rb][4 * qd + e] * inv;
+                    if (!PRECISE) {
+                        mx = fmaxf(fmaxf(mx, __builtin_fabsf(x[0])), __builtin_fabsf(x[1]));
+                        mx = fmaxf(fmaxf(mx, __builtin_fabsf(x[2])), __builtin_fabsf(x[3]));
+                    }
+                    u32x2 w;
+                    w[0] = pack_bf16(x[0], x[1]);
+                    w[1] = pack_bf16(x[2], x[3]);
+                    *(u32x2 *)(op + db * 64 + qd * 16) = w;
+                }
+            big = big || (mx >= kRedoMagnitude && r0 + rb * 32 + ln < R);
+        }
+    } else if constexpr (!DECODE && !PRECISE) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             const float rsum = s_lpart[M + rb * 32 + ln];
@@ -849,9 +881,11 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
                 for (int e = 0; e < 16; ++e) mx = fmaxf(mx, __builtin_fabsf(o[db][rb][e]));
             big = big || (rsum > 0.f && mx >= kRedoMagnitude * rsum && r0 + rb * 32 + ln < R);
         }
-        if (__any(big) && lane == 0) *s_redo = 1;
+    }
+    if constexpr (!DECODE) {
+        if (!PRECISE && __any(big) && lane == 0) *s_redo = 1;
         lds_barrier();
-        if (*(volatile int *)s_redo) return true;
+        if (!PRECISE && *(volatile int *)s_redo) return true;
     }
 
     if (!DECODE) {
@@ -861,18 +895,37 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
             p.lse[((int64_t)b * p.Hq + (int64_t)g * G + hh) * Sq + r_row] =
                 (m_ref + __builtin_amdgcn_logf(s_lpart[wr * 32 + ln])) * 0.69314718055994530942f;
         }
+        if constexpr (!OUTF32) {
+            constexpr int LPR = DV / 8, RPI = 64 / LPR;  // lanes per row, rows per store instruction
+            const int first = wave * (M / NW) + lane / LPR;
+            int64_t i = (r0 + first) / G;
+            int hh = (int)(r0 + first - i * G);
+#pragma unroll 4
+            for (int step = 0; step < M / NW / RPI; ++step) {
+                const int row = first + step * RPI;
+                if (r0 + row < R) {
+                    const u32x4 w = *(const u32x4 *)(smem + row * C::OUTROW + (lane % LPR) * 16);
+                    const int64_t o_row = ((int64_t)b * Sq + i) * p.Hq + (int64_t)g * G + hh;
+                    __builtin_nontemporal_store(w, (u32x4 *)(p.out + o_row * DV + (lane % LPR) * 8));
+                }
+                hh += RPI;
+                if (hh >= G) {
+                    const int d = hh / G;
+                    i += d;
+                    hh -= d * G;
+                }
+            }
+        } else {
+            // unrounded output (the calibration blend rounds once, after mixing two of these)
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            const int64_t row = r0 + rb * 32 + ln;
-            const float rsum = s_lpart[M + rb * 32 + ln];
-            const float inv = rsum > 0.f ? 1.0f / rsum : 0.f;  // a row without a live key gives 0
-            if (row < R) {
-                const int64_t i = row / G;
-                const int hh = (int)(row - i * G);
-                const int64_t o_idx = ((((int64_t)b * Sq + i) * p.Hq + (int64_t)g * G + hh) * DV) + vw * C::DVW + 4 * lh;
-                if constexpr (OUTF32) {
-                    // unrounded output (the calibration blend rounds once, after mixing two of these)
-                    float *op = p.out_f32 + o_idx;
+            for (int rb = 0; rb < RB; ++rb) {
+                const int64_t row = r0 + rb * 32 + ln;
+                const float rsum = s_lpart[M + rb * 32 + ln];
+                const float inv = rsum > 0.f ? 1.0f / rsum : 0.f;  // a row without a live key gives 0
+                if (row < R) {
+                    const int64_t i = row / G;
+                    const int hh = (int)(row - i * G);
+                    float *op = p.out_f32 + ((((int64_t)b * Sq + i) * p.Hq + (int64_t)g * G + hh) * DV) + vw * C::DVW + 4 * lh;
 #pragma unroll
                     for (int db = 0; db < C::DVB; ++db)
 #pragma unroll
@@ -883,17 +936,6 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
                             w.z = o[db][rb][4 * qd + 2] * inv;
                             w.w = o[db][rb][4 * qd + 3] * inv;
                             *(float4 *)(op + db * 32 + qd * 8) = w;
-                        }
-                } else {
-                    uint16_t *op = p.out + o_idx;
-#pragma unroll
-                    for (int db = 0; db < C::DVB; ++db)
-#pragma unroll
-                        for (int qd = 0; qd < 4; ++qd) {
-                            u32x2 w;
-                            w[0] = pack_bf16(o[db][rb][4 * qd + 0] * inv, o[db][rb][4 * qd + 1] * inv);
-                            w[1] = pack_bf16(o[db][rb][4 * qd + 2] * inv, o[db][rb][4 * qd + 3] * inv);
-                            *(u32x2 *)(op + db * 32 + qd * 8) = w;
                         }
                 }
             }
