@@ -225,8 +225,8 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
     int i_min = 0, i_max = 0, w_lo_max = 0;
     if (!KEYS) {
         const int64_t r_last = (int64_t)xt * 64 + 63 < R ? (int64_t)xt * 64 + 63 : R - 1;
-        i_min = (int)(((int64_t)xt * 64) / G);
-        i_max = (int)(r_last / G);
+        i_min = (int)row_position((int64_t)xt * 64, G);
+        i_max = (int)row_position(r_last, G);
         const int sink_end = n_sink < i_max + 1 ? n_sink : i_max + 1;
         const int win_begin = window_begin_of(i_min, window, block);
         w_lo_max = window_begin_of(i_max, window, block);
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
     {
         const uint16_t *xp;
         if (!KEYS) {
-            const int64_t i = x_c / G;
+            const int64_t i = row_position(x_c, G);
             const int hh = (int)(x_c - i * G);
             x_i = (int)i;
             const int64_t qrow = (((int64_t)b * S + i) * p.Hq + (int64_t)g * G + hh);
@@ -687,7 +687,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
         const int64_t xi = (int64_t)xt * 64 + x2 * 32 + ln;
         if (xi >= (KEYS ? S : R)) continue;
         if (!KEYS) {
-            const int64_t i = xi / G;
+            const int64_t i = row_position(xi, G);
             const int hh = (int)(xi - i * G);
             uint16_t *op = p.dq + (((int64_t)b * S + i) * p.Hq + (int64_t)g * G + hh) * DQK + 4 * lh;
 #pragma unroll

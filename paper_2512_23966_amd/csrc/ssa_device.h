@@ -89,6 +89,15 @@ __device__ __forceinline__ int window_begin_of(int i, int window, int block)
     return window > qb ? 0 : (qb - window + 1) * block;
 }
 
+// Position of query row r (rows are position-major, G heads of a group together). A wave that starts has
+// nothing to hide an integer division by a run-time value behind (64-bit: more than a hundred dependent
+// instructions, half a dozen of them before the first load); group sizes are nearly always powers of two.
+__device__ __forceinline__ int64_t row_position(int64_t r, int G)
+{
+    if ((G & (G - 1)) == 0) return r >> __builtin_ctz((unsigned)G);
+    return r / G;
+}
+
 // Prefill tiles that start below this position are computed with two-term P (p = hi + lo, both
 // bf16) from the outset: with so few live keys the output is as large as single value rows, and the
 // bf16 rounding of P would be a visible share of the error budget there.

@@ -123,8 +123,8 @@ __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
     const int64_t pos0 = L - Sq;
     const int64_t R = Sq * G, r0 = (int64_t)rt * M;
     const int n_sink = p.n_sink, window = p.window, block = p.block;
-    const int i_min = (int)(pos0 + r0 / G);
-    const int i_max = (int)(pos0 + ((r0 + M - 1 < R) ? r0 + M - 1 : R - 1) / G);
+    const int i_min = (int)(pos0 + row_position(r0, G));
+    const int i_max = (int)(pos0 + row_position((r0 + M - 1 < R) ? r0 + M - 1 : R - 1, G));
 
     // ---- this wave's live key tiles: sink tiles [0, nA), then window tiles [wt0, wt0 + nB), dealt out ---
     const int sink_end = i_max < 0 ? 0 : (n_sink < i_max + 1 ? n_sink : i_max + 1);
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
     int i_row, w_lo_row;
     {
         const int64_t row = r0 + n16, rc = row < R ? row : R - 1;
-        const int64_t qi = rc / G;
+        const int64_t qi = row_position(rc, G);
         const int hh = (int)(rc - qi * G);
         i_row = (int)(pos0 + qi);
         w_lo_row = window_begin_of(i_row < 0 ? 0 : i_row, window, block);
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
             lo += a * *(const f32x4 *)op;
             hi += a * *(const f32x4 *)(op + 16);
         }
-        const int64_t qi = row / G;
+        const int64_t qi = row_position(row, G);
         const int64_t h = (int64_t)g * G + (row - qi * G);
         const int64_t o_row = ((int64_t)b * Sq + qi) * p.Hq + h;
         if (p.n_splits > 1) {
