@@ -180,10 +180,10 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
     // ---- the query row this lane scores ---------------------------------------------------------
     const int64_t my_row = r0 + wr * 32 + ln;
     const int64_t my_row_c = my_row < R ? my_row : R - 1;
-    const int r_row = DECODE ? 0 : (int)(my_row_c / G);           // index of the query among the Sq
+    const int r_row = DECODE ? 0 : (int)row_position(my_row_c, G);           // index of the query among the Sq
     const int i_row = DECODE ? (int)(L - 1) : (int)(pos0 + r_row);
-    const int i_min = DECODE ? (int)(L - 1) : (int)(pos0 + r0 / G);
-    const int i_max = DECODE ? (int)(L - 1) : (int)(pos0 + ((r0 + M - 1 < R) ? r0 + M - 1 : R - 1) / G);
+    const int i_min = DECODE ? (int)(L - 1) : (int)(pos0 + row_position(r0, G));
+    const int i_max = DECODE ? (int)(L - 1) : (int)(pos0 + row_position((r0 + M - 1 < R) ? r0 + M - 1 : R - 1, G));
     // Tiles among the first positions, and every tile of a pattern that leaves all rows few live keys,
     // take the two-term pass right away.
     if (!DECODE && !PRECISE && (p.all_precise || i_min < kPrecisePositions)) return true;
@@ -898,7 +898,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
         if constexpr (!OUTF32) {
             constexpr int LPR = DV / 8, RPI = 64 / LPR;  // lanes per row, rows per store instruction
             const int first = wave * (M / NW) + lane / LPR;
-            int64_t i = (r0 + first) / G;
+            int64_t i = row_position(r0 + first, G);
             int hh = (int)(r0 + first - i * G);
 #pragma unroll 4
             for (int step = 0; step < M / NW / RPI; ++step) {
@@ -923,7 +923,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
                 const float rsum = s_lpart[M + rb * 32 + ln];
                 const float inv = rsum > 0.f ? 1.0f / rsum : 0.f;  // a row without a live key gives 0
                 if (row < R) {
-                    const int64_t i = row / G;
+                    const int64_t i = row_position(row, G);
                     const int hh = (int)(row - i * G);
                     float *op = p.out_f32 + ((((int64_t)b * Sq + i) * p.Hq + (int64_t)g * G + hh) * DV) + vw * C::DVW + 4 * lh;
 #pragma unroll
@@ -1140,7 +1140,7 @@ __global__ __launch_bounds__(DV / 4) void ssa_decode_merge_kernel(const FwdParam
 // A pattern that leaves rows beyond the first kPrecisePositions positions with fewer live keys than
 // that takes the two-term variant throughout. The smallest live set of such a row is at position
 // kPrecisePositions - 1 or at the first query of a block whose window has reached full length.
-static bool pattern_needs_precise(const FwdParams &p)
+bool pattern_needs_precise(const FwdParams &p)
 {
     auto live_at = [&](int64_t i) {
         const int64_t se = p.n_sink < i + 1 ? p.n_sink : i + 1;
@@ -1306,19 +1306,33 @@ bool bf16_shape_supported(int d_qk, int d_v, bool alias)
 int prefill_rows_per_tile() { return 128; }
 int decode_rows_per_tile() { return 64; }
 
+// Heads of width 128: the kernel of 256-row tiles (ssa_d128.hip) or the one of 128-row tiles here. The former is
+// 1.03 to 1.29 times as fast (32 heads, window 4096: 8,192 tokens 521 against 590 us; 2,048 tokens 78 against
+// 94) except where its tiles leave compute units idle (1,024 tokens of 32 heads are 128 of them: 46 against 44
+// us) or mostly pad (chunks of 300 tokens: 122 against 120 us).
+static bool d128_tiles_pay(const FwdParams &p)
+{
+    const int64_t rows = (p.seqlens ? (int64_t)p.q_len : p.S) * p.G, big = (rows + 255) / 256, small = (rows + 127) / 128;
+    return big * p.Hkv * p.B >= 160 && big * 256 * 4 <= small * 128 * 5;
+}
+
 hipError_t launch_prefill_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream)
 {
     if (d_qk == 576 && d_v == 512 && alias) return launch_prefill_t<576, 512, true>(p, stream);
-    if (d_qk == 128 && d_v == 128) return alias ? launch_prefill_t<128, 128, true>(p, stream)
-                                                : launch_prefill_t<128, 128, false>(p, stream);
+    if (d_qk == 128 && d_v == 128) {
+        if (d128_tiles_pay(p)) return launch_d128_bf16(p, alias, stream);
+        return alias ? launch_prefill_t<128, 128, true>(p, stream) : launch_prefill_t<128, 128, false>(p, stream);
+    }
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_extend_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream)
 {
     if (d_qk == 576 && d_v == 512 && alias) return launch_extend_t<576, 512, true>(p, stream);
-    if (d_qk == 128 && d_v == 128) return alias ? launch_extend_t<128, 128, true>(p, stream)
-                                                : launch_extend_t<128, 128, false>(p, stream);
+    if (d_qk == 128 && d_v == 128) {
+        if (d128_tiles_pay(p)) return launch_d128_bf16(p, alias, stream);
+        return alias ? launch_extend_t<128, 128, true>(p, stream) : launch_extend_t<128, 128, false>(p, stream);
+    }
     return hipErrorInvalidValue;
 }
 

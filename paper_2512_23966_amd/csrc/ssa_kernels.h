@@ -58,6 +58,10 @@ int decode_rows_per_tile();
 hipError_t launch_prefill_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
 hipError_t launch_extend_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
 hipError_t launch_decode_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
+// Whether a pattern leaves rows beyond the first positions so few live keys that every tile takes two-term weights.
+bool pattern_needs_precise(const FwdParams &p);
+// Heads of width 128, many query rows (ssa_d128.hip): prefill (seqlens null) or extend.
+hipError_t launch_d128_bf16(const FwdParams &p, bool alias, hipStream_t stream);
 // Few query rows (ssa_rows.hip): prefill (seqlens null), extend or decode (q_len = 1; n_splits key splits
 // and a merge).
 hipError_t launch_rows_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
