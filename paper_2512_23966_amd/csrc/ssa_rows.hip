@@ -39,11 +39,16 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // One global -> LDS copy instruction (1 KB), unknown to the compiler's wait counters: the loop waits
-// with explicit counts.
+// with explicit counts. NT: the rows are read by this workgroup only (non-temporal hint).
+template <bool NT>
 __device__ __forceinline__ void copy_1k(const char *base, uint32_t off, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %2\n s_nop 0\n global_load_lds_dwordx4 %0, %1"
-                 :: "v"(off), "s"(base), "s"(lds_addr) : "memory", "m0");
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %2\n s_nop 0\n global_load_lds_dwordx4 %0, %1 nt"
+                     :: "v"(off), "s"(base), "s"(lds_addr) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %2\n s_nop 0\n global_load_lds_dwordx4 %0, %1"
+                     :: "v"(off), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
 
 template <int N>
@@ -86,7 +91,7 @@ struct RowsCfg {
     static_assert(LDS_BYTES <= 160 * 1024, "does not fit the 160 KB LDS");
 };
 
-template <int DQK, int DV, bool ALIAS>
+template <int DQK, int DV, bool ALIAS, bool NT>
 __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
 {
     using C = RowsCfg<DQK, DV, ALIAS>;
@@ -188,14 +193,14 @@ __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
         return tc;
     };
     // copy instruction i of a tile whose rows all exist
-    auto copy_nth = [&](const TileCopy &tc, int i) { copy_1k(i < C::KI ? tc.k : tc.v, off[i], tc.dst + i * 1024); };
+    auto copy_nth = [&](const TileCopy &tc, int i) { copy_1k<NT>(i < C::KI ? tc.k : tc.v, off[i], tc.dst + i * 1024); };
     // the tile that holds the sequence end: rows past it fetch the last valid row instead (they are dead
     // and only have to be finite)
     auto copy_ragged = [&](const TileCopy &tc) {
 #pragma unroll
         for (int i = 0; i < C::NI; ++i) {
             const uint32_t o = i < C::KI ? offset_of(i, C::CK, k_stride, tc.rows) : offset_of(i - C::KI, C::CV, v_stride, tc.rows);
-            copy_1k(i < C::KI ? tc.k : tc.v, o, tc.dst + i * 1024);
+            copy_1k<NT>(i < C::KI ? tc.k : tc.v, o, tc.dst + i * 1024);
         }
     };
     auto copy_tile = [&](const TileCopy &tc) {
@@ -436,15 +441,13 @@ __global__ __launch_bounds__(DV / 4 * 8) void ssa_rows_merge_kernel(const FwdPar
     }
 }
 
-template <int DQK, int DV, bool ALIAS>
-static hipError_t launch_rows_t(FwdParams p, hipStream_t stream)
+template <int DQK, int DV, bool ALIAS, bool NT>
+static hipError_t launch_rows_t(const FwdParams &p, hipStream_t stream)
 {
     using C = RowsCfg<DQK, DV, ALIAS>;
-    constexpr auto kern = ssa_rows_kernel<DQK, DV, ALIAS>;
+    constexpr auto kern = ssa_rows_kernel<DQK, DV, ALIAS, NT>;
     hipError_t e = allow_lds<kern>(C::LDS_BYTES);
     if (e != hipSuccess) return e;
-    const int64_t rows = (p.seqlens ? (int64_t)p.q_len : p.S) * p.G;
-    p.row_tiles = (int)((rows + 15) / 16);
     const int64_t blocks = (int64_t)p.n_splits * p.row_tiles * p.Hkv * p.B;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), C::LDS_BYTES, stream, p);
     e = hipGetLastError();
@@ -453,10 +456,21 @@ static hipError_t launch_rows_t(FwdParams p, hipStream_t stream)
     return hipGetLastError();
 }
 
+// One group of rows per key head reads every key row once: its copies carry the non-temporal hint (d = 128, 4
+// query heads on a key head, 16 sequences, window 4096: 48.5 against 57.0 us). Several groups share the rows
+// through L2 and keep the default policy.
+template <int DQK, int DV, bool ALIAS>
+static hipError_t launch_rows_d(FwdParams p, hipStream_t stream)
+{
+    const int64_t rows = (p.seqlens ? (int64_t)p.q_len : p.S) * p.G;
+    p.row_tiles = (int)((rows + 15) / 16);
+    return p.row_tiles == 1 ? launch_rows_t<DQK, DV, ALIAS, true>(p, stream) : launch_rows_t<DQK, DV, ALIAS, false>(p, stream);
+}
+
 hipError_t launch_rows_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream)
 {
-    if (d_qk == 576 && d_v == 512 && alias) return launch_rows_t<576, 512, true>(p, stream);
-    if (d_qk == 128 && d_v == 128) return alias ? launch_rows_t<128, 128, true>(p, stream) : launch_rows_t<128, 128, false>(p, stream);
+    if (d_qk == 576 && d_v == 512 && alias) return launch_rows_d<576, 512, true>(p, stream);
+    if (d_qk == 128 && d_v == 128) return alias ? launch_rows_d<128, 128, true>(p, stream) : launch_rows_d<128, 128, false>(p, stream);
     return hipErrorInvalidValue;
 }
 
