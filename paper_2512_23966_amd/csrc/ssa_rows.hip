@@ -458,7 +458,7 @@ static hipError_t launch_rows_t(const FwdParams &p, hipStream_t stream)
 
 // One group of rows per key head reads every key row once: its copies carry the non-temporal hint (d = 128, 4
 // query heads on a key head, 16 sequences, window 4096: 48.5 against 57.0 us). Several groups share the rows
-// through L2 and keep the default policy.
+// through L2 and keep the default policy (with the hint, 43 sequences of the paper's pattern: 33.3 against 30.9 us).
 template <int DQK, int DV, bool ALIAS>
 static hipError_t launch_rows_d(FwdParams p, hipStream_t stream)
 {
