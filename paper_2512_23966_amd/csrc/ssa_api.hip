@@ -509,7 +509,7 @@ static void backward_plan(loza::BwdParams &p)
 // The key-stationary kernel's work items (key tiles, chunks of sink tiles) take about the same time each,
 // and one workgroup fills a compute unit: what is left over after the last full round of 256 is cut into
 // chunks that fill the chip (16,384 tokens of 1 + 7 blocks of 128, absorbed MLA: 286 items ran two rounds,
-// 9.0 ms; 256 whole ones and 30 in 8 chunks each: 5.3). The chunks leave fp32 partial sums in `dq`, which
+// 9.0 ms; 256 whole ones and 30 in 8 chunks each: 6.0). The chunks leave fp32 partial sums in `dq`, which
 // is free until the row-stationary kernel writes it (the workspace is sized without them); where that does
 // not hold them, the plan stays as it is.
 static void backward_balance(loza::BwdParams &p, int d_qk, int d_v, bool alias)
