@@ -235,7 +235,8 @@ struct Paging {
 static int check_paging(const Paging &pg, int *page_shift, int64_t *capacity)
 {
     if (!pg.block_table) return LOZA_ERR_NULL;
-    // pages hold a power-of-two number of rows that key tiles (32 rows) divide
+    // pages hold a power-of-two number of rows, at least 32: what a kernel copies at a time (16 or 32 rows; the
+    // stages of 64 keys in ssa_d128.hip have a table entry for each half) lies in one page
     if (pg.page_size < 32 || (pg.page_size & (pg.page_size - 1)) != 0) return LOZA_ERR_SHAPE;
     if (pg.num_pages < 1 || pg.num_pages > 2147483647LL || pg.max_pages < 1) return LOZA_ERR_SHAPE;
     if ((int64_t)pg.max_pages * pg.page_size > kMaxSeq) return LOZA_ERR_SHAPE;

@@ -137,7 +137,6 @@ static __device__ __forceinline__ bool ssa_d128_tile(const FwdParams &p, char *s
     const char *kbase = (const char *)p.k + (seq_row0 * p.Hkv + g) * (int64_t)ROW;
     const char *vbase = (const char *)p.v + (seq_row0 * p.Hkv + g) * (int64_t)ROW;
     const i32x4 table_rsrc = paged ? table_row_resource(p.block_table + (int64_t)b * p.max_pages, p.max_pages) : i32x4{0, 0, 0, 0};
-    const int last32 = (int)((L - 1) & ~(int64_t)31);    // first row of the last group of 32 that holds a valid one
     struct StageCopy {
         int64_t row[2];    // cache row a half starts at, relative to kbase / vbase (in rows)
         int lim[2];        // its last valid row
@@ -148,8 +147,12 @@ static __device__ __forceinline__ bool ssa_d128_tile(const FwdParams &p, char *s
         const int j0 = key_tile(t) * N;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            // (a half past the sequence end fetches the last valid rows instead: dead, and only finite)
-            const int j = j0 + 32 * h < last32 ? j0 + 32 * h : last32;
+            // A half without a live key of this row tile (between the sink and the first window key, or past the
+            // last query) is never read: its page may be evicted or stale, and weight 0 times a NaN is a NaN. The
+            // stage's other half, which has one, is copied in its place, and masked there.
+            const int jh = j0 + 32 * h;
+            const bool live = jh < sink_end || (jh + 31 >= win_begin && jh <= i_max);
+            const int j = live ? jh : j0 + 32 * (1 - h);
             const int left = (int)(L - 1) - j;
             sc.lim[h] = left < 31 ? left : 31;
             sc.row[h] = j;
