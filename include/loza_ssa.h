@@ -111,11 +111,11 @@ int loza_ssa_prefill_f32(const float *q, const float *k, const float *v, float *
  * Supported (d_qk, d_v) and scale: as loza_ssa_prefill. Cache rows at or beyond seqlens[b] are
  * never read. The split count depends on the sizes only (and on LOZA_DECODE_SPLITS, see above), and
  * the merge adds the splits in a fixed order: the result is deterministic.
- * Numerics: as loza_ssa_prefill with two-term weights; calls with many sequences and long windows on
- * key heads of more than 32 query heads take one-term weights, except that a query with fewer than
- * 128 live keys, and a query whose merged result reaches magnitude 1.97 in some column, is then
- * computed from the cache rows directly in fp32 (weights not rounded at all; a rare, slower path: one
- * workgroup walks all live keys of that query).
+ * Numerics: as loza_ssa_prefill, but the weights are not rounded (three bf16 terms hold an fp32 weight; w
+ * of the bound above is that of fp32 arithmetic, about 2^-23). Calls with many sequences and long windows
+ * on key heads of more than 32 query heads take one-term weights, except that a query with fewer than 128
+ * live keys, and a query whose merged result reaches magnitude 1.97 in some column, is then computed from
+ * the cache rows directly in fp32 (a rare, slower path: one workgroup walks all live keys of that query).
  */
 int loza_ssa_decode(const void *q, const void *kcache, const void *vcache, const int32_t *seqlens,
                     void *out, float *lse, int B, int Hq, int Hkv, int64_t S_max,

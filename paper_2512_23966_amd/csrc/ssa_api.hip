@@ -293,10 +293,10 @@ static int prefill_bf16(const void *q, const void *k, const void *v, void *out, 
             p.block_table = paging->block_table;
             p.page_shift = page_shift; p.max_pages = paging->max_pages; p.num_pages = (int)paging->num_pages;
         }
-        if (few_rows) return loza::launch_rows_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
+        if (few_rows) return loza::launch_rows_bf16(p, d_qk, d_v, alias, false, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
         return loza::launch_extend_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
     }
-    if (few_rows) return loza::launch_rows_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
+    if (few_rows) return loza::launch_rows_bf16(p, d_qk, d_v, alias, false, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
     return loza::launch_prefill_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
 }
 
@@ -757,7 +757,7 @@ static int decode_bf16(const void *q, const void *kcache, const void *vcache, co
     set_rescale_policy(p);
     if (plan.rows) {
         p.q_len = 1;
-        return loza::launch_rows_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
+        return loza::launch_rows_bf16(p, d_qk, d_v, alias, true, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
     }
     return loza::launch_decode_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
 }

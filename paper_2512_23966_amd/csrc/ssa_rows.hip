@@ -15,7 +15,9 @@
 //     rounded to bf16, slots 4..7 what that rounding lost (again bf16), and the A operand carries the
 //     four keys' values twice. One 16x16x32 instruction thus accumulates 16 keys with weights good to
 //     2^-17, at the price of one-term weights: no row has to be computed again because it is large or
-//     has few live keys.
+//     has few live keys. A decode takes what two terms leave as a third, in an instruction of its own: three
+//     bf16 terms hold all 24 bits of an fp32 weight (43 sequences of 1,024 live keys, wide shape: 33.0 us with
+//     it, 30.3 without; 8,192 live keys of one sequence 18.7 and 17.8; d = 128, 16 sequences: no difference).
 //   * each key row is read from LDS once for the scores and once (transposing) for the values per 16
 //     rows: LDS bandwidth bounds the loop (16 keys of the wide shape: 18 KB at 104 B/clk, 16 KB at 64
 //     B/clk and the incoming 18 KB: about 580 cycles per tile and compute unit).
@@ -91,7 +93,8 @@ struct RowsCfg {
     static_assert(LDS_BYTES <= 160 * 1024, "does not fit the 160 KB LDS");
 };
 
-template <int DQK, int DV, bool ALIAS, bool NT>
+// EXACT: three-term weights (decode)
+template <int DQK, int DV, bool ALIAS, bool NT, bool EXACT>
 __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
 {
     using C = RowsCfg<DQK, DV, ALIAS>;
@@ -309,20 +312,44 @@ __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
         u32x4 w;
         w[0] = pack_bf16(e4[0], e4[1]);
         w[1] = pack_bf16(e4[2], e4[3]);
-        w[2] = pack_bf16(e4[0] - __builtin_bit_cast(float, w[0] << 16), e4[1] - __builtin_bit_cast(float, w[0] & 0xffff0000u));
-        w[3] = pack_bf16(e4[2] - __builtin_bit_cast(float, w[1] << 16), e4[3] - __builtin_bit_cast(float, w[1] & 0xffff0000u));
-        const bf16x8 pb = __builtin_bit_cast(bf16x8, w);
-
-        // values: O^T[16 columns][16 rows] += V^T P^T, both terms of the weights in one instruction
+        auto lost = [](float x, uint32_t pair, int half) {        // what rounding x to that half of the pair lost
+            return x - __builtin_bit_cast(float, half ? pair & 0xffff0000u : pair << 16);
+        };
+        float r4[4];
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            const char *va = tile + vrd[cb & 3] + (cb >> 2) * 128;
-            const s16x4 v4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(va));
-            const u32x2 v2 = __builtin_bit_cast(u32x2, v4);
-            u32x4 a4;
-            a4[0] = v2[0]; a4[1] = v2[1]; a4[2] = v2[0]; a4[3] = v2[1];
-            const bf16x8 a = __builtin_bit_cast(bf16x8, a4);
-            o[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pb, o[cb], 0, 0, 0);
+        for (int e = 0; e < 4; ++e) r4[e] = lost(e4[e], w[e >> 1], e & 1);
+        w[2] = pack_bf16(r4[0], r4[1]);
+        w[3] = pack_bf16(r4[2], r4[3]);
+        const bf16x8 pb = __builtin_bit_cast(bf16x8, w);
+        u32x4 w3 = {0, 0, 0, 0};
+        if constexpr (EXACT) {
+            w3[0] = pack_bf16(lost(r4[0], w[2], 0), lost(r4[1], w[2], 1));
+            w3[1] = pack_bf16(lost(r4[2], w[3], 0), lost(r4[3], w[3], 1));
+        }
+
+        // values: O^T[16 columns][16 rows] += V^T P^T, two terms of the weights in one instruction
+        constexpr int GRP = EXACT ? 4 : 1;     // (the two instructions on one accumulator stand apart)
+#pragma unroll
+        for (int c0 = 0; c0 < CB; c0 += GRP) {
+            bf16x8 a[GRP];
+#pragma unroll
+            for (int x = 0; x < GRP; ++x) {
+                const int cb = c0 + x;
+                const char *va = tile + vrd[cb & 3] + (cb >> 2) * 128;
+                const s16x4 v4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(va));
+                const u32x2 v2 = __builtin_bit_cast(u32x2, v4);
+                u32x4 a4;
+                a4[0] = v2[0]; a4[1] = v2[1]; a4[2] = v2[0]; a4[3] = v2[1];
+                a[x] = __builtin_bit_cast(bf16x8, a4);
+            }
+#pragma unroll
+            for (int x = 0; x < GRP; ++x) o[c0 + x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], pb, o[c0 + x], 0, 0, 0);
+            // (half of this one's contraction is zeros; the shorter 16x16x16 must not follow on the same accumulators:
+            // a gap of a few instructions between the two shapes lost results of the first)
+            if constexpr (EXACT) {
+#pragma unroll
+                for (int x = 0; x < GRP; ++x) o[c0 + x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], __builtin_bit_cast(bf16x8, w3), o[c0 + x], 0, 0, 0);
+            }
         }
         // every LDS read of this stage is done before the next iteration's copies may land in it
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -441,11 +468,11 @@ __global__ __launch_bounds__(DV / 4 * 8) void ssa_rows_merge_kernel(const FwdPar
     }
 }
 
-template <int DQK, int DV, bool ALIAS, bool NT>
+template <int DQK, int DV, bool ALIAS, bool NT, bool EXACT>
 static hipError_t launch_rows_t(const FwdParams &p, hipStream_t stream)
 {
     using C = RowsCfg<DQK, DV, ALIAS>;
-    constexpr auto kern = ssa_rows_kernel<DQK, DV, ALIAS, NT>;
+    constexpr auto kern = ssa_rows_kernel<DQK, DV, ALIAS, NT, EXACT>;
     hipError_t e = allow_lds<kern>(C::LDS_BYTES);
     if (e != hipSuccess) return e;
     const int64_t blocks = (int64_t)p.n_splits * p.row_tiles * p.Hkv * p.B;
@@ -460,17 +487,18 @@ static hipError_t launch_rows_t(const FwdParams &p, hipStream_t stream)
 // query heads on a key head, 16 sequences, window 4096: 48.5 against 57.0 us). Several groups share the rows
 // through L2 and keep the default policy (with the hint, 43 sequences of the paper's pattern: 33.3 against 30.9 us).
 template <int DQK, int DV, bool ALIAS>
-static hipError_t launch_rows_d(FwdParams p, hipStream_t stream)
+static hipError_t launch_rows_d(FwdParams p, bool decode, hipStream_t stream)
 {
     const int64_t rows = (p.seqlens ? (int64_t)p.q_len : p.S) * p.G;
     p.row_tiles = (int)((rows + 15) / 16);
-    return p.row_tiles == 1 ? launch_rows_t<DQK, DV, ALIAS, true>(p, stream) : launch_rows_t<DQK, DV, ALIAS, false>(p, stream);
+    if (decode) return p.row_tiles == 1 ? launch_rows_t<DQK, DV, ALIAS, true, true>(p, stream) : launch_rows_t<DQK, DV, ALIAS, false, true>(p, stream);
+    return p.row_tiles == 1 ? launch_rows_t<DQK, DV, ALIAS, true, false>(p, stream) : launch_rows_t<DQK, DV, ALIAS, false, false>(p, stream);
 }
 
-hipError_t launch_rows_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream)
+hipError_t launch_rows_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, bool decode, hipStream_t stream)
 {
-    if (d_qk == 576 && d_v == 512 && alias) return launch_rows_d<576, 512, true>(p, stream);
-    if (d_qk == 128 && d_v == 128) return alias ? launch_rows_d<128, 128, true>(p, stream) : launch_rows_d<128, 128, false>(p, stream);
+    if (d_qk == 576 && d_v == 512 && alias) return launch_rows_d<576, 512, true>(p, decode, stream);
+    if (d_qk == 128 && d_v == 128) return alias ? launch_rows_d<128, 128, true>(p, decode, stream) : launch_rows_d<128, 128, false>(p, decode, stream);
     return hipErrorInvalidValue;
 }
 
