@@ -32,6 +32,7 @@
 #include <stdint.h>
 
 #include "ssa_device.h"
+#include "ssa_direct.h"
 #include "ssa_kernels.h"
 
 namespace loza {
@@ -89,8 +90,9 @@ struct RowsCfg {
     static constexpr int OROW = DV * 4 + 16;           // LDS bytes per row of a wave's partial output
     static constexpr int REGION = NST * STAGE > N * OROW ? NST * STAGE : N * OROW;
     static constexpr int OFF_ML = NW * REGION;         // float[NW][16][2]: reference maximum, sum
-    static constexpr int LDS_BYTES = OFF_ML + NW * 16 * 8;
-    static_assert(LDS_BYTES <= 160 * 1024, "does not fit the 160 KB LDS");
+    static constexpr int OFF_ODD = OFF_ML + NW * 16 * 8;   // uint32_t: finished rows that hold a NaN or an infinity
+    static constexpr int LDS_BYTES = OFF_ODD + 16;
+    static_assert(LDS_BYTES + 4096 <= 160 * 1024, "does not fit the 160 KB LDS");   // (and decode_row_direct's)
 };
 
 // EXACT: three-term weights (decode)
@@ -372,6 +374,9 @@ __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) *(f32x4 *)(op + cb * 64) = o[cb];
     }
+    uint32_t *odd = (uint32_t *)(smem + C::OFF_ODD);
+    constexpr bool CHECK = EXACT && !ALIAS;
+    if (CHECK && tid == 0) *odd = 0;
     __syncthreads();
     // wave w finishes rows 4 w .. 4 w + 3 of the block, 512 (or 4 x 128) columns at a time
     constexpr int LPR = DV / 8, RPI = 64 / LPR;   // lanes per row (8 columns each), rows per step
@@ -424,19 +429,45 @@ __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
             w[3] = pack_bf16(hi[2], hi[3]);
             *(u32x4 *)(p.out + o_row * DV + c) = w;
         }
+        if constexpr (CHECK) {
+            float z = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z += lo[e] * 0.f + hi[e] * 0.f;
+            if (z != 0.f) atomicOr(odd, 1u << rr);
+        }
         if (c == 0) p.lse[((int64_t)b * p.Hq + h) * Sq + qi] = (m_all + __builtin_amdgcn_logf(l_all)) * 0.69314718055994530942f;
+    }
+    if constexpr (CHECK) {
+        // An infinite value at a live key gives an infinity, but the lower terms of its weight may be 0 or negative
+        // and made it a NaN (so does the weight 0 of a masked key): such a query is computed again in fp32. (Where
+        // the values are part of the keys the score of such a key is not finite either, and a NaN is the result.)
+        if (p.n_splits == 1) {
+            lds_barrier();                         // (the stores of the results may still be on their way)
+            uint32_t left = *(volatile uint32_t *)odd;
+            if (left != 0) {                       // (what has been stored of those rows arrives first)
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+                __syncthreads();
+            }
+            for (; left != 0; left &= left - 1) {
+                const int64_t h = (int64_t)b * p.Hq + (int64_t)g * G + r0 + __builtin_ctz(left);
+                decode_row_direct<DQK, DV>(p, h, decode_keys(p, h));
+                __syncthreads();
+            }
+        }
     }
 }
 
 // Merge of the key splits of one decode query that ssa_rows_kernel left (log-sum-exp rule, fixed order):
 // DV / 4 threads of four columns each, times eight groups of splits that are added in LDS at the end (a
-// single chain over 64 splits took 23 us for 64 queries).
-template <int DV>
+// single chain over 64 splits took 23 us for 64 queries). With separate values, a result that holds a NaN or an
+// infinity is computed again in fp32 (see above).
+template <int DQK, int DV, bool ALIAS>
 __global__ __launch_bounds__(DV / 4 * 8) void ssa_rows_merge_kernel(const FwdParams p)
 {
     constexpr int TC = DV / 4, NG = 8;
     __shared__ f32x4 s_acc[NG][TC];
-    __shared__ float s_w[64], s_l[64];
+    __shared__ float s_w[64];
+    __shared__ int s_odd;
     const int64_t h = blockIdx.x;
     const int tc = threadIdx.x % TC, grp = threadIdx.x / TC, n = p.n_splits;
     const float *ml = p.part_ml + h * n * 4;
@@ -449,6 +480,7 @@ __global__ __launch_bounds__(DV / 4 * 8) void ssa_rows_merge_kernel(const FwdPar
         float ls = w * l;
         for (int d = 32; d > 0; d >>= 1) ls += __shfl_xor(ls, d, 64);
         s_w[s] = ls > 0.f ? w / ls : 0.f;          // (an empty cache gives 0)
+        if (s == 0) s_odd = 0;
         if (s == 0) p.lse[h] = (mx + __builtin_amdgcn_logf(ls)) * 0.69314718055994530942f;
     }
     __syncthreads();
@@ -458,14 +490,21 @@ __global__ __launch_bounds__(DV / 4 * 8) void ssa_rows_merge_kernel(const FwdPar
     for (int s = grp; s < n; s += NG) acc += s_w[s] * *(const f32x4 *)(po + (int64_t)s * DV);
     s_acc[grp][tc] = acc;
     __syncthreads();
-    if (grp == 0) {
+    if (grp != 0) return;
 #pragma unroll
-        for (int q = 1; q < NG; ++q) acc += s_acc[q][tc];
-        u32x2 w2;
-        w2[0] = pack_bf16(acc[0], acc[1]);
-        w2[1] = pack_bf16(acc[2], acc[3]);
-        *(u32x2 *)(p.out + h * DV + tc * 4) = w2;
+    for (int q = 1; q < NG; ++q) acc += s_acc[q][tc];
+    if constexpr (!ALIAS) {
+        if ((acc[0] * 0.f + acc[1] * 0.f) + (acc[2] * 0.f + acc[3] * 0.f) != 0.f) s_odd = 1;
+        lds_barrier();
+        if (*(volatile int *)&s_odd) {
+            decode_row_direct<DQK, DV>(p, h, decode_keys(p, h));
+            return;
+        }
     }
+    u32x2 w2;
+    w2[0] = pack_bf16(acc[0], acc[1]);
+    w2[1] = pack_bf16(acc[2], acc[3]);
+    *(u32x2 *)(p.out + h * DV + tc * 4) = w2;
 }
 
 template <int DQK, int DV, bool ALIAS, bool NT, bool EXACT>
@@ -479,7 +518,7 @@ static hipError_t launch_rows_t(const FwdParams &p, hipStream_t stream)
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), C::LDS_BYTES, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess || p.n_splits == 1) return e;
-    hipLaunchKernelGGL((ssa_rows_merge_kernel<DV>), dim3((unsigned)((int64_t)p.B * p.Hq)), dim3(DV / 4 * 8), 0, stream, p);
+    hipLaunchKernelGGL((ssa_rows_merge_kernel<DQK, DV, ALIAS>), dim3((unsigned)((int64_t)p.B * p.Hq)), dim3(DV / 4 * 8), 0, stream, p);
     return hipGetLastError();
 }
 
