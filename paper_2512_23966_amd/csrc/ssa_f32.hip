@@ -7,6 +7,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "ssa_kernels.h"
 
 namespace loza {
@@ -28,7 +30,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // took 80 us, this 9.
 // The online softmax takes each row's own running maximum in every tile, and a tile without a live key of a
 // row leaves that row's state exactly as it was: a row's result does not depend on the rows it shares a
-// workgroup with, and a decode gives the bits of the prefill's last row.
+// workgroup with, and a decode gives the bits of the prefill's last row. (The matrix instruction multiplies
+// every row's weight, 0 where the key is dead, with every value of the tile: a wave whose sums are not all
+// finite walks its keys again and adds each to the rows that see it.)
 // ND: blocks of 64 features and columns (the widths are cut to d_qk and d_v inside). VEC: widths that are
 // multiples of 4 (rows 16-byte aligned); otherwise the 16-byte loads are four guarded scalar ones.
 template <int ND>
@@ -111,61 +115,100 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
     };
 
     f32x4 o[ND][4];
-#pragma unroll
-    for (int d = 0; d < ND; ++d)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[d][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m = -INFINITY, l = 0.f;
-    int t = next_tile(0);
-    if (t <= wt1) load_keys(t);
-    while (t <= wt1) {
-        f32x4 vf[4][ND];                                        // values of keys 4 j4 + i
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float *vr = vb + (int64_t)live_key(t * N + 4 * j4 + i) * vstep;
-#pragma unroll
-            for (int d = 0; d < ND; ++d) vf[i][d] = load4(vr, d * 64 + n16 * 4, p.d_v);
-        }
-        f32x4 s4[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s4[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < ND * 4; ++kk)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s4[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kk][e], qf[kk][e], s4[e], 0, 0, 0);
-        const int t_next = next_tile(t + 1);
-        if (t_next <= wt1) load_keys(t_next);
-        f32x4 s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-        float cm = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int j = t * N + 4 * j4 + i;
-            const bool ok = (j <= i_row) & ((j < n_sink) | (j >= w_lo_row));
-            s[i] = ok ? s[i] * p.scale : -INFINITY;
-            cm = fmaxf(cm, s[i]);
-        }
-        cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
-        cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
-        const float m_new = fmaxf(m, cm);
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;   // a row without a live key so far
-        const float alpha = cm > m ? expf(m - m_use) : 1.f;
-        m = m_new;
-        float ps = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            s[i] = s[i] == -INFINITY ? 0.f : expf(s[i] - m_use);
-            ps += s[i];
-        }
-        l = l * alpha + ps;
+    float m, l;
+    auto walk = [&](auto by_key_c) {
+        constexpr bool BY_KEY = decltype(by_key_c)::value;
 #pragma unroll
         for (int d = 0; d < ND; ++d)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                o[d][e] *= alpha;
+            for (int e = 0; e < 4; ++e) o[d][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m = -INFINITY;
+        l = 0.f;
+        int t = next_tile(0);
+        if (t <= wt1) load_keys(t);
+        while (t <= wt1) {
+            f32x4 vf[4][ND];                                    // values of keys 4 j4 + i
+            if constexpr (!BY_KEY) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) o[d][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][d][e], s[i], o[d][e], 0, 0, 0);
+                for (int i = 0; i < 4; ++i) {
+                    const float *vr = vb + (int64_t)live_key(t * N + 4 * j4 + i) * vstep;
+#pragma unroll
+                    for (int d = 0; d < ND; ++d) vf[i][d] = load4(vr, d * 64 + n16 * 4, p.d_v);
+                }
             }
-        t = t_next;
+            f32x4 s4[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s4[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < ND * 4; ++kk)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s4[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kk][e], qf[kk][e], s4[e], 0, 0, 0);
+            const int t_next = next_tile(t + 1);
+            if (t_next <= wt1) load_keys(t_next);
+            f32x4 s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+            float cm = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = t * N + 4 * j4 + i;
+                const bool ok = (j <= i_row) & ((j < n_sink) | (j >= w_lo_row));
+                s[i] = ok ? s[i] * p.scale : -INFINITY;
+                cm = fmaxf(cm, s[i]);
+            }
+            cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
+            cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
+            const float m_new = fmaxf(m, cm);
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;   // a row without a live key so far
+            const float alpha = cm > m ? expf(m - m_use) : 1.f;
+            m = m_new;
+            float ps = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                s[i] = s[i] == -INFINITY ? 0.f : expf(s[i] - m_use);
+                ps += s[i];
+            }
+            l = l * alpha + ps;
+#pragma unroll
+            for (int d = 0; d < ND; ++d)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    o[d][e] *= alpha;
+                    if constexpr (!BY_KEY) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) o[d][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][d][e], s[i], o[d][e], 0, 0, 0);
+                    }
+                }
+            if constexpr (BY_KEY) {
+#pragma unroll 1
+                for (int jq = 0; jq < 4; ++jq)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int j = t * N + 4 * jq + i;
+                        const float w = __shfl(s[i], jq * 16 + n16, 64);
+                        if (!((j <= i_row) & ((j < n_sink) | (j >= w_lo_row)))) continue;
+                        const float *vr = vb + (int64_t)live_key(j) * vstep;
+#pragma unroll
+                        for (int d = 0; d < ND; ++d)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {        // columns of o[d][.][r]
+                                const f32x4 x = load4(vr, d * 64 + j4 * 16 + r * 4, p.d_v);
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) o[d][e][r] = fmaf(w, x[e], o[d][e][r]);
+                            }
+                    }
+            }
+            t = t_next;
+        }
+    };
+    walk(std::false_type{});
+    {
+        float odd[4] = {0.f, 0.f, 0.f, 0.f};                    // 0 if every accumulator is finite, else NaN
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) odd[i] = fmaf(o[d][e][i], 0.f, odd[i]);
+        if (__any((odd[0] + odd[1]) + (odd[2] + odd[3]) != 0.f)) walk(std::true_type{});
     }
 
     // ---- the waves' partial results meet in LDS ---------------------------------------------------------
@@ -199,7 +242,8 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
             l_all += a * ml[(w * 16 + rr) * 2 + 1];
             acc += a * *(const f32x4 *)(smem_f + (w * 16 + rr) * OROW + c);
         }
-        const float inv = l_all > 0.f ? 1.0f / l_all : 0.f;      // an empty cache gives 0
+        // (an empty cache gives 0 and -inf; live keys whose scores are all -inf have no softmax)
+        const float inv = L > 0 ? 1.0f / l_all : 0.f;
         const int64_t i = row / G;
         const int64_t h = (int64_t)g * G + (row - i * G);
         float *op = p.out + (((int64_t)b * Sq + i) * p.Hq + h) * p.d_v + c;
@@ -210,7 +254,7 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
             for (int e = 0; e < 4; ++e)
                 if (c + e < p.d_v) op[e] = acc[e] * inv;
         }
-        if (c == 0) p.lse[((int64_t)b * p.Hq + h) * Sq + i] = m_all + logf(l_all);
+        if (c == 0) p.lse[((int64_t)b * p.Hq + h) * Sq + i] = L > 0 && l_all == 0.f ? __builtin_nanf("") : m_all + logf(l_all);
     }
 }
 

@@ -45,3 +45,36 @@ def test_decode_values(gpu_device, monkeypatch, splits, Hq, Hkv, L, ns, win):
     assert int(torch.isinf(ref).sum()) == 2 * Hq and int(torch.isnan(ref).sum()) == 2 * Hq
     _same_kind(out, ref, 1e-2)
     assert bool(torch.isfinite(lse).all())
+
+
+@pytest.mark.parametrize("d_qk,d_v", [(64, 64), (100, 66), (200, 130), (256, 255)])
+@pytest.mark.parametrize("S,Hq,Hkv,ns,win", [(75, 2, 1, 5, 20), (140, 3, 3, 0, 33)])
+def test_f32_values(gpu_device, d_qk, d_v, S, Hq, Hkv, ns, win):
+    g = torch.Generator(device=gpu_device).manual_seed(6)
+    r = lambda *s: torch.randn(*s, generator=g, device=gpu_device)
+    q, k, v, scale = r(1, S, Hq, d_qk), r(1, S, Hkv, d_qk), r(1, S, Hkv, d_v), d_qk ** -0.5
+    inf, nan = float("inf"), float("nan")
+    v[0, 41, :, 3], v[0, 50, :, 5], v[0, 50, :, 3], v[0, 2, :, 60] = inf, nan, -inf, -inf
+    k[0, 44] = nan
+    q[0, 30, 0] = nan
+    out, lse = H.run_prefill(q, k, v, ns, win, scale)
+    kc, vc, lens = k, v, torch.tensor([S], dtype=torch.int32, device=gpu_device)
+    out_d, lse_d = H.run_decode_f32(q[:, S - 1].contiguous(), kc, vc, lens, ns, win, scale)
+    dev = gpu_device
+    ref = torch.empty(1, S, Hq, d_v, dtype=torch.float64, device=dev)
+    for i in range(S):
+        live = torch.tensor(sorted(set(range(min(ns, i + 1))) | set(range(max(0, i - win + 1), i + 1))), device=dev)
+        for h in range(Hq):
+            ref[0, i, h] = _reference(q[0, i, h], k[0, :, h * Hkv // Hq], v[0, :, h * Hkv // Hq], i, live, scale)
+    assert 0 < int(torch.isnan(ref).sum()) < ref.numel() // 2 and int(torch.isinf(ref).sum()) > 0
+    _same_kind(out, ref, 1e-5)
+    _same_kind(out_d, ref[:, S - 1], 1e-5)
+    assert torch.equal(torch.isnan(lse[0].T), torch.isnan(ref[0]).all(-1))
+
+
+def test_f32_scores_that_are_all_minus_infinity(gpu_device):
+    """Finite inputs whose products overflow: -inf for every live key has no softmax (NaN, not a silent 0)."""
+    q, k = torch.full((1, 20, 1, 8), 3e20, device=gpu_device), torch.full((1, 20, 1, 8), -3e20, device=gpu_device)
+    v = torch.ones(1, 20, 1, 8, device=gpu_device)
+    out, lse = H.run_prefill(q, k, v, 1, 4, 1.0)
+    assert bool(torch.isnan(out).all()) and bool(torch.isnan(lse).all())
