@@ -17,6 +17,7 @@ constexpr int F32_MAX_D = 256;
 constexpr int F32_WAVES = 4;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_dword __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte load, 4-byte aligned
 
 // Forward. A workgroup owns 16 query rows (position, head) of one key/value head; its NW waves share the
 // keys in tiles of 16 (tile number mod NW), each with its own softmax state and accumulators, and the
@@ -34,7 +35,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // every row's weight, 0 where the key is dead, with every value of the tile: a wave whose sums are not all
 // finite walks its keys again and adds each to the rows that see it.)
 // ND: blocks of 64 features and columns (the widths are cut to d_qk and d_v inside). VEC: widths that are
-// multiples of 4 (rows 16-byte aligned); otherwise the 16-byte loads are four guarded scalar ones.
+// multiples of 4 (rows 16-byte aligned); otherwise the 16-byte loads are aligned to 4 bytes, and at the end of a
+// row four scalar ones.
 template <int ND>
 struct F32RowsCfg {
     static constexpr int NW = ND <= 2 ? 8 : 4;         // (wider rows need the registers)
@@ -66,14 +68,19 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
     };
     const int i_min = (int)(pos0 + r0 / G), i_max = (int)(pos0 + ((r0 + 15 < R ? r0 + 15 : R - 1) / G));
 
-    auto load4 = [&](const float *row, int c, int d) -> f32x4 {
+    // elements c .. c + 3 of a row of d, 0 past its end; the wave's lanes ask for [base, base + span) together
+    auto load4 = [&](const float *row, int c, int d, int base, int span) -> f32x4 {
         f32x4 x = {0.f, 0.f, 0.f, 0.f};
         if constexpr (VEC) {
             if (c < d) x = *(const f32x4 *)(row + c);
+        } else if (base + span <= d) {
+            x = *(const f32x4_dword *)(row + c);
         } else {
+            // (a lane past the end loads the row's start and drops it: no branch around every load)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (c + e < d) x[e] = row[c + e];
+            for (int e = 0; e < 4; ++e) x[e] = row[c + e < d ? c + e : 0];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = c + e < d ? x[e] : 0.f;
         }
         return x;
     };
@@ -84,7 +91,7 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
     const int64_t q_row = ((int64_t)b * Sq + qi) * p.Hq + (int64_t)g * G + (row_c - qi * G);
     f32x4 qf[ND * 4];
 #pragma unroll
-    for (int kk = 0; kk < ND * 4; ++kk) qf[kk] = load4(p.q + q_row * p.d_qk, kk * 16 + j4 * 4, p.d_qk);
+    for (int kk = 0; kk < ND * 4; ++kk) qf[kk] = load4(p.q + q_row * p.d_qk, kk * 16 + j4 * 4, p.d_qk, kk * 16, 16);
 
     // live key tiles: [0, nA) and [wt0, wt1]; this wave takes those whose number is `wave` mod NW
     const int win_begin = window_begin(i_min < 0 ? 0 : i_min);
@@ -111,7 +118,7 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
     auto load_keys = [&](int t) {
         const float *kr = kb + (int64_t)live_key(t * N + n16) * kstep;
 #pragma unroll
-        for (int kk = 0; kk < ND * 4; ++kk) kf[kk] = load4(kr, kk * 16 + j4 * 4, p.d_qk);
+        for (int kk = 0; kk < ND * 4; ++kk) kf[kk] = load4(kr, kk * 16 + j4 * 4, p.d_qk, kk * 16, 16);
     };
 
     f32x4 o[ND][4];
@@ -133,7 +140,7 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
                 for (int i = 0; i < 4; ++i) {
                     const float *vr = vb + (int64_t)live_key(t * N + 4 * j4 + i) * vstep;
 #pragma unroll
-                    for (int d = 0; d < ND; ++d) vf[i][d] = load4(vr, d * 64 + n16 * 4, p.d_v);
+                    for (int d = 0; d < ND; ++d) vf[i][d] = load4(vr, d * 64 + n16 * 4, p.d_v, d * 64, 64);
                 }
             }
             f32x4 s4[4];
@@ -190,7 +197,7 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
                         for (int d = 0; d < ND; ++d)
 #pragma unroll
                             for (int r = 0; r < 4; ++r) {        // columns of o[d][.][r]
-                                const f32x4 x = load4(vr, d * 64 + j4 * 16 + r * 4, p.d_v);
+                                const f32x4 x = load4(vr, d * 64 + j4 * 16 + r * 4, p.d_v, d * 64, 64);
 #pragma unroll
                                 for (int e = 0; e < 4; ++e) o[d][e][r] = fmaf(w, x[e], o[d][e][r]);
                             }
