@@ -412,7 +412,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
     uint32_t sm_pk_lo[PRECISE ? 8 : 1];
     auto sm_mask = [&](f32x16 &s, const int j0) {
         // tiles the pattern cuts: causal diagonal, trailing edge of the window, end of the sink
-        // (j0 + N - 1 cannot overflow: j0 <= 0x3fffffff, the "no such tile" marker, masks everything)
+        // (j0 + N - 1 cannot overflow: j0 <= kNoTile, which masks everything)
         const bool interior = (j0 + N - 1 <= i_min) && ((j0 + N - 1 < n_sink) || (j0 >= w_lo_max));
         if (!interior) {
             const int jb = j0 + 4 * lh;
@@ -761,7 +761,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
             }
             rescale_tile(u & 1, flags);
             {
-                const int j0_next = u + 1 < nt ? key_tile(t_begin + u + 1) * N : 0x3fffffff;
+                const int j0_next = u + 1 < nt ? key_tile(t_begin + u + 1) * N : kNoTile;
                 const bool exact = u + 1 < p.exact_tiles;
                 if constexpr (PRECISE || !C::SPEC_SOFTMAX) {
                     value_tile(st_v, u & 1, vf, std::integral_constant<int, 1>{}, s, j0_next, (u + 1) & 1, exact ? 0.f : p.lazy_log2, [](int, int) {});
@@ -797,7 +797,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
             const int st_l = st_v == 0 ? NSTAGE - 1 : st_v - 1;
             if (WEAVE && u + AHEAD < nt) score_tile_copy(st_k, s, t_begin + u + AHEAD, st_l, row_now);
             else score_tile(st_k, s);
-            softmax_tile(s, u + 1 < nt ? key_tile(t_begin + u + 1) * N : 0x3fffffff, (u + 1) & 1,
+            softmax_tile(s, u + 1 < nt ? key_tile(t_begin + u + 1) * N : kNoTile, (u + 1) & 1,
                          u + 1 < p.exact_tiles ? 0.f : p.lazy_log2);
             st_v = st_k;
         }

@@ -249,7 +249,7 @@ static __device__ __forceinline__ bool ssa_d128_tile(const FwdParams &p, char *s
     };
     // address of step u (32 keys): half u & 1 of stage (u >> 1) % NST
     auto step_tile = [&](int u) { return (const char *)smem + ((u >> 1) & (NST - 1)) * C::STAGE + (u & 1) * 32 * ROW; };
-    auto step_key = [&](int u) { return (u >> 1) < nt ? key_tile(u >> 1) * N + (u & 1) * 32 : 0x3fffffff; };
+    auto step_key = [&](int u) { return (u >> 1) < nt ? key_tile(u >> 1) * N + (u & 1) * 32 : kNoTile; };
 
     f32x16 s[2][RB];                            // scores of the steps of either parity, exponentials in place
     u32x4 pk[2][2][RB];                         // [parity][key half]: rounded weights, B operands

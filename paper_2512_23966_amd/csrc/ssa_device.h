@@ -89,6 +89,10 @@ __device__ __forceinline__ int window_begin_of(int i, int window, int block)
     return window > qb ? 0 : (qb - window + 1) * block;
 }
 
+// In the place of a tile's first key where there is no such tile: behind every position a sequence can have
+// (at most 2^31 - 130), so the masks kill all of its 32 keys, whose numbers just do not overflow.
+constexpr int kNoTile = 0x7fffffff - 31;
+
 // Position of query row r (rows are position-major, G heads of a group together). A wave that starts has
 // nothing to hide an integer division by a run-time value behind (64-bit: more than a hundred dependent
 // instructions, half a dozen of them before the first load); group sizes are nearly always powers of two.
