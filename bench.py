@@ -176,7 +176,7 @@ def main() -> int:
         "prefill_tflops": round(prefill_tflops, 2),
         "decode_us": round(decode_ms * 1e3, 2),
         "decode_gbps": round(decode_gbps, 1),
-        "decode_num_splits": loza.loza_ssa_decode_num_splits(dc.B, dc.Hq, dc.Hkv, dc.S_max, dc.n_sink, dc.window),
+        "decode_num_splits": loza.loza_ssa_decode_kernel(dc.B, dc.Hq, dc.Hkv, dc.S_max, dc.d_qk, dc.n_sink, dc.window)[1],
         "roofline": {
             "kernel": "ssa_fwd_kernel<576,512> prefill", "bound": "mfma",
             "achieved": round(prefill_tflops, 2), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",

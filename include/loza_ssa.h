@@ -150,6 +150,29 @@ size_t loza_ssa_decode_workspace_bytes(int B, int Hq, int Hkv, int64_t S_max, in
 int loza_ssa_decode_num_splits(int B, int Hq, int Hkv, int64_t S_max, int64_t n_sink, int64_t window);
 
 /*
+ * Host-only (ours), for tests and tools: which kernels a bf16 call of these sizes runs. The pattern as the
+ * _blocks entry points take it; block = 1: n_sink and window in tokens. Negative (a loza_status) on sizes
+ * that the call itself refuses.
+ *   loza_ssa_forward_kernel   prefill (n_queries = S), calibration or extend (n_queries = q_len, S = S_max):
+ *                             a loza_kernel
+ *   loza_ssa_decode_kernel    a loza_kernel; *n_splits (may be NULL): the key splits it takes
+ *   loza_ssa_backward_split   how many key tiles of 64 (per sequence and key head) the dK/dV kernel cuts into
+ *                             chunks of rows for balance; *n_chunks, *n_whole (may be NULL): the chunks of
+ *                             each, and the work items of the launch that are not such chunks
+ */
+typedef enum {
+    LOZA_KERNEL_TILES = 1, /* tiles of 128 (decode: 64) query rows      */
+    LOZA_KERNEL_ROWS = 2,  /* few query rows: 16 a workgroup            */
+    LOZA_KERNEL_D128 = 3   /* width 128: tiles of 256 query rows        */
+} loza_kernel;
+int loza_ssa_forward_kernel(int B, int Hq, int Hkv, int64_t n_queries, int64_t S, int d_qk,
+                            int64_t sink_blocks, int64_t local_blocks, int64_t block);
+int loza_ssa_decode_kernel(int B, int Hq, int Hkv, int64_t S_max, int d_qk,
+                           int64_t sink_blocks, int64_t local_blocks, int64_t block, int *n_splits);
+int loza_ssa_backward_split(int B, int Hq, int Hkv, int64_t S, int d_qk, int d_v, int64_t sink_blocks,
+                            int64_t local_blocks, int64_t block, int v_aliases_k, int *n_chunks, int64_t *n_whole);
+
+/*
  * Host-only, no GPU involved: the live set of query i as at most two half-open key ranges,
  * [0, *sink_end) and [*win_begin, *win_end), disjoint and in order (sink_end <= win_begin).
  * This is the arithmetic the kernels enumerate tiles with (Eq. 4's pattern, "single uniform

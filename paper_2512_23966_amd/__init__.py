@@ -19,4 +19,5 @@ from .binding import (  # noqa: F401
     loza_ssa_decode_f32, loza_ssa_decode_blocks_f32,
     loza_ssa_calibration_alpha_grad, loza_ssa_calibration_alpha_grad_workspace_bytes,
     loza_ssa_decode_static, LOZA_DECODE_STATIC_BYTES,
+    loza_ssa_forward_kernel, loza_ssa_decode_kernel, loza_ssa_backward_split, KERNEL_TILES, KERNEL_ROWS, KERNEL_D128,
 )

@@ -35,7 +35,9 @@ EXPORTS = (
     "loza_ssa_decode_f32", "loza_ssa_decode_blocks_f32",
     "loza_ssa_calibration_alpha_grad", "loza_ssa_calibration_alpha_grad_workspace_bytes",
     "loza_ssa_decode_static",
+    "loza_ssa_forward_kernel", "loza_ssa_decode_kernel", "loza_ssa_backward_split",
 )
+KERNEL_TILES, KERNEL_ROWS, KERNEL_D128 = 1, 2, 3
 
 
 class LozaError(RuntimeError):
@@ -116,6 +118,12 @@ def lib() -> ctypes.CDLL:
         L.loza_ssa_backward_workspace_bytes.argtypes = [ci, ci, ci, i64, ci, ci, i64, i64, ci]
         L.loza_ssa_backward_workspace_bytes_blocks.restype = sz
         L.loza_ssa_backward_workspace_bytes_blocks.argtypes = [ci, ci, ci, i64, ci, ci, i64, i64, i64, ci]
+        L.loza_ssa_forward_kernel.restype = ci
+        L.loza_ssa_forward_kernel.argtypes = [ci, ci, ci, i64, i64, ci, i64, i64, i64]
+        L.loza_ssa_decode_kernel.restype = ci
+        L.loza_ssa_decode_kernel.argtypes = [ci, ci, ci, i64, ci, i64, i64, i64, ctypes.POINTER(ci)]
+        L.loza_ssa_backward_split.restype = ci
+        L.loza_ssa_backward_split.argtypes = [ci, ci, ci, i64, ci, ci, i64, i64, i64, ci, ctypes.POINTER(ci), ctypes.POINTER(i64)]
         L.loza_status_str.restype = ctypes.c_char_p
         L.loza_status_str.argtypes = [ci]
         _lib = L
@@ -215,6 +223,33 @@ def loza_ssa_live_pairs_blocks(S: int, sink_blocks: int, local_blocks, block: in
 
 def loza_ssa_decode_num_splits(B, Hq, Hkv, S_max, n_sink, window) -> int:
     return int(lib().loza_ssa_decode_num_splits(B, Hq, Hkv, int(S_max), int(n_sink), _win(window)))
+
+
+def _checked(value: int, where: str) -> int:
+    if value < 0:
+        raise LozaError(value, where)
+    return value
+
+
+def loza_ssa_forward_kernel(B, Hq, Hkv, n_queries, S, d_qk, sink, local, block=1) -> int:
+    """Which kernel (KERNEL_...) a bf16 prefill or extend of these sizes runs. Host only, like the two below."""
+    return _checked(lib().loza_ssa_forward_kernel(B, Hq, Hkv, int(n_queries), int(S), d_qk, int(sink), _win(local), int(block)),
+                    "loza_ssa_forward_kernel")
+
+
+def loza_ssa_decode_kernel(B, Hq, Hkv, S_max, d_qk, sink, local, block=1):
+    """(kernel, key splits) of a bf16 decode."""
+    n = ctypes.c_int()
+    k = lib().loza_ssa_decode_kernel(B, Hq, Hkv, int(S_max), d_qk, int(sink), _win(local), int(block), ctypes.byref(n))
+    return _checked(k, "loza_ssa_decode_kernel"), n.value
+
+
+def loza_ssa_backward_split(B, Hq, Hkv, S, d_qk, d_v, sink, local, block=1, v_aliases_k=False):
+    """(key tiles cut for balance, chunks of each, other work items) of a bf16 backward's dK/dV kernel."""
+    n, w = ctypes.c_int(), ctypes.c_int64()
+    t = lib().loza_ssa_backward_split(B, Hq, Hkv, int(S), d_qk, d_v, int(sink), _win(local), int(block), int(bool(v_aliases_k)),
+                                      ctypes.byref(n), ctypes.byref(w))
+    return _checked(t, "loza_ssa_backward_split"), n.value, w.value
 
 
 def loza_ssa_decode_workspace_bytes(B, Hq, Hkv, S_max, d_v, n_sink, window) -> int:

@@ -96,8 +96,11 @@ struct DecodePlan {
     int n_splits;
 };
 
-DecodePlan decode_plan(int B, int Hkv, int G, int64_t live, int d_qk, int most)
+DecodePlan decode_plan(int B, int Hq, int Hkv, int64_t S_max, int d_qk, int64_t n_sink, int64_t window)
 {
+    const int G = Hq / Hkv, most = decode_splits(B, Hq, Hkv, S_max, n_sink, window);
+    int64_t live = (n_sink < S_max ? n_sink : S_max) + (window < S_max ? window : S_max);
+    if (live > S_max) live = S_max;
     const int64_t groups = (G + 15) / 16, rows_base = (int64_t)B * Hkv * groups;
     const int64_t tile_base = (int64_t)B * Hkv * ((G + loza::decode_rows_per_tile() - 1) / loza::decode_rows_per_tile());
     auto cut = [&](int64_t base) { const int64_t n = kComputeUnits / base; return (int)(n < 1 ? 1 : n < most ? n : most); };
@@ -298,6 +301,19 @@ static int prefill_bf16(const void *q, const void *k, const void *v, void *out, 
     }
     if (few_rows) return loza::launch_rows_bf16(p, d_qk, d_v, alias, false, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
     return loza::launch_prefill_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
+}
+
+int loza_ssa_forward_kernel(int B, int Hq, int Hkv, int64_t n_queries, int64_t S, int d_qk,
+                            int64_t sink_blocks, int64_t local_blocks, int64_t block)
+{
+    if (int rc = check_common(B, Hq, Hkv, S, d_qk, 1, sink_blocks, local_blocks, 1.0f)) return rc;
+    if (int rc = check_blocks(sink_blocks, local_blocks, block)) return rc;
+    if (n_queries < 1 || n_queries > S) return LOZA_ERR_SHAPE;
+    if (!loza::bf16_width_supported(d_qk)) return LOZA_ERR_UNSUPPORTED;
+    const int G = Hq / Hkv;
+    if (loza::few_rows_bf16(B, Hkv, n_queries * G)) return LOZA_KERNEL_ROWS;
+    const Pattern pat = block_pattern(sink_blocks, local_blocks, block, S);
+    return d_qk == 128 && loza::d128_tiles_pay(B, Hkv, G, n_queries, S, pat.n_sink, pat.window, pat.block) ? LOZA_KERNEL_D128 : LOZA_KERNEL_TILES;
 }
 
 int loza_ssa_extend(const void *q, const void *kcache, const void *vcache, const int32_t *seqlens, void *out, float *lse,
@@ -614,6 +630,17 @@ static int backward_bf16(const void *q, const void *k, const void *v, const void
     return loza::launch_backward_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
 }
 
+int loza_ssa_backward_split(int B, int Hq, int Hkv, int64_t S, int d_qk, int d_v, int64_t sink_blocks,
+                            int64_t local_blocks, int64_t block, int v_aliases_k, int *n_chunks, int64_t *n_whole)
+{
+    loza::BwdParams p{};
+    if (int rc = backward_fill(p, B, Hq, Hkv, S, d_qk, d_v, sink_blocks, local_blocks, block, true, 1.0f, v_aliases_k != 0)) return rc;
+    backward_balance(p, d_qk, d_v, v_aliases_k != 0);
+    if (n_chunks) *n_chunks = p.n_split_kt > 0 ? p.split_chunks : 1;
+    if (n_whole) *n_whole = ((int64_t)p.split_kt0() * p.max_chunks + (S + 63) / 64 - p.split_kt0() - p.n_split_kt) * Hkv * B;
+    return p.n_split_kt;
+}
+
 int loza_ssa_backward(const void *q, const void *k, const void *v, const void *out, const float *lse,
                       const void *dout, void *dq, void *dk, void *dv,
                       int B, int Hq, int Hkv, int64_t S, int d_qk, int d_v,
@@ -707,6 +734,17 @@ size_t loza_ssa_decode_workspace_bytes(int B, int Hq, int Hkv, int64_t S_max, in
     return (size_t)B * Hq * n * ((size_t)d_v + 4) * sizeof(float);
 }
 
+int loza_ssa_decode_kernel(int B, int Hq, int Hkv, int64_t S_max, int d_qk,
+                           int64_t sink_blocks, int64_t local_blocks, int64_t block, int *n_splits)
+{
+    if (int rc = check_common(B, Hq, Hkv, S_max, d_qk, 1, sink_blocks, local_blocks, 1.0f)) return rc;
+    if (int rc = check_blocks(sink_blocks, local_blocks, block)) return rc;
+    if (!loza::bf16_width_supported(d_qk)) return LOZA_ERR_UNSUPPORTED;
+    const DecodePlan plan = decode_plan(B, Hq, Hkv, S_max, d_qk, sat_mul(sink_blocks, block), sat_mul(local_blocks, block));
+    if (n_splits) *n_splits = plan.n_splits;
+    return plan.rows ? LOZA_KERNEL_ROWS : LOZA_KERNEL_TILES;
+}
+
 static int decode_bf16(const void *q, const void *kcache, const void *vcache, const int32_t *seqlens,
                        void *out, float *lse, int B, int Hq, int Hkv, int64_t S_max,
                        int d_qk, int d_v, int64_t sink, int64_t local, int64_t block, bool blocks, float scale,
@@ -732,9 +770,7 @@ static int decode_bf16(const void *q, const void *kcache, const void *vcache, co
         return LOZA_ERR_ALIGN;
     const int G = Hq / Hkv;
     const int rows = loza::decode_rows_per_tile();
-    int64_t live = (n_sink < S_max ? n_sink : S_max) + (window < S_max ? window : S_max);
-    if (live > S_max) live = S_max;
-    const DecodePlan plan = decode_plan(B, Hkv, G, live, d_qk, decode_splits(B, Hq, Hkv, S_max, n_sink, window));
+    const DecodePlan plan = decode_plan(B, Hq, Hkv, S_max, d_qk, n_sink, window);
     const int n_splits = plan.n_splits;
     const int64_t row_tiles = (G + rows - 1) / rows;
     if (row_tiles * Hkv * B * decode_splits(B, Hq, Hkv, S_max, n_sink, window) > 2147483647LL) return LOZA_ERR_SHAPE;

@@ -1213,6 +1213,8 @@ bool bf16_shape_supported(int d_qk, int d_v, bool alias)
     return false;
 }
 
+bool bf16_width_supported(int d_qk) { return d_qk == 576 || d_qk == 128; }
+
 int prefill_rows_per_tile() { return 128; }
 int decode_rows_per_tile() { return 64; }
 
@@ -1220,10 +1222,15 @@ int decode_rows_per_tile() { return 64; }
 // 1.03 to 1.29 times as fast (32 heads, window 4096: 8,192 tokens 521 against 590 us; 2,048 tokens 78 against
 // 94) except where its tiles leave compute units idle (1,024 tokens of 32 heads are 128 of them: 46 against 44
 // us) or mostly pad (chunks of 300 tokens: 122 against 120 us).
+bool d128_tiles_pay(int B, int Hkv, int G, int64_t queries, int64_t S, int n_sink, int window, int block)
+{
+    const int64_t rows = queries * G, big = (rows + 255) / 256, small = (rows + 127) / 128;
+    return big * Hkv * B >= 160 && big * 256 * 4 <= small * 128 * 5;
+}
+
 static bool d128_tiles_pay(const FwdParams &p)
 {
-    const int64_t rows = (p.seqlens ? (int64_t)p.q_len : p.S) * p.G, big = (rows + 255) / 256, small = (rows + 127) / 128;
-    return big * p.Hkv * p.B >= 160 && big * 256 * 4 <= small * 128 * 5;
+    return d128_tiles_pay(p.B, p.Hkv, p.G, p.seqlens ? (int64_t)p.q_len : p.S, p.S, p.n_sink, p.window, p.block);
 }
 
 hipError_t launch_prefill_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream)

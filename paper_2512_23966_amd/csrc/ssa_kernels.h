@@ -53,6 +53,7 @@ static hipError_t allow_lds(int bytes)
 }
 
 bool bf16_shape_supported(int d_qk, int d_v, bool alias);
+bool bf16_width_supported(int d_qk);
 int prefill_rows_per_tile();
 int decode_rows_per_tile();
 hipError_t launch_prefill_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
@@ -62,6 +63,7 @@ hipError_t launch_decode_bf16(const FwdParams &p, int d_qk, int d_v, bool alias,
 bool pattern_needs_precise(const FwdParams &p);
 // Heads of width 128, many query rows (ssa_d128.hip): prefill (seqlens null) or extend.
 hipError_t launch_d128_bf16(const FwdParams &p, bool alias, hipStream_t stream);
+bool d128_tiles_pay(int B, int Hkv, int G, int64_t queries, int64_t S, int n_sink, int window, int block);
 // Few query rows (ssa_rows.hip): prefill (seqlens null), extend or decode (q_len = 1; n_splits key splits
 // and a merge; weights that are not rounded at all).
 hipError_t launch_rows_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, bool decode, hipStream_t stream);

@@ -1,0 +1,32 @@
+"""Which kernels a call runs, on the host: the rules' edges, and that no plan exceeds what its workspace is sized for."""
+import pytest
+
+import paper_2512_23966_amd as loza
+from paper_2512_23966_amd import KERNEL_D128, KERNEL_ROWS, KERNEL_TILES
+
+
+def test_few_rows_are_at_most_512_groups_of_16():
+    f = loza.loza_ssa_forward_kernel
+    assert f(1, 64, 1, 128, 5000, 576, 128, 1024) == KERNEL_ROWS
+    assert f(1, 64, 1, 129, 5000, 576, 128, 1024) == KERNEL_TILES
+    assert f(4, 32, 32, 64, 5000, 128, 128, 4096) == KERNEL_ROWS
+    assert f(1, 32, 32, 4096, 4096, 128, 128, 4096) == KERNEL_D128
+
+
+@pytest.mark.parametrize("d", [128, 576])
+@pytest.mark.parametrize("Hq,Hkv", [(64, 1), (32, 8), (128, 1), (6, 6)])
+@pytest.mark.parametrize("sink,local,block", [(128, 8192, 1), (1, 7, 128), (0, 1, 1), (5, None, 1)])
+def test_decode_plans_fit_their_workspace(d, Hq, Hkv, sink, local, block):
+    for B in (1, 2, 7, 40, 64, 129, 300):
+        for S in (1, 64, 5000, 262144):
+            kernel, n = loza.loza_ssa_decode_kernel(B, Hq, Hkv, S, d, sink, local, block)
+            assert kernel in (KERNEL_ROWS, KERNEL_TILES)
+            assert 1 <= n <= loza.loza_ssa_decode_num_splits(B, Hq, Hkv, S, sink * block, None if local is None else local * block)
+
+
+def test_refused_sizes():
+    for call in (lambda: loza.loza_ssa_forward_kernel(1, 3, 2, 8, 8, 128, 0, 1), lambda: loza.loza_ssa_forward_kernel(1, 2, 2, 9, 8, 128, 0, 1),
+                 lambda: loza.loza_ssa_decode_kernel(1, 2, 2, 8, 64, 0, 1), lambda: loza.loza_ssa_decode_kernel(0, 2, 2, 8, 128, 0, 1),
+                 lambda: loza.loza_ssa_backward_split(1, 96, 1, 8, 64, 64, 0, 1), lambda: loza.loza_ssa_backward_split(1, 2, 1, 8, 128, 128, 0, 0)):
+        with pytest.raises(loza.LozaError):
+            call()
