@@ -1218,14 +1218,29 @@ bool bf16_width_supported(int d_qk) { return d_qk == 576 || d_qk == 128; }
 int prefill_rows_per_tile() { return 128; }
 int decode_rows_per_tile() { return 64; }
 
-// Heads of width 128: the kernel of 256-row tiles (ssa_d128.hip) or the one of 128-row tiles here. The former is
-// 1.03 to 1.29 times as fast (32 heads, window 4096: 8,192 tokens 521 against 590 us; 2,048 tokens 78 against
-// 94) except where its tiles leave compute units idle (1,024 tokens of 32 heads are 128 of them: 46 against 44
-// us) or mostly pad (chunks of 300 tokens: 122 against 120 us).
+// Heads of width 128: the kernel of 256-row tiles (ssa_d128.hip), one workgroup a compute unit, or the one of
+// 128-row tiles here, two. The line is a time model of either in microseconds: rounds of workgroups times (start
+// and end of a tile, plus the keys it walks), fitted to the measured times of both (32 query heads; key heads,
+// tokens, sink + window: 256-row against 128-row tiles). The larger tile takes less time per key and row
+// (32, 8,192, 128 + 4096: 507 against 577 us; 8, 8,192, one and seven blocks of 128: 166 against 200), but its
+// rows span more positions, which matters when the window is short and few heads share a key (32, 8,192,
+// 16 + 256: 148 against 124; 8 key heads: 99 against 102), it costs more to start, and its last round is a whole
+// one (4,100 tokens are 544 tiles: 114 against 108 us in blocks of 128). With few tiles (160: 45.0 against 44.2
+// us; 168: 41.7 against 43.1) or mostly padded ones (chunks of 300 tokens: 122 against 120) it does not pay.
 bool d128_tiles_pay(int B, int Hkv, int G, int64_t queries, int64_t S, int n_sink, int window, int block)
 {
-    const int64_t rows = queries * G, big = (rows + 255) / 256, small = (rows + 127) / 128;
-    return big * Hkv * B >= 160 && big * 256 * 4 <= small * 128 * 5;
+    const int64_t rows = queries * G, big = (rows + 255) / 256, small = (rows + 127) / 128, heads = (int64_t)B * Hkv;
+    if (big * heads <= 160 || big * 256 * 4 > small * 128 * 5) return false;
+    // keys that the rows of a tile of M rows see between them, in tiles of N
+    auto keys = [&](int64_t M, int64_t N) {
+        const int64_t positions = (M + G - 1) / G;
+        int64_t span = (int64_t)window * block + positions - (block > 1 ? (positions < block ? positions : block) : 0);
+        span = (n_sink + N - 1) / N * N + (span < S ? span : S) + N;
+        return (double)(span < S + N ? span : S + N);
+    };
+    const int64_t rest = small * heads % 512;
+    const double rounds_big = (double)((big * heads + 255) / 256), rounds_small = small * heads / 512 + (rest == 0 ? 0.0 : rest <= 256 ? 0.7 : 1.0);
+    return rounds_big * (13.6 + 6.8 / G + 0.0259 * keys(256, 64)) <= rounds_small * (14.3 + 3.0 / G + 0.0351 * keys(128, 32));
 }
 
 static bool d128_tiles_pay(const FwdParams &p)

@@ -13,6 +13,21 @@ def test_few_rows_are_at_most_512_groups_of_16():
     assert f(1, 32, 32, 4096, 4096, 128, 128, 4096) == KERNEL_D128
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,queries,S,sink,local,block,kernel", [
+    (1, 32, 32, 8192, 8192, 16, 256, 1, KERNEL_TILES),      # 148 against 124 us: a short window, every head its own keys
+    (1, 32, 32, 8192, 8192, 128, 4096, 1, KERNEL_D128),     # 507 against 577
+    (1, 32, 8, 8192, 8192, 16, 256, 1, KERNEL_D128),        # 99 against 102
+    (1, 32, 8, 8192, 8192, 1, 7, 128, KERNEL_D128),         # 166 against 200
+    (1, 32, 32, 4100, 4100, 1, 7, 128, KERNEL_TILES),       # 114 against 108: two tiles a head beyond two rounds
+    (1, 32, 32, 4100, 4100, 128, 4096, 1, KERNEL_D128),     # 230 against 248
+    (4, 32, 32, 520, 8192, 16, 256, 1, KERNEL_TILES),       # 79 against 64
+    (1, 32, 32, 1100, 1100, 128, 4096, 1, KERNEL_TILES),    # 160 tiles: 45.7 against 45.6
+    (8, 32, 32, 300, 8192, 128, 4096, 1, KERNEL_TILES),     # mostly padding
+])
+def test_width_128_takes_the_larger_tiles_where_they_are_faster(B, Hq, Hkv, queries, S, sink, local, block, kernel):
+    assert loza.loza_ssa_forward_kernel(B, Hq, Hkv, queries, S, 128, sink, local, block) == kernel
+
+
 @pytest.mark.parametrize("d", [128, 576])
 @pytest.mark.parametrize("Hq,Hkv", [(64, 1), (32, 8), (128, 1), (6, 6)])
 @pytest.mark.parametrize("sink,local,block", [(128, 8192, 1), (1, 7, 128), (0, 1, 1), (5, None, 1)])

@@ -22,18 +22,20 @@ def _live_pages(L, q_len, ns, win, block, page):
     return sorted(set((np.nonzero(j)[0] // page).tolist()))
 
 
-# 8 row tiles of 256 rows on each of 24 key heads: the kernel that copies 64 keys at a time
+# enough tiles of 256 rows for the kernel that copies 64 keys at a time
 @pytest.mark.parametrize("alias", [False, True])
-@pytest.mark.parametrize("lens,q_len,ns,win,block,page", [
-    ([1500], 512, 32, 400, None, 32),     # the second half of the sink's 64 keys is dead
-    ([1500], 512, 0, 380, None, 32),      # so is the first half of the first window tile
-    ([1490, 1303], 512, 33, 450, None, 32),
-    ([1535], 512, 1, 13, 32, 32),         # block-granular
-    ([1700], 509, 70, 600, None, 64),
-    ([600], 512, 5, 90, None, 32),        # the chunk is nearly the whole sequence
+@pytest.mark.parametrize("lens,q_len,Hq,Hkv,ns,win,block,page", [
+    ([1500], 512, 96, 24, 32, 400, None, 32),     # the second half of the sink's 64 keys is dead
+    ([1500], 512, 96, 24, 0, 380, None, 32),      # so is the first half of the first window tile
+    ([1490, 1303], 512, 48, 12, 33, 450, None, 32),
+    ([1535], 512, 96, 24, 1, 13, 32, 32),         # block-granular
+    ([1700], 509, 96, 24, 70, 600, None, 64),
+    ([600], 512, 96, 6, 5, 90, None, 32),         # the chunk is nearly the whole sequence
 ])
-def test_d128_extend_reads_only_pages_with_a_live_key(gpu_device, alias, lens, q_len, ns, win, block, page):
-    Hq, Hkv, B = 96, 24, len(lens)
+def test_d128_extend_reads_only_pages_with_a_live_key(gpu_device, alias, lens, q_len, Hq, Hkv, ns, win, block, page):
+    B = len(lens)
+    cap = (max(lens) + page - 1) // page * page
+    assert loza.loza_ssa_forward_kernel(B, Hq, Hkv, q_len, cap, 128, ns, win, block or 1) == loza.KERNEL_D128
     g = torch.Generator(device=gpu_device).manual_seed(61)
     r = lambda *s: torch.randn(*s, generator=g, device=gpu_device).to(torch.bfloat16)
     max_pages = (max(lens) + page - 1) // page
