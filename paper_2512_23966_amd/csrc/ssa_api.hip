@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/loza_ssa.h"
@@ -523,24 +524,91 @@ static void backward_plan(loza::BwdParams &p)
     p.max_chunks = p.n_sink_kt > 0 ? (int)((hi - lo + 1 + ct - 1) / ct) : 1;
 }
 
-// The key-stationary kernel's work items (key tiles, chunks of sink tiles) take about the same time each,
-// and one workgroup fills a compute unit: what is left over after the last full round of 256 is cut into
-// chunks that fill the chip (16,384 tokens of 1 + 7 blocks of 128, absorbed MLA: 286 items ran two rounds,
-// 9.0 ms; 256 whole ones and 30 in 8 chunks each: 6.0). The chunks leave fp32 partial sums in `dq`, which
-// is free until the row-stationary kernel writes it (the workspace is sized without them); where that does
-// not hold them, the plan stays as it is.
+// Time of the key-stationary kernel's launch by a model, in row tiles of work: workgroups go to the eight XCDs
+// round-robin by number and there, in order, to the next of 32 compute units with room, which holds one of the
+// wide shape and two of width 128 (each of two then has 0.8 of its speed alone). Of the wide shape a row tile of a
+// chunk that is split for balance counts 1.2: it writes fp32 partial sums that are read back, and fewer
+// workgroups share the rows it streams. With these constants the model sides with the measured times of 130
+// plans, whole against split, but for one that it takes whole and loses 2 %.
+static float backward_time(const loza::BwdParams &p, bool wide)
+{
+    const int64_t n_kt = (p.S + 63) / 64, BH = (int64_t)p.B * p.Hkv, kt0 = p.split_kt0();
+    const int64_t whole = kt0 * p.max_chunks + (n_kt - kt0 - p.n_split_kt), split = (int64_t)p.n_split_kt * p.split_chunks;
+    float work[9216];                                                 // of one (sequence, key head), 0: an empty chunk
+    if (whole + split > 9216) return INFINITY;                        // (backward_balance asks for fewer)
+    for (int64_t i = 0; i < whole + split; ++i) {
+        int64_t kt, chunk = 0, ct = 0;
+        if (i >= whole) { kt = kt0 + (i - whole) / p.split_chunks; chunk = (i - whole) % p.split_chunks; }
+        else if (i < kt0 * p.max_chunks) { kt = i / p.max_chunks; chunk = i % p.max_chunks; ct = p.chunk_tiles; }
+        else kt = i - kt0 * p.max_chunks + kt0 + p.n_split_kt;
+        int lo, hi;
+        loza::bwd_key_tile_rows(p, (int)kt, lo, hi);
+        int64_t len = hi - lo + 1;
+        if (i >= whole) ct = (len + p.split_chunks - 1) / p.split_chunks;
+        if (ct > 0) len = len - chunk * ct < ct ? len - chunk * ct : ct;
+        work[i] = len <= 0 ? 0.f : (float)len * (i >= whole && wide ? 1.2f : 1.f) + 16.f;
+    }
+    const float shared = wide ? 1.f : 0.8f;
+    float longest = 0.f;
+    for (int xcd = 0; xcd < 8; ++xcd) {
+        // per compute unit: what its one or two workgroups have left at time `at`, and when the first is done
+        float left[2][32] = {}, at[32] = {}, next[32];
+        auto speed = [&](int c) { return left[0][c] > 0.f && left[1][c] > 0.f ? shared : 1.f; };
+        auto due = [&](int c) {
+            const float a = left[0][c], b = left[1][c], first = a > 0.f && (b <= 0.f || a < b) ? a : b;
+            next[c] = first > 0.f ? at[c] + first / speed(c) : 0.f;
+        };
+        int64_t id = xcd;
+        // (the kernel's own way from a workgroup's number to its work)
+        auto take = [&]() {
+            float w = 0.f;
+            for (; id < (whole + split) * BH && w == 0.f; id += 8) {
+                const int64_t n = id < whole * BH ? whole : split, x = id < whole * BH ? id : id - whole * BH, eighth = n * BH / 8;
+                const int64_t item = (x < eighth * 8 ? x % 8 * eighth + x / 8 : x) % n;
+                w = work[id < whole * BH ? item : whole + item];
+            }
+            return w;
+        };
+        for (int slot = 0; slot < (wide ? 1 : 2); ++slot)
+            for (int c = 0; c < 32; ++c) left[slot][c] = take();
+        for (int c = 0; c < 32; ++c) due(c);
+        for (float w = take(); w > 0.f; w = take()) {
+            const int c = (int)(std::min_element(next, next + 32) - next);
+            const float done = (next[c] - at[c]) * speed(c);
+            const int s = left[0][c] > 0.f && (left[1][c] <= 0.f || left[0][c] < left[1][c]) ? 0 : 1;
+            left[1 - s][c] -= left[1 - s][c] > 0.f ? done : 0.f;
+            left[s][c] = w;
+            at[c] = next[c];
+            due(c);
+        }
+        for (int c = 0; c < 32; ++c) {
+            const float a = left[0][c], b = left[1][c], m = a < b ? a : b;   // two together, then the longer one alone
+            const float end = at[c] + (m > 0.f ? m / shared : 0.f) + (a + b - 2.f * m);
+            if (end > longest) longest = end;
+        }
+    }
+    return longest;
+}
+
+// The key-stationary kernel's work items are key tiles and chunks of sink tiles: what is left over after the
+// last full round of 256 is cut into chunks that fill the chip where that ends sooner by the model above (16,384 tokens of 1 + 7 blocks of 128, absorbed MLA: 286 items ran two
+// rounds, 9.0 ms; 256 whole ones and 30 in 8 chunks each: 6.0. 16,384 tokens of 128 + 8192: 258 items, of which
+// the last are short; in chunks 57 ms forward and backward, whole 53). The chunks leave fp32 partial sums in
+// `dq`, which is free until the row-stationary kernel writes it (the workspace is sized without them); where
+// that does not hold them, the plan stays as it is.
 static void backward_balance(loza::BwdParams &p, int d_qk, int d_v, bool alias)
 {
     const int64_t n_kt = (p.S + 63) / 64, BH = (int64_t)p.B * p.Hkv, cus = kComputeUnits;
     const int64_t cols = alias ? d_qk : d_qk + d_v, room = (int64_t)p.B * p.S * p.Hq * d_qk * 2 / (64 * cols * 4);
     const int64_t kt0 = p.split_kt0(), total = (kt0 * p.max_chunks + n_kt - kt0) * BH, rest = total % cus;
+    if (total > 10 * cus) return;                                     // little to gain in the last of many rounds
     int lo, hi;
     loza::bwd_key_tile_rows(p, (int)(kt0 < n_kt ? kt0 : n_kt - 1), lo, hi);
     const int64_t len = hi - lo + 1;                                  // row tiles of the first tile to be split
     int64_t n_split = (rest + BH - 1) / BH;
     if (n_split > n_kt - kt0) n_split = n_kt - kt0;
     if (n_split < 1) return;
-    // time of the last rounds in units of a whole item, each chunk costing about a hundredth more
+    // how many chunks: last rounds in units of a whole item, each chunk a hundredth more, all items alike
     int64_t best_k = 1, best = INT64_MAX;
     for (int64_t k = 1; k <= 16 && len / k >= 32; ++k) {
         const int64_t t = ((n_split * BH * k + cus - 1) / cus) * 1000 / k + 10 * k;
@@ -556,7 +624,7 @@ static void backward_balance(loza::BwdParams &p, int d_qk, int d_v, bool alias)
         q.max_chunks = (hi - lo + q.chunk_tiles) / q.chunk_tiles;
     }
     const int64_t slots = BH * ((q.max_chunks > 1 ? (int64_t)q.n_sink_kt * q.max_chunks : 0) + n_split * best_k);
-    if (slots > room) return;
+    if (slots > room || backward_time(q, d_qk > 128) >= backward_time(p, d_qk > 128)) return;
     q.part = (float *)p.dq;
     p = q;
 }

@@ -39,6 +39,19 @@ def test_decode_plans_fit_their_workspace(d, Hq, Hkv, sink, local, block):
             assert 1 <= n <= loza.loza_ssa_decode_num_splits(B, Hq, Hkv, S, sink * block, None if local is None else local * block)
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,S,sink,local,block,split", [
+    (64, 1, 576, 16384, 1, 7, 128, (30, 8, 256)),           # backward 12.9 ms whole, 10.5 in chunks
+    (64, 1, 576, 16384, 128, 8192, 1, (0, 1, 258)),         # 53.1 whole (the last items are short), 56.8 in chunks
+    (64, 1, 576, 14000, 128, 2048, 1, (0, 1, 231)),         # 14.6 and 16.6: 231 items nearly fill the chip
+    (64, 1, 576, 8000, 128, 2048, 1, (123, 2, 16)),         # 11.2 and 8.2
+    (32, 8, 128, 5000, 0, 2500, 1, (0, 1, 632)),            # 0.79 and 0.84: two workgroups a compute unit
+    (32, 1, 128, 8000, 128, 1024, 1, (123, 2, 30)),         # 1.48 and 1.11
+])
+def test_backward_key_tiles_are_cut_where_that_ends_sooner(Hq, Hkv, d, S, sink, local, block, split):
+    d_v, shared = (512, True) if d == 576 else (128, False)
+    assert loza.loza_ssa_backward_split(1, Hq, Hkv, S, d, d_v, sink, local, block, shared) == split
+
+
 def test_refused_sizes():
     for call in (lambda: loza.loza_ssa_forward_kernel(1, 3, 2, 8, 8, 128, 0, 1), lambda: loza.loza_ssa_forward_kernel(1, 2, 2, 9, 8, 128, 0, 1),
                  lambda: loza.loza_ssa_decode_kernel(1, 2, 2, 8, 64, 0, 1), lambda: loza.loza_ssa_decode_kernel(0, 2, 2, 8, 128, 0, 1),
