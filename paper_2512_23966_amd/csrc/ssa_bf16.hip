@@ -849,6 +849,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
         // wave stores whole rows, past the L2's keys (14.0 thousand; prefill with 1 + 7 blocks 1.7 % faster).
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
+            if (r0 + rb * 32 >= R) continue;                   // (chunks of a few rows a head are mostly padding)
             const float rsum = s_lpart[M + rb * 32 + ln];
             const float inv = rsum > 0.f ? 1.0f / rsum : 0.f;  // a row without a live key gives 0
             char *op = smem + (rb * 32 + ln) * C::OUTROW + (vw * C::DVW + 4 * lh) * 2;
