@@ -5,11 +5,11 @@
 #include <stdint.h>
 #include <stdlib.h>
 
-#include <algorithm>
 #include <mutex>
 
 #include "../../include/loza_ssa.h"
 #include "ssa_kernels.h"
+#include "ssa_schedule.h"
 
 // Scratch memory of loza_ssa_decode_static: the split kernel's partial results, in the place of a
 // caller's workspace. One copy per GPU, at an address of its own on each; the name below is only a
@@ -524,12 +524,11 @@ static void backward_plan(loza::BwdParams &p)
     p.max_chunks = p.n_sink_kt > 0 ? (int)((hi - lo + 1 + ct - 1) / ct) : 1;
 }
 
-// Time of the key-stationary kernel's launch by a model, in row tiles of work: workgroups go to the eight XCDs
-// round-robin by number and there, in order, to the next of 32 compute units with room, which holds one of the
-// wide shape and two of width 128 (each of two then has 0.8 of its speed alone). Of the wide shape a row tile of a
-// chunk that is split for balance counts 1.2: it writes fp32 partial sums that are read back, and fewer
-// workgroups share the rows it streams. With these constants the model sides with the measured times of 130
-// plans, whole against split, but for one that it takes whole and loses 2 %.
+// Time of the key-stationary kernel's launch by the model of ssa_schedule.h, in row tiles of work: a compute unit
+// holds one workgroup of the wide shape and two of width 128 (each of two then has 0.8 of its speed alone). Of the
+// wide shape a row tile of a chunk that is split for balance counts 1.2: it writes fp32 partial sums that are
+// read back, and fewer workgroups share the rows it streams. With these constants the model sides with the
+// measured times of 130 plans, whole against split, but for one that it takes whole and loses 2 %.
 static float backward_time(const loza::BwdParams &p, bool wide)
 {
     const int64_t n_kt = (p.S + 63) / 64, BH = (int64_t)p.B * p.Hkv, kt0 = p.split_kt0();
@@ -548,44 +547,20 @@ static float backward_time(const loza::BwdParams &p, bool wide)
         if (ct > 0) len = len - chunk * ct < ct ? len - chunk * ct : ct;
         work[i] = len <= 0 ? 0.f : (float)len * (i >= whole && wide ? 1.2f : 1.f) + 16.f;
     }
-    const float shared = wide ? 1.f : 0.8f;
     float longest = 0.f;
     for (int xcd = 0; xcd < 8; ++xcd) {
-        // per compute unit: what its one or two workgroups have left at time `at`, and when the first is done
-        float left[2][32] = {}, at[32] = {}, next[32];
-        auto speed = [&](int c) { return left[0][c] > 0.f && left[1][c] > 0.f ? shared : 1.f; };
-        auto due = [&](int c) {
-            const float a = left[0][c], b = left[1][c], first = a > 0.f && (b <= 0.f || a < b) ? a : b;
-            next[c] = first > 0.f ? at[c] + first / speed(c) : 0.f;
-        };
         int64_t id = xcd;
-        // (the kernel's own way from a workgroup's number to its work)
-        auto take = [&]() {
+        const float t = loza::xcd_time(wide ? 1 : 2, 0.8f, [&]() {
             float w = 0.f;
             for (; id < (whole + split) * BH && w == 0.f; id += 8) {
+                // (the kernel's own way from a workgroup's number to its work)
                 const int64_t n = id < whole * BH ? whole : split, x = id < whole * BH ? id : id - whole * BH, eighth = n * BH / 8;
                 const int64_t item = (x < eighth * 8 ? x % 8 * eighth + x / 8 : x) % n;
                 w = work[id < whole * BH ? item : whole + item];
             }
             return w;
-        };
-        for (int slot = 0; slot < (wide ? 1 : 2); ++slot)
-            for (int c = 0; c < 32; ++c) left[slot][c] = take();
-        for (int c = 0; c < 32; ++c) due(c);
-        for (float w = take(); w > 0.f; w = take()) {
-            const int c = (int)(std::min_element(next, next + 32) - next);
-            const float done = (next[c] - at[c]) * speed(c);
-            const int s = left[0][c] > 0.f && (left[1][c] <= 0.f || left[0][c] < left[1][c]) ? 0 : 1;
-            left[1 - s][c] -= left[1 - s][c] > 0.f ? done : 0.f;
-            left[s][c] = w;
-            at[c] = next[c];
-            due(c);
-        }
-        for (int c = 0; c < 32; ++c) {
-            const float a = left[0][c], b = left[1][c], m = a < b ? a : b;   // two together, then the longer one alone
-            const float end = at[c] + (m > 0.f ? m / shared : 0.f) + (a + b - 2.f * m);
-            if (end > longest) longest = end;
-        }
+        });
+        if (t > longest) longest = t;
     }
     return longest;
 }

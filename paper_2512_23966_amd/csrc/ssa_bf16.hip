@@ -42,6 +42,7 @@
 #include "ssa_device.h"
 #include "ssa_direct.h"
 #include "ssa_kernels.h"
+#include "ssa_schedule.h"
 
 namespace loza {
 
@@ -1220,28 +1221,48 @@ int prefill_rows_per_tile() { return 128; }
 int decode_rows_per_tile() { return 64; }
 
 // Heads of width 128: the kernel of 256-row tiles (ssa_d128.hip), one workgroup a compute unit, or the one of
-// 128-row tiles here, two. The line is a time model of either in microseconds: rounds of workgroups times (start
-// and end of a tile, plus the keys it walks), fitted to the measured times of both (32 query heads; key heads,
-// tokens, sink + window: 256-row against 128-row tiles). The larger tile takes less time per key and row
-// (32, 8,192, 128 + 4096: 507 against 577 us; 8, 8,192, one and seven blocks of 128: 166 against 200), but its
-// rows span more positions, which matters when the window is short and few heads share a key (32, 8,192,
-// 16 + 256: 148 against 124; 8 key heads: 99 against 102), it costs more to start, and its last round is a whole
-// one (4,100 tokens are 544 tiles: 114 against 108 us in blocks of 128). With few tiles (160: 45.0 against 44.2
-// us; 168: 41.7 against 43.1) or mostly padded ones (chunks of 300 tokens: 122 against 120) it does not pay.
+// 128-row tiles here, two. The line is a time model of either in microseconds: start and end of a tile plus the
+// keys it walks, fitted to the measured times of both (32 query heads; key heads, tokens, sink + window: 256-row
+// against 128-row tiles). The larger tile takes less time per key and row (32, 8,192, 128 + 4096: 507 against 577
+// us; 8, 8,192, one and seven blocks of 128: 166 against 200), but its rows span more positions, which matters
+// when the window is short and few heads share a key (32, 8,192, 16 + 256: 148 against 124; 8 key heads: 99
+// against 102), it costs more to start, and its last round is a whole one (4,100 tokens are 544 tiles: 114 against
+// 108 us in blocks of 128). With few tiles (160: 45.0 against 44.2 us; 168: 41.7 against 43.1) or mostly padded
+// ones (chunks of 300 tokens: 122 against 120) it does not pay.
+// A prefill, or a chunk that (nearly) fills its cache, starts at position 0: its first tiles have few keys, and the
+// launch is simulated (128 heads of their own keys: 512 tokens 32 against 37 us, 800 tokens, 128 + 512, 80 against
+// 75). Otherwise, and from eight rounds on, every tile has a full window, and rounds are counted. The cache's
+// capacity decides nothing else: a paged and a contiguous cache take the same kernel.
 bool d128_tiles_pay(int B, int Hkv, int G, int64_t queries, int64_t S, int n_sink, int window, int block)
 {
     const int64_t rows = queries * G, big = (rows + 255) / 256, small = (rows + 127) / 128, heads = (int64_t)B * Hkv;
     if (big * heads <= 160 || big * 256 * 4 > small * 128 * 5) return false;
-    // keys that the rows of a tile of M rows see between them, in tiles of N
+    auto cost_big = [&](double keys) { return 13.1 + 7.6 / G + 0.0259 * keys; };
+    auto cost_small = [&](double keys) { return 14.3 + 3.5 / G + 0.0351 * keys; };
+    if (S * 8 <= queries * 9 && small * heads <= 4096) {
+        // keys that row tile rt of M rows walks, in tiles of N (as the kernels enumerate them)
+        auto keys = [&](int64_t rt, int64_t M, int64_t N) {
+            const int64_t i0 = rt * M / G, i1 = (rt * M + M < rows ? rt * M + M - 1 : rows - 1) / G;
+            const int64_t nA = ((n_sink < i1 + 1 ? n_sink : i1 + 1) + N - 1) / N;
+            const int64_t wt0 = window_begin_of((int)i0, window, block) / N, wt1 = i1 / N;
+            return (double)(wt0 <= nA ? wt1 + 1 : nA + wt1 - wt0 + 1) * N;
+        };
+        // (one XCD stands for all: each takes an eighth of the tiles, the latest of a head first)
+        auto walk = [&](int64_t tiles, int per_cu, float shared, auto &&cost) {
+            int64_t i = 0;
+            const int64_t n = (tiles * heads + 7) / 8;
+            return xcd_time(per_cu, shared, [&]() { return i < n ? (float)cost(tiles - 1 - i++ % tiles) : 0.f; });
+        };
+        return walk(big, 1, 1.f, [&](int64_t rt) { return cost_big(keys(rt, 256, 64)); }) <=
+               walk(small, 2, 0.72f, [&](int64_t rt) { return 0.72 * cost_small(keys(rt, 128, 32)); });
+    }
     auto keys = [&](int64_t M, int64_t N) {
         const int64_t positions = (M + G - 1) / G;
-        int64_t span = (int64_t)window * block + positions - (block > 1 ? (positions < block ? positions : block) : 0);
-        span = (n_sink + N - 1) / N * N + (span < S ? span : S) + N;
-        return (double)(span < S + N ? span : S + N);
+        return (double)((n_sink + N - 1) / N * N + N + (int64_t)window * block + positions - (block > 1 ? (positions < block ? positions : block) : 0));
     };
     const int64_t rest = small * heads % 512;
     const double rounds_big = (double)((big * heads + 255) / 256), rounds_small = small * heads / 512 + (rest == 0 ? 0.0 : rest <= 256 ? 0.7 : 1.0);
-    return rounds_big * (13.6 + 6.8 / G + 0.0259 * keys(256, 64)) <= rounds_small * (14.3 + 3.0 / G + 0.0351 * keys(128, 32));
+    return rounds_big * cost_big(keys(256, 64)) <= rounds_small * cost_small(keys(128, 32));
 }
 
 static bool d128_tiles_pay(const FwdParams &p)

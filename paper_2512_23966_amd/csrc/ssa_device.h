@@ -83,7 +83,7 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 
 // First key of the window of query i: the window holds the `window` most recent blocks of `block`
 // tokens, the query's own block included (block = 1: the `window` most recent tokens).
-__device__ __forceinline__ int window_begin_of(int i, int window, int block)
+__host__ __device__ __forceinline__ int window_begin_of(int i, int window, int block)
 {
     const int qb = block == 1 ? i : i / block;
     return window > qb ? 0 : (qb - window + 1) * block;
