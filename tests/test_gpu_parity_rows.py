@@ -87,14 +87,15 @@ def test_prefill_f32_widths(gpu_device, d_qk, d_v, S, Hq, Hkv, ns, win):
     H.compare_prefill(q, k, v, out, lse, rb, rh, ri, ns, win, scale, f"f32 widths {d_qk},{d_v} S{S}")
 
 
-# Heads of width 128, many rows: 256-row tiles (at least 160 of them) and the 128-row tiles below that; ragged
-# ends, sink and window edges inside a step of 32 keys, whole tiles of two-term weights, shared and separate values
+# Heads of width 128, more rows than that: tiles of 128 rows (the 256-row kernel's cases are in
+# test_gpu_parity_kernels_by_size.py); ragged ends, sink and window edges inside a step of 32 keys, whole tiles of
+# two-term weights, shared and separate values
 @pytest.mark.parametrize("B,S,Hq,Hkv,alias,ns,win,block", [
-    (2, 277, 160, 40, False, 37, 70, None),      # 400 tiles; the last row tile is ragged
+    (2, 277, 160, 40, False, 37, 70, None),      # the last row tile is ragged
     (1, 530, 128, 64, True, 0, 200, None),
     (1, 600, 96, 96, False, 1, 3, 48),
-    (3, 300, 64, 64, False, 128, None, None),    # 2 tiles a head, mostly padding: the 128-row kernel
-    (1, 300, 40, 40, False, 5, 33, None),        # too few tiles: the 128-row kernel
+    (3, 300, 64, 64, False, 128, None, None),    # a last tile of 44 rows
+    (1, 300, 40, 40, False, 5, 33, None),
 ])
 def test_d128_prefill_tiles(gpu_device, B, S, Hq, Hkv, alias, ns, win, block):
     q, k = _rand((B, S, Hq, 128), 11, gpu_device), _rand((B, S, Hkv, 128), 12, gpu_device)
@@ -107,7 +108,7 @@ def test_d128_prefill_tiles(gpu_device, B, S, Hq, Hkv, alias, ns, win, block):
 
 
 def test_d128_extend_paged_of_32_rows(gpu_device):
-    """A stage of 64 keys straddles pages of 32 rows; peaked rows take the two-term pass."""
+    """Pages of 32 rows; peaked rows take the two-term pass."""
     B, q_len, H_, S_max, page, ns, win, scale = 2, 500, 48, 640, 32, 40, 150, 128 ** -0.5
     lens_h = [S_max - 3, 555]
     q, kc, vc = _rand((B, q_len, H_, 128), 14, gpu_device), _rand((B, S_max, H_, 128), 15, gpu_device), _rand((B, S_max, H_, 128), 16, gpu_device)
