@@ -263,13 +263,15 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
             bwd_key_tile_rows(p, last < n_kt - 1 ? last : n_kt - 1, a_lo, a_hi);
             if (a_lo >= yt_begin && a_lo < yt_end) yt_start = a_lo;
         } else if (is_split) {
-            // (an XCD runs all chunks of 32 / split_chunks key tiles at a time: those of equal number go together)
-            const int kt0 = p.split_kt0(), grp = p.split_chunks < 32 ? 32 / p.split_chunks : 1;
-            const int last = kt0 + ((xt - kt0) / grp) * grp + grp - 1, end = kt0 + p.n_split_kt - 1;
-            int a_lo, a_hi;
-            bwd_key_tile_rows(p, last < end ? last : end, a_lo, a_hi);
-            a_lo += chunk * ((a_hi - a_lo + p.split_chunks) / p.split_chunks);
-            if (a_lo >= yt_begin && a_lo < yt_end) yt_start = a_lo;
+            // (an XCD runs all chunks of 32 / split_chunks key tiles at a time: those of equal number go together,
+            // unless chunks are so short that the tiles' own shift has them start where other chunks do)
+            const int kt0 = p.split_kt0(), grp = p.split_chunks < 32 ? 32 / p.split_chunks : 1, end = kt0 + p.n_split_kt - 1;
+            const int first = kt0 + ((xt - kt0) / grp) * grp, last = first + grp - 1 < end ? first + grp - 1 : end;
+            int f_lo, a_lo, a_hi;
+            bwd_key_tile_rows(p, first, f_lo, a_hi);
+            bwd_key_tile_rows(p, last, a_lo, a_hi);
+            const int ct = (a_hi - a_lo + p.split_chunks) / p.split_chunks, start = a_lo + chunk * ct;
+            if (a_lo - f_lo < ct && start >= yt_begin && start < yt_end) yt_start = start;
         }
     }
     const int yt_wrap = yt_begin + nt;
