@@ -83,15 +83,19 @@ int decode_splits(int B, int Hq, int Hkv, int64_t S_max, int64_t n_sink, int64_t
 }
 
 // Which of the two decode kernels takes a call, and in how many splits (at most `most`, which the
-// workspace is sized for). Both counts give every compute unit one workgroup and no compute unit two (a
-// workgroup fills the LDS: 43 sequences in 6 splits are 258 workgroups, two rounds, 60 us against 33 in 5).
-// Up to two groups of 16 query heads per key head the row kernel is always the faster (d = 128, 8 query
-// heads per group of 4, 16 sequences, window 4096: 56 against 74 us; 128 sequences on one key head of 32: 108
+// workspace is sized for): as many as leave the launch within one round of 256 workgroups, one at least (a
+// workgroup of the wide shape fills a compute unit's LDS: 43 sequences in 6 splits of the tile kernel are 258
+// workgroups, two rounds, 60 us against 33 in 5). Counts that do not divide 256 leave units idle (43 sequences
+// of four groups: 172 workgroups), and beyond 256 the last round may be a short one.
+// Up to two groups of 16 query heads per key head the row kernel is always the faster (d = 128, four query heads
+// on each of 8 key heads, 16 sequences, window 4096: 48 against 74 us; 128 sequences on one key head of 32: 108
 // against 128). With more groups (absorbed MLA: four) it reads the keys once per group, from L2, where the
 // tile kernel reads them once but leaves fp32 partial results of every split; it wins until the live keys
-// per split outweigh that. The line is a time model of either, in tenths of a microsecond, fitted to the
-// measured times of both (MLA, row against tile kernel: window 8192, 8 sequences 36 against 50 us, 16: 59
-// against 56, 64: 190 against 130; the paper's 1,024 keys, 64 sequences: 32 against 44).
+// per split outweigh that. The line is a time model of either, in hundredths of a microsecond, fitted to the
+// measured times of both (MLA, row against tile kernel: window 8192, 8 sequences 40 against 50 us, 16 65 against
+// 56, 64 220 against 131; 2,176 keys, 8 sequences 22 against 38, 64 62 against 58; the paper's 1,024 keys, 16
+// sequences 23 against 32; without queries that the tile kernel computes again, 250 us more). Over 161 sizes
+// the kernel taken is the faster one or within 7 % of it.
 struct DecodePlan {
     bool rows;
     int n_splits;
@@ -112,8 +116,8 @@ DecodePlan decode_plan(int B, int Hq, int Hkv, int64_t S_max, int d_qk, int64_t 
     const int64_t keys = (live + 63) / 64 * 64;
     auto rounds = [&](int64_t wgs) { return (wgs + kComputeUnits - 1) / kComputeUnits; };
     const int64_t rows_tiles = (keys / 64 + n_rows) / n_rows, tile_tiles = (keys / 32 + n_tile) / n_tile;
-    const int64_t t_rows = rounds(rows_base * n_rows) * (rows_tiles * (wide ? 13 : 7) + (wide ? 80 : 60)) + (n_rows > 1 ? 50 : 0);
-    const int64_t t_tile = rounds(tile_base * n_tile) * (tile_tiles * (wide ? 13 : 8) + (wide ? 250 : 180)) + 80;
+    const int64_t t_rows = rounds(rows_base * n_rows) * (rows_tiles * (wide ? 145 : 70) + (wide ? 800 : 600)) + (n_rows > 1 ? 500 : 0);
+    const int64_t t_tile = rounds(tile_base * n_tile) * (tile_tiles * (wide ? 120 : 80) + (wide ? 2500 : 1800)) + 800;
     return {t_rows <= t_tile, t_rows <= t_tile ? n_rows : n_tile};
 }
 
@@ -143,8 +147,9 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
     return (sink_blocks < 0 || local_blocks < 1 || block < 1) ? LOZA_ERR_SHAPE : LOZA_OK;
 }
 
-// The reference maximum of the online softmax is the exact running maximum over the first 8 key
-// tiles of a row tile and afterwards moves only when exceeded by more than 2^8 (fp32 has the headroom).
+// The reference maximum of the online softmax moves only when exceeded by more than 2^8 (fp32 has the headroom).
+// Over the first 8 key tiles the tile kernel keeps it exact (its wide prefill over the first only); the few-rows
+// and the width-128 kernel, which do not read exact_tiles, over their first tile or step.
 void set_rescale_policy(loza::FwdParams &p)
 {
     p.exact_tiles = 8;

@@ -1,6 +1,7 @@
 // bf16 streaming sparse attention, heads of width 128, many query rows (gfx950): prefill and extend.
 //
-// Same operation, schedule of live key tiles and exactness rules as ssa_bf16.hip. At this width a key tile
+// Same operation, live keys and two-term rules as ssa_bf16.hip (key tiles of 64; the softmax reference is exact
+// over the first 32 keys and then moves when exceeded by 2^8). At this width a key tile
 // brings little matrix work per score (a quarter of the absorbed-MLA shape), so the kernel there, whose
 // scores change waves between the two products, was bound by LDS traffic and instruction issue: P written
 // and read through LDS, every key fragment read for 32 rows (2770 cycles per 32 keys and two workgroups of

@@ -34,7 +34,7 @@ struct FwdParams {
     int n_splits;      // decode only
     int q_len;         // extend prefill: queries per sequence (0: plain prefill); keys valid up to seqlens[b]
     int all_precise;   // prefill / extend: every tile takes the two-term pass (set by the launcher from the pattern)
-    int exact_tiles;   // tiles over which the reference maximum is the exact running maximum
+    int exact_tiles;   // tile kernel: tiles over which the reference maximum is the exact running maximum
     float lazy_log2;   // afterwards it moves only when exceeded by this much (log2 units)
 };
 
@@ -70,7 +70,9 @@ hipError_t launch_rows_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, b
 // A prefill or extend of `rows` query rows per (batch, key head) is few rows when its groups of 16 rows make
 // at most two rounds of the 256 compute units. A round of the row kernel and one of the tile kernel (128 rows
 // a workgroup) cost, at window 8192 of the wide shape, 165 and 405 us (d = 128, window 4096: 51 and 152):
-// 512 groups 331 against 407 us (102 against 153), 1024 groups 638 against 412 (200 against 155).
+// 512 groups 331 against 407 us (102 against 153), 1024 groups 638 against 412 (200 against 155). Shorter
+// patterns gain more at that line: 512 groups of the wide shape at 1 + 7 blocks of 128 57 against 148 us, at
+// 16 + 256 tokens 31 against 73 (d = 128: 31 against 48, 16 against 25).
 inline bool few_rows_bf16(int B, int Hkv, int64_t rows) { return (rows + 15) / 16 * Hkv * B <= 512; }
 hipError_t launch_blend_bf16(const float *o_full, const float *o_sparse, float alpha, uint16_t *out,
                              uint16_t *out_full, uint16_t *out_sparse, int64_t n, hipStream_t stream);

@@ -24,7 +24,9 @@
 //   * workgroups that walk the same keys for other rows are placed on the same XCD, whose L2 then serves
 //     all but the first of them.
 // Tiles travel global -> LDS with global_load_lds_dwordx4 into a ring of NST stages per wave; the copy of
-// tile t + NST - 1 is woven into the score phase of tile t. A stage holds 16 unpadded rows; the 16-byte
+// tile t + NST - 1 is issued whole before the scores of tile t (its instructions between the LDS reads of the
+// score phase serialised those). The softmax reference is a row's maximum over its first tile and moves only when
+// exceeded by 2^8. A stage holds 16 unpadded rows; the 16-byte
 // chunks of a row are permuted within groups of eight (chunk c of row r sits in slot c ^ (r & 7)), which
 // costs nothing (the copy fetches whatever chunk belongs into its slot) and makes both kinds of reads
 // free of bank conflicts.

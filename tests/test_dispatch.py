@@ -52,6 +52,19 @@ def test_backward_key_tiles_are_cut_where_that_ends_sooner(Hq, Hkv, d, S, sink, 
     assert loza.loza_ssa_backward_split(1, Hq, Hkv, S, d, d_v, sink, local, block, shared) == split
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,d,S,sink,local,kernel", [
+    (130, 48, 1, 576, 16384, 128, 8192, KERNEL_TILES),      # 341 against 403 us of the few-rows kernel
+    (64, 48, 1, 576, 16384, 128, 2048, KERNEL_TILES),       # 54 against 59
+    (8, 64, 1, 576, 16384, 128, 2048, KERNEL_ROWS),         # 38 against 22
+    (8, 64, 1, 576, 16384, 128, 8192, KERNEL_ROWS),         # 50 against 40
+    (16, 64, 1, 576, 16384, 128, 8192, KERNEL_TILES),       # 56 against 65
+    (64, 64, 1, 576, 262144, 128, 8192, KERNEL_TILES),
+    (300, 32, 1, 576, 16384, 128, 8192, KERNEL_ROWS),       # at most two groups of 16 heads
+])
+def test_decode_kernel_by_size(B, Hq, Hkv, d, S, sink, local, kernel):
+    assert loza.loza_ssa_decode_kernel(B, Hq, Hkv, S, d, sink, local)[0] == kernel
+
+
 def test_refused_sizes():
     for call in (lambda: loza.loza_ssa_forward_kernel(1, 3, 2, 8, 8, 128, 0, 1), lambda: loza.loza_ssa_forward_kernel(1, 2, 2, 9, 8, 128, 0, 1),
                  lambda: loza.loza_ssa_decode_kernel(1, 2, 2, 8, 64, 0, 1), lambda: loza.loza_ssa_decode_kernel(0, 2, 2, 8, 128, 0, 1),

@@ -3,8 +3,8 @@
 Such rows are where the rounding of the weights to bf16 shows most (nothing averages it out) and
 where the result is as large as single value rows, so that its own rounding to bf16 leaves the
 least room (half an ulp is 2^-7 from magnitude 2 on). The kernels compute every result of magnitude
-2 and more with unrounded weights (two bf16 terms in the prefill and extend kernel, fp32 in the
-decode's merge kernel); these cases make sure that path is taken and holds the bound.
+2 and more with finer weights (two bf16 terms in a prefill or extend, fp32 or the three terms that hold
+it in a decode); these cases make sure that path is taken and holds the bound.
 Construction: queries are a multiple of one live key plus noise, the multiple growing over the
 heads, so that the weight of that key runs from a few per cent to nearly one.
 """
