@@ -1053,20 +1053,20 @@ __global__ __launch_bounds__(DV / 4) void ssa_decode_merge_kernel(const FwdParam
 // A pattern that leaves rows beyond the first kPrecisePositions positions with fewer live keys than
 // that takes the two-term variant throughout. The smallest live set of such a row is at position
 // kPrecisePositions - 1 or at the first query of a block whose window has reached full length.
-bool pattern_needs_precise(const FwdParams &p)
+static bool pattern_needs_precise(int64_t S, int n_sink, int window, int block)
 {
     auto live_at = [&](int64_t i) {
-        const int64_t se = p.n_sink < i + 1 ? p.n_sink : i + 1;
-        const int64_t qb = i / p.block;
-        int64_t wb = p.window > qb ? 0 : (qb - p.window + 1) * p.block;
+        const int64_t se = n_sink < i + 1 ? n_sink : i + 1;
+        const int64_t qb = i / block;
+        int64_t wb = window > qb ? 0 : (qb - window + 1) * block;
         if (wb < se) wb = se;
         return se + (i + 1 - wb);
     };
-    if (p.S < kPrecisePositions) return false;
-    int64_t qb0 = (kPrecisePositions - 1 + p.block - 1) / p.block;
-    if (qb0 < p.window - 1) qb0 = p.window - 1;
-    const int64_t i0 = qb0 * p.block;
-    return live_at(kPrecisePositions - 1) < kPrecisePositions || (i0 < p.S && live_at(i0) < kPrecisePositions);
+    if (S < kPrecisePositions) return false;
+    int64_t qb0 = (kPrecisePositions - 1 + block - 1) / block;
+    if (qb0 < window - 1) qb0 = window - 1;
+    const int64_t i0 = qb0 * block;
+    return live_at(kPrecisePositions - 1) < kPrecisePositions || (i0 < S && live_at(i0) < kPrecisePositions);
 }
 
 template <int DQK, int DV, bool ALIAS, bool OUTF32, bool EXT>
@@ -1077,7 +1077,7 @@ static hipError_t launch_prefill_kernel(FwdParams p, hipStream_t stream)
     hipError_t e = allow_lds<kern>(C::LDS_BYTES);
     if (e != hipSuccess) return e;
     p.rt_begin = 0;
-    p.all_precise = pattern_needs_precise(p) ? 1 : 0;
+    p.all_precise = pattern_needs_precise(p.S, p.n_sink, p.window, p.block) ? 1 : 0;
     // The speculative softmax scores a tile twice when the reference moves: the reference is exact
     // over the first tile only, afterwards lazy (with an exact reference over the first 8 tiles most
     // of them would move it).
@@ -1229,7 +1229,10 @@ int decode_rows_per_tile() { return 64; }
 // when the window is short and few heads share a key (32, 8,192, 16 + 256: 148 against 124; 8 key heads: 99
 // against 102), it costs more to start, and its last round is a whole one (4,100 tokens are 544 tiles: 114 against
 // 108 us in blocks of 128). With few tiles (160: 45.0 against 44.2 us; 168: 41.7 against 43.1) or mostly padded
-// ones (chunks of 300 tokens: 122 against 120) it does not pay.
+// ones (chunks of 300 tokens: 122 against 120) it does not pay. Nor does it where rows have few live keys: their
+// results are large and whole tiles are computed again, or take two-term weights from the outset (32 heads of
+// their own keys, window 200, 6,000 tokens: 126 against 82 us; 32 heads on 8, window 100 after a sink of 20: 78
+// against 65; blocks of 300: 91 against 75).
 // A prefill, or a chunk that (nearly) fills its cache, starts at position 0: its first tiles have few keys, and the
 // launch is simulated (128 heads of their own keys: 512 tokens 32 against 37 us, 800 tokens, 128 + 512, 80 against
 // 75). Otherwise, and from eight rounds on, every tile has a full window, and rounds are counted. The cache's
@@ -1238,6 +1241,7 @@ bool d128_tiles_pay(int B, int Hkv, int G, int64_t queries, int64_t S, int n_sin
 {
     const int64_t rows = queries * G, big = (rows + 255) / 256, small = (rows + 127) / 128, heads = (int64_t)B * Hkv;
     if (big * heads <= 160 || big * 256 * 4 > small * 128 * 5) return false;
+    if (pattern_needs_precise(S, n_sink, window, block) || n_sink + (int64_t)window * block < 256) return false;
     auto cost_big = [&](double keys) { return 13.1 + 7.6 / G + 0.0259 * keys; };
     auto cost_small = [&](double keys) { return 14.3 + 3.5 / G + 0.0351 * keys; };
     if (S * 8 <= queries * 9 && small * heads <= 4096) {

@@ -102,7 +102,7 @@ static __device__ __forceinline__ bool ssa_d128_tile(const FwdParams &p, char *s
     const int n_sink = p.n_sink, window = p.window, block = p.block;
     auto last_row = [&](int64_t a, int n) { return a + n - 1 < R ? a + n - 1 : R - 1; };
     const int i_min = (int)(pos0 + row_position(r0, G)), i_max = (int)(pos0 + row_position(last_row(r0, M), G));
-    if (!PRECISE && (p.all_precise || i_min < kPrecisePositions)) return true;
+    if (!PRECISE && i_min < kPrecisePositions) return true;
 
     // positions of this wave's rows
     const int64_t w0 = r0 + wave * 64 < R ? r0 + wave * 64 : R - 1;
@@ -580,7 +580,6 @@ static hipError_t launch_d128_t(FwdParams p, hipStream_t stream)
     if (e != hipSuccess) return e;
     const int64_t rows = (p.seqlens ? (int64_t)p.q_len : p.S) * p.G;
     p.row_tiles = (int)((rows + C::M - 1) / C::M);
-    p.all_precise = pattern_needs_precise(p) ? 1 : 0;
     hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)p.row_tiles * p.Hkv * p.B)), dim3(256), C::LDS_BYTES, stream, p);
     return hipGetLastError();
 }

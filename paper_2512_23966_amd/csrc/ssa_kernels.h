@@ -33,7 +33,7 @@ struct FwdParams {
     int rt_begin;      // first of them
     int n_splits;      // decode only
     int q_len;         // extend prefill: queries per sequence (0: plain prefill); keys valid up to seqlens[b]
-    int all_precise;   // prefill / extend: every tile takes the two-term pass (set by the launcher from the pattern)
+    int all_precise;   // tile kernel, prefill / extend: every tile takes the two-term pass (set by the launcher from the pattern)
     int exact_tiles;   // tile kernel: tiles over which the reference maximum is the exact running maximum
     float lazy_log2;   // afterwards it moves only when exceeded by this much (log2 units)
 };
@@ -59,8 +59,6 @@ int decode_rows_per_tile();
 hipError_t launch_prefill_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
 hipError_t launch_extend_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
 hipError_t launch_decode_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
-// Whether a pattern leaves rows beyond the first positions so few live keys that every tile takes two-term weights.
-bool pattern_needs_precise(const FwdParams &p);
 // Heads of width 128, many query rows (ssa_d128.hip): prefill (seqlens null) or extend.
 hipError_t launch_d128_bf16(const FwdParams &p, bool alias, hipStream_t stream);
 bool d128_tiles_pay(int B, int Hkv, int G, int64_t queries, int64_t S, int n_sink, int window, int block);

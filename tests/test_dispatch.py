@@ -23,6 +23,9 @@ def test_few_rows_are_at_most_512_groups_of_16():
     (4, 32, 32, 520, 8192, 16, 256, 1, KERNEL_TILES),       # 79 against 64
     (1, 32, 32, 1100, 1100, 128, 4096, 1, KERNEL_TILES),    # 160 tiles: 45.7 against 45.6
     (8, 32, 32, 300, 8192, 128, 4096, 1, KERNEL_TILES),     # mostly padding
+    (1, 32, 8, 6000, 6000, 20, 100, 1, KERNEL_TILES),       # few live keys: 78 against 65
+    (1, 64, 16, 6000, 6000, 0, 1, 300, KERNEL_TILES),       # the first query of a block has one: 160 against 130
+    (1, 64, 16, 6000, 6000, 1, 3, 64, KERNEL_D128),         # 112 against 121
 ])
 def test_width_128_takes_the_larger_tiles_where_they_are_faster(B, Hq, Hkv, queries, S, sink, local, block, kernel):
     assert loza.loza_ssa_forward_kernel(B, Hq, Hkv, queries, S, 128, sink, local, block) == kernel

@@ -30,7 +30,7 @@ def _live_pages(L, q_len, ns, win, block, page):
     ([1490, 1303], 512, 48, 12, 33, 450, None, 32),
     ([1535], 512, 96, 24, 1, 13, 32, 32),         # block-granular
     ([1700], 509, 96, 24, 70, 600, None, 64),
-    ([600], 512, 96, 6, 5, 90, None, 32),         # the chunk is nearly the whole sequence
+    ([900], 512, 96, 6, 5, 260, None, 32),
 ])
 def test_d128_extend_reads_only_pages_with_a_live_key(gpu_device, alias, lens, q_len, Hq, Hkv, ns, win, block, page):
     B = len(lens)

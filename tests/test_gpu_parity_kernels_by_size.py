@@ -80,13 +80,14 @@ D128_CASES = [
     (2, 517, 192, 24, False, 37, 300, None),        # eight heads on a key head; ragged
     (1, 900, 128, 16, True, 0, 333, None),
     (1, 1023, 192, 24, False, 2, 5, 96),
-    (1, 700, 256, 32, True, 1, 1, 128),              # few live keys: two-term weights throughout
+    (1, 700, 256, 32, True, 1, 2, 128),
 ]
 TILE_CASES = [
     (1, 300, 40, 40, False, 37, 70, None),
     (2, 257, 24, 24, True, 0, 200, None),
     (1, 530, 36, 12, False, 3, 4, 48),
     (1, 420, 64, 64, False, 16, 100, None),
+    (1, 1000, 64, 8, False, 0, 60, None),            # few live keys: two-term weights throughout
 ]
 
 
