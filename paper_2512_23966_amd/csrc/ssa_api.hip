@@ -114,10 +114,10 @@ DecodePlan decode_plan(int B, int Hq, int Hkv, int64_t S_max, int d_qk, int64_t 
     if (groups <= 2) return {true, n_rows};
     const bool wide = d_qk > 128;
     const int64_t keys = (live + 63) / 64 * 64;
-    auto rounds = [&](int64_t wgs) { return (wgs + kComputeUnits - 1) / kComputeUnits; };
+    auto rounds = [&](int64_t base, int n) { return ceil((double)base * n / kComputeUnits); };
     const int64_t rows_tiles = (keys / 64 + n_rows) / n_rows, tile_tiles = (keys / 32 + n_tile) / n_tile;
-    const int64_t t_rows = rounds(rows_base * n_rows) * (rows_tiles * (wide ? 145 : 70) + (wide ? 800 : 600)) + (n_rows > 1 ? 500 : 0);
-    const int64_t t_tile = rounds(tile_base * n_tile) * (tile_tiles * (wide ? 120 : 80) + (wide ? 2500 : 1800)) + 800;
+    const double t_rows = rounds(rows_base, n_rows) * (rows_tiles * (wide ? 145 : 70) + (wide ? 800 : 600)) + (n_rows > 1 ? 500 : 0);
+    const double t_tile = rounds(tile_base, n_tile) * (tile_tiles * (wide ? 120 : 80) + (wide ? 2500 : 1800)) + 800;
     return {t_rows <= t_tile, t_rows <= t_tile ? n_rows : n_tile};
 }
 
