@@ -254,6 +254,24 @@ int loza_ssa_extend_paged_blocks(const void *q, const void *k_pages, const void 
                                  int64_t sink_blocks, int64_t local_blocks, int64_t block, float scale, void *stream);
 
 /*
+ * Any of the four extends with scratch memory, so that several workgroups can share the keys of a query (few
+ * new tokens against long windows otherwise leave most of the GPU idle): block_table == NULL is
+ * loza_ssa_extend_blocks (num_pages, page_size, max_pages_per_seq unused), a table is
+ * loza_ssa_extend_paged_blocks (S_max unused); block = 1 is the token-granular pattern. Results agree with
+ * theirs to the order of the sums. `workspace` (16-byte aligned, device): loza_ssa_extend_workspace_bytes
+ * (S_max = max_pages_per_seq * page_size of a paged cache; 0: these sizes need none, the pointer may be
+ * NULL, and the call is the one without). It must stay untouched until the launches have run; its contents do
+ * not matter before and mean nothing afterwards.
+ */
+int loza_ssa_extend_with_workspace(const void *q, const void *k, const void *v, const int32_t *block_table, const int32_t *seqlens,
+                                   void *out, float *lse, int B, int Hq, int Hkv, int64_t S_max, int64_t num_pages,
+                                   int page_size, int max_pages_per_seq, int q_len, int d_qk, int d_v, int64_t sink_blocks,
+                                   int64_t local_blocks, int64_t block, float scale, void *workspace, size_t workspace_bytes,
+                                   void *stream);
+size_t loza_ssa_extend_workspace_bytes(int B, int Hq, int Hkv, int64_t S_max, int q_len, int d_qk, int d_v,
+                                       int64_t sink_blocks, int64_t local_blocks, int64_t block);
+
+/*
  * SSA decode against a PAGED KV cache (the cache layout of a serving engine; the paper's
  * Efficiency section measures its decode kernel inside one). The rows of sequence b live in pages
  * of `page_size` rows: logical row j is row j % page_size of physical page

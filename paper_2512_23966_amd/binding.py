@@ -7,6 +7,7 @@ fallback: if the shared library is missing, importing a symbol from it raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from pathlib import Path
 
@@ -29,6 +30,7 @@ EXPORTS = (
     "loza_ssa_decode_paged", "loza_ssa_decode_paged_blocks",
     "loza_ssa_prefill_calibration_blocks", "loza_ssa_calibration_workspace_bytes",
     "loza_ssa_extend", "loza_ssa_extend_blocks", "loza_ssa_extend_paged", "loza_ssa_extend_paged_blocks",
+    "loza_ssa_extend_with_workspace", "loza_ssa_extend_workspace_bytes",
     "loza_ssa_backward", "loza_ssa_backward_blocks",
     "loza_ssa_backward_workspace_bytes", "loza_ssa_backward_workspace_bytes_blocks",
     "loza_ssa_backward_f32", "loza_ssa_backward_blocks_f32",
@@ -98,6 +100,10 @@ def lib() -> ctypes.CDLL:
         L.loza_ssa_extend_paged.argtypes = [vp, vp, vp, vp, vp, vp, vp, ci, ci, ci, i64, ci, ci, ci, ci, ci, i64, i64, f32, vp]
         L.loza_ssa_extend_paged_blocks.restype = ci
         L.loza_ssa_extend_paged_blocks.argtypes = [vp, vp, vp, vp, vp, vp, vp, ci, ci, ci, i64, ci, ci, ci, ci, ci, i64, i64, i64, f32, vp]
+        L.loza_ssa_extend_with_workspace.restype = ci
+        L.loza_ssa_extend_with_workspace.argtypes = [vp] * 7 + [ci, ci, ci, i64, i64, ci, ci, ci, ci, ci, i64, i64, i64, f32, vp, sz, vp]
+        L.loza_ssa_extend_workspace_bytes.restype = sz
+        L.loza_ssa_extend_workspace_bytes.argtypes = [ci, ci, ci, i64, ci, ci, ci, i64, i64, i64]
         L.loza_ssa_backward.restype = ci
         L.loza_ssa_backward.argtypes = [vp] * 9 + [ci, ci, ci, i64, ci, ci, i64, i64, f32, vp, sz, vp]
         L.loza_ssa_backward_blocks.restype = ci
@@ -432,9 +438,54 @@ def loza_ssa_calibration_alpha_grad(dout, out_full, out_sparse, dalpha, workspac
         raise LozaError(rc, "loza_ssa_calibration_alpha_grad")
 
 
-def _extend_common(fn_name, q, kcache, vcache, seqlens, out, lse, pattern, scale, stream):
+@functools.lru_cache(maxsize=1024)
+def loza_ssa_extend_workspace_bytes(B, Hq, Hkv, S_max, q_len, d_qk, d_v, sink, local, block=1) -> int:
+    """Bytes of scratch memory with which an extend of these sizes lets several workgroups share the keys of a query
+    (0: it has no use for any). Host only."""
+    return int(lib().loza_ssa_extend_workspace_bytes(B, Hq, Hkv, S_max, q_len, d_qk, d_v, sink, _win(local), block))
+
+
+def _scratch(nbytes: int, stream):
+    """Scratch memory for launches on `stream`, from torch's allocator and of that stream (given back when the caller
+    drops it, it can only be handed out again behind those launches). None where there is none to be had: no memory
+    left, or a stream under capture, whose graph would keep the address of memory that is given back."""
+    if stream is not None and _stream(stream) != torch.cuda.current_stream().cuda_stream:
+        if not isinstance(stream, torch.cuda.Stream):
+            stream = torch.cuda.ExternalStream(_stream(stream))
+        with torch.cuda.stream(stream):
+            return _scratch(nbytes, None)
+    if torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    except torch.OutOfMemoryError:
+        return None
+
+
+def _extend_call(fn_name, pointers, table, sizes, paging, S_max, q_len, d_qk, d_v, pattern, scale, workspace, stream):
+    """The extend entry point of that name, or, where scratch memory helps and is there, the one that takes it."""
+    B, Hq, Hkv = sizes
+    blocks = pattern if len(pattern) == 3 else (*pattern, 1)
+    need = loza_ssa_extend_workspace_bytes(B, Hq, Hkv, S_max, q_len, d_qk, d_v, *blocks)
+    if need and workspace is None:
+        workspace = _scratch(need, stream)
+    if need and workspace is not None:
+        fn_name = "loza_ssa_extend_with_workspace"
+        rc = lib().loza_ssa_extend_with_workspace(*pointers[:3], table, *pointers[3:], B, Hq, Hkv, S_max, *(paging or (0, 0, 0)), q_len, d_qk, d_v,
+                                                  *blocks, scale, _dev_ptr(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(stream))
+    elif paging:
+        rc = getattr(lib(), fn_name)(*pointers[:3], table, *pointers[3:], B, Hq, Hkv, *paging, q_len, d_qk, d_v, *pattern, scale, _stream(stream))
+    else:
+        rc = getattr(lib(), fn_name)(*pointers, B, Hq, Hkv, S_max, q_len, d_qk, d_v, *pattern, scale, _stream(stream))
+    if rc != LOZA_OK:
+        raise LozaError(rc, fn_name)
+
+
+def _extend_common(fn_name, q, kcache, vcache, seqlens, out, lse, pattern, scale, workspace, stream):
     """bf16 SSA extend. q [B,q_len,Hq,d_qk], kcache [B,S_max,Hkv,d_qk], vcache [B,S_max,Hkv,d_v] or
-    ``vcache is kcache``, seqlens [B] int32 on the GPU, out [B,q_len,Hq,d_v] bf16, lse [B,Hq,q_len] fp32."""
+    ``vcache is kcache``, seqlens [B] int32 on the GPU, out [B,q_len,Hq,d_v] bf16, lse [B,Hq,q_len] fp32.
+    workspace: uint8 GPU tensor of at least ``loza_ssa_extend_workspace_bytes`` bytes; without one, scratch memory
+    comes from torch's allocator (or, under capture, the call does without)."""
     B, q_len, Hq, d_qk = q.shape
     _, S_max, Hkv, _ = kcache.shape
     d_v = out.shape[3]
@@ -446,25 +497,22 @@ def _extend_common(fn_name, q, kcache, vcache, seqlens, out, lse, pattern, scale
     bf = torch.bfloat16
     qp, kp = _dev_ptr(q, bf, "q"), _dev_ptr(kcache, bf, "kcache")
     vp = kp if vcache is kcache else _dev_ptr(vcache, bf, "vcache")
-    rc = getattr(lib(), fn_name)(qp, kp, vp, _dev_ptr(seqlens, torch.int32, "seqlens"), _dev_ptr(out, bf, "out"),
-                                 _dev_ptr(lse, torch.float32, "lse"), B, Hq, Hkv, S_max, q_len, d_qk, d_v,
-                                 *pattern, float(scale), _stream(stream))
-    if rc != LOZA_OK:
-        raise LozaError(rc, fn_name)
+    _extend_call(fn_name, (qp, kp, vp, _dev_ptr(seqlens, torch.int32, "seqlens"), _dev_ptr(out, bf, "out"), _dev_ptr(lse, torch.float32, "lse")),
+                 None, (B, Hq, Hkv), None, S_max, q_len, d_qk, d_v, pattern, float(scale), workspace, stream)
 
 
-def loza_ssa_extend(q, kcache, vcache, seqlens, out, lse, n_sink, window, scale, stream=None):
+def loza_ssa_extend(q, kcache, vcache, seqlens, out, lse, n_sink, window, scale, stream=None, workspace=None):
     """q_len new tokens per sequence against its cache, token-granular pattern (see :func:`_extend_common`)."""
-    _extend_common("loza_ssa_extend", q, kcache, vcache, seqlens, out, lse, (int(n_sink), _win(window)), scale, stream)
+    _extend_common("loza_ssa_extend", q, kcache, vcache, seqlens, out, lse, (int(n_sink), _win(window)), scale, workspace, stream)
 
 
-def loza_ssa_extend_blocks(q, kcache, vcache, seqlens, out, lse, sink_blocks, local_blocks, block, scale, stream=None):
+def loza_ssa_extend_blocks(q, kcache, vcache, seqlens, out, lse, sink_blocks, local_blocks, block, scale, stream=None, workspace=None):
     """q_len new tokens per sequence against its cache, block-granular pattern."""
     _extend_common("loza_ssa_extend_blocks", q, kcache, vcache, seqlens, out, lse,
-                   (int(sink_blocks), _win(local_blocks), int(block)), scale, stream)
+                   (int(sink_blocks), _win(local_blocks), int(block)), scale, workspace, stream)
 
 
-def _extend_paged_common(fn_name, q, k_pages, v_pages, block_table, seqlens, out, lse, pattern, scale, stream):
+def _extend_paged_common(fn_name, q, k_pages, v_pages, block_table, seqlens, out, lse, pattern, scale, workspace, stream):
     """bf16 SSA extend against a paged cache: q [B,q_len,Hq,d_qk], k_pages [num_pages,page_size,Hkv,d_qk],
     v_pages likewise with d_v (or ``v_pages is k_pages``), block_table [B,max_pages] int32, seqlens [B] int32,
     out [B,q_len,Hq,d_v] bf16, lse [B,Hq,q_len] fp32."""
@@ -479,25 +527,23 @@ def _extend_paged_common(fn_name, q, k_pages, v_pages, block_table, seqlens, out
     bf = torch.bfloat16
     qp, kp = _dev_ptr(q, bf, "q"), _dev_ptr(k_pages, bf, "k_pages")
     vp = kp if v_pages is k_pages else _dev_ptr(v_pages, bf, "v_pages")
-    rc = getattr(lib(), fn_name)(qp, kp, vp, _dev_ptr(block_table, torch.int32, "block_table"),
-                                 _dev_ptr(seqlens, torch.int32, "seqlens"), _dev_ptr(out, bf, "out"),
-                                 _dev_ptr(lse, torch.float32, "lse"), B, Hq, Hkv, num_pages, page_size,
-                                 block_table.shape[1], q_len, d_qk, d_v, *pattern, float(scale), _stream(stream))
-    if rc != LOZA_OK:
-        raise LozaError(rc, fn_name)
+    max_pages = block_table.shape[1]
+    _extend_call(fn_name, (qp, kp, vp, _dev_ptr(seqlens, torch.int32, "seqlens"), _dev_ptr(out, bf, "out"), _dev_ptr(lse, torch.float32, "lse")),
+                 _dev_ptr(block_table, torch.int32, "block_table"), (B, Hq, Hkv), (num_pages, page_size, max_pages), max_pages * page_size,
+                 q_len, d_qk, d_v, pattern, float(scale), workspace, stream)
 
 
-def loza_ssa_extend_paged(q, k_pages, v_pages, block_table, seqlens, out, lse, n_sink, window, scale, stream=None):
+def loza_ssa_extend_paged(q, k_pages, v_pages, block_table, seqlens, out, lse, n_sink, window, scale, stream=None, workspace=None):
     """Extend against a paged cache, token-granular pattern (see :func:`_extend_paged_common`)."""
     _extend_paged_common("loza_ssa_extend_paged", q, k_pages, v_pages, block_table, seqlens, out, lse,
-                         (int(n_sink), _win(window)), scale, stream)
+                         (int(n_sink), _win(window)), scale, workspace, stream)
 
 
 def loza_ssa_extend_paged_blocks(q, k_pages, v_pages, block_table, seqlens, out, lse, sink_blocks, local_blocks, block,
-                                 scale, stream=None):
+                                 scale, stream=None, workspace=None):
     """Extend against a paged cache, block-granular pattern."""
     _extend_paged_common("loza_ssa_extend_paged_blocks", q, k_pages, v_pages, block_table, seqlens, out, lse,
-                         (int(sink_blocks), _win(local_blocks), int(block)), scale, stream)
+                         (int(sink_blocks), _win(local_blocks), int(block)), scale, workspace, stream)
 
 
 def loza_ssa_backward_workspace_bytes(B, Hq, Hkv, S, d_qk, d_v, n_sink, window, v_aliases_k) -> int:

@@ -147,6 +147,49 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
     return (sink_blocks < 0 || local_blocks < 1 || block < 1) ? LOZA_ERR_SHAPE : LOZA_OK;
 }
 
+// How many workgroups share the keys of a row in an extend that has scratch memory, and which kernel they run. Few
+// new tokens leave most compute units idle: 2 tokens of one sequence are 8 groups of 16 rows of the absorbed-MLA
+// shape, and took the same 153 us (window 8192) as 128 tokens. Splits of the few-rows kernel are merged row by row
+// (2 tokens 22 us, 16 tokens 37 to 59); with more rows the tile kernel, which reads its keys once for 128 rows, is ahead
+// (4 tokens of 16 sequences 166 -> 97 us, 144 tokens 388 -> 203, 256 tokens 390 -> 282), until its tiles fill the
+// chip by themselves (444 tokens 404 us, split 392). The line is a time model of both in microseconds, fitted to
+// 60 sizes: workgroups go in rounds, a round costs a start and a step per tile of keys, and every set of partial
+// results of a row is written and read once. A split has to promise 7 %, which is what the model is worth. A chunk
+// that (nearly) fills its cache is a prefill, and has its bits.
+struct ExtendPlan {
+    bool rows;
+    int n_splits;
+};
+
+ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk, const Pattern &pat)
+{
+    const bool wide = d_qk > 128;
+    const int64_t rows = q_len * G, heads = (int64_t)B * Hkv, groups = (rows + 15) / 16 * heads;
+    const int64_t tiles = (rows + loza::kTileRows - 1) / loza::kTileRows * heads;
+    int64_t live = (int64_t)pat.n_sink + (int64_t)pat.window * pat.block;
+    if (live > S) live = S;
+    auto rounds = [](int64_t workgroups, int slots) { return (double)((workgroups + slots - 1) / slots); };
+    const double set = wide ? 1.05e-3 : 0.28e-3;                       // one set of partial results of one row
+    auto t_rows = [&](int64_t n) {
+        const double steps = (double)((live / 16 + 2 + 4 * n - 1) / (4 * n));
+        return rounds(groups * n, kComputeUnits) * (wide ? 8 + 1.15 * steps : 5 + 0.7 * steps) + (n > 1 ? 3.5 + set * rows * heads * n : 0);
+    };
+    // (two workgroups of the narrow tile kernel share a compute unit)
+    const int slots = wide ? kComputeUnits : 2 * kComputeUnits;
+    auto t_tile = [&](int64_t n) {
+        const double steps = (double)((live / 32 + 2 + n - 1) / n), step = wide ? 1.65 : tiles * n <= kComputeUnits ? 1.1 : 1.5;
+        return rounds(tiles * n, slots) * (12 + step * steps) + (n > 1 ? 6 + set * rows * heads * n : 0);
+    };
+    ExtendPlan best{loza::few_rows_bf16(B, Hkv, rows), 1};
+    if (S * 8 <= q_len * 9) return best;
+    double t = 0.93 * (best.rows ? t_rows(1) : t_tile(1));
+    for (int n = 2; n <= kMaxSplits && groups * n <= kComputeUnits; ++n)
+        if (t_rows(n) < t) { t = t_rows(n); best = {true, n}; }
+    for (int n = 2; n <= kMaxSplits && tiles * n <= 2 * slots; ++n)
+        if (t_tile(n) < t) { t = t_tile(n); best = {false, n}; }
+    return best;
+}
+
 // The reference maximum of the online softmax moves only when exceeded by more than 2^8 (fp32 has the headroom).
 // Over the first 8 key tiles the tile kernel keeps it exact (its wide prefill over the first only); the few-rows
 // and the width-128 kernel, which do not read exact_tiles, over their first tile or step.
@@ -257,14 +300,22 @@ static int check_paging(const Paging &pg, int *page_shift, int64_t *capacity)
     return LOZA_OK;
 }
 
+// Partial results of the rows of a call whose keys n workgroups share: fp32 results, then maximum and sums.
+static size_t split_bytes(int B, int Hq, int64_t q_len, int d_v, int n)
+{
+    return (size_t)B * Hq * q_len * n * ((size_t)d_v + 4) * sizeof(float);
+}
+
 static int prefill_bf16(const void *q, const void *k, const void *v, void *out, float *lse,
                         int B, int Hq, int Hkv, int64_t S, int d_qk, int d_v,
                         int64_t sink, int64_t local, int64_t block, bool blocks, float scale, void *stream,
                         float *out_f32 = nullptr, bool validate_only = false,
-                        const int32_t *seqlens = nullptr, int64_t q_len = 0, const Paging *paging = nullptr)
+                        const int32_t *seqlens = nullptr, int64_t q_len = 0, const Paging *paging = nullptr,
+                        bool scratch = false, void *workspace = nullptr, size_t workspace_bytes = 0)
 {
     // seqlens != nullptr: "extend" form, q_len queries per sequence against a cache of S rows
-    // (with a paging description: of max_pages * page_size rows behind a block table)
+    // (with a paging description: of max_pages * page_size rows behind a block table); scratch: the caller offers
+    // `workspace`, and the keys of a row may be shared by several workgroups
     const bool extend = seqlens != nullptr;
     if (!q || !k || !v || (!out && !out_f32) || !lse) return LOZA_ERR_NULL;
     int page_shift = 0;
@@ -295,8 +346,19 @@ static int prefill_bf16(const void *q, const void *k, const void *v, void *out, 
     p.scale_log2 = scale * 1.44269504088896340736f;
     p.row_tiles = (int)row_tiles; p.n_splits = 1;
     set_rescale_policy(p);
-    const bool few_rows = loza::few_rows_bf16(B, Hkv, (extend ? q_len : S) * G);
+    bool few_rows = loza::few_rows_bf16(B, Hkv, (extend ? q_len : S) * G);
     if (extend) {
+        if (scratch) {
+            const ExtendPlan plan = extend_plan(B, Hkv, G, q_len, S, d_qk, pat);
+            if (plan.n_splits > 1) {
+                if (!workspace || workspace_bytes < split_bytes(B, Hq, q_len, d_v, plan.n_splits)) return LOZA_ERR_WORKSPACE;
+                if (!aligned16(workspace)) return LOZA_ERR_ALIGN;
+                few_rows = plan.rows;
+                p.n_splits = plan.n_splits;
+                p.part_o = (float *)workspace;
+                p.part_ml = (float *)workspace + (size_t)B * Hq * q_len * plan.n_splits * d_v;
+            }
+        }
         p.seqlens = seqlens; p.q_len = (int)q_len;
         if (paging) {
             p.block_table = paging->block_table;
@@ -360,6 +422,28 @@ int loza_ssa_extend_blocks(const void *q, const void *kcache, const void *vcache
     if (!seqlens) return LOZA_ERR_NULL;
     return prefill_bf16(q, kcache, vcache, out, lse, B, Hq, Hkv, S_max, d_qk, d_v, sink_blocks, local_blocks, block, true,
                         scale, stream, nullptr, false, seqlens, q_len);
+}
+
+int loza_ssa_extend_with_workspace(const void *q, const void *k, const void *v, const int32_t *block_table, const int32_t *seqlens,
+                                   void *out, float *lse, int B, int Hq, int Hkv, int64_t S_max, int64_t num_pages,
+                                   int page_size, int max_pages_per_seq, int q_len, int d_qk, int d_v, int64_t sink_blocks,
+                                   int64_t local_blocks, int64_t block, float scale, void *workspace, size_t workspace_bytes,
+                                   void *stream)
+{
+    if (!seqlens) return LOZA_ERR_NULL;
+    const Paging pg{block_table, num_pages, page_size, max_pages_per_seq};
+    return prefill_bf16(q, k, v, out, lse, B, Hq, Hkv, block_table ? 1 : S_max, d_qk, d_v, sink_blocks, local_blocks, block, true,
+                        scale, stream, nullptr, false, seqlens, q_len, block_table ? &pg : nullptr, true, workspace, workspace_bytes);
+}
+
+size_t loza_ssa_extend_workspace_bytes(int B, int Hq, int Hkv, int64_t S_max, int q_len, int d_qk, int d_v,
+                                       int64_t sink_blocks, int64_t local_blocks, int64_t block)
+{
+    if (check_common(B, Hq, Hkv, S_max, d_qk, d_v, sink_blocks, local_blocks, 1.0f) != LOZA_OK) return 0;
+    if (check_blocks(sink_blocks, local_blocks, block) != LOZA_OK || q_len < 1 || q_len > S_max) return 0;
+    if (!loza::bf16_width_supported(d_qk)) return 0;
+    const ExtendPlan plan = extend_plan(B, Hkv, Hq / Hkv, q_len, S_max, d_qk, block_pattern(sink_blocks, local_blocks, block, S_max));
+    return plan.n_splits > 1 ? split_bytes(B, Hq, q_len, d_v, plan.n_splits) : 0;
 }
 
 int loza_ssa_prefill(const void *q, const void *k, const void *v, void *out, float *lse,

@@ -42,6 +42,7 @@
 #include "ssa_device.h"
 #include "ssa_direct.h"
 #include "ssa_kernels.h"
+#include "ssa_rows.h"
 #include "ssa_schedule.h"
 
 namespace loza {
@@ -104,7 +105,11 @@ struct TileCfg {
     static constexpr int OFF_FLAG = OFF_ALPHA + 2 * M * 4;        // int[2][4] (one per row block, padded)
     static constexpr int OFF_LPART = OFF_FLAG + 2 * 16;           // float[2][M]
     static constexpr int OFF_REDO = OFF_LPART + 2 * M * 4;        // int: the tile has to be computed again, with two-term P
-    static constexpr int LDS_BYTES = OFF_REDO + 16;
+    // Groups of 16 rows that are computed again by themselves (as many as the whole tile would take the time of);
+    // width 128: none, their passes' LDS would halve the workgroups of a compute unit.
+    static constexpr int REDO_GROUPS = !DECODE && DQK > 128 ? 4 : 0;
+    static constexpr int TILE_BYTES = OFF_REDO + 16;
+    static constexpr int LDS_BYTES = REDO_GROUPS > 0 && RowsCfg<DQK, DV, ALIAS>::LDS_BYTES > TILE_BYTES ? RowsCfg<DQK, DV, ALIAS>::LDS_BYTES : TILE_BYTES;
     // The softmax between the matrix instructions of the value phase takes the speculative form (below)
     // where that phase has a matrix instruction for every one of its jobs; with fewer (narrow values)
     // the vector ALU is the bound either way and the ordinary form has fewer instructions.
@@ -117,10 +122,15 @@ struct TileCfg {
     static_assert(DECODE || M * OUTROW <= OFF_ALPHA, "the output tile must fit the stages and P");
 };
 
-// One pass over one workgroup tile. PRECISE: P goes to the value phase as two bf16 terms. Returns
-// true (the same in every wave) when the tile has been left unwritten for a PRECISE pass.
-template <int DQK, int DV, int RB, bool ALIAS, bool DECODE, bool PRECISE, bool OUTF32, bool EXT>
-static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *smem)
+// What is left of a tile after a pass (the same in every wave): nothing, all of it (it has been left unwritten for
+// a PRECISE pass), or the groups of 16 rows whose bits are set.
+constexpr int kTileDone = 0, kTileAgain = -1;
+
+// One pass over one workgroup tile. PRECISE: P goes to the value phase as two bf16 terms. SPLIT (extend): the
+// workgroup takes every n_splits-th live key tile and leaves fp32 partial results, as a decode's does; the kernel
+// that adds them up (ssa_rows.hip) also answers the tiles that must not come from once-rounded weights.
+template <int DQK, int DV, int RB, bool ALIAS, bool DECODE, bool PRECISE, bool OUTF32, bool EXT, bool SPLIT = false>
+static __device__ __forceinline__ int ssa_fwd_tile(const FwdParams &p, char *smem)
 {
     using C = TileCfg<DQK, DV, RB, ALIAS, DECODE>;
     constexpr int M = C::M, N = C::N, NSTAGE = C::NSTAGE;
@@ -141,7 +151,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
 
     // ---- which tile of which (batch, kv head) ------------------------------------------------
     int id = blockIdx.x;
-    if (!DECODE && DQK == 128) {
+    if (!DECODE && !SPLIT && DQK == 128) {
         // Workgroups go to the eight XCDs round-robin and every XCD has an L2 of its own. With one
         // head per kv group a row tile is 128 positions, and 32 concurrent workgroups that are every
         // eighth row tile make each L2 hold the keys of 32768 positions; handing every XCD one
@@ -151,7 +161,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
         if (id < chunk * 8) id = (id % 8) * chunk + id / 8;
     }
     int split = 0;
-    if (DECODE) { split = id % p.n_splits; id /= p.n_splits; }
+    if (DECODE || SPLIT) { split = id % p.n_splits; id /= p.n_splits; }
     const int rt = p.rt_begin + p.row_tiles - 1 - (id % p.row_tiles);  // heaviest (latest) row tiles first
     id /= p.row_tiles;
     const int g = id % p.Hkv;
@@ -176,7 +186,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
         const int64_t se = n_sink < L ? n_sink : L;
         const int64_t wb = L > 0 ? window_begin_of((int)(L - 1), p.window, p.block) : 0;
         const int64_t n_live = se + (L - (wb > se ? wb : se));
-        if (n_live < kDirectKeys) return false;
+        if (n_live < kDirectKeys) return kTileDone;
     }
 
     // ---- the query row this lane scores ---------------------------------------------------------
@@ -188,7 +198,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
     const int i_max = DECODE ? (int)(L - 1) : (int)(pos0 + row_position((r0 + M - 1 < R) ? r0 + M - 1 : R - 1, G));
     // Tiles among the first positions, and every tile of a pattern that leaves all rows few live keys,
     // take the two-term pass right away.
-    if (!DECODE && !PRECISE && (p.all_precise || i_min < kPrecisePositions)) return true;
+    if (!DECODE && !PRECISE && (p.all_precise || i_min < kPrecisePositions)) return kTileAgain;
 
     bf16x8 qf[DQK / 16];
 
@@ -206,7 +216,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
     // A decode split takes every n_splits-th live tile: the splits of a sequence then walk through
     // the same stretch of the cache together (measured a little faster than a contiguous quarter each).
     int t_stride = 1, t_first = 0;
-    if (DECODE) {
+    if (DECODE || SPLIT) {
         t_stride = p.n_splits; t_first = split;
         t_end = n_tiles > split ? (n_tiles - split + p.n_splits - 1) / p.n_splits : 0;
     }
@@ -841,10 +851,16 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
 
     // A result of magnitude 2 or more leaves the error budget little beyond its own rounding to bf16
     // (half an ulp is 2^-7 there), and it can only come from a row whose weight sits on a few keys, where
-    // the rounding of P to bf16 shows most. A tile with such a row is not written: it is computed again
-    // with two-term P (the caller runs the PRECISE pass when this one says so).
-    bool big = false;
-    if constexpr (!DECODE && !OUTF32) {
+    // the rounding of P to bf16 shows most. The groups of 16 rows that have such a row are not written: the
+    // caller computes them again with two-term weights, group by group (wide shape), or, where they are many, the
+    // whole tile. (1,024 live keys: a group takes 26 us, the tile 116; with N(0, 1) inputs one tile in twenty has
+    // such a row, mostly one. 32,768 tokens of 1 + 7 blocks: 4,963 -> 4,699 us; chunks of 1,000 tokens 4,279 -> 3,949.)
+    uint32_t redo = 0;
+    auto groups_of = [&](bool big, int rb) -> uint32_t {   // bit of every group of block rb that has such a row
+        const uint64_t m = __ballot(big);
+        return ((m & 0x0000ffff0000ffffull) ? 1u << (2 * rb) : 0u) | ((m & 0xffff0000ffff0000ull) ? 2u << (2 * rb) : 0u);
+    };
+    if constexpr (!DECODE && !SPLIT && !OUTF32) {
         // Every lane holds 4 of the 512 (128) columns of 32 rows at a time: stored from here, every store
         // instruction touches 32 rows (check and stores of a wide tile: 19.1 thousand cycles). Through LDS a
         // wave stores whole rows, past the L2's keys (14.0 thousand). With the positions below that take no 64-bit
@@ -872,9 +888,9 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
                     w[1] = pack_bf16(x[2], x[3]);
                     *(u32x2 *)(op + db * 64 + qd * 16) = w;
                 }
-            big = big || (mx >= kRedoMagnitude && r0 + rb * 32 + ln < R);
+            if (!PRECISE) redo |= groups_of(mx >= kRedoMagnitude && r0 + rb * 32 + ln < R, rb);
         }
-    } else if constexpr (!DECODE && !PRECISE) {
+    } else if constexpr (!DECODE && !SPLIT && !PRECISE) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             const float rsum = s_lpart[M + rb * 32 + ln];
@@ -883,18 +899,21 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
             for (int db = 0; db < C::DVB; ++db)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) mx = fmaxf(mx, __builtin_fabsf(o[db][rb][e]));
-            big = big || (rsum > 0.f && mx >= kRedoMagnitude * rsum && r0 + rb * 32 + ln < R);
+            redo |= groups_of(rsum > 0.f && mx >= kRedoMagnitude * rsum && r0 + rb * 32 + ln < R, rb);
         }
     }
-    if constexpr (!DECODE) {
-        if (!PRECISE && __any(big) && lane == 0) *s_redo = 1;
+    if constexpr (!DECODE && !SPLIT) {
+        if (!PRECISE && redo != 0 && lane == 0) atomicOr(s_redo, (int)redo);
         lds_barrier();
-        if (!PRECISE && *(volatile int *)s_redo) return true;
+        if (!PRECISE) {
+            redo = (uint32_t)__builtin_amdgcn_readfirstlane(*(volatile int *)s_redo);
+            if (__builtin_popcount(redo) > C::REDO_GROUPS) return kTileAgain;
+        }
     }
 
-    if (!DECODE) {
+    if constexpr (!DECODE && !SPLIT) {
         // lse = ln(sum_j exp(scale q.k_j)) = (m_ref + log2 l) * ln 2
-        if (scorer && lh == 0 && my_row < R) {
+        if (scorer && lh == 0 && my_row < R && !(redo >> ((wr * 32 + ln) >> 4) & 1)) {
             const int hh = (int)(my_row - (int64_t)r_row * G);
             p.lse[((int64_t)b * p.Hq + (int64_t)g * G + hh) * Sq + r_row] =
                 (m_ref + __builtin_amdgcn_logf(s_lpart[wr * 32 + ln])) * 0.69314718055994530942f;
@@ -907,7 +926,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
 #pragma unroll 4
             for (int step = 0; step < M / NW / RPI; ++step) {
                 const int row = first + step * RPI;
-                if (r0 + row < R) {
+                if (r0 + row < R && !(redo >> (row >> 4) & 1)) {
                     const u32x4 w = *(const u32x4 *)(smem + row * C::OUTROW + (lane % LPR) * 16);
                     const int64_t o_row = ((int64_t)b * Sq + i) * p.Hq + (int64_t)g * G + hh;
                     __builtin_nontemporal_store(w, (u32x4 *)(p.out + o_row * DV + (lane % LPR) * 8));
@@ -946,8 +965,13 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
         }
     } else {
         // partial result of this key split: unnormalised O (relative to m_ref), m_ref, l, rounded l
+        auto part_row = [&](int64_t row) -> int64_t {          // row of `out` (flat)
+            if (DECODE) return (int64_t)b * p.Hq + (int64_t)g * G + row;
+            const int64_t i = row_position(row, G);
+            return ((int64_t)b * Sq + i) * p.Hq + (int64_t)g * G + (row - i * G);
+        };
         if (scorer && lh == 0 && my_row < R) {
-            const int64_t h = (int64_t)b * p.Hq + (int64_t)g * G + my_row;
+            const int64_t h = part_row(my_row);
             p.part_ml[(h * p.n_splits + split) * 4 + 0] = m_ref;
             p.part_ml[(h * p.n_splits + split) * 4 + 1] = s_lpart[wr * 32 + ln];
             p.part_ml[(h * p.n_splits + split) * 4 + 2] = s_lpart[M + wr * 32 + ln];
@@ -955,8 +979,8 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             const int64_t row = r0 + rb * 32 + ln;
-            if (!scorer && row < R) {
-                const int64_t h = (int64_t)b * p.Hq + (int64_t)g * G + row;
+            if ((SPLIT || !scorer) && row < R) {
+                const int64_t h = part_row(row);
                 float *op = p.part_o + (h * p.n_splits + split) * DV + vw * C::DVW + 4 * lh;
 #pragma unroll
                 for (int db = 0; db < C::DVB; ++db)
@@ -972,21 +996,36 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
             }
         }
     }
-    return false;
+    return (int)redo;
 }
 
 // Prefill / extend: every tile is computed with P rounded to bf16 once; a tile that cannot afford
 // that (few live keys per row, or a result large enough that its own rounding fills the error
-// budget) is computed with two-term P instead. Decode: one pass of the split kernel.
-template <int DQK, int DV, int RB, bool ALIAS, bool DECODE, bool OUTF32 = false, bool EXT = false>
+// budget) is computed with two-term P instead, or those of its rows that cannot. Decode: one pass of the split kernel.
+template <int DQK, int DV, int RB, bool ALIAS, bool DECODE, bool OUTF32 = false, bool EXT = false, bool SPLIT = false>
 __global__ __launch_bounds__(256) void ssa_fwd_kernel(const FwdParams p)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     if constexpr (DECODE) {
         ssa_fwd_tile<DQK, DV, RB, ALIAS, true, false, false, false>(p, smem);
+    } else if constexpr (SPLIT) {
+        ssa_fwd_tile<DQK, DV, RB, ALIAS, false, false, false, true, true>(p, smem);
     } else {
-        if (ssa_fwd_tile<DQK, DV, RB, ALIAS, false, false, OUTF32, EXT>(p, smem))
+        using C = TileCfg<DQK, DV, RB, ALIAS, DECODE>;
+        const int left = ssa_fwd_tile<DQK, DV, RB, ALIAS, false, false, OUTF32, EXT>(p, smem);
+        if (left == kTileAgain) {
             ssa_fwd_tile<DQK, DV, RB, ALIAS, false, true, OUTF32, EXT>(p, smem);
+        } else if constexpr (C::REDO_GROUPS > 0) {
+            int id = blockIdx.x;
+            const int rt = p.row_tiles - 1 - id % p.row_tiles;
+            id /= p.row_tiles;
+            const int g = id % p.Hkv, b = id / p.Hkv;
+#pragma unroll 1
+            for (uint32_t groups = (uint32_t)left; groups != 0; groups &= groups - 1) {
+                __syncthreads();
+                ssa_rows_pass<DQK, DV, ALIAS, false, false>(p, smem, b, g, rt * (C::M / 16) + __builtin_ctz(groups), 0, 1);
+            }
+        }
     }
 }
 
@@ -1069,11 +1108,11 @@ static bool pattern_needs_precise(int64_t S, int n_sink, int window, int block)
     return live_at(kPrecisePositions - 1) < kPrecisePositions || (i0 < S && live_at(i0) < kPrecisePositions);
 }
 
-template <int DQK, int DV, bool ALIAS, bool OUTF32, bool EXT>
+template <int DQK, int DV, bool ALIAS, bool OUTF32, bool EXT, bool SPLIT = false>
 static hipError_t launch_prefill_kernel(FwdParams p, hipStream_t stream)
 {
     using C = TileCfg<DQK, DV, 4, ALIAS, false>;
-    constexpr auto kern = ssa_fwd_kernel<DQK, DV, 4, ALIAS, false, OUTF32, EXT>;
+    constexpr auto kern = ssa_fwd_kernel<DQK, DV, 4, ALIAS, false, OUTF32, EXT, SPLIT>;
     hipError_t e = allow_lds<kern>(C::LDS_BYTES);
     if (e != hipSuccess) return e;
     p.rt_begin = 0;
@@ -1082,9 +1121,13 @@ static hipError_t launch_prefill_kernel(FwdParams p, hipStream_t stream)
     // over the first tile only, afterwards lazy (with an exact reference over the first 8 tiles most
     // of them would move it).
     if (C::SPEC_SOFTMAX) p.exact_tiles = 1;
-    const int64_t blocks = (int64_t)p.row_tiles * p.Hkv * p.B;
+    const int64_t blocks = (int64_t)p.row_tiles * p.Hkv * p.B * (SPLIT ? p.n_splits : 1);
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), C::LDS_BYTES, stream, p);
-    return hipGetLastError();
+    e = hipGetLastError();
+    if constexpr (SPLIT) {
+        if (e == hipSuccess) e = launch_rows_finish_bf16(p, DQK, DV, ALIAS, stream);
+    }
+    return e;
 }
 
 template <int DQK, int DV, bool ALIAS>
@@ -1098,6 +1141,7 @@ static hipError_t launch_prefill_t(const FwdParams &p, hipStream_t stream)
 template <int DQK, int DV, bool ALIAS>
 static hipError_t launch_extend_t(const FwdParams &p, hipStream_t stream)
 {
+    if (p.n_splits > 1) return launch_prefill_kernel<DQK, DV, ALIAS, false, true, true>(p, stream);
     return launch_prefill_kernel<DQK, DV, ALIAS, false, true>(p, stream);
 }
 
@@ -1218,7 +1262,7 @@ bool bf16_shape_supported(int d_qk, int d_v, bool alias)
 
 bool bf16_width_supported(int d_qk) { return d_qk == 576 || d_qk == 128; }
 
-int prefill_rows_per_tile() { return 128; }
+int prefill_rows_per_tile() { return kTileRows; }
 int decode_rows_per_tile() { return 64; }
 
 // Heads of width 128: the kernel of 256-row tiles (ssa_d128.hip), one workgroup a compute unit, or the one of
@@ -1289,7 +1333,7 @@ hipError_t launch_extend_bf16(const FwdParams &p, int d_qk, int d_v, bool alias,
 {
     if (d_qk == 576 && d_v == 512 && alias) return launch_extend_t<576, 512, true>(p, stream);
     if (d_qk == 128 && d_v == 128) {
-        if (d128_tiles_pay(p)) return launch_d128_bf16(p, alias, stream);
+        if (p.n_splits == 1 && d128_tiles_pay(p)) return launch_d128_bf16(p, alias, stream);
         return alias ? launch_extend_t<128, 128, true>(p, stream) : launch_extend_t<128, 128, false>(p, stream);
     }
     return hipErrorInvalidValue;

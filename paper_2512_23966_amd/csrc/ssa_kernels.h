@@ -7,6 +7,9 @@
 
 namespace loza {
 
+// Query rows of a prefill or extend tile of ssa_bf16.hip.
+constexpr int kTileRows = 128;
+
 // Arguments of the bf16 forward kernels. `S` is the sequence length of a prefill, or the row
 // count (stride) of each sequence's cache in a decode. The live set of query i is
 //   { j <= i : j < n_sink  or  j >= max(0, i / block - window + 1) * block },
@@ -18,8 +21,8 @@ struct FwdParams {
     uint16_t *out;
     float *out_f32;  // prefill only: when set, the output goes here unrounded instead of to `out`
     float *lse;
-    float *part_o;   // decode: [B, Hq, n_splits, d_v] unnormalised partial outputs
-    float *part_ml;  // decode: [B, Hq, n_splits, 4]   reference max (log2 domain), sum, rounded sum, pad
+    float *part_o;   // n_splits > 1: [rows of out, n_splits, d_v] unnormalised partial outputs
+    float *part_ml;  // n_splits > 1: [rows of out, n_splits, 4]   reference max (log2 domain), sum, rounded sum, pad
     const int32_t *seqlens;
     // paged decode cache (else nullptr): logical page j >> page_shift of sequence b is physical page
     // block_table[b * max_pages + (j >> page_shift)] of k / v, which are then [num_pages, 2^page_shift, Hkv, d]
@@ -31,7 +34,7 @@ struct FwdParams {
     float scale_log2;  // scale * log2(e)
     int row_tiles;     // workgroup tiles per (batch, kv head) in this launch
     int rt_begin;      // first of them
-    int n_splits;      // decode only
+    int n_splits;      // decode and extend: workgroups that share the keys of a row (1: no partial results)
     int q_len;         // extend prefill: queries per sequence (0: plain prefill); keys valid up to seqlens[b]
     int all_precise;   // tile kernel, prefill / extend: every tile takes the two-term pass (set by the launcher from the pattern)
     int exact_tiles;   // tile kernel: tiles over which the reference maximum is the exact running maximum
@@ -65,6 +68,8 @@ bool d128_tiles_pay(int B, int Hkv, int G, int64_t queries, int64_t S, int n_sin
 // Few query rows (ssa_rows.hip): prefill (seqlens null), extend or decode (q_len = 1; n_splits key splits
 // and a merge; weights that are not rounded at all).
 hipError_t launch_rows_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, bool decode, hipStream_t stream);
+// Second launch of an extend whose key tiles the tile kernel has split (p.n_splits sets of partial results).
+hipError_t launch_rows_finish_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
 // A prefill or extend of `rows` query rows per (batch, key head) is few rows when its groups of 16 rows make
 // at most two rounds of the 256 compute units. A round of the row kernel and one of the tile kernel (128 rows
 // a workgroup) cost, at window 8192 of the wide shape, 165 and 405 us (d = 128, window 4096: 51 and 152):

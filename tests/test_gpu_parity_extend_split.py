@@ -1,0 +1,166 @@
+"""Extends whose keys several workgroups share (scratch memory for their partial results): both kernels that split, at
+the edges of what they handle, against the oracle; the rows that must not come from once-rounded weights; scratch
+memory given or not, too small, on another stream and under capture."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2512_23966_amd as loza
+from paper_2512_23966_amd import binding as B_
+from tests import helpers as H
+from tests.test_gpu_parity_extend import _rand, _run, _run_paged
+
+FAKE = 4096
+
+
+def _plan(B, Hq, Hkv, S_max, q_len, d, ns, win, block=1):
+    """Sets of partial results per row (1: none)."""
+    d_v = 512 if d == 576 else 128
+    return loza.loza_ssa_extend_workspace_bytes(B, Hq, Hkv, S_max, q_len, d, d_v, ns, win, block) // (B * Hq * q_len * (d_v + 4) * 4) or 1
+
+
+def _check(q, kc, vc, lens, out, lse, pattern, scale, label, block=None, step=1):
+    """Every `step`-th row (b, r, h) of a position >= 0 against the oracle; the others must be 0 / -inf."""
+    B, q_len, Hq, _ = q.shape
+    rows = [(b, r, h) for b, L in enumerate(lens) for r in range(q_len) if L - q_len + r >= 0 for h in range(Hq)][::step]
+    for b, L in enumerate(lens):
+        dead = max(0, q_len - L)
+        assert (out[b, :dead] == 0).all() and torch.isneginf(lse[b, :, :dead]).all(), f"{label}: queries before the start"
+    rb, rr, rh = (np.asarray(x, dtype=np.int64) for x in zip(*rows))
+    ri = np.asarray(lens, dtype=np.int64)[rb] - q_len + rr
+    tb, tr, th = (torch.as_tensor(x, device=q.device) for x in (rb, rr, rh))
+    ref_out, ref_lse = oracle.ssa_rows(q[tb, tr, th].contiguous().cpu(), kc.cpu(), ("alias", out.shape[3]) if vc is kc else vc.cpu(), rb, rh, ri,
+                                       Hq=Hq, n_sink=pattern[0], window=pattern[1], scale=scale, block=block)
+    H._judge(out[tb, tr, th].double().cpu().numpy(), ref_out, lse[tb, th, tr].double().cpu().numpy(), ref_lse, torch.bfloat16, len(rb), label)
+
+
+# B, Hq, Hkv, d, S_max, q_len, lens, n_sink, window, block, page, rows of the oracle
+CASES = [
+    (1, 64, 1, 576, 2600, 1, [2600], 128, 2048, None, 0, 1),             # one token: splits of a tile or two a wave
+    (3, 64, 1, 576, 2560, 4, [2509, 131, 2], 128, 1500, None, 128, 1),   # around position 128; queries before the start
+    (2, 64, 1, 576, 3000, 11, [2999, 0], 1, 7, 128, 0, 1),               # blocks; an empty cache; rows no multiple of 16
+    (1, 128, 2, 576, 2048, 3, [2047], 0, 1200, None, 32, 1),             # two latents
+    (2, 8, 2, 128, 4000, 5, [4000, 77], 70, 3000, None, 0, 1),           # separate values, 4 heads a group
+    (1, 6, 2, 128, 2048, 19, [2011], 16, 1500, None, 64, 1),             # 3 heads a group
+    (4, 64, 1, 576, 6144, 11, [6143, 5001, 130, 4], 128, 5000, None, 0, 5),    # the tile kernel; tiles among the first positions
+    (2, 64, 1, 576, 8192, 33, [8192, 7001], 0, 7000, None, 128, 7),      # odd number of positions: half a tile at the end
+    (4, 32, 8, 128, 2304, 64, [2304, 2111, 150, 64], 64, 2000, None, 0, 13),   # narrow tiles, separate values
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hkv,d,S_max,q_len,lens,ns,win,block,page,step", CASES)
+def test_split_extend(gpu_device, B, Hq, Hkv, d, S_max, q_len, lens, ns, win, block, page, step):
+    n = _plan(B, Hq, Hkv, S_max, q_len, d, ns, win, block or 1)
+    assert n > 1
+    q, kc = _rand((B, q_len, Hq, d), 61, torch.bfloat16, gpu_device), _rand((B, S_max, Hkv, d), 62, torch.bfloat16, gpu_device)
+    vc = kc if d == 576 else _rand((B, S_max, Hkv, d), 63, torch.bfloat16, gpu_device)
+    for b, L in enumerate(lens):
+        kc[b, L:] = float("nan")
+        vc[b, L:] = float("nan")
+    seqlens, scale, d_v = torch.tensor(lens, dtype=torch.int32, device=gpu_device), (192 if d == 576 else 128) ** -0.5, 512 if d == 576 else 128
+    if page:
+        from tests.test_gpu_parity_paged import _paginate
+        pages, table = _paginate(kc, lens, page, seed=3)
+        vpages = pages if vc is kc else _paginate(vc, lens, page, seed=3)[0]
+        out, lse = _run_paged(q, pages, vpages, table, seqlens, (ns, win), scale, d_v, block)
+    else:
+        out, lse = _run(q, kc, vc, seqlens, (ns, win), scale, d_v, block)
+    _check(q, kc, vc, lens, out, lse, (ns, win), scale, f"split {n}: q{q_len} lens{lens} ns{ns} W{win} b{block}", block, step)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [576, 128])
+def test_large_results_do_not_come_from_split_tiles(gpu_device, d):
+    """Rows whose weight sits on one key, in some groups of 16 rows and not in others."""
+    B, Hq, Hkv, S_max, q_len = (4, 64, 1, 6144, 11) if d == 576 else (4, 32, 8, 2304, 64)
+    ns, win, lens = 16, 5000 if d == 576 else 2000, [S_max, S_max - 7, S_max - 500, S_max - 1001]
+    assert _plan(B, Hq, Hkv, S_max, q_len, d, ns, win) > 1
+    q, kc = _rand((B, q_len, Hq, d), 64, torch.bfloat16, gpu_device), _rand((B, S_max, Hkv, d), 65, torch.bfloat16, gpu_device)
+    vc = kc if d == 576 else _rand((B, S_max, Hkv, d), 66, torch.bfloat16, gpu_device)
+    q[0, 3, 5] = 2 * kc[0, S_max - 100, 5 * Hkv // Hq]      # its weight sits on that key
+    q[2] *= 4
+    seqlens, scale, d_v = torch.tensor(lens, dtype=torch.int32, device=gpu_device), (192 if d == 576 else 128) ** -0.5, 512 if d == 576 else 128
+    out, lse = _run(q, kc, vc, seqlens, (ns, win), scale, d_v)
+    assert out[0, 3, 5].abs().max() >= 2
+    _check(q, kc, vc, lens, out, lse, (ns, win), scale, f"large results d{d}", None, 3)
+    k0 = kc[:1]
+    _check(q[:1, 3:4], k0, k0 if vc is kc else vc[:1], [S_max - q_len + 4], out[:1, 3:4], lse[:1, :, 3:4], (ns, win), scale, f"peaked row d{d}")
+
+
+@pytest.mark.gpu
+def test_scratch_memory(gpu_device):
+    B, Hq, S_max, q_len, lens, pat, scale = 2, 64, 3000, 5, [3000, 1234], (128, 2000), 192 ** -0.5
+    q, kc = _rand((B, q_len, Hq, 576), 67, torch.bfloat16, gpu_device), _rand((B, S_max, 1, 576), 68, torch.bfloat16, gpu_device)
+    seqlens = torch.tensor(lens, dtype=torch.int32, device=gpu_device)
+    need = loza.loza_ssa_extend_workspace_bytes(B, Hq, 1, S_max, q_len, 576, 512, *pat)
+    assert need > 0
+    same = lambda a, b: all(torch.equal(x.view(torch.int16), y.view(torch.int16)) for x, y in zip(a, b))
+    fresh = lambda: (torch.full((B, q_len, Hq, 512), float("nan"), dtype=torch.bfloat16, device=gpu_device),
+                     torch.full((B, Hq, q_len), float("nan"), device=gpu_device))
+    call = lambda o, **kw: loza.loza_ssa_extend(q, kc, kc, seqlens, *o, *pat, scale, **kw)
+    ref = fresh()
+    call(ref)
+    torch.cuda.synchronize()
+    # a workspace of the caller's, between guard bytes, with anything in it
+    ws = torch.full((need + 512,), 255, dtype=torch.uint8, device=gpu_device)
+    got = fresh()
+    call(got, workspace=ws[256:256 + need])
+    torch.cuda.synchronize()
+    assert same(got, ref) and (ws[:256] == 255).all() and (ws[256 + need:] == 255).all()
+    with pytest.raises(loza.LozaError) as e:
+        call(got, workspace=ws[256:256 + need - 1])
+    assert e.value.status == -4
+    # another stream, by object and by handle
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    for stream in (side, side.cuda_stream):
+        got = fresh()
+        torch.cuda.synchronize()
+        call(got, stream=stream)
+        side.synchronize()
+        assert same(got, ref)
+    # under capture: without scratch memory of the caller's the launches without it, with it the same as above
+    whole = fresh()
+    L = B_.lib()
+    assert L.loza_ssa_extend(q.data_ptr(), kc.data_ptr(), kc.data_ptr(), seqlens.data_ptr(), whole[0].data_ptr(), whole[1].data_ptr(), B, Hq, 1,
+                             S_max, q_len, 576, 512, *pat, scale, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    for kw, want in (({}, whole), ({"workspace": ws[256:256 + need]}, ref)):
+        got = fresh()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            call(got, **kw)
+        for _ in range(3):
+            got[0].zero_()
+            torch.randn(1 << 20, device=gpu_device).sum().item()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert same(got, want)
+
+
+def test_what_splits_and_what_does_not():
+    assert _plan(1, 64, 1, 65536, 2, 576, 128, 8192) >= 16
+    assert _plan(16, 64, 1, 65536, 4, 576, 128, 8192) >= 4
+    assert _plan(4, 64, 1, 65536, 1000, 576, 128, 8192) == 1          # fills the chip by itself
+    assert _plan(1, 64, 1, 450, 450, 576, 16, 130) == 1               # the whole sequence: a prefill
+    for bad in ((0, 64, 1, 100, 2, 576, 512, 1, 9, 1), (1, 64, 1, 100, 101, 576, 512, 1, 9, 1), (1, 64, 1, 100, 2, 577, 512, 1, 9, 1),
+                (1, 64, 1, 100, 2, 576, 512, -1, 9, 1), (1, 64, 1, 100, 2, 576, 512, 1, 0, 1), (1, 64, 1, 100, 2, 576, 512, 1, 9, 0)):
+        assert loza.loza_ssa_extend_workspace_bytes(*bad) == 0
+    for B in (1, 2, 5, 16, 200):                                      # the scratch memory stays below 2 rounds of tiles
+        for q_len in (1, 2, 7, 100, 2048):
+            for Hq, Hkv, d in ((64, 1, 576), (32, 8, 128), (32, 32, 128), (3, 1, 128)):
+                n = _plan(B, Hq, Hkv, 1 << 20, q_len, d, 128, 8192)
+                assert 1 <= n <= 64 and (n == 1 or n * B * Hq * q_len <= 1024 * 128 + 128 * n * B * Hkv)
+
+
+def test_bad_arguments_are_rejected_before_any_launch():
+    def call(ws=FAKE, nbytes=1 << 40, table=None, seqlens=FAKE, q_len=4, page=64, block=1, scale=0.07):
+        return B_.lib().loza_ssa_extend_with_workspace(FAKE, FAKE, FAKE, table, seqlens, FAKE, FAKE, 2, 64, 1, 8192, 256, page, 128, q_len, 576, 512, 128,
+                                                       4096, block, scale, ws, nbytes, None)
+    assert call(ws=None) == -4 and call(nbytes=1000) == -4 and call(ws=FAKE + 4) == -6
+    assert call(seqlens=None) == -1 and call(q_len=0) == -2 and call(block=0) == -2 and call(scale=0.0) == -2
+    assert call(table=FAKE, page=48) == -2 and call(table=FAKE + 2) == -6
