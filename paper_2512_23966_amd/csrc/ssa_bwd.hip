@@ -13,6 +13,7 @@
 // Three kernels:
 //   * ssa_bwd_rowstat_kernel: per query row, (lse log2(e), D) in the row order the main kernel
 //     walks through (position-major, heads of a group together).
+//   * (heads of width 128 take ssa_bwd128.hip in the place of the two below)
 //   * ssa_bwd_kernel<.., KEYS = false>: one workgroup keeps 64 query rows (Q and dO as matrix-core
 //     operands in registers) and streams the live key tiles of 32 keys past them: dQ.
 //   * ssa_bwd_kernel<.., KEYS = true>: one workgroup keeps 64 keys (K and V in registers) and
@@ -39,6 +40,7 @@
 #include <type_traits>
 
 #include "score_asm.h"
+#include "ssa_bwd_items.h"
 #include "ssa_device.h"
 #include "ssa_kernels.h"
 
@@ -71,17 +73,18 @@ __device__ __forceinline__ bf16x8 read_transposed(const char *tile, int row, int
 
 }  // namespace
 
-// (lse log2(e), dO . O) of every query row, stored [B, Hkv, Rpad] with row index i * G + head-in-group.
+// The statistics of every query row, stored [B, Hkv, Rpad] with row index i * G + head-in-group: (lse log2(e), D = dO . O).
 template <int DV>
 __global__ __launch_bounds__(256) void ssa_bwd_rowstat_kernel(const BwdParams p)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // flat (b, i, h)
+    constexpr int LPR = DV / 8 < 64 ? DV / 8 : 64;                     // lanes per row, 16 bytes each
+    const int lane = threadIdx.x % LPR;
+    const int64_t row = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;  // flat (b, i, h)
     const int64_t n_rows = (int64_t)p.B * p.S * p.Hq;
     if (row >= n_rows) return;
     const uint16_t *o = p.out + row * DV, *d = p.dout + row * DV;
     float acc = 0.f;
-    for (int c = lane * 8; c < DV; c += 512) {
+    for (int c = lane * 8; c < DV; c += LPR * 8) {
         const u32x4 a = *(const u32x4 *)(o + c), b = *(const u32x4 *)(d + c);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -90,23 +93,43 @@ __global__ __launch_bounds__(256) void ssa_bwd_rowstat_kernel(const BwdParams p)
         }
     }
 #pragma unroll
-    for (int s = 32; s > 0; s >>= 1) acc += __shfl_xor(acc, s, 64);
+    for (int s = LPR / 2; s > 0; s >>= 1) acc += __shfl_xor(acc, s, 64);
     if (lane == 0) {
         const int h = (int)(row % p.Hq);
         const int64_t bi = row / p.Hq, i = bi % p.S, b = bi / p.S;
         const int g = h / p.G, hh = h - g * p.G;
-        float2 st;
-        st.x = p.lse[(b * p.Hq + h) * p.S + i] * 1.44269504088896340736f;
-        st.y = acc;
-        p.rowstat[(b * p.Hkv + g) * p.r_pad + i * p.G + hh] = st;
+        const float lse = p.lse[(b * p.Hq + h) * p.S + i];
+        const int64_t at = (b * p.Hkv + g) * p.r_pad + i * p.G + hh;
+        if constexpr (DV == 128) {
+            // - lse / scale and - D as three bf16 terms each (all 24 bits), for ssa_bwd128.hip to add by matrix instructions
+            auto terms = [](float x, uint32_t &a, uint32_t &b) {
+                const uint32_t w = pack_bf16(x, 0.f) & 0xffffu;
+                const float r = __builtin_fabsf(x) == __builtin_inff() ? 0.f : x - __builtin_bit_cast(float, w << 16);
+                const uint32_t w2 = pack_bf16(r, 0.f) & 0xffffu;
+                a = w | w2 << 16;
+                b = pack_bf16(r - __builtin_bit_cast(float, w2 << 16), 0.f) & 0xffffu;
+            };
+            u32x4 rec;
+            uint32_t x, y;
+            terms(-lse / p.scale, x, y);
+            rec[0] = x; rec[1] = y;
+            terms(-acc, x, y);
+            rec[2] = x; rec[3] = y;
+            ((u32x4 *)p.rowstat)[at] = rec;
+        } else {
+            float2 st;
+            st.x = lse * 1.44269504088896340736f;
+            st.y = acc;
+            p.rowstat[at] = st;
+        }
     }
 }
 
-template <int DQK, int DV, bool ALIAS, bool KEYS>
+template <int DQK, int DV, bool KEYS>
 struct BwdCfg {
     static constexpr int ROW1 = DQK * 2 + 16, ROW2 = DV * 2 + 16;   // padded LDS rows of the streamed tiles
     static constexpr int CPR1 = ROW1 / 16, CPR2 = ROW2 / 16;
-    static constexpr bool HAS_Y2 = KEYS || !ALIAS;    // a second streamed tile (dO rows, or separate values)
+    static constexpr bool HAS_Y2 = KEYS;              // a second streamed tile (dO rows; the values are the key rows' prefix)
     static constexpr int N1 = (32 * CPR1 + 63) / 64;  // 1 KB copy instructions per tile
     static constexpr int N2 = HAS_Y2 ? (32 * CPR2 + 63) / 64 : 0;
     static constexpr int NSTAT = KEYS ? 1 : 0;        // + the row statistics of the tile
@@ -123,7 +146,7 @@ struct BwdCfg {
     // of phase 1 are more than the compute unit's memory pipeline takes at that pace (the waves queue
     // on it); only A2_WOVEN of the second sub-tile's are woven into phase 1, the others go out in pairs
     // during the elementwise step (measured: in threes slightly worse, in fours much worse).
-    static constexpr int A2_WOVEN = (KEYS && DQK == 576 && DV == 512) ? 2 : A2;
+    static constexpr int A2_WOVEN = KEYS ? 2 : A2;
     static constexpr int STAGE = NI * 1024;
     static constexpr int OFF_Y2 = N1 * 1024, OFF_STAT = (N1 + N2) * 1024;
     static constexpr int PROW = 32 * 2 + 16;          // LDS bytes per row of the dS / p buffers
@@ -134,26 +157,24 @@ struct BwdCfg {
     static constexpr int LDS_BYTES = OFF_XCH + 2 * XCH;
     static_assert(LDS_BYTES <= 160 * 1024, "does not fit the 160 KB LDS");
     // accumulator blocks (32 columns x 32 items of X) per wave
-    static constexpr bool SPLIT_KV = KEYS && !ALIAS;  // half the waves take dK, the other half dV
-    static_assert(!SPLIT_KV || DQK == DV, "separate values: equal widths only");
     // Phase 2: every wave accumulates a few column blocks (32 columns) for BOTH blocks of X, so that a
     // transposed fragment of the streamed tile, once fetched from LDS, feeds two matrix instructions
     // (fetched once per block of X, LDS bandwidth bounds the kernel). ND0 / ND1: column blocks of a
     // wave of role 0 / role 1; role 0 (longer phase 1, four more operand fragments) takes the smaller share.
     static constexpr int NBLK = DQK / 32;
-    static constexpr int ND0 = SPLIT_KV ? NBLK / 2 : NBLK / 4;
-    static constexpr int ND1 = SPLIT_KV ? (DV / 32) / 2 : (NBLK - 2 * ND0) / 2;
-    static_assert(SPLIT_KV || 2 * ND0 + 2 * ND1 == NBLK, "column blocks must split over the four waves");
+    static constexpr int ND0 = NBLK / 4;
+    static constexpr int ND1 = (NBLK - 2 * ND0) / 2;
+    static_assert(2 * ND0 + 2 * ND1 == NBLK, "column blocks must split over the four waves");
     // of a role-1 wave's blocks, how many also take the second product (dV, columns below d_v)
-    static constexpr int NDBL1 = (KEYS && !SPLIT_KV) ? (DV / 32 - 2 * ND0) / 2 : 0;
+    static constexpr int NDBL1 = KEYS ? (DV / 32 - 2 * ND0) / 2 : 0;
     static_assert(NDBL1 >= 0 && NDBL1 <= ND1, "split of the d_v columns");
     static_assert(DQK % 64 == 0 && DV % 32 == 0 && DV <= DQK, "head widths");
 };
 
-template <int DQK, int DV, bool ALIAS, bool KEYS>
+template <int DQK, int DV, bool KEYS>
 __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
 {
-    using C = BwdCfg<DQK, DV, ALIAS, KEYS>;
+    using C = BwdCfg<DQK, DV, KEYS>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const uint32_t smem_lds = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char *)smem);
     const int tid = threadIdx.x;
@@ -169,10 +190,8 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
     auto div_g = [&](int r) { return g_log2 >= 0 ? r >> g_log2 : r / G; };
 
     // ---- which work item ----------------------------------------------------------------------------
-    const int n_kt = (int)((S + 63) / 64);  // key tiles of 64 keys
-    int b, g, xt, chunk = 0;
-    bool partial = false;  // KEYS: leave an fp32 partial sum for the reduce kernel
-    bool is_split = false; // KEYS: a chunk of a key tile that is split for balance
+    int b, g, xt;
+    BwdItem it{};
     if (!KEYS) {
         const int x_tiles = (int)((R + 63) / 64);
         int id = blockIdx.x;
@@ -181,41 +200,10 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
         g = id % p.Hkv;
         b = id / p.Hkv;
     } else {
-        const int kt0 = p.max_chunks > 1 ? p.n_sink_kt : 0;               // key tiles before it run in chunks
-        const int items = kt0 * p.max_chunks + (n_kt - kt0 - p.n_split_kt), BH = p.B * p.Hkv;
-        // Workgroups go to the eight XCDs round-robin and every XCD has an L2 of its own. Handing every
-        // XCD one contiguous eighth of the items makes the workgroups that share an L2 neighbouring key
-        // tiles, whose row ranges overlap almost completely (see the rotation below). The chunks of split
-        // tiles come last, dealt out the same way among themselves.
-        auto per_xcd = [](int id, int total) {
-            const int eighth = total / 8;
-            return id < eighth * 8 ? (id % 8) * eighth + id / 8 : id;
-        };
-        int id = blockIdx.x;
-        is_split = id >= items * BH;
-        int it, per;
-        if (!is_split) {
-            id = per_xcd(id, items * BH);
-            per = items;
-        } else {
-            per = p.n_split_kt * p.split_chunks;
-            id = per_xcd(id - items * BH, per * BH);
-        }
-        it = id % per;
-        id /= per;
-        g = id % p.Hkv;
-        b = id / p.Hkv;
-        if (is_split) {
-            xt = kt0 + it / p.split_chunks;
-            chunk = it % p.split_chunks;
-            partial = true;
-        } else if (it < kt0 * p.max_chunks) {
-            xt = it / p.max_chunks;
-            chunk = it % p.max_chunks;
-            partial = true;
-        } else {
-            xt = kt0 + p.n_split_kt + (it - kt0 * p.max_chunks);
-        }
+        it = bwd_key_item(p, blockIdx.x);
+        b = it.b;
+        g = it.g;
+        xt = it.xt;
     }
 
     // ---- streamed tiles of this item -------------------------------------------------------------
@@ -237,42 +225,10 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
         if (wt0 <= nA) { nA = wt1 + 1; nB = 0; } else { nB = wt1 - wt0 + 1; }
         nt = nA + nB;
     } else {
-        int yt_lo, yt_hi;
-        bwd_key_tile_rows(p, xt, yt_lo, yt_hi);
-        yt_begin = yt_lo;
-        int yt_end = yt_hi + 1;
-        if (partial) {
-            const int ct = is_split ? (yt_end - yt_lo + p.split_chunks - 1) / p.split_chunks : p.chunk_tiles;
-            yt_begin = yt_lo + chunk * ct;
-            if (yt_begin + ct < yt_end) yt_end = yt_begin + ct;
-        }
-        nt = yt_end - yt_begin;
+        nt = it.nt;
         if (nt <= 0) return;  // a chunk beyond the rows of this key tile (the reduce kernel knows)
-        // Neighbouring key tiles see almost the same rows, each range shifted by 64 positions. Left to
-        // start at its own first row tile, every workgroup would stream its q and dout rows at a
-        // different place at any moment, and all of it would come from HBM (at the 128K shape: 2.4 TB
-        // per launch). Instead the 32 key tiles of a group (the workgroups that run together on one
-        // XCD) all start at the first row tile of the group's last member and wrap around inside their
-        // own range: they then ask for the same row tile at about the same time, and one fetch into
-        // the shared L2 serves all of them.
-        yt_start = yt_begin;
-        if (xt >= p.n_sink_kt && !is_split) {
-            const int k0 = p.max_chunks > 1 || p.n_split_kt > p.n_sink_kt ? p.split_kt0() + p.n_split_kt : p.n_sink_kt;
-            const int last = k0 + ((xt - k0) / 32) * 32 + 31;
-            int a_lo, a_hi;
-            bwd_key_tile_rows(p, last < n_kt - 1 ? last : n_kt - 1, a_lo, a_hi);
-            if (a_lo >= yt_begin && a_lo < yt_end) yt_start = a_lo;
-        } else if (is_split) {
-            // (an XCD runs all chunks of 32 / split_chunks key tiles at a time: those of equal number go together,
-            // unless chunks are so short that the tiles' own shift has them start where other chunks do)
-            const int kt0 = p.split_kt0(), grp = p.split_chunks < 32 ? 32 / p.split_chunks : 1, end = kt0 + p.n_split_kt - 1;
-            const int first = kt0 + ((xt - kt0) / grp) * grp, last = first + grp - 1 < end ? first + grp - 1 : end;
-            int f_lo, a_lo, a_hi;
-            bwd_key_tile_rows(p, first, f_lo, a_hi);
-            bwd_key_tile_rows(p, last, a_lo, a_hi);
-            const int ct = (a_hi - a_lo + p.split_chunks) / p.split_chunks, start = a_lo + chunk * ct;
-            if (a_lo - f_lo < ct && start >= yt_begin && start < yt_end) yt_start = start;
-        }
+        yt_begin = it.yt_begin;
+        yt_start = it.yt_start;
     }
     const int yt_wrap = yt_begin + nt;
     auto y_tile = [&](int t) {
@@ -331,7 +287,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
             x_D = st.y;
         } else {
             const int64_t krow = ((int64_t)b * S + x_c) * p.Hkv + g;
-            xp = ROLE == 0 ? p.k + krow * DQK : p.v + krow * (ALIAS ? DQK : DV);
+            xp = ROLE == 0 ? p.k + krow * DQK : p.v + krow * DQK;
         }
         xp += lh * 8;
 #pragma unroll
@@ -361,7 +317,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
         if (G >= 32) return (uint32_t)(item * width * 2);               // 32 heads of one position
         return (uint32_t)(((int64_t)(item / G) * pos_stride + item % G) * width * 2);
     };
-    constexpr int W2 = (!KEYS && ALIAS) ? DQK : DV;                      // element width of a Y2 row in memory
+    constexpr int W2 = KEYS ? DV : DQK;                                  // element width of a Y2 row in memory
     // per-lane byte offset of this lane's 16 bytes within the global tile, for instruction n of a sub-tile
     auto lane_offset = [&](int kind, int n) -> uint32_t {
         if (kind == 3) return (lane < 15 ? lane : 15) * 16;  // 32 rows x 8 bytes of statistics
@@ -442,9 +398,8 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
     // Which column blocks: the two waves of a role (xb = 0, 1) take alternate runs. With a shared
     // accumulator for dK and dV, blocks below d_v take both products; role 1's blocks are dealt so that
     // both of its waves get the same number of those (a < NDBL take two products, the rest one).
-    constexpr int NDBL = (KEYS && !C::SPLIT_KV) ? (ROLE == 0 ? ND : C::NDBL1) : 0;
+    constexpr int NDBL = KEYS ? (ROLE == 0 ? ND : C::NDBL1) : 0;
     auto col_block = [&](int a) {
-        if (C::SPLIT_KV) return xb * ND + a;
         if (ROLE == 0) return xb * ND + a;
         if (!KEYS) return 2 * C::ND0 + xb * ND + a;
         return a < NDBL ? 2 * C::ND0 + xb * NDBL + a : DV / 32 + xb * (ND - NDBL) + (a - NDBL);
@@ -475,14 +430,13 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
         // S reads the first streamed tile; T the second when there is one (else the values are the key
         // rows' prefix)
         constexpr int A_OFF = (ROLE == 1 && C::HAS_Y2) ? C::OFF_Y2 : 0, A_ROW = (ROLE == 1 && C::HAS_Y2) ? C::ROW2 : C::ROW1;
-        constexpr bool WIDE = (DQK == 576 && DV == 512);
-        if constexpr (WIDE) {
+        {
             // Wide rows: the whole phase is one generated asm statement (score_asm.h), as the forward's
             // score phase is: fragment kk + 6 is fetched from LDS while fragment kk feeds the matrix core,
             // with the exact lgkmcnt each step needs, and this wave's copy instructions of the next tile
             // issue between the matrix instructions.
-            static_assert(!WIDE || (C::A1 == 9 && C::A2 == (KEYS ? 8 : 0) && C::A2_WOVEN == (KEYS ? 2 : 0)), "one asm variant per copy plan");
-            static_assert(!WIDE || IN_AGPR == (ROLE == 0 ? 32 : 24), "one asm variant per register split");
+            static_assert(C::A1 == 9 && C::A2 == (KEYS ? 8 : 0) && C::A2_WOVEN == (KEYS ? 2 : 0), "one asm variant per copy plan");
+            static_assert(IN_AGPR == (ROLE == 0 ? 32 : 24), "one asm variant per register split");
             bf16x8 kf[LOZA_SCORE_DEPTH_576];
             uint32_t tmp;
             const uint32_t a_addr = smem_lds + st * C::STAGE + A_OFF + ln * A_ROW + lh * 16;
@@ -493,30 +447,6 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
                 if constexpr (ROLE == 0) LOZA_BWD_PHASE1_K36_A9_B0_G32(c, kf, tmp, a_addr, xf, yoff, tc, wave, C::NEXTRA);
                 else LOZA_BWD_PHASE1_K32_A9_B0_G24(c, kf, tmp, a_addr, xf, yoff, tc, wave, C::NEXTRA);
             }
-        } else {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) c[e] = 0.f;
-        // (fragments of the streamed tile are fetched PF steps ahead of the matrix instruction that
-        // uses them; the scheduling barriers keep the compiler from hoisting all of them to the top,
-        // which costs registers it then finds by spilling -- and a reload from scratch waits for every
-        // vector-memory operation in flight, the copy of the next tile included)
-        {
-            constexpr int NS = ROLE == 0 ? DQK / 16 : DV / 16, PF = 8, EVERY = NS / C::PER_WAVE > 0 ? NS / C::PER_WAVE : 1;
-            const char *ya = tile + A_OFF + ln * A_ROW + lh * 16;
-            bf16x8 af[PF];
-#pragma unroll
-            for (int d = 0; d < PF; ++d) af[d] = *(const bf16x8 *)(ya + d * 32);
-#pragma unroll
-            for (int kk = 0; kk < NS; ++kk) {
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk % PF], xf[kk], c, 0, 0, 0);
-                if (kk + PF < NS) af[kk % PF] = *(const bf16x8 *)(ya + (kk + PF) * 32);
-                if (kk % EVERY == 0 && kk / EVERY < C::PER_WAVE) issue_one(tc, kk / EVERY);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // (copies that did not find a slot above)
-#pragma unroll
-            for (int cu = (NS + EVERY - 1) / EVERY; cu < C::PER_WAVE; ++cu) issue_one(tc, cu);
-        }
         }
     };
     auto hand_over = [&](const f32x16 &c) {
@@ -641,8 +571,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
             auto frag = [&](int m) {
                 int ks, a, prod;
                 entry(m, ks, a, prod);
-                const bool second = C::SPLIT_KV ? ROLE == 1 : prod == 1;
-                return second ? read_transposed(t2, C::ROW2, col_block(a), ks, lane) : read_transposed(t1, C::ROW1, col_block(a), ks, lane);
+                return prod == 1 ? read_transposed(t2, C::ROW2, col_block(a), ks, lane) : read_transposed(t1, C::ROW1, col_block(a), ks, lane);
             };
             bf16x8 b_ds[2], b_p[2];
             auto load_b = [&](int ks) {
@@ -660,7 +589,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
             for (int m = 0; m < NF; ++m) {
                 int ks, a, prod;
                 entry(m, ks, a, prod);
-                const bool use_p = C::SPLIT_KV ? ROLE == 1 : prod == 1;
+                const bool use_p = prod == 1;
                 const bf16x8 f = fr[m % PF];
                 acc[a][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, use_p ? b_p[0] : b_ds[0], acc[a][0], 0, 0, 0);
                 acc[a][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, use_p ? b_p[1] : b_ds[1], acc[a][1], 0, 0, 0);
@@ -709,14 +638,8 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
                     w[1] = pack_bf16(acc[a][x2][4 * qd + 2], acc[a][x2][4 * qd + 3]);
                     *(u32x2 *)(op + col_block(a) * 32 + qd * 8) = w;
                 }
-        } else if (partial) {
-            // row [dK (d_qk) | dV (d_v, separate values only)] of fp32 partial sums
-            constexpr int COLS = C::SPLIT_KV ? DQK + DV : DQK;
-            const int64_t bg = (int64_t)b * p.Hkv + g;
-            const int64_t slot = is_split ? (p.max_chunks > 1 ? (int64_t)p.B * p.Hkv * p.n_sink_kt * p.max_chunks : 0) +
-                                                (bg * p.n_split_kt + (xt - p.split_kt0())) * p.split_chunks + chunk
-                                          : (bg * p.n_sink_kt + xt) * p.max_chunks + chunk;
-            float *op = p.part + slot * 64 * COLS + (int64_t)(x2 * 32 + ln) * COLS + ((C::SPLIT_KV && ROLE == 1) ? DQK : 0) + 4 * lh;
+        } else if (it.partial) {
+            float *op = p.part + (it.slot * 64 + x2 * 32 + ln) * DQK + 4 * lh;   // fp32 partial sums
 #pragma unroll
             for (int a = 0; a < ND; ++a)
 #pragma unroll
@@ -727,7 +650,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_kernel(const BwdParams p)
                 }
         } else {
             const int64_t krow = ((int64_t)b * S + xi) * p.Hkv + g;
-            uint16_t *op = ((C::SPLIT_KV && ROLE == 1) ? p.dv + krow * DV : p.dk + krow * DQK) + 4 * lh;
+            uint16_t *op = p.dk + krow * DQK + 4 * lh;
 #pragma unroll
             for (int a = 0; a < ND; ++a)
 #pragma unroll
@@ -788,20 +711,22 @@ template <int DQK, int DV, bool ALIAS>
 static hipError_t launch_backward_t(const BwdParams &p, hipStream_t stream)
 {
     const int64_t n_rows = (int64_t)p.B * p.S * p.Hq;
-    hipLaunchKernelGGL((ssa_bwd_rowstat_kernel<DV>), dim3((unsigned)((n_rows + 3) / 4)), dim3(256), 0, stream, p);
+    constexpr int RPB = 256 / (DV / 8 < 64 ? DV / 8 : 64);             // rows per workgroup
+    hipLaunchKernelGGL((ssa_bwd_rowstat_kernel<DV>), dim3((unsigned)((n_rows + RPB - 1) / RPB)), dim3(256), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    {
-        using C = BwdCfg<DQK, DV, ALIAS, true>;
-        auto kern = ssa_bwd_kernel<DQK, DV, ALIAS, true>;
-        e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
-        if (e != hipSuccess) return e;
-        const int64_t n_kt = (p.S + 63) / 64;
-        const int64_t kt0 = p.split_kt0();
-        const int64_t blocks = (kt0 * p.max_chunks + (n_kt - kt0 - p.n_split_kt) + (int64_t)p.n_split_kt * p.split_chunks) * p.Hkv * p.B;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), C::LDS_BYTES, stream, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+    const int64_t n_kt = (p.S + 63) / 64, kt0 = p.split_kt0();
+    const int64_t items = (kt0 * p.max_chunks + (n_kt - kt0 - p.n_split_kt) + (int64_t)p.n_split_kt * p.split_chunks) * p.Hkv * p.B;
+    if constexpr (DQK == 128) {
+        e = launch_bwd128_keys(p, ALIAS, items, stream);
+    } else {
+        using C = BwdCfg<DQK, DV, true>;
+        constexpr auto kern = ssa_bwd_kernel<DQK, DV, true>;
+        if ((e = allow_lds<kern>(C::LDS_BYTES)) != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)items), dim3(256), C::LDS_BYTES, stream, p);
+        e = hipGetLastError();
     }
+    if (e != hipSuccess) return e;
     // (the partial results may lie in dq, which the row-stationary kernel writes after they have been added)
     auto reduce = [&](auto kern, int64_t tiles) {
         constexpr int COLS = ALIAS ? DQK : DQK + DV;
@@ -811,16 +736,16 @@ static hipError_t launch_backward_t(const BwdParams &p, hipStream_t stream)
     };
     if (p.max_chunks > 1 && (e = reduce(ssa_bwd_reduce_kernel<DQK, DV, ALIAS, false>, p.n_sink_kt)) != hipSuccess) return e;
     if (p.n_split_kt > 0 && (e = reduce(ssa_bwd_reduce_kernel<DQK, DV, ALIAS, true>, p.n_split_kt)) != hipSuccess) return e;
-    {
-        using C = BwdCfg<DQK, DV, ALIAS, false>;
-        auto kern = ssa_bwd_kernel<DQK, DV, ALIAS, false>;
-        e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
-        if (e != hipSuccess) return e;
+    if constexpr (DQK == 128) {
+        return launch_bwd128_rows(p, ALIAS, stream);
+    } else {
+        using C = BwdCfg<DQK, DV, false>;
+        constexpr auto kern = ssa_bwd_kernel<DQK, DV, false>;
+        if ((e = allow_lds<kern>(C::LDS_BYTES)) != hipSuccess) return e;
         const int64_t blocks = ((p.S * p.G + 63) / 64) * p.Hkv * p.B;
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), C::LDS_BYTES, stream, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        return hipGetLastError();
     }
-    return hipSuccess;
 }
 
 // The row tiles of the key-stationary kernel must not straddle positions unevenly: heads per group a

@@ -90,7 +90,8 @@ struct BwdParams {
     const uint16_t *q, *k, *v, *out, *dout;
     const float *lse;
     uint16_t *dq, *dk, *dv;   // dv is unused when v aliases k (dk then holds the gradient of the shared tensor)
-    float2 *rowstat;          // workspace: [B, Hkv, r_pad] (lse * log2(e), dO . O), row index i * G + head-in-group
+    float2 *rowstat;          // workspace: [B, Hkv, r_pad] (lse * log2(e), dO . O), row index i * G + head-in-group;
+                              // width 128: 16 bytes a row, - lse / scale and - dO . O as three bf16 terms each
     // fp32 partial dK | dV: [B, Hkv, n_sink_kt, max_chunks, 64, columns] of the key tiles that hold sink keys,
     // then [B, Hkv, n_split_kt, split_chunks, 64, columns] of the key tiles that are split for balance
     float *part;
@@ -125,6 +126,9 @@ __host__ __device__ inline void bwd_key_tile_rows(const BwdParams &p, int kt, in
     yt_hi = (int)(((i_hi + 1) * p.G - 1) / 32);
 }
 
+// The two passes of the width-128 backward (ssa_bwd128.hip): `items` work items of 64 keys each, and dQ.
+hipError_t launch_bwd128_keys(const BwdParams &p, bool alias, int64_t items, hipStream_t stream);
+hipError_t launch_bwd128_rows(const BwdParams &p, bool alias, hipStream_t stream);
 bool bwd_group_supported(int G);
 hipError_t launch_backward_bf16(const BwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
 
