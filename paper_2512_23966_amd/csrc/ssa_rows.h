@@ -101,18 +101,6 @@ struct RowsCfg {
     static_assert(LDS_BYTES + 4096 <= 160 * 1024, "does not fit the 160 KB LDS");   // (and decode_row_direct's)
 };
 
-// eight columns of a finished row
-template <int DV>
-__device__ __forceinline__ void rows_store(const FwdParams &p, int64_t o_row, int c, f32x4 lo, f32x4 hi)
-{
-    u32x4 w;
-    w[0] = pack_bf16(lo[0], lo[1]);
-    w[1] = pack_bf16(lo[2], lo[3]);
-    w[2] = pack_bf16(hi[0], hi[1]);
-    w[3] = pack_bf16(hi[2], hi[3]);
-    *(u32x4 *)(p.out + o_row * DV + c) = w;
-}
-
 // One pass: rows 16 rt .. 16 rt + 15 of (batch b, key head g), tiles `split` of n_splits. EXACT: three-term weights
 // (decode). NT: the key rows are read by this workgroup only. All 256 threads call it together; the LDS it uses
 // (RowsCfg::LDS_BYTES) must not be in use when it starts.
@@ -292,6 +280,7 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
             const float a = m_new == LOZA_NEG_INF ? 1.0f : __builtin_amdgcn_exp2f(m_ref - m_new);
             m_ref = m_new;
             l_run *= a;
+            if (t > 0) {   // (not behind the first tile, whose accumulators are 0: 2,000 cycles; one sequence of window 8192 18.6 -> 17.4 us)
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) {
                 // (the accumulators live in the AGPR half of the register file; pinned there on both
@@ -301,6 +290,7 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
                 x *= a;
                 asm volatile("" : "+a"(x));
                 o[cb] = x;
+            }
             }
         }
         const float m_use = m_ref == LOZA_NEG_INF ? 0.f : m_ref;   // a row with no live key so far
@@ -376,10 +366,11 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
     if (CHECK && tid == 0) *odd = 0;
     __syncthreads();
     // wave w finishes rows 4 w .. 4 w + 3 of the block, 512 (or 4 x 128) columns at a time
-    constexpr int LPR = DV / 8, RPI = 64 / LPR;   // lanes per row (8 columns each), rows per step
+    // (a lane's columns c .. c + 3 of either half of the row: reads of 16 bytes a lane side by side, whole lines stored)
+    constexpr int LPR = DV / 8, RPI = 64 / LPR, HALF = DV / 2;   // lanes per row (8 columns each), rows per step
 #pragma unroll
     for (int step = 0; step < 4 / RPI; ++step) {
-        const int rr = wave * 4 + step * RPI + lane / LPR, c = (lane % LPR) * 8;
+        const int rr = wave * 4 + step * RPI + lane / LPR, c = (lane % LPR) * 4;
         const int64_t row = r0 + rr;
         if (row >= R) continue;
         float mw[C::NW], m_all = LOZA_NEG_INF, l_all = 0.f;
@@ -395,7 +386,7 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
             l_all += a * ml[(w * M + rr) * 2 + 1];
             const char *op = smem + w * C::REGION + rr * C::OROW + c * 4;
             lo += a * *(const f32x4 *)op;
-            hi += a * *(const f32x4 *)(op + 16);
+            hi += a * *(const f32x4 *)(op + HALF * 4);
         }
         const int64_t qi = row_position(row, G);
         const int64_t h = (int64_t)g * G + (row - qi * G);
@@ -403,7 +394,7 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
         if (n_splits > 1) {
             float *po = p.part_o + (o_row * n_splits + split) * DV + c;
             *(f32x4 *)po = lo;
-            *(f32x4 *)(po + 4) = hi;
+            *(f32x4 *)(po + HALF) = hi;
             if (c == 0) {
                 float *pm = p.part_ml + (o_row * n_splits + split) * 4;
                 pm[0] = m_all;
@@ -416,9 +407,15 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
         hi *= inv;
         if (p.out_f32) {
             *(f32x4 *)(p.out_f32 + o_row * DV + c) = lo;
-            *(f32x4 *)(p.out_f32 + o_row * DV + c + 4) = hi;
+            *(f32x4 *)(p.out_f32 + o_row * DV + c + HALF) = hi;
         } else {
-            rows_store<DV>(p, o_row, c, lo, hi);
+            u32x2 w;
+            w[0] = pack_bf16(lo[0], lo[1]);
+            w[1] = pack_bf16(lo[2], lo[3]);
+            *(u32x2 *)(p.out + o_row * DV + c) = w;
+            w[0] = pack_bf16(hi[0], hi[1]);
+            w[1] = pack_bf16(hi[2], hi[3]);
+            *(u32x2 *)(p.out + o_row * DV + c + HALF) = w;
         }
         if constexpr (CHECK) {
             float z = 0.f;

@@ -11,6 +11,22 @@
 
 namespace loza {
 
+namespace {
+
+// eight columns of a finished row
+template <int DV>
+__device__ __forceinline__ void rows_store(const FwdParams &p, int64_t o_row, int c, f32x4 lo, f32x4 hi)
+{
+    u32x4 w;
+    w[0] = pack_bf16(lo[0], lo[1]);
+    w[1] = pack_bf16(lo[2], lo[3]);
+    w[2] = pack_bf16(hi[0], hi[1]);
+    w[3] = pack_bf16(hi[2], hi[3]);
+    *(u32x4 *)(p.out + o_row * DV + c) = w;
+}
+
+}  // namespace
+
 // FINISH: the second launch of an extend whose key tiles ssa_bf16.hip's tile kernel has split: the workgroup adds
 // the partial results of its 16 rows and is done, unless they must not come from once-rounded weights (a tile among
 // the first positions, a pattern of few live keys, a large result): then it computes its rows from the keys, as it
@@ -110,18 +126,19 @@ __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
 
 // Merge of the key splits of one query row that ssa_rows_kernel left (log-sum-exp rule, fixed order), of a decode
 // or (EXT) an extend:
-// DV / 4 threads of four columns each, times eight groups of splits that are added in LDS at the end (a
-// single chain over 64 splits took 23 us for 64 queries). With separate values, a result that holds a NaN or an
+// 128 columns a workgroup, 32 threads of four columns each, times eight groups of splits that are added in LDS at the
+// end (a single chain over 64 splits took 23 us for 64 queries; whole rows a workgroup left three quarters of the
+// chip idle for them: one sequence, window 8192, decode 17.4 us, now 16.9). With separate values, a result that holds a NaN or an
 // infinity is computed again in fp32 (decode, see above).
 template <int DQK, int DV, bool ALIAS, bool EXT>
-__global__ __launch_bounds__(DV / 4 * 8) void ssa_rows_merge_kernel(const FwdParams p)
+__global__ __launch_bounds__(256) void ssa_rows_merge_kernel(const FwdParams p)
 {
-    constexpr int TC = DV / 4, NG = 8;
+    constexpr int TC = 32, NG = 8;
     __shared__ f32x4 s_acc[NG][TC];
     __shared__ float s_w[64];
     __shared__ int s_odd;
-    const int64_t h = blockIdx.x;
-    const int tc = threadIdx.x % TC, grp = threadIdx.x / TC, n = p.n_splits;
+    const int64_t h = blockIdx.x / (DV / 128);
+    const int tc = threadIdx.x % TC, grp = threadIdx.x / TC, n = p.n_splits, col = (int)(blockIdx.x % (DV / 128)) * 128 + tc * 4;
     const float *ml = p.part_ml + h * n * 4;
     if (threadIdx.x < 64) {                        // one wave; n <= 64
         const int s = threadIdx.x;
@@ -133,7 +150,7 @@ __global__ __launch_bounds__(DV / 4 * 8) void ssa_rows_merge_kernel(const FwdPar
         for (int d = 32; d > 0; d >>= 1) ls += __shfl_xor(ls, d, 64);
         s_w[s] = ls > 0.f ? w / ls : 0.f;          // (an empty cache gives 0)
         if (s == 0) s_odd = 0;
-        if (s == 0) {
+        if (s == 0 && col == 0) {
             int64_t at = h;
             if constexpr (EXT) {                   // row (b, qi, head) of out, [b, head, qi] of lse
                 const int64_t bq = h / p.Hq, b = bq / p.q_len;
@@ -144,7 +161,7 @@ __global__ __launch_bounds__(DV / 4 * 8) void ssa_rows_merge_kernel(const FwdPar
     }
     __syncthreads();
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    const float *po = p.part_o + h * n * DV + tc * 4;
+    const float *po = p.part_o + h * n * DV + col;
 #pragma unroll 4
     for (int s = grp; s < n; s += NG) acc += s_w[s] * *(const f32x4 *)(po + (int64_t)s * DV);
     s_acc[grp][tc] = acc;
@@ -163,7 +180,7 @@ __global__ __launch_bounds__(DV / 4 * 8) void ssa_rows_merge_kernel(const FwdPar
     u32x2 w2;
     w2[0] = pack_bf16(acc[0], acc[1]);
     w2[1] = pack_bf16(acc[2], acc[3]);
-    *(u32x2 *)(p.out + h * DV + tc * 4) = w2;
+    *(u32x2 *)(p.out + h * DV + col) = w2;
 }
 
 template <int DQK, int DV, bool ALIAS, bool NT, bool EXACT>
@@ -177,7 +194,7 @@ static hipError_t launch_rows_t(const FwdParams &p, hipStream_t stream)
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), C::LDS_BYTES, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess || p.n_splits == 1) return e;
-    hipLaunchKernelGGL((ssa_rows_merge_kernel<DQK, DV, ALIAS, !EXACT>), dim3((unsigned)((int64_t)p.B * p.q_len * p.Hq)), dim3(DV / 4 * 8), 0, stream, p);
+    hipLaunchKernelGGL((ssa_rows_merge_kernel<DQK, DV, ALIAS, !EXACT>), dim3((unsigned)((int64_t)p.B * p.q_len * p.Hq * (DV / 128))), dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 
