@@ -9,6 +9,7 @@
 
 #include <type_traits>
 
+#include "ssa_device.h"
 #include "ssa_kernels.h"
 
 namespace loza {
@@ -28,8 +29,9 @@ typedef float f32x4_dword __attribute__((ext_vector_type(4), aligned(4)));   // 
 // 16 kk + 4 j + e takes part in step e, column 64 d + 4 m + e is row m of block e.
 // What bounds it at these sizes is latency (1024 rows of 320 keys of width 64 are 64 workgroups of three
 // tiles a wave): one wave per row, one key per lane with strided 4-byte loads and a serial sum over the keys
-// took 80 us, this 9.
-// The online softmax takes each row's own running maximum in every tile, and a tile without a live key of a
+// took 80 us, this 9 (in a graph, without the host's share: 9.95 with a branch around every load and the maximum
+// exchanged in every tile, now 9.4; 2,048 rows of 4 heads of width 128, window 512: 45.7 and 40).
+// The online softmax takes each row's own running maximum, and a tile without a live key of a
 // row leaves that row's state exactly as it was: a row's result does not depend on the rows it shares a
 // workgroup with, and a decode gives the bits of the prefill's last row. (The matrix instruction multiplies
 // every row's weight, 0 where the key is dead, with every value of the tile: a wave whose sums are not all
@@ -45,33 +47,56 @@ struct F32RowsCfg {
     static_assert(LDS_BYTES <= 160 * 1024, "does not fit the 160 KB LDS");
 };
 
-template <int ND, bool VEC>
+// DX: d_qk = d_v = DX (64, 96, 128), known to the compiler: no lane asks whether its columns exist, and no step of
+// the scores is taken of nothing; 0: any widths.
+template <int ND, bool VEC, int DX>
 __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(const F32Params p, const int row_tiles)
 {
     using C = F32RowsCfg<ND>;
+    static_assert(DX == 0 || (VEC && DX <= 64 * ND), "widths");
+    const int d_qk = DX ? DX : p.d_qk, d_v = DX ? DX : p.d_v;
+    constexpr int KQ = DX ? DX / 16 : ND * 4;               // steps of 16 features
     constexpr int NW = C::NW, N = 16, OROW = C::OROW;
     extern __shared__ __attribute__((aligned(16))) float smem_f[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, n16 = lane & 15, j4 = lane >> 4;
-    int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
     if (id >= (int64_t)row_tiles * p.Hkv * p.B) return;
-    const int rt = (int)(id % row_tiles);
-    id /= row_tiles;
-    const int g = (int)(id % p.Hkv), b = (int)(id / p.Hkv), G = p.Hq / p.Hkv;
+    int rt, g, b;
+    if (id <= 0x7fffffff) {                                  // (a 64-bit division takes more than a hundred instructions)
+        const int bg = (int)id / row_tiles;
+        rt = (int)id - bg * row_tiles;
+        b = bg / p.Hkv;
+        g = bg - b * p.Hkv;
+    } else {
+        const int64_t bg = id / row_tiles;
+        rt = (int)(id - bg * row_tiles);
+        b = (int)(bg / p.Hkv);
+        g = (int)(bg - (int64_t)b * p.Hkv);
+    }
+    const int G = p.Hq / p.Hkv;
     const bool decode = p.seqlens != nullptr;
     // valid keys (a length beyond the cache is cut to it); queries are its last (decode) or all positions
     const int64_t L = decode ? ((int64_t)p.seqlens[b] < p.S ? (int64_t)p.seqlens[b] : p.S) : p.S;
     const int64_t Sq = decode ? 1 : p.S, pos0 = L - Sq, R = Sq * G, r0 = (int64_t)rt * 16;
     const int n_sink = p.n_sink, block = p.block;
     auto window_begin = [&](int i) {
-        const int qblk = i / block;
+        const int qblk = block == 1 ? i : i / block;
         return p.window > qblk ? 0 : (qblk - p.window + 1) * block;
     };
-    const int i_min = (int)(pos0 + r0 / G), i_max = (int)(pos0 + ((r0 + 15 < R ? r0 + 15 : R - 1) / G));
+    const int i_min = (int)(pos0 + row_position(r0, G)), i_max = (int)(pos0 + row_position(r0 + 15 < R ? r0 + 15 : R - 1, G));
 
     // elements c .. c + 3 of a row of d, 0 past its end; the wave's lanes ask for [base, base + span) together
     auto load4 = [&](const float *row, int c, int d, int base, int span) -> f32x4 {
         f32x4 x = {0.f, 0.f, 0.f, 0.f};
-        if constexpr (VEC) {
+        if constexpr (DX > 0) {
+            if (base + span <= DX) {
+                x = *(const f32x4 *)(row + c);
+            } else {                                         // (96: half of the second block's lanes; the others load what they drop)
+                const f32x4 y = *(const f32x4 *)(row + (c < DX ? c : 0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = c < DX ? y[e] : 0.f;
+            }
+        } else if constexpr (VEC) {
             if (c < d) x = *(const f32x4 *)(row + c);
         } else if (base + span <= d) {
             x = *(const f32x4_dword *)(row + c);
@@ -86,12 +111,12 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
     };
 
     // this lane's query row (its matrix-core operand), and the row's window
-    const int64_t my_row = r0 + n16, row_c = my_row < R ? my_row : R - 1, qi = row_c / G;
+    const int64_t my_row = r0 + n16, row_c = my_row < R ? my_row : R - 1, qi = row_position(row_c, G);
     const int i_row = (int)(pos0 + qi), w_lo_row = window_begin(i_row < 0 ? 0 : i_row);
     const int64_t q_row = ((int64_t)b * Sq + qi) * p.Hq + (int64_t)g * G + (row_c - qi * G);
-    f32x4 qf[ND * 4];
+    f32x4 qf[KQ];
 #pragma unroll
-    for (int kk = 0; kk < ND * 4; ++kk) qf[kk] = load4(p.q + q_row * p.d_qk, kk * 16 + j4 * 4, p.d_qk, kk * 16, 16);
+    for (int kk = 0; kk < KQ; ++kk) qf[kk] = load4(p.q + q_row * d_qk, kk * 16 + j4 * 4, d_qk, kk * 16, 16);
 
     // live key tiles: [0, nA) and [wt0, wt1]; this wave takes those whose number is `wave` mod NW
     const int win_begin = window_begin(i_min < 0 ? 0 : i_min);
@@ -114,11 +139,11 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
         if (j >= n_sink && j < win_begin) j = win_begin;
         return j < i_max ? j : i_max;
     };
-    f32x4 kf[ND * 4];
+    f32x4 kf[KQ];
     auto load_keys = [&](int t) {
         const float *kr = kb + (int64_t)live_key(t * N + n16) * kstep;
 #pragma unroll
-        for (int kk = 0; kk < ND * 4; ++kk) kf[kk] = load4(kr, kk * 16 + j4 * 4, p.d_qk, kk * 16, 16);
+        for (int kk = 0; kk < KQ; ++kk) kf[kk] = load4(kr, kk * 16 + j4 * 4, d_qk, kk * 16, 16);
     };
 
     f32x4 o[ND][4];
@@ -140,14 +165,14 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
                 for (int i = 0; i < 4; ++i) {
                     const float *vr = vb + (int64_t)live_key(t * N + 4 * j4 + i) * vstep;
 #pragma unroll
-                    for (int d = 0; d < ND; ++d) vf[i][d] = load4(vr, d * 64 + n16 * 4, p.d_v, d * 64, 64);
+                    for (int d = 0; d < ND; ++d) vf[i][d] = load4(vr, d * 64 + n16 * 4, d_v, d * 64, 64);
                 }
             }
             f32x4 s4[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) s4[e] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kk = 0; kk < ND * 4; ++kk)
+            for (int kk = 0; kk < KQ; ++kk)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) s4[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kk][e], qf[kk][e], s4[e], 0, 0, 0);
             const int t_next = next_tile(t + 1);
@@ -161,29 +186,35 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
                 s[i] = ok ? s[i] * p.scale : -INFINITY;
                 cm = fmaxf(cm, s[i]);
             }
-            cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
-            cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
-            const float m_new = fmaxf(m, cm);
-            const float m_use = m_new == -INFINITY ? 0.f : m_new;   // a row without a live key so far
-            const float alpha = cm > m ? expf(m - m_use) : 1.f;
-            m = m_new;
+            // (each row's running maximum, whatever the rows beside it do; past the first tiles it seldom moves. A
+            // reference that may be exceeded by e^8 and a shorter exponential were another 4 % faster, and 0.4 % less exact.)
+            if (__any(cm > m)) {
+                cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
+                cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
+                const float alpha = cm > m ? expf(m - cm) : 1.f;
+                m = fmaxf(m, cm);
+                l *= alpha;
+#pragma unroll
+                for (int d = 0; d < ND; ++d)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[d][e] *= alpha;
+            }
+            const float m_use = m == -INFINITY ? 0.f : m;           // a row without a live key so far
             float ps = 0.f;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 s[i] = s[i] == -INFINITY ? 0.f : expf(s[i] - m_use);
                 ps += s[i];
             }
-            l = l * alpha + ps;
+            l += ps;
+            if constexpr (!BY_KEY) {
 #pragma unroll
-            for (int d = 0; d < ND; ++d)
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    o[d][e] *= alpha;
-                    if constexpr (!BY_KEY) {
+                    for (int d = 0; d < ND; ++d)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) o[d][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][d][e], s[i], o[d][e], 0, 0, 0);
-                    }
-                }
+                        for (int e = 0; e < 4; ++e) o[d][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][d][e], s[i], o[d][e], 0, 0, 0);
+            }
             if constexpr (BY_KEY) {
 #pragma unroll 1
                 for (int jq = 0; jq < 4; ++jq)
@@ -197,7 +228,7 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
                         for (int d = 0; d < ND; ++d)
 #pragma unroll
                             for (int r = 0; r < 4; ++r) {        // columns of o[d][.][r]
-                                const f32x4 x = load4(vr, d * 64 + j4 * 16 + r * 4, p.d_v, d * 64, 64);
+                                const f32x4 x = load4(vr, d * 64 + j4 * 16 + r * 4, d_v, d * 64, 64);
 #pragma unroll
                                 for (int e = 0; e < 4; ++e) o[d][e][r] = fmaf(w, x[e], o[d][e][r]);
                             }
@@ -238,7 +269,7 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
     for (int x = threadIdx.x; x < 16 * ND * 16; x += 64 * NW) {
         const int rr = x / (ND * 16), c = (x % (ND * 16)) * 4;
         const int64_t row = r0 + rr;
-        if (row >= R || c >= p.d_v) continue;
+        if (row >= R || c >= d_v) continue;
         float m_all = -INFINITY, l_all = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, ml[(w * 16 + rr) * 2]);
@@ -251,25 +282,25 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
         }
         // (an empty cache gives 0 and -inf; live keys whose scores are all -inf have no softmax)
         const float inv = L > 0 ? 1.0f / l_all : 0.f;
-        const int64_t i = row / G;
+        const int64_t i = row_position(row, G);
         const int64_t h = (int64_t)g * G + (row - i * G);
-        float *op = p.out + (((int64_t)b * Sq + i) * p.Hq + h) * p.d_v + c;
+        float *op = p.out + (((int64_t)b * Sq + i) * p.Hq + h) * d_v + c;
         if constexpr (VEC) {
             *(f32x4 *)op = acc * inv;
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (c + e < p.d_v) op[e] = acc[e] * inv;
+                if (c + e < d_v) op[e] = acc[e] * inv;
         }
         if (c == 0) p.lse[((int64_t)b * p.Hq + h) * Sq + i] = L > 0 && l_all == 0.f ? __builtin_nanf("") : m_all + logf(l_all);
     }
 }
 
-template <int ND, bool VEC>
+template <int ND, bool VEC, int DX = 0>
 static hipError_t launch_rows_f32_t(const F32Params &p, hipStream_t stream)
 {
     using C = F32RowsCfg<ND>;
-    constexpr auto kern = ssa_rows_f32_kernel<ND, VEC>;
+    constexpr auto kern = ssa_rows_f32_kernel<ND, VEC, DX>;
     hipError_t e = allow_lds<kern>(C::LDS_BYTES);
     if (e != hipSuccess) return e;
     const int64_t rows = (p.seqlens ? 1 : p.S) * (p.Hq / p.Hkv), row_tiles = (rows + 15) / 16;
@@ -283,6 +314,11 @@ template <bool VEC>
 static hipError_t launch_rows_f32(const F32Params &p, hipStream_t stream)
 {
     const int d = p.d_qk > p.d_v ? p.d_qk : p.d_v;
+    if constexpr (VEC) {
+        if (p.d_qk == p.d_v && d == 64) return launch_rows_f32_t<1, true, 64>(p, stream);
+        if (p.d_qk == p.d_v && d == 96) return launch_rows_f32_t<2, true, 96>(p, stream);
+        if (p.d_qk == p.d_v && d == 128) return launch_rows_f32_t<2, true, 128>(p, stream);
+    }
     if (d <= 64) return launch_rows_f32_t<1, VEC>(p, stream);
     if (d <= 128) return launch_rows_f32_t<2, VEC>(p, stream);
     if (d <= 192) return launch_rows_f32_t<3, VEC>(p, stream);
