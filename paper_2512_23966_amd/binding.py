@@ -152,7 +152,8 @@ def _dev_ptr(t: torch.Tensor, dtype, name: str) -> int:
 
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # torch.cuda.current_stream().cuda_stream without the object around it (2.8 us of a 10 us call)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -449,7 +450,7 @@ def _scratch(nbytes: int, stream):
     """Scratch memory for launches on `stream`, from torch's allocator and of that stream (given back when the caller
     drops it, it can only be handed out again behind those launches). None where there is none to be had: no memory
     left, or a stream under capture, whose graph would keep the address of memory that is given back."""
-    if stream is not None and _stream(stream) != torch.cuda.current_stream().cuda_stream:
+    if stream is not None and _stream(stream) != _stream(None):
         if not isinstance(stream, torch.cuda.Stream):
             stream = torch.cuda.ExternalStream(_stream(stream))
         with torch.cuda.stream(stream):
