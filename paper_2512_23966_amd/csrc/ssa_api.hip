@@ -720,7 +720,7 @@ static int backward_fill(loza::BwdParams &p, int B, int Hq, int Hkv, int64_t S, 
 
 static size_t backward_bytes(const loza::BwdParams &p, int d_qk, int d_v, bool alias, size_t *part_offset)
 {
-    size_t stat = (size_t)p.B * p.Hkv * (size_t)p.r_pad * (d_qk == 128 ? 16 : sizeof(float2));
+    size_t stat = (size_t)p.B * p.Hkv * (size_t)p.r_pad * sizeof(float2);
     stat = (stat + 255) / 256 * 256;
     if (part_offset) *part_offset = stat;
     const size_t cols = alias ? (size_t)d_qk : (size_t)d_qk + d_v;

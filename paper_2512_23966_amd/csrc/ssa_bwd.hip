@@ -100,28 +100,10 @@ __global__ __launch_bounds__(256) void ssa_bwd_rowstat_kernel(const BwdParams p)
         const int g = h / p.G, hh = h - g * p.G;
         const float lse = p.lse[(b * p.Hq + h) * p.S + i];
         const int64_t at = (b * p.Hkv + g) * p.r_pad + i * p.G + hh;
-        if constexpr (DV == 128) {
-            // - lse / scale and - D as three bf16 terms each (all 24 bits), for ssa_bwd128.hip to add by matrix instructions
-            auto terms = [](float x, uint32_t &a, uint32_t &b) {
-                const uint32_t w = pack_bf16(x, 0.f) & 0xffffu;
-                const float r = __builtin_fabsf(x) == __builtin_inff() ? 0.f : x - __builtin_bit_cast(float, w << 16);
-                const uint32_t w2 = pack_bf16(r, 0.f) & 0xffffu;
-                a = w | w2 << 16;
-                b = pack_bf16(r - __builtin_bit_cast(float, w2 << 16), 0.f) & 0xffffu;
-            };
-            u32x4 rec;
-            uint32_t x, y;
-            terms(-lse / p.scale, x, y);
-            rec[0] = x; rec[1] = y;
-            terms(-acc, x, y);
-            rec[2] = x; rec[3] = y;
-            ((u32x4 *)p.rowstat)[at] = rec;
-        } else {
-            float2 st;
-            st.x = lse * 1.44269504088896340736f;
-            st.y = acc;
-            p.rowstat[at] = st;
-        }
+        float2 st;
+        st.x = lse * 1.44269504088896340736f;
+        st.y = acc;
+        p.rowstat[at] = st;
     }
 }
 

@@ -31,6 +31,7 @@ namespace loza {
 
 namespace {
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // One global -> LDS copy instruction (1 KB), unknown to the compiler's wait counters: the loop waits with explicit counts.
@@ -47,10 +48,17 @@ __device__ __forceinline__ uint32_t pack2(float a, float b)
     return r;
 }
 
-// the number whose three bf16 terms a row's record holds
-__device__ __forceinline__ float three_terms(uint32_t a, uint32_t b)
+// Three bf16 terms that add up to x (all 24 bits), as a matrix operand's first three features. An infinity has no
+// remainder.
+__device__ __forceinline__ u32x2 three_terms(float x)
 {
-    return (__builtin_bit_cast(float, a << 16) + __builtin_bit_cast(float, a & 0xffff0000u)) + __builtin_bit_cast(float, b << 16);
+    const uint32_t w = pack2(x, 0.f);
+    const float r = __builtin_fabsf(x) == __builtin_inff() ? 0.f : x - __builtin_bit_cast(float, w << 16);
+    const uint32_t w2 = pack2(r, 0.f);
+    u32x2 t;
+    t[0] = w | w2 << 16;
+    t[1] = pack2(r - __builtin_bit_cast(float, w2 << 16), 0.f);
+    return t;
 }
 
 template <int N>
@@ -168,7 +176,7 @@ __global__ __launch_bounds__(256, 2) void ssa_bwd128_kernel(const BwdParams p)
     const uint32_t full = item_offset(31) + ROW - 16;
     const char *y1_all = (const char *)(KEYS ? p.q : p.k), *y2_all = (const char *)(KEYS ? p.dout : p.v);
     const int64_t row_base = KEYS ? (int64_t)b * S * p.Hq + (int64_t)g * G : (int64_t)b * S * p.Hkv + g;
-    const u32x4 *stats = (const u32x4 *)p.rowstat + ((int64_t)b * p.Hkv + g) * p.r_pad;
+    const float2 *stats = p.rowstat + ((int64_t)b * p.Hkv + g) * p.r_pad;
     auto copy_one = [&](int t, uint32_t stage, int half) {
         const int y0 = y_first(t);
         const int64_t row0 = KEYS ? row_base + y0 + (int64_t)div_g(y0) * (p.Hq - G) : row_base + (int64_t)y0 * p.Hkv;
@@ -182,7 +190,7 @@ __global__ __launch_bounds__(256, 2) void ssa_bwd128_kernel(const BwdParams p)
             copy_1k(b1, o, dst + x * C::NW * 1024);
             if (C::HAS_Y2) copy_1k(b2, o, dst + C::TILE + x * C::NW * 1024);
         }
-        if (KEYS && wave == half) copy_1k((const char *)(stats + y0), (uint32_t)ln * 16u, stage + half * C::TSTAGE + C::OFF_STAT);
+        if (KEYS && wave == half) copy_1k((const char *)(stats + y0), (uint32_t)(lane & 15) * 16u, stage + half * C::TSTAGE + C::OFF_STAT);
     };
     // step u: tiles PAIRS u, ... (past the last tile, that one again: the wait counts are the same throughout)
     auto copy_step = [&](int u, int st) {
@@ -203,9 +211,9 @@ __global__ __launch_bounds__(256, 2) void ssa_bwd128_kernel(const BwdParams p)
             const int64_t i = row_position(x_c, G);
             x_i = (int)i;
             row = ((int64_t)b * S + i) * p.Hq + (int64_t)g * G + (x_c - i * G);
-            const u32x4 st = stats[x_c];
-            x_lse2 = three_terms(st[0], st[1]) * p.scale_log2;
-            x_D = three_terms(st[2], st[3]);
+            const float2 st = stats[x_c];
+            x_lse2 = -st.x;
+            x_D = -st.y;
         } else {
             row = ((int64_t)b * S + x_c) * p.Hkv + g;
         }
@@ -269,6 +277,7 @@ __global__ __launch_bounds__(256, 2) void ssa_bwd128_kernel(const BwdParams p)
         return r < R ? (int)r : (int)R - 1;
     };
     int y_lo = 0, y_hi = 0;                                                         // of this lane's key
+    const float to_score = -1.0f / p.scale_log2;                                    // lse log2(e) -> - lse in units of the scores
     int any_lo = 0, any_hi = 0, all_lo = 0, all_hi = 0;                             // of some, of all of the wave's keys
     if constexpr (KEYS) {
         const int64_t kj0 = (int64_t)it.xt * C::X + xb * 32, kj1 = kj0 + 31;
@@ -306,13 +315,14 @@ __global__ __launch_bounds__(256, 2) void ssa_bwd128_kernel(const BwdParams p)
                 // The rows' - lse / scale and - D, three bf16 terms each, are one more step of either contraction
                 // (read as they are, 16 values a lane, they were a third of this phase's LDS time). The second half
                 // of the wave, whose part of the contraction is empty, takes zeros.
-                const u32x4 rec = *(__attribute__((address_space(3))) const u32x4 *)(uintptr_t)(t1 + C::OFF_STAT + ln * 16);
-                auto add = [&](uint32_t a, uint32_t b, f32x16 &x) {
-                    const u32x4 terms = {lh == 0 ? a : 0, lh == 0 ? b : 0, 0, 0}, ones = {0x3f803f80u, 0x3f80u, 0, 0};
+                const f32x2 rec = *(__attribute__((address_space(3))) const f32x2 *)(uintptr_t)(t1 + C::OFF_STAT + ln * 8);
+                auto add = [&](float v, f32x16 &x) {
+                    const u32x2 t3 = three_terms(v);
+                    const u32x4 terms = {lh == 0 ? t3[0] : 0, lh == 0 ? t3[1] : 0, 0, 0}, ones = {0x3f803f80u, 0x3f80u, 0, 0};
                     x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, terms), __builtin_bit_cast(bf16x8, ones), x, 0, 0, 0);
                 };
-                add(rec[0], rec[1], s);
-                add(rec[2], rec[3], t);
+                add(rec[0] * to_score, s);
+                add(-rec[1], t);
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll

@@ -90,8 +90,7 @@ struct BwdParams {
     const uint16_t *q, *k, *v, *out, *dout;
     const float *lse;
     uint16_t *dq, *dk, *dv;   // dv is unused when v aliases k (dk then holds the gradient of the shared tensor)
-    float2 *rowstat;          // workspace: [B, Hkv, r_pad] (lse * log2(e), dO . O), row index i * G + head-in-group;
-                              // width 128: 16 bytes a row, - lse / scale and - dO . O as three bf16 terms each
+    float2 *rowstat;          // workspace: [B, Hkv, r_pad] (lse * log2(e), dO . O), row index i * G + head-in-group
     // fp32 partial dK | dV: [B, Hkv, n_sink_kt, max_chunks, 64, columns] of the key tiles that hold sink keys,
     // then [B, Hkv, n_split_kt, split_chunks, 64, columns] of the key tiles that are split for balance
     float *part;
