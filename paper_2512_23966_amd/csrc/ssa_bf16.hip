@@ -1280,7 +1280,9 @@ int decode_rows_per_tile() { return 64; }
 // A prefill, or a chunk that (nearly) fills its cache, starts at position 0: its first tiles have few keys, and the
 // launch is simulated (128 heads of their own keys: 512 tokens 32 against 37 us, 800 tokens, 128 + 512, 80 against
 // 75). Otherwise, and from eight rounds on, every tile has a full window, and rounds are counted. The cache's
-// capacity decides nothing else: a paged and a contiguous cache take the same kernel.
+// capacity decides nothing else: a paged and a contiguous cache take the same kernel. (The figures are of the 256-row
+// kernel as it was with four waves of 64 rows; with eight of 32 it takes 0.74 to 0.97 of that time over 46 sizes, most
+// where windows are short: the line is on the safe side.)
 bool d128_tiles_pay(int B, int Hkv, int G, int64_t queries, int64_t S, int n_sink, int window, int block)
 {
     const int64_t rows = queries * G, big = (rows + 255) / 256, small = (rows + 127) / 128, heads = (int64_t)B * Hkv;
