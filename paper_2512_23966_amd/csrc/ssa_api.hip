@@ -150,9 +150,10 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
 // How many workgroups share the keys of a row in an extend that has scratch memory, and which kernel they run. Few
 // new tokens leave most compute units idle: 2 tokens of one sequence are 8 groups of 16 rows of the absorbed-MLA
 // shape, and took the same 153 us (window 8192) as 128 tokens. Splits of the few-rows kernel are merged row by row
-// (2 tokens 22 us, 16 tokens 37 to 59); with more rows the tile kernel, which reads its keys once for 128 rows, is ahead
-// (4 tokens of 16 sequences 166 -> 97 us, 144 tokens 388 -> 203, 256 tokens 390 -> 282), until its tiles fill the
-// chip by themselves (444 tokens 404 us, split 392). The line is a time model of both in microseconds, fitted to
+// (2 tokens 22 us, 16 tokens 37 to 59); calls too large for that kernel split the tile kernel's keys (144 tokens 388 ->
+// 203 us, 256 tokens 390 -> 282), until its tiles fill the chip by themselves (444 tokens 404 us, split 392). Calls of
+// the few-rows kernel never go over to the tile kernel, though it would be ahead (4 tokens of 16 sequences 166 and 97 us):
+// its weights are rounded to bf16 once, theirs hold two terms (error against 64 bits 1.9e-3 and 1.7e-3). The line is a time model of both in microseconds, fitted to
 // 60 sizes: workgroups go in rounds, a round costs a start and a step per tile of keys, and every set of partial
 // results of a row is written and read once. A split has to promise 7 %, which is what the model is worth. A chunk
 // that (nearly) fills its cache is a prefill, and has its bits.
@@ -183,9 +184,9 @@ ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk
     ExtendPlan best{loza::few_rows_bf16(B, Hkv, rows), 1};
     if (S * 8 <= q_len * 9) return best;
     double t = 0.93 * (best.rows ? t_rows(1) : t_tile(1));
-    for (int n = 2; n <= kMaxSplits && groups * n <= kComputeUnits; ++n)
+    for (int n = 2; best.rows && n <= kMaxSplits && groups * n <= kComputeUnits; ++n)
         if (t_rows(n) < t) { t = t_rows(n); best = {true, n}; }
-    for (int n = 2; n <= kMaxSplits && tiles * n <= 2 * slots; ++n)
+    for (int n = 2; !best.rows && n <= kMaxSplits && tiles * n <= 2 * slots; ++n)
         if (t_tile(n) < t) { t = t_tile(n); best = {false, n}; }
     return best;
 }

@@ -45,9 +45,9 @@ CASES = [
     (1, 128, 2, 576, 2048, 3, [2047], 0, 1200, None, 32, 1),             # two latents
     (2, 8, 2, 128, 4000, 5, [4000, 77], 70, 3000, None, 0, 1),           # separate values, 4 heads a group
     (1, 6, 2, 128, 2048, 19, [2011], 16, 1500, None, 64, 1),             # 3 heads a group
-    (4, 64, 1, 576, 6144, 11, [6143, 5001, 130, 4], 128, 5000, None, 0, 5),    # the tile kernel; tiles among the first positions
-    (2, 64, 1, 576, 8192, 33, [8192, 7001], 0, 7000, None, 128, 7),      # odd number of positions: half a tile at the end
-    (4, 32, 8, 128, 2304, 64, [2304, 2111, 150, 64], 64, 2000, None, 0, 13),   # narrow tiles, separate values
+    (4, 64, 1, 576, 6144, 33, [6143, 5001, 150, 20], 128, 5000, None, 0, 23),  # the tile kernel; tiles among the first positions
+    (2, 64, 1, 576, 8192, 65, [8192, 7001], 0, 7000, None, 128, 29),     # odd number of positions: half a tile at the end
+    (4, 32, 8, 128, 2304, 70, [2304, 2111, 150, 64], 64, 2000, None, 0, 29),   # narrow tiles, separate values
 ]
 
 
@@ -76,7 +76,7 @@ def test_split_extend(gpu_device, B, Hq, Hkv, d, S_max, q_len, lens, ns, win, bl
 @pytest.mark.parametrize("d", [576, 128])
 def test_large_results_do_not_come_from_split_tiles(gpu_device, d):
     """Rows whose weight sits on one key, in some groups of 16 rows and not in others."""
-    B, Hq, Hkv, S_max, q_len = (4, 64, 1, 6144, 11) if d == 576 else (4, 32, 8, 2304, 64)
+    B, Hq, Hkv, S_max, q_len = (4, 64, 1, 6144, 33) if d == 576 else (4, 32, 8, 2304, 70)
     ns, win, lens = 16, 5000 if d == 576 else 2000, [S_max, S_max - 7, S_max - 500, S_max - 1001]
     assert _plan(B, Hq, Hkv, S_max, q_len, d, ns, win) > 1
     q, kc = _rand((B, q_len, Hq, d), 64, torch.bfloat16, gpu_device), _rand((B, S_max, Hkv, d), 65, torch.bfloat16, gpu_device)
@@ -86,7 +86,7 @@ def test_large_results_do_not_come_from_split_tiles(gpu_device, d):
     seqlens, scale, d_v = torch.tensor(lens, dtype=torch.int32, device=gpu_device), (192 if d == 576 else 128) ** -0.5, 512 if d == 576 else 128
     out, lse = _run(q, kc, vc, seqlens, (ns, win), scale, d_v)
     assert out[0, 3, 5].abs().max() >= 2
-    _check(q, kc, vc, lens, out, lse, (ns, win), scale, f"large results d{d}", None, 3)
+    _check(q, kc, vc, lens, out, lse, (ns, win), scale, f"large results d{d}", None, 17)
     k0 = kc[:1]
     _check(q[:1, 3:4], k0, k0 if vc is kc else vc[:1], [S_max - q_len + 4], out[:1, 3:4], lse[:1, :, 3:4], (ns, win), scale, f"peaked row d{d}")
 
@@ -144,7 +144,8 @@ def test_scratch_memory(gpu_device):
 
 def test_what_splits_and_what_does_not():
     assert _plan(1, 64, 1, 65536, 2, 576, 128, 8192) >= 16
-    assert _plan(16, 64, 1, 65536, 4, 576, 128, 8192) >= 4
+    assert _plan(16, 64, 1, 65536, 4, 576, 128, 8192) == 1            # 256 groups of 16 rows: a round of the few-rows kernel
+    assert _plan(4, 64, 1, 65536, 36, 576, 128, 8192) >= 2            # the tile kernel
     assert _plan(4, 64, 1, 65536, 1000, 576, 128, 8192) == 1          # fills the chip by itself
     assert _plan(1, 64, 1, 450, 450, 576, 16, 130) == 1               # the whole sequence: a prefill
     for bad in ((0, 64, 1, 100, 2, 576, 512, 1, 9, 1), (1, 64, 1, 100, 101, 576, 512, 1, 9, 1), (1, 64, 1, 100, 2, 577, 512, 1, 9, 1),
