@@ -42,7 +42,6 @@
 #include "ssa_device.h"
 #include "ssa_direct.h"
 #include "ssa_kernels.h"
-#include "ssa_rows.h"
 #include "ssa_schedule.h"
 
 namespace loza {
@@ -105,11 +104,7 @@ struct TileCfg {
     static constexpr int OFF_FLAG = OFF_ALPHA + 2 * M * 4;        // int[2][4] (one per row block, padded)
     static constexpr int OFF_LPART = OFF_FLAG + 2 * 16;           // float[2][M]
     static constexpr int OFF_REDO = OFF_LPART + 2 * M * 4;        // int: the tile has to be computed again, with two-term P
-    // Groups of 16 rows that are computed again by themselves (as many as the whole tile would take the time of);
-    // width 128: none, their passes' LDS would halve the workgroups of a compute unit.
-    static constexpr int REDO_GROUPS = !DECODE && DQK > 128 ? 4 : 0;
-    static constexpr int TILE_BYTES = OFF_REDO + 16;
-    static constexpr int LDS_BYTES = REDO_GROUPS > 0 && RowsCfg<DQK, DV, ALIAS>::LDS_BYTES > TILE_BYTES ? RowsCfg<DQK, DV, ALIAS>::LDS_BYTES : TILE_BYTES;
+    static constexpr int LDS_BYTES = OFF_REDO + 16;
     // The softmax between the matrix instructions of the value phase takes the speculative form (below)
     // where that phase has a matrix instruction for every one of its jobs; with fewer (narrow values)
     // the vector ALU is the bound either way and the ordinary form has fewer instructions.
@@ -122,15 +117,12 @@ struct TileCfg {
     static_assert(DECODE || M * OUTROW <= OFF_ALPHA, "the output tile must fit the stages and P");
 };
 
-// What is left of a tile after a pass (the same in every wave): nothing, all of it (it has been left unwritten for
-// a PRECISE pass), or the groups of 16 rows whose bits are set.
-constexpr int kTileDone = 0, kTileAgain = -1;
-
-// One pass over one workgroup tile. PRECISE: P goes to the value phase as two bf16 terms. SPLIT (extend): the
+// One pass over one workgroup tile. PRECISE: P goes to the value phase as two bf16 terms. Returns
+// true (the same in every wave) when the tile has been left unwritten for a PRECISE pass. SPLIT (extend): the
 // workgroup takes every n_splits-th live key tile and leaves fp32 partial results, as a decode's does; the kernel
 // that adds them up (ssa_rows.hip) also answers the tiles that must not come from once-rounded weights.
 template <int DQK, int DV, int RB, bool ALIAS, bool DECODE, bool PRECISE, bool OUTF32, bool EXT, bool SPLIT = false>
-static __device__ __forceinline__ int ssa_fwd_tile(const FwdParams &p, char *smem)
+static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *smem)
 {
     using C = TileCfg<DQK, DV, RB, ALIAS, DECODE>;
     constexpr int M = C::M, N = C::N, NSTAGE = C::NSTAGE;
@@ -186,7 +178,7 @@ static __device__ __forceinline__ int ssa_fwd_tile(const FwdParams &p, char *sme
         const int64_t se = n_sink < L ? n_sink : L;
         const int64_t wb = L > 0 ? window_begin_of((int)(L - 1), p.window, p.block) : 0;
         const int64_t n_live = se + (L - (wb > se ? wb : se));
-        if (n_live < kDirectKeys) return kTileDone;
+        if (n_live < kDirectKeys) return false;
     }
 
     // ---- the query row this lane scores ---------------------------------------------------------
@@ -198,7 +190,7 @@ static __device__ __forceinline__ int ssa_fwd_tile(const FwdParams &p, char *sme
     const int i_max = DECODE ? (int)(L - 1) : (int)(pos0 + row_position((r0 + M - 1 < R) ? r0 + M - 1 : R - 1, G));
     // Tiles among the first positions, and every tile of a pattern that leaves all rows few live keys,
     // take the two-term pass right away.
-    if (!DECODE && !PRECISE && (p.all_precise || i_min < kPrecisePositions)) return kTileAgain;
+    if (!DECODE && !PRECISE && (p.all_precise || i_min < kPrecisePositions)) return true;
 
     bf16x8 qf[DQK / 16];
 
@@ -851,15 +843,9 @@ static __device__ __forceinline__ int ssa_fwd_tile(const FwdParams &p, char *sme
 
     // A result of magnitude 2 or more leaves the error budget little beyond its own rounding to bf16
     // (half an ulp is 2^-7 there), and it can only come from a row whose weight sits on a few keys, where
-    // the rounding of P to bf16 shows most. The groups of 16 rows that have such a row are not written: the
-    // caller computes them again with two-term weights, group by group (wide shape), or, where they are many, the
-    // whole tile. (1,024 live keys: a group takes 26 us, the tile 116; with N(0, 1) inputs one tile in twenty has
-    // such a row, mostly one. 32,768 tokens of 1 + 7 blocks: 4,963 -> 4,699 us; chunks of 1,000 tokens 4,279 -> 3,949.)
-    uint32_t redo = 0;
-    auto groups_of = [&](bool big, int rb) -> uint32_t {   // bit of every group of block rb that has such a row
-        const uint64_t m = __ballot(big);
-        return ((m & 0x0000ffff0000ffffull) ? 1u << (2 * rb) : 0u) | ((m & 0xffff0000ffff0000ull) ? 2u << (2 * rb) : 0u);
-    };
+    // the rounding of P to bf16 shows most. A tile with such a row is not written: it is computed again
+    // with two-term P (the caller runs the PRECISE pass when this one says so), all 128 rows of it.
+    bool big = false;
     if constexpr (!DECODE && !SPLIT && !OUTF32) {
         // Every lane holds 4 of the 512 (128) columns of 32 rows at a time: stored from here, every store
         // instruction touches 32 rows (check and stores of a wide tile: 19.1 thousand cycles). Through LDS a
@@ -888,7 +874,7 @@ static __device__ __forceinline__ int ssa_fwd_tile(const FwdParams &p, char *sme
                     w[1] = pack_bf16(x[2], x[3]);
                     *(u32x2 *)(op + db * 64 + qd * 16) = w;
                 }
-            if (!PRECISE) redo |= groups_of(mx >= kRedoMagnitude && r0 + rb * 32 + ln < R, rb);
+            big = big || (mx >= kRedoMagnitude && r0 + rb * 32 + ln < R);
         }
     } else if constexpr (!DECODE && !SPLIT && !PRECISE) {
 #pragma unroll
@@ -899,21 +885,18 @@ static __device__ __forceinline__ int ssa_fwd_tile(const FwdParams &p, char *sme
             for (int db = 0; db < C::DVB; ++db)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) mx = fmaxf(mx, __builtin_fabsf(o[db][rb][e]));
-            redo |= groups_of(rsum > 0.f && mx >= kRedoMagnitude * rsum && r0 + rb * 32 + ln < R, rb);
+            big = big || (rsum > 0.f && mx >= kRedoMagnitude * rsum && r0 + rb * 32 + ln < R);
         }
     }
     if constexpr (!DECODE && !SPLIT) {
-        if (!PRECISE && redo != 0 && lane == 0) atomicOr(s_redo, (int)redo);
+        if (!PRECISE && __any(big) && lane == 0) *s_redo = 1;
         lds_barrier();
-        if (!PRECISE) {
-            redo = (uint32_t)__builtin_amdgcn_readfirstlane(*(volatile int *)s_redo);
-            if (__builtin_popcount(redo) > C::REDO_GROUPS) return kTileAgain;
-        }
+        if (!PRECISE && *(volatile int *)s_redo) return true;
     }
 
     if constexpr (!DECODE && !SPLIT) {
         // lse = ln(sum_j exp(scale q.k_j)) = (m_ref + log2 l) * ln 2
-        if (scorer && lh == 0 && my_row < R && !(redo >> ((wr * 32 + ln) >> 4) & 1)) {
+        if (scorer && lh == 0 && my_row < R) {
             const int hh = (int)(my_row - (int64_t)r_row * G);
             p.lse[((int64_t)b * p.Hq + (int64_t)g * G + hh) * Sq + r_row] =
                 (m_ref + __builtin_amdgcn_logf(s_lpart[wr * 32 + ln])) * 0.69314718055994530942f;
@@ -926,7 +909,7 @@ static __device__ __forceinline__ int ssa_fwd_tile(const FwdParams &p, char *sme
 #pragma unroll 4
             for (int step = 0; step < M / NW / RPI; ++step) {
                 const int row = first + step * RPI;
-                if (r0 + row < R && !(redo >> (row >> 4) & 1)) {
+                if (r0 + row < R) {
                     const u32x4 w = *(const u32x4 *)(smem + row * C::OUTROW + (lane % LPR) * 16);
                     const int64_t o_row = ((int64_t)b * Sq + i) * p.Hq + (int64_t)g * G + hh;
                     __builtin_nontemporal_store(w, (u32x4 *)(p.out + o_row * DV + (lane % LPR) * 8));
@@ -996,12 +979,12 @@ static __device__ __forceinline__ int ssa_fwd_tile(const FwdParams &p, char *sme
             }
         }
     }
-    return (int)redo;
+    return false;
 }
 
 // Prefill / extend: every tile is computed with P rounded to bf16 once; a tile that cannot afford
 // that (few live keys per row, or a result large enough that its own rounding fills the error
-// budget) is computed with two-term P instead, or those of its rows that cannot. Decode: one pass of the split kernel.
+// budget) is computed with two-term P instead. Decode: one pass of the split kernel.
 template <int DQK, int DV, int RB, bool ALIAS, bool DECODE, bool OUTF32 = false, bool EXT = false, bool SPLIT = false>
 __global__ __launch_bounds__(256) void ssa_fwd_kernel(const FwdParams p)
 {
@@ -1011,21 +994,8 @@ __global__ __launch_bounds__(256) void ssa_fwd_kernel(const FwdParams p)
     } else if constexpr (SPLIT) {
         ssa_fwd_tile<DQK, DV, RB, ALIAS, false, false, false, true, true>(p, smem);
     } else {
-        using C = TileCfg<DQK, DV, RB, ALIAS, DECODE>;
-        const int left = ssa_fwd_tile<DQK, DV, RB, ALIAS, false, false, OUTF32, EXT>(p, smem);
-        if (left == kTileAgain) {
+        if (ssa_fwd_tile<DQK, DV, RB, ALIAS, false, false, OUTF32, EXT>(p, smem))
             ssa_fwd_tile<DQK, DV, RB, ALIAS, false, true, OUTF32, EXT>(p, smem);
-        } else if constexpr (C::REDO_GROUPS > 0) {
-            int id = blockIdx.x;
-            const int rt = p.row_tiles - 1 - id % p.row_tiles;
-            id /= p.row_tiles;
-            const int g = id % p.Hkv, b = id / p.Hkv;
-#pragma unroll 1
-            for (uint32_t groups = (uint32_t)left; groups != 0; groups &= groups - 1) {
-                __syncthreads();
-                ssa_rows_pass<DQK, DV, ALIAS, false, false>(p, smem, b, g, rt * (C::M / 16) + __builtin_ctz(groups), 0, 1);
-            }
-        }
     }
 }
 

@@ -1,5 +1,5 @@
 // Sixteen query rows of one key/value head against their live keys: the pass that the kernels for few query rows
-// are made of (ssa_rows.hip), and that answers the rows of a tile that once-rounded weights cannot (ssa_bf16.hip).
+// are made of (ssa_rows.hip).
 //
 // The tile kernel of ssa_bf16.hip gives a workgroup 64 (decode) or 128 query rows and lets its four
 // waves share every key tile, which is right where rows are plenty. With few rows it leaves the chip
