@@ -150,13 +150,16 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
 // How many workgroups share the keys of a row in an extend that has scratch memory, and which kernel they run. Few
 // new tokens leave most compute units idle: 2 tokens of one sequence are 8 groups of 16 rows of the absorbed-MLA
 // shape, and took the same 153 us (window 8192) as 128 tokens. Splits of the few-rows kernel are merged row by row
-// (2 tokens 22 us, 16 tokens 37 to 59); calls too large for that kernel split the tile kernel's keys (144 tokens 388 ->
-// 203 us, 256 tokens 390 -> 282), until its tiles fill the chip by themselves (444 tokens 404 us, split 392). Calls of
-// the few-rows kernel never go over to the tile kernel, though it would be ahead (4 tokens of 16 sequences 166 and 97 us):
-// its weights are rounded to bf16 once, theirs hold two terms (error against 64 bits 1.9e-3 and 1.7e-3). The line is a time model of both in microseconds, fitted to
-// 60 sizes: workgroups go in rounds, a round costs a start and a step per tile of keys, and every set of partial
-// results of a row is written and read once. A split has to promise 7 %, which is what the model is worth. A chunk
-// that (nearly) fills its cache is a prefill, and has its bits.
+// (2 tokens 22 us, 16 tokens 37 to 59); calls too large for that kernel split the tile kernel's keys, until its tiles
+// fill the chip by themselves. A split tile has two-term weights throughout (2.7 us a step, 1.45 with weights rounded
+// once): which rows have a large result is known only when the parts have been added, and a tile that has one may keep
+// none of its rows from once-rounded weights. 144 tokens of window 8192 386 -> 264 us; 256 tokens 400, in two 403: not
+// split. (d = 128, 8 key heads, window 4096: 280 tokens 152 -> 87, 600 tokens 153 -> 113.) Calls of the few-rows kernel
+// are split by that kernel only. The line is a time model of both in microseconds, fitted to 170 sizes: workgroups go in
+// rounds, a round costs a start and a step per tile of keys, and every set of partial results of a row is written and
+// read once. (Of a call that is not split, without tiles that are computed again for a large result; with 1 + 7 blocks
+// and N(0, 1) inputs nearly every call has one: 148 us instead of 61.) A split has to promise 7 %, which is what the
+// model is worth. A chunk that (nearly) fills its cache is a prefill, and has its bits.
 struct ExtendPlan {
     bool rows;
     int n_splits;
@@ -170,7 +173,7 @@ ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk
     int64_t live = (int64_t)pat.n_sink + (int64_t)pat.window * pat.block;
     if (live > S) live = S;
     auto rounds = [](int64_t workgroups, int slots) { return (double)((workgroups + slots - 1) / slots); };
-    const double set = wide ? 1.05e-3 : 0.28e-3;                       // one set of partial results of one row
+    const double set = wide ? 1.05e-3 : 0.28e-3;                       // one set of partial results of one row, merged by row
     auto t_rows = [&](int64_t n) {
         const double steps = (double)((live / 16 + 2 + 4 * n - 1) / (4 * n));
         return rounds(groups * n, kComputeUnits) * (wide ? 8 + 1.15 * steps : 5 + 0.7 * steps) + (n > 1 ? 3.5 + set * rows * heads * n : 0);
@@ -178,8 +181,10 @@ ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk
     // (two workgroups of the narrow tile kernel share a compute unit)
     const int slots = wide ? kComputeUnits : 2 * kComputeUnits;
     auto t_tile = [&](int64_t n) {
-        const double steps = (double)((live / 32 + 2 + n - 1) / n), step = wide ? 1.65 : tiles * n <= kComputeUnits ? 1.1 : 1.5;
-        return rounds(tiles * n, slots) * (12 + step * steps) + (n > 1 ? 6 + set * rows * heads * n : 0);
+        const double steps = (double)((live / 32 + 2 + n - 1) / n);
+        const bool alone = tiles * n <= kComputeUnits;
+        const double step = n > 1 ? (wide ? 2.7 : alone ? 1.4 : 2.0) : (wide ? 1.45 : alone ? 1.05 : 1.36);
+        return rounds(tiles * n, slots) * (12 + step * steps) + (n > 1 ? 6 + (wide ? 0.45e-3 : 0.11e-3) * rows * heads * n : 0);
     };
     ExtendPlan best{loza::few_rows_bf16(B, Hkv, rows), 1};
     if (S * 8 <= q_len * 9) return best;

@@ -119,8 +119,8 @@ struct TileCfg {
 
 // One pass over one workgroup tile. PRECISE: P goes to the value phase as two bf16 terms. Returns
 // true (the same in every wave) when the tile has been left unwritten for a PRECISE pass. SPLIT (extend): the
-// workgroup takes every n_splits-th live key tile and leaves fp32 partial results, as a decode's does; the kernel
-// that adds them up (ssa_rows.hip) also answers the tiles that must not come from once-rounded weights.
+// workgroup takes every n_splits-th live key tile and leaves fp32 partial results, as a decode's does; which rows have
+// a large result is not known before these have been added up, so all of them are PRECISE.
 template <int DQK, int DV, int RB, bool ALIAS, bool DECODE, bool PRECISE, bool OUTF32, bool EXT, bool SPLIT = false>
 static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *smem)
 {
@@ -984,7 +984,7 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
 
 // Prefill / extend: every tile is computed with P rounded to bf16 once; a tile that cannot afford
 // that (few live keys per row, or a result large enough that its own rounding fills the error
-// budget) is computed with two-term P instead. Decode: one pass of the split kernel.
+// budget) is computed with two-term P instead. Decode, and an extend whose keys are split: one pass.
 template <int DQK, int DV, int RB, bool ALIAS, bool DECODE, bool OUTF32 = false, bool EXT = false, bool SPLIT = false>
 __global__ __launch_bounds__(256) void ssa_fwd_kernel(const FwdParams p)
 {
@@ -992,7 +992,7 @@ __global__ __launch_bounds__(256) void ssa_fwd_kernel(const FwdParams p)
     if constexpr (DECODE) {
         ssa_fwd_tile<DQK, DV, RB, ALIAS, true, false, false, false>(p, smem);
     } else if constexpr (SPLIT) {
-        ssa_fwd_tile<DQK, DV, RB, ALIAS, false, false, false, true, true>(p, smem);
+        ssa_fwd_tile<DQK, DV, RB, ALIAS, false, true, false, true, true>(p, smem);
     } else {
         if (ssa_fwd_tile<DQK, DV, RB, ALIAS, false, false, OUTF32, EXT>(p, smem))
             ssa_fwd_tile<DQK, DV, RB, ALIAS, false, true, OUTF32, EXT>(p, smem);
@@ -1078,6 +1078,39 @@ static bool pattern_needs_precise(int64_t S, int n_sink, int window, int block)
     return live_at(kPrecisePositions - 1) < kPrecisePositions || (i0 < S && live_at(i0) < kPrecisePositions);
 }
 
+// Second launch of an extend whose key tiles are split: adds the partial results of a row (a few, of two-term weights:
+// the normaliser is the sum of the rounded ones, as in a PRECISE tile), eight columns a thread.
+template <int DV>
+__global__ __launch_bounds__(256) void ssa_split_add_kernel(const FwdParams p)
+{
+    constexpr int LPR = DV / 8;                    // threads per row
+    const int64_t row = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;   // of out: (b, qi, head)
+    if (row >= (int64_t)p.B * p.q_len * p.Hq) return;
+    const int n = p.n_splits, c = (int)(threadIdx.x % LPR) * 8;
+    const float *ml = p.part_ml + row * n * 4, *po = p.part_o + row * n * DV + c;
+    float m_all = LOZA_NEG_INF;
+    for (int s = 0; s < n; ++s) m_all = fmaxf(m_all, ml[4 * s]);
+    float den = 0.f, den_r = 0.f, x[8] = {};
+#pragma unroll 4
+    for (int s = 0; s < n; ++s) {
+        const float a = ml[4 * s] == LOZA_NEG_INF ? 0.f : __builtin_amdgcn_exp2f(ml[4 * s] - m_all);
+        const float4 lo = *(const float4 *)(po + (int64_t)s * DV), hi = *(const float4 *)(po + (int64_t)s * DV + 4);
+        den += a * ml[4 * s + 1];
+        den_r += a * ml[4 * s + 2];
+        x[0] += a * lo.x; x[1] += a * lo.y; x[2] += a * lo.z; x[3] += a * lo.w;
+        x[4] += a * hi.x; x[5] += a * hi.y; x[6] += a * hi.z; x[7] += a * hi.w;
+    }
+    const float inv = den_r > 0.f ? 1.0f / den_r : 0.f;   // a row without a live key gives 0
+    u32x4 w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = pack_bf16(x[2 * e] * inv, x[2 * e + 1] * inv);
+    *(u32x4 *)(p.out + row * DV + c) = w;
+    if (c == 0) {
+        const int64_t bq = row / p.Hq, b = bq / p.q_len;   // [b, head, qi] of lse
+        p.lse[(b * p.Hq + (row - bq * p.Hq)) * p.q_len + (bq - b * p.q_len)] = (m_all + __builtin_amdgcn_logf(den)) * 0.69314718055994530942f;
+    }
+}
+
 template <int DQK, int DV, bool ALIAS, bool OUTF32, bool EXT, bool SPLIT = false>
 static hipError_t launch_prefill_kernel(FwdParams p, hipStream_t stream)
 {
@@ -1095,7 +1128,10 @@ static hipError_t launch_prefill_kernel(FwdParams p, hipStream_t stream)
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), C::LDS_BYTES, stream, p);
     e = hipGetLastError();
     if constexpr (SPLIT) {
-        if (e == hipSuccess) e = launch_rows_finish_bf16(p, DQK, DV, ALIAS, stream);
+        if (e != hipSuccess) return e;
+        const int64_t threads = (int64_t)p.B * p.q_len * p.Hq * (DV / 8);
+        hipLaunchKernelGGL(ssa_split_add_kernel<DV>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, p);
+        e = hipGetLastError();
     }
     return e;
 }

@@ -68,8 +68,6 @@ bool d128_tiles_pay(int B, int Hkv, int G, int64_t queries, int64_t S, int n_sin
 // Few query rows (ssa_rows.hip): prefill (seqlens null), extend or decode (q_len = 1; n_splits key splits
 // and a merge; weights that are not rounded at all).
 hipError_t launch_rows_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, bool decode, hipStream_t stream);
-// Second launch of an extend whose key tiles the tile kernel has split (p.n_splits sets of partial results).
-hipError_t launch_rows_finish_bf16(const FwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
 // A prefill or extend of `rows` query rows per (batch, key head) is few rows when its groups of 16 rows make
 // at most two rounds of the 256 compute units. A round of the row kernel and one of the tile kernel (128 rows
 // a workgroup) cost, at window 8192 of the wide shape, 165 and 405 us (d = 128, window 4096: 51 and 152):

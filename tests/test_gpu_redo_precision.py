@@ -9,9 +9,10 @@ import pytest
 import torch
 
 import oracle
+import paper_2512_23966_amd as loza
 from paper_2512_23966_amd import binding as B_
 from tests import helpers as H
-from tests.test_gpu_parity_extend import _rand
+from tests.test_gpu_parity_extend import _rand, _run
 
 pytestmark = pytest.mark.gpu
 
@@ -37,20 +38,26 @@ def test_wide_prefill_tile_with_a_large_result(gpu_device):
     assert share < 0.02
 
 
+# the tile kernel; workgroups that share the keys of a tile (scratch memory), or one of them
+@pytest.mark.parametrize("scratch", [False, True])
 @pytest.mark.parametrize("d", [576, 128])
-def test_extend_tile_with_a_large_result(gpu_device, d):
+def test_extend_tile_with_a_large_result(gpu_device, d, scratch):
     B, Hq, Hkv, S_max, q_len, tile = (4, 64, 1, 6144, 33, 2) if d == 576 else (4, 32, 8, 2304, 70, 32)   # positions a tile
     d_v, pattern, scale = 512 if d == 576 else 128, (16, 5000 if d == 576 else 2000), (192 if d == 576 else 128) ** -0.5
     lens = [S_max, S_max - 7, S_max - 500, S_max - 1001]
+    assert loza.loza_ssa_extend_workspace_bytes(B, Hq, Hkv, S_max, q_len, d, d_v, *pattern) > 0
     q, kc = _rand((B, q_len, Hq, d), 73, torch.bfloat16, gpu_device), _rand((B, S_max, Hkv, d), 74, torch.bfloat16, gpu_device)
     vc = kc if d == 576 else _rand((B, S_max, Hkv, d), 75, torch.bfloat16, gpu_device)
     r, h, G = 3, 5, Hq // Hkv
     q[0, r, h] = 2 * kc[0, S_max - 100, h // G]
     seqlens = torch.tensor(lens, dtype=torch.int32, device=gpu_device)
-    out, lse = torch.empty(B, q_len, Hq, d_v, dtype=torch.bfloat16, device=gpu_device), torch.empty(B, Hq, q_len, device=gpu_device)
-    assert B_.lib().loza_ssa_extend(q.data_ptr(), kc.data_ptr(), vc.data_ptr(), seqlens.data_ptr(), out.data_ptr(), lse.data_ptr(), B, Hq, Hkv,
-                                    S_max, q_len, d, d_v, *pattern, scale, torch.cuda.current_stream().cuda_stream) == 0
-    torch.cuda.synchronize()
+    if scratch:
+        out, _ = _run(q, kc, vc, seqlens, pattern, scale, d_v)
+    else:
+        out, lse = torch.empty(B, q_len, Hq, d_v, dtype=torch.bfloat16, device=gpu_device), torch.empty(B, Hq, q_len, device=gpu_device)
+        assert B_.lib().loza_ssa_extend(q.data_ptr(), kc.data_ptr(), vc.data_ptr(), seqlens.data_ptr(), out.data_ptr(), lse.data_ptr(), B, Hq, Hkv,
+                                        S_max, q_len, d, d_v, *pattern, scale, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
     assert out[0, r, h].abs().max() >= 2
     r0 = r // tile * tile
     rows = [(0, x, y) for x in range(r0, r0 + tile) for y in range(h // G * G, h // G * G + G)]
