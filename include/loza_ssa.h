@@ -154,7 +154,7 @@ int loza_ssa_decode_num_splits(int B, int Hq, int Hkv, int64_t S_max, int64_t n_
  * _blocks entry points take it; block = 1: n_sink and window in tokens. Negative (a loza_status) on sizes
  * that the call itself refuses.
  *   loza_ssa_forward_kernel   prefill (n_queries = S), calibration or extend (n_queries = q_len, S = S_max):
- *                             a loza_kernel
+ *                             a loza_kernel (with scratch memory the workgroups of the same kernel share keys)
  *   loza_ssa_decode_kernel    a loza_kernel; *n_splits (may be NULL): the key splits it takes
  *   loza_ssa_backward_split   how many key tiles of 64 (per sequence and key head) the dK/dV kernel cuts into
  *                             chunks of rows for balance; *n_chunks, *n_whole (may be NULL): the chunks of

@@ -147,25 +147,22 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
     return (sink_blocks < 0 || local_blocks < 1 || block < 1) ? LOZA_ERR_SHAPE : LOZA_OK;
 }
 
-// How many workgroups share the keys of a row in an extend that has scratch memory, and which kernel they run. Few
+// How many workgroups share the keys of a row in an extend that has scratch memory (of the kernel that takes the call
+// without it; 1: no sharing). Few
 // new tokens leave most compute units idle: 2 tokens of one sequence are 8 groups of 16 rows of the absorbed-MLA
 // shape, and took the same 153 us (window 8192) as 128 tokens. Splits of the few-rows kernel are merged row by row
 // (2 tokens 22 us, 16 tokens 37 to 59); calls too large for that kernel split the tile kernel's keys, until its tiles
 // fill the chip by themselves. A split tile has two-term weights throughout (2.7 us a step, 1.45 with weights rounded
 // once): which rows have a large result is known only when the parts have been added, and a tile that has one may keep
 // none of its rows from once-rounded weights. 144 tokens of window 8192 386 -> 264 us; 256 tokens 400, in two 403: not
-// split. (d = 128, 8 key heads, window 4096: 280 tokens 152 -> 87, 600 tokens 153 -> 113.) Calls of the few-rows kernel
-// are split by that kernel only. The line is a time model of both in microseconds, fitted to 170 sizes: workgroups go in
+// split. (d = 128, 8 key heads, window 4096: 280 tokens 152 -> 87, 600 tokens 153 -> 113.) Calls of the 256-row tiles of
+// width 128 have enough workgroups, and tiles twice as fast (3 sequences of 385 tokens 130 us, as three parts of the
+// 128-row tiles 212). The line is a time model of both in microseconds, fitted to 170 sizes: workgroups go in
 // rounds, a round costs a start and a step per tile of keys, and every set of partial results of a row is written and
 // read once. (Of a call that is not split, without tiles that are computed again for a large result; with 1 + 7 blocks
 // and N(0, 1) inputs nearly every call has one: 148 us instead of 61.) A split has to promise 7 %, which is what the
 // model is worth. A chunk that (nearly) fills its cache is a prefill, and has its bits.
-struct ExtendPlan {
-    bool rows;
-    int n_splits;
-};
-
-ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk, const Pattern &pat)
+int extend_splits(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk, const Pattern &pat)
 {
     const bool wide = d_qk > 128;
     const int64_t rows = q_len * G, heads = (int64_t)B * Hkv, groups = (rows + 15) / 16 * heads;
@@ -186,13 +183,15 @@ ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk
         const double step = n > 1 ? (wide ? 2.7 : alone ? 1.4 : 2.0) : (wide ? 1.45 : alone ? 1.05 : 1.36);
         return rounds(tiles * n, slots) * (12 + step * steps) + (n > 1 ? 6 + (wide ? 0.45e-3 : 0.11e-3) * rows * heads * n : 0);
     };
-    ExtendPlan best{loza::few_rows_bf16(B, Hkv, rows), 1};
-    if (S * 8 <= q_len * 9) return best;
-    double t = 0.93 * (best.rows ? t_rows(1) : t_tile(1));
-    for (int n = 2; best.rows && n <= kMaxSplits && groups * n <= kComputeUnits; ++n)
-        if (t_rows(n) < t) { t = t_rows(n); best = {true, n}; }
-    for (int n = 2; !best.rows && n <= kMaxSplits && tiles * n <= 2 * slots; ++n)
-        if (t_tile(n) < t) { t = t_tile(n); best = {false, n}; }
+    const bool few = loza::few_rows_bf16(B, Hkv, rows);
+    if (S * 8 <= q_len * 9) return 1;
+    if (!few && !wide && loza::d128_tiles_pay(B, Hkv, G, q_len, S, pat.n_sink, pat.window, pat.block)) return 1;
+    int best = 1;
+    double t = 0.93 * (few ? t_rows(1) : t_tile(1));
+    for (int n = 2; few && n <= kMaxSplits && groups * n <= kComputeUnits; ++n)
+        if (t_rows(n) < t) { t = t_rows(n); best = n; }
+    for (int n = 2; !few && n <= kMaxSplits && tiles * n <= 2 * slots; ++n)
+        if (t_tile(n) < t) { t = t_tile(n); best = n; }
     return best;
 }
 
@@ -352,17 +351,15 @@ static int prefill_bf16(const void *q, const void *k, const void *v, void *out, 
     p.scale_log2 = scale * 1.44269504088896340736f;
     p.row_tiles = (int)row_tiles; p.n_splits = 1;
     set_rescale_policy(p);
-    bool few_rows = loza::few_rows_bf16(B, Hkv, (extend ? q_len : S) * G);
+    const bool few_rows = loza::few_rows_bf16(B, Hkv, (extend ? q_len : S) * G);
     if (extend) {
         if (scratch) {
-            const ExtendPlan plan = extend_plan(B, Hkv, G, q_len, S, d_qk, pat);
-            if (plan.n_splits > 1) {
-                if (!workspace || workspace_bytes < split_bytes(B, Hq, q_len, d_v, plan.n_splits)) return LOZA_ERR_WORKSPACE;
+            p.n_splits = extend_splits(B, Hkv, G, q_len, S, d_qk, pat);
+            if (p.n_splits > 1) {
+                if (!workspace || workspace_bytes < split_bytes(B, Hq, q_len, d_v, p.n_splits)) return LOZA_ERR_WORKSPACE;
                 if (!aligned16(workspace)) return LOZA_ERR_ALIGN;
-                few_rows = plan.rows;
-                p.n_splits = plan.n_splits;
                 p.part_o = (float *)workspace;
-                p.part_ml = (float *)workspace + (size_t)B * Hq * q_len * plan.n_splits * d_v;
+                p.part_ml = (float *)workspace + (size_t)B * Hq * q_len * p.n_splits * d_v;
             }
         }
         p.seqlens = seqlens; p.q_len = (int)q_len;
@@ -448,8 +445,8 @@ size_t loza_ssa_extend_workspace_bytes(int B, int Hq, int Hkv, int64_t S_max, in
     if (check_common(B, Hq, Hkv, S_max, d_qk, d_v, sink_blocks, local_blocks, 1.0f) != LOZA_OK) return 0;
     if (check_blocks(sink_blocks, local_blocks, block) != LOZA_OK || q_len < 1 || q_len > S_max) return 0;
     if (!loza::bf16_width_supported(d_qk)) return 0;
-    const ExtendPlan plan = extend_plan(B, Hkv, Hq / Hkv, q_len, S_max, d_qk, block_pattern(sink_blocks, local_blocks, block, S_max));
-    return plan.n_splits > 1 ? split_bytes(B, Hq, q_len, d_v, plan.n_splits) : 0;
+    const int n = extend_splits(B, Hkv, Hq / Hkv, q_len, S_max, d_qk, block_pattern(sink_blocks, local_blocks, block, S_max));
+    return n > 1 ? split_bytes(B, Hq, q_len, d_v, n) : 0;
 }
 
 int loza_ssa_prefill(const void *q, const void *k, const void *v, void *out, float *lse,

@@ -1341,7 +1341,7 @@ hipError_t launch_extend_bf16(const FwdParams &p, int d_qk, int d_v, bool alias,
 {
     if (d_qk == 576 && d_v == 512 && alias) return launch_extend_t<576, 512, true>(p, stream);
     if (d_qk == 128 && d_v == 128) {
-        if (p.n_splits == 1 && d128_tiles_pay(p)) return launch_d128_bf16(p, alias, stream);
+        if (d128_tiles_pay(p)) return launch_d128_bf16(p, alias, stream);
         return alias ? launch_extend_t<128, 128, true>(p, stream) : launch_extend_t<128, 128, false>(p, stream);
     }
     return hipErrorInvalidValue;

@@ -68,6 +68,18 @@ def test_decode_kernel_by_size(B, Hq, Hkv, d, S, sink, local, kernel):
     assert loza.loza_ssa_decode_kernel(B, Hq, Hkv, S, d, sink, local)[0] == kernel
 
 
+@pytest.mark.parametrize("Hkv,pattern", [(8, (128, 4096, 1)), (32, (128, 4096, 1)), (1, (128, 8192, 1)), (8, (1, 7, 128)), (16, (128, 32000, 1))])
+def test_extends_of_the_larger_tiles_take_no_scratch_memory(Hkv, pattern):
+    """3 sequences of 385 tokens, 8 key heads, 128 + 4096: 130 us, as three parts of the smaller tiles 212."""
+    larger = 0
+    for B in (1, 2, 3, 6, 7, 8, 16):
+        for q_len in (*range(100, 700, 3), 1283, 1300):
+            if loza.loza_ssa_forward_kernel(B, 32, Hkv, q_len, 65536, 128, *pattern) == KERNEL_D128:
+                larger += 1
+                assert loza.loza_ssa_extend_workspace_bytes(B, 32, Hkv, 65536, q_len, 128, 128, *pattern) == 0, (B, q_len)
+    assert larger > 50
+
+
 def test_refused_sizes():
     for call in (lambda: loza.loza_ssa_forward_kernel(1, 3, 2, 8, 8, 128, 0, 1), lambda: loza.loza_ssa_forward_kernel(1, 2, 2, 9, 8, 128, 0, 1),
                  lambda: loza.loza_ssa_decode_kernel(1, 2, 2, 8, 64, 0, 1), lambda: loza.loza_ssa_decode_kernel(0, 2, 2, 8, 128, 0, 1),
