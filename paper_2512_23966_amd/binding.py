@@ -150,6 +150,9 @@ def _dev_ptr(t: torch.Tensor, dtype, name: str) -> int:
     return t.data_ptr()
 
 
+_STREAM_LEGACY, _STREAM_PER_THREAD = 1, 2   # HIP's handles for the default stream and for each thread's own
+
+
 def _stream(stream) -> int:
     if stream is None:
         # torch.cuda.current_stream().cuda_stream without the object around it (2.8 us of a 10 us call)
@@ -449,10 +452,15 @@ def loza_ssa_extend_workspace_bytes(B, Hq, Hkv, S_max, q_len, d_qk, d_v, sink, l
 def _scratch(nbytes: int, stream):
     """Scratch memory for launches on `stream`, from torch's allocator and of that stream (given back when the caller
     drops it, it can only be handed out again behind those launches). None where there is none to be had: no memory
-    left, or a stream under capture, whose graph would keep the address of memory that is given back."""
+    left, a stream under capture, whose graph would keep the address of memory that is given back, or the per-thread
+    stream, whose one handle names many streams."""
     if stream is not None and _stream(stream) != _stream(None):
         if not isinstance(stream, torch.cuda.Stream):
-            stream = torch.cuda.ExternalStream(_stream(stream))
+            handle = _stream(stream)
+            if handle == _STREAM_PER_THREAD:
+                return None
+            # (torch takes a handle of 0 as none given, and makes a stream of its pool of it)
+            stream = torch.cuda.default_stream() if handle in (0, _STREAM_LEGACY) else torch.cuda.ExternalStream(handle)
         with torch.cuda.stream(stream):
             return _scratch(nbytes, None)
     if torch.cuda.is_current_stream_capturing():
