@@ -130,6 +130,9 @@ def lib() -> ctypes.CDLL:
         L.loza_ssa_decode_kernel.argtypes = [ci, ci, ci, i64, ci, i64, i64, i64, ctypes.POINTER(ci)]
         L.loza_ssa_backward_split.restype = ci
         L.loza_ssa_backward_split.argtypes = [ci, ci, ci, i64, ci, ci, i64, i64, i64, ci, ctypes.POINTER(ci), ctypes.POINTER(i64)]
+        # (of the HIP runtime that the library is linked with)
+        L.hipThreadExchangeStreamCaptureMode.restype = ci
+        L.hipThreadExchangeStreamCaptureMode.argtypes = [ctypes.POINTER(ci)]
         L.loza_status_str.restype = ctypes.c_char_p
         L.loza_status_str.argtypes = [ci]
         _lib = L
@@ -151,6 +154,7 @@ def _dev_ptr(t: torch.Tensor, dtype, name: str) -> int:
 
 
 _STREAM_LEGACY, _STREAM_PER_THREAD = 1, 2   # HIP's handles for the default stream and for each thread's own
+_CAPTURE_MODE_RELAXED = 2                    # hipStreamCaptureModeRelaxed
 
 
 def _stream(stream) -> int:
@@ -465,10 +469,15 @@ def _scratch(nbytes: int, stream):
             return _scratch(nbytes, None)
     if torch.cuda.is_current_stream_capturing():
         return None
+    # (an allocation that reaches the driver ends the captures of other threads, unless this thread says it may not matter)
+    mode = ctypes.c_int(_CAPTURE_MODE_RELAXED)
+    lib().hipThreadExchangeStreamCaptureMode(ctypes.byref(mode))
     try:
         return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
     except torch.OutOfMemoryError:
         return None
+    finally:
+        lib().hipThreadExchangeStreamCaptureMode(ctypes.byref(mode))
 
 
 def _extend_call(fn_name, pointers, table, sizes, paging, S_max, q_len, d_qk, d_v, pattern, scale, workspace, stream):

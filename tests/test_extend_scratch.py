@@ -1,6 +1,7 @@
 """Where the binding's scratch memory for extends comes from, with torch's streams and allocator replaced by a model of them
 (torch.cuda.ExternalStream(0) is a stream of torch's pool, as there)."""
 import contextlib
+import threading
 import types
 
 import pytest
@@ -60,6 +61,22 @@ def test_the_per_thread_stream_gets_none(monkeypatch):
     assert B._scratch(64, 2) is None and streams.owner is None
 
 
+def test_no_memory_is_no_error_and_the_capture_mode_is_as_before(monkeypatch):
+    """The allocation happens in HIP's relaxed capture mode of this thread, which is then what it was."""
+    Streams(0).install(monkeypatch)
+    modes, thread_mode = [], [0]
+
+    def exchange(ref):
+        thread_mode[0], ref._obj.value = ref._obj.value, thread_mode[0]
+
+    def empty(n, **_):
+        modes.append(thread_mode[0])
+        raise torch.OutOfMemoryError("none left")
+    monkeypatch.setattr(torch, "empty", empty)
+    monkeypatch.setattr(B, "lib", lambda: types.SimpleNamespace(hipThreadExchangeStreamCaptureMode=exchange))
+    assert B._scratch(64, None) is None and modes == [2] and thread_mode == [0]
+
+
 SIZES = dict(B=2, Hq=64, S_max=3000, q_len=5, lens=[3000, 1234], pattern=(128, 2000), scale=192 ** -0.5)
 
 
@@ -88,4 +105,33 @@ def test_default_stream_by_its_handle_beside_another_current_stream(gpu_device):
     with torch.cuda.stream(torch.cuda.Stream()):
         call(*got, stream=0)
     torch.cuda.synchronize()
+    assert _same(got, ref)
+
+
+@pytest.mark.gpu
+def test_a_call_leaves_another_threads_capture_alone(gpu_device):
+    fresh, call = _call(gpu_device)
+    ref, got, x, side = fresh(), fresh(), torch.zeros(1000, device=gpu_device), torch.cuda.Stream()
+    call(*ref)
+    x.add_(0)
+    errors = []
+
+    def other():
+        try:
+            with torch.cuda.stream(side):
+                call(*got)
+        except Exception as e:   # (reported by the thread that waits)
+            errors.append(e)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):        # (empties the allocator's cache: the call's scratch memory comes from the driver)
+        x.add_(1)
+        t = threading.Thread(target=other)
+        t.start()
+        t.join()
+        x.add_(1)
+    assert not errors
+    for n in (1, 2, 3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (x == 2 * n).all()
     assert _same(got, ref)
