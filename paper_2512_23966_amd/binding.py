@@ -488,7 +488,6 @@ def _extend_call(fn_name, pointers, table, sizes, paging, S_max, q_len, d_qk, d_
     if need and workspace is None:
         workspace = _scratch(need, stream)
     if need and workspace is not None:
-        fn_name = "loza_ssa_extend_with_workspace"
         rc = lib().loza_ssa_extend_with_workspace(*pointers[:3], table, *pointers[3:], B, Hq, Hkv, S_max, *(paging or (0, 0, 0)), q_len, d_qk, d_v,
                                                   *blocks, scale, _dev_ptr(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(stream))
     elif paging:

@@ -77,6 +77,14 @@ def test_no_memory_is_no_error_and_the_capture_mode_is_as_before(monkeypatch):
     assert B._scratch(64, None) is None and modes == [2] and thread_mode == [0]
 
 
+@pytest.mark.parametrize("pattern", [(128, 8192), (1, 7, 128)])
+def test_a_refused_call_names_the_entry_point_that_was_called(monkeypatch, pattern):
+    monkeypatch.setattr(B, "_scratch", lambda n, stream: types.SimpleNamespace(numel=lambda: n))
+    monkeypatch.setattr(B, "_dev_ptr", lambda t, dtype, name: 4096)
+    with pytest.raises(B.LozaError, match="^loza_ssa_extend_of_this_name: LOZA_ERR_SHAPE"):
+        B._extend_call("loza_ssa_extend_of_this_name", (4096,) * 6, None, (1, 64, 1), None, 65536, 2, 576, 512, pattern, 0.0, None, 640)
+
+
 SIZES = dict(B=2, Hq=64, S_max=3000, q_len=5, lens=[3000, 1234], pattern=(128, 2000), scale=192 ** -0.5)
 
 
