@@ -201,7 +201,7 @@ __global__ __launch_bounds__(256, 2) void ssa_bwd128_kernel(const BwdParams p)
 
     // ---- the stationary side: matrix-core B operands, item ln of this wave's block ----------------------
     bf16x8 x1[8], x2[ALIAS && KEYS ? 1 : 8];
-    const int x_idx = it.xt * C::X + xb * 32 + ln;                                  // (S G < 2^31 - 64)
+    const int x_idx = it.xt * C::X + xb * 32 + ln;                                  // (S G <= 2^31 - 65: the last of 128 rows is 2^31 - 1 at most)
     const int64_t x_c = x_idx < (KEYS ? S : R) ? x_idx : (KEYS ? S : R) - 1;
     int x_i = 0;                                                                    // !KEYS: position of this lane's row
     float x_lse2 = 0.f, x_D = 0.f;                                                  // - lse log2(e), - D
@@ -496,8 +496,11 @@ static hipError_t launch_t(const BwdParams &p, int64_t blocks, hipStream_t strea
     return hipGetLastError();
 }
 
-hipError_t launch_bwd128_keys(const BwdParams &p, bool alias, int64_t items, hipStream_t stream)
+// The key-stationary kernel works in units of the scores, where lse / scale has to be finite: a smaller scale is taken as
+// 2^-100 in front of the scores (log-sum-exps up to 2^26 then are; the weights' exponents move by at most 2^-100 |q . k|).
+hipError_t launch_bwd128_keys(BwdParams p, bool alias, int64_t items, hipStream_t stream)
 {
+    if (p.scale_log2 < 0x1p-100f) p.scale_log2 = 0x1p-100f;
     return alias ? launch_t<true, true>(p, items, stream) : launch_t<false, true>(p, items, stream);
 }
 

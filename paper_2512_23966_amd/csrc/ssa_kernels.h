@@ -124,7 +124,7 @@ __host__ __device__ inline void bwd_key_tile_rows(const BwdParams &p, int kt, in
 }
 
 // The two passes of the width-128 backward (ssa_bwd128.hip): `items` work items of 64 keys each, and dQ.
-hipError_t launch_bwd128_keys(const BwdParams &p, bool alias, int64_t items, hipStream_t stream);
+hipError_t launch_bwd128_keys(BwdParams p, bool alias, int64_t items, hipStream_t stream);
 hipError_t launch_bwd128_rows(const BwdParams &p, bool alias, hipStream_t stream);
 bool bwd_group_supported(int G);
 hipError_t launch_backward_bf16(const BwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);

@@ -30,6 +30,20 @@ def test_backward_d128_edges(gpu_device, B, S, Hq, Hkv, alias, ns, win, block):
     H.compare_backward(q, k, v, out, lse, dout, got, ns, win, scale, f"d128 bwd S{S} Hq{Hq}/{Hkv} ns{ns} W{win} b{block}", block)
 
 
+@pytest.mark.parametrize("alias", [False, True])
+@pytest.mark.parametrize("scale", [1e-25, 2e-30, 1.2e-38, 1e-40])
+def test_scales_so_small_that_lse_over_scale_is_no_number(gpu_device, scale, alias):
+    """Every live key has the same weight; below about 1e-37, lse / scale exceeds fp32."""
+    S, ns, win = 300, 0, None
+    g = torch.Generator(device=gpu_device).manual_seed(93)
+    r = lambda *s: torch.randn(*s, generator=g, device=gpu_device).to(torch.bfloat16)
+    q, k, dout = r(1, S, 4, 128), r(1, S, 2, 128), r(1, S, 4, 128)
+    v = k if alias else r(1, S, 2, 128)
+    out, lse = H.oracle_forward_all(q, k, v, ns, win, scale, 128, None)
+    got = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, None)
+    H.compare_backward(q, k, v, out, lse, dout, got, ns, win, scale, f"d128 bwd scale {scale} alias {alias}", None)
+
+
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 def test_a_bad_gradient_row_reaches_only_what_it_may(gpu_device, bad):
     """dout of one row of one head is not finite: dQ of the other rows is untouched, dK and dV of the keys it cannot see."""
