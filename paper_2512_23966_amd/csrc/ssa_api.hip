@@ -157,9 +157,11 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
 // none of its rows from once-rounded weights. 144 tokens of window 8192 386 -> 264 us; 256 tokens 400, in two 403: not
 // split. (d = 128, 8 key heads, window 4096: 280 tokens 152 -> 87, 600 tokens 153 -> 113.) Calls of the 256-row tiles of
 // width 128 have enough workgroups, and tiles twice as fast (3 sequences of 385 tokens 130 us, as three parts of the
-// 128-row tiles 212). The line is a time model of both in microseconds, fitted to 170 sizes: workgroups go in
-// rounds, a round costs a start and a step per tile of keys, and every set of partial results of a row is written and
-// read once. (Of a call that is not split, without tiles that are computed again for a large result; with 1 + 7 blocks
+// 128-row tiles 212). The line is a time model of both in microseconds, fitted to 260 sizes: workgroups go in
+// rounds, a round costs a start and a step per tile of keys, every row has a workgroup of the merge, and every set of
+// partial results of a row is written and read once; the host's part counts, since a short call waits for it (28
+// tokens of 1 + 7 blocks 25.6 us, in two parts 28.5 and 5 of the host; d = 128, 4 tokens 12.2, in 16 parts 8.5 and 5:
+// not split; 8 tokens 24.4 and 17.3 + 5). (Of a call that is not split, without tiles that are computed again for a large result; with 1 + 7 blocks
 // and N(0, 1) inputs nearly every call has one: 148 us instead of 61.) A split has to promise 7 %, which is what the
 // model is worth. A chunk that (nearly) fills its cache is a prefill, and has its bits.
 int extend_splits(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk, const Pattern &pat)
@@ -170,10 +172,11 @@ int extend_splits(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk, con
     int64_t live = (int64_t)pat.n_sink + (int64_t)pat.window * pat.block;
     if (live > S) live = S;
     auto rounds = [](int64_t workgroups, int slots) { return (double)((workgroups + slots - 1) / slots); };
-    const double set = wide ? 1.05e-3 : 0.28e-3;                       // one set of partial results of one row, merged by row
+    const double host = 5;                                             // of a call with scratch memory: to get it, and a launch
     auto t_rows = [&](int64_t n) {
-        const double steps = (double)((live / 16 + 2 + 4 * n - 1) / (4 * n));
-        return rounds(groups * n, kComputeUnits) * (wide ? 8 + 1.15 * steps : 5 + 0.7 * steps) + (n > 1 ? 3.5 + set * rows * heads * n : 0);
+        const double steps = (double)((live / 16 + 2 + 4 * n - 1) / (4 * n)), all = (double)(rows * heads);
+        return rounds(groups * n, kComputeUnits) * (wide ? 6.5 + 1.08 * steps : 3.7 + 0.55 * steps) +
+               (n > 1 ? host + (wide ? 2.5 + all * (2.8e-3 + 1.17e-3 * n) : 3.2 + all * (0.4e-3 + 0.25e-3 * n)) : 0);
     };
     // (two workgroups of the narrow tile kernel share a compute unit)
     const int slots = wide ? kComputeUnits : 2 * kComputeUnits;
@@ -181,7 +184,7 @@ int extend_splits(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk, con
         const double steps = (double)((live / 32 + 2 + n - 1) / n);
         const bool alone = tiles * n <= kComputeUnits;
         const double step = n > 1 ? (wide ? 2.7 : alone ? 1.4 : 2.0) : (wide ? 1.45 : alone ? 1.05 : 1.36);
-        return rounds(tiles * n, slots) * (12 + step * steps) + (n > 1 ? 6 + (wide ? 0.45e-3 : 0.11e-3) * rows * heads * n : 0);
+        return rounds(tiles * n, slots) * (12 + step * steps) + (n > 1 ? host + 6 + (wide ? 0.45e-3 : 0.11e-3) * rows * heads * n : 0);
     };
     const bool few = loza::few_rows_bf16(B, Hkv, rows);
     if (S * 8 <= q_len * 9) return 1;

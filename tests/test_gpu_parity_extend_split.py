@@ -41,7 +41,7 @@ def _check(q, kc, vc, lens, out, lse, pattern, scale, label, block=None, step=1)
 CASES = [
     (1, 64, 1, 576, 2600, 1, [2600], 128, 2048, None, 0, 1),             # one token: splits of a tile or two a wave
     (3, 64, 1, 576, 2560, 4, [2509, 131, 2], 128, 1500, None, 128, 1),   # around position 128; queries before the start
-    (2, 64, 1, 576, 3000, 11, [2999, 0], 1, 7, 128, 0, 1),               # blocks; an empty cache; rows no multiple of 16
+    (2, 64, 1, 576, 3000, 11, [2999, 0], 1, 20, 128, 0, 1),              # blocks; an empty cache; rows no multiple of 16
     (1, 128, 2, 576, 2048, 3, [2047], 0, 1200, None, 32, 1),             # two latents
     (2, 8, 2, 128, 4000, 5, [4000, 77], 70, 3000, None, 0, 1),           # separate values, 4 heads a group
     (1, 6, 2, 128, 2048, 19, [2011], 16, 1500, None, 64, 1),             # 3 heads a group
@@ -148,6 +148,11 @@ def test_what_splits_and_what_does_not():
     assert _plan(4, 64, 1, 65536, 36, 576, 128, 8192) >= 2            # the tile kernel
     assert _plan(4, 64, 1, 65536, 1000, 576, 128, 8192) == 1          # fills the chip by itself
     assert _plan(1, 64, 1, 450, 450, 576, 16, 130) == 1               # the whole sequence: a prefill
+    # few live keys: what the host and the merge take is more than the split saves
+    assert _plan(1, 64, 1, 16384, 28, 576, 1, 7, 128) == 1            # 25.6 us, in two parts 28.5
+    assert _plan(9, 64, 1, 16384, 3, 576, 1, 7, 128) == 1             # 25.6 and 28.3
+    assert _plan(1, 32, 8, 16384, 4, 128, 1, 7, 128) == 1             # 11.9, in 16 parts 8.6 and 5 of the host
+    assert _plan(1, 64, 1, 16384, 2, 576, 1, 7, 128) > 1              # 25.1 and 14.1
     for bad in ((0, 64, 1, 100, 2, 576, 512, 1, 9, 1), (1, 64, 1, 100, 101, 576, 512, 1, 9, 1), (1, 64, 1, 100, 2, 577, 512, 1, 9, 1),
                 (1, 64, 1, 100, 2, 576, 512, -1, 9, 1), (1, 64, 1, 100, 2, 576, 512, 1, 0, 1), (1, 64, 1, 100, 2, 576, 512, 1, 9, 0)):
         assert loza.loza_ssa_extend_workspace_bytes(*bad) == 0
