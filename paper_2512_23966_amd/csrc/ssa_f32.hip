@@ -187,8 +187,10 @@ __global__ __launch_bounds__(64 * F32RowsCfg<ND>::NW) void ssa_rows_f32_kernel(c
                 cm = fmaxf(cm, s[i]);
             }
             // (each row's running maximum, whatever the rows beside it do; past the first tiles it seldom moves. A
-            // reference that may be exceeded by e^8 and a shorter exponential were another 4 % faster, and 0.4 % less exact.)
-            if (__any(cm > m)) {
+            // reference that may be exceeded by e^8 and a shorter exponential were another 4 % faster, and 0.4 % less exact.
+            // With the branches of any widths around every load, asking first costs more than the exchange: 1,548 rows
+            // of width 32, 27.2 us and 26.6.)
+            if (DX == 0 || __any(cm > m)) {
                 cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
                 cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
                 const float alpha = cm > m ? expf(m - cm) : 1.f;
@@ -314,6 +316,9 @@ template <bool VEC>
 static hipError_t launch_rows_f32(const F32Params &p, hipStream_t stream)
 {
     const int d = p.d_qk > p.d_v ? p.d_qk : p.d_v;
+    // The usual head widths are known to the compiler: without a branch around every load 1,024 rows of one head of width
+    // 64 take 9.4 us instead of 9.95, 2,048 rows of 4 heads of width 128 40 instead of 45.7, 266 rows of width 96 11.5
+    // instead of 12.9. Any other width would gain by a kernel of its own likewise; these three are what is in use.
     if constexpr (VEC) {
         if (p.d_qk == p.d_v && d == 64) return launch_rows_f32_t<1, true, 64>(p, stream);
         if (p.d_qk == p.d_v && d == 96) return launch_rows_f32_t<2, true, 96>(p, stream);
