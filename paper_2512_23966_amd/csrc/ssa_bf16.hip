@@ -1273,22 +1273,20 @@ int decode_rows_per_tile() { return 64; }
 
 // Heads of width 128: the kernel of 256-row tiles (ssa_d128.hip), one workgroup a compute unit, or the one of
 // 128-row tiles here, two. The line is a time model of either in microseconds: start and end of a tile plus the
-// keys it walks, fitted to the measured times of both (32 query heads; key heads, tokens, sink + window: 256-row
-// against 128-row tiles). The larger tile takes less time per key and row (32, 8,192, 128 + 4096: 507 against 577
-// us; 8, 8,192, one and seven blocks of 128: 166 against 200), but its rows span more positions, which matters
-// when the window is short and few heads share a key (32, 8,192, 16 + 256: 148 against 124; 8 key heads: 99
-// against 102), it costs more to start, and its last round is a whole one (4,100 tokens are 544 tiles: 114 against
-// 108 us in blocks of 128). With few tiles (160: 45.0 against 44.2 us; 168: 41.7 against 43.1) or mostly padded
-// ones (chunks of 300 tokens: 122 against 120) it does not pay. Nor does it where rows have few live keys: their
-// results are large and whole tiles are computed again, or take two-term weights from the outset (32 heads of
-// their own keys, window 200, 6,000 tokens: 126 against 82 us; 32 heads on 8, window 100 after a sink of 20: 78
-// against 65; blocks of 300: 91 against 75).
-// A prefill, or a chunk that (nearly) fills its cache, starts at position 0: its first tiles have few keys, and the
-// launch is simulated (128 heads of their own keys: 512 tokens 32 against 37 us, 800 tokens, 128 + 512, 80 against
-// 75). Otherwise, and from eight rounds on, every tile has a full window, and rounds are counted. The cache's
-// capacity decides nothing else: a paged and a contiguous cache take the same kernel. (The figures are of the 256-row
-// kernel as it was with four waves of 64 rows; with eight of 32 it takes 0.74 to 0.97 of that time over 46 sizes, most
-// where windows are short: the line is on the safe side.)
+// keys it walks. A prefill, or a chunk that (nearly) fills its cache, starts at position 0: its first tiles have few
+// keys, and the launch is simulated. Otherwise, and from eight rounds on, every tile has a full window, and rounds are
+// counted. The cache's capacity decides nothing else: a paged and a contiguous cache take the same kernel. Patterns of
+// fewer than 128 live keys stay here for their two-term weights.
+// The larger tile takes less time per key and row (32 query heads; key heads, tokens, sink + window: 256-row against
+// 128-row tiles; 32, 8,192, 128 + 4096: 484 against 606 us; 8, 8,192, one and seven blocks of 128: 158 against 200), but
+// its last round is a whole one: 3 sequences of 622 tokens are 288 of them, two rounds, and 480 of the others, one: 83
+// against 65. The model's constants were fitted to the 256-row kernel when it had four waves of 64 rows. As it is, with
+// eight of 32, the line is well on the safe side: of 243 sizes the larger tiles are the faster ones on 238, also where
+// it keeps the smaller (32, 8,192, 16 + 256: 109 against 137; 4,100 tokens in blocks of 128: 90 against 105; at most 160
+// tiles, 1,100 tokens: 37 against 45; mostly padding, chunks of 300 tokens: 338 against 392; fewer than 256 live keys,
+// window 200, 6,000 tokens: 73 against 82): on 152 sizes, 12 % of the time on average. (Over those sizes 7.5 + 1.0 / G + 0.028
+// keys for the larger tile and 13 + 4 / G + 0.0365 keys for the smaller, at 0.78 of its speed beside another and 0.9 of
+// a round for at most 256 of them, tell the faster kernel within 0.1 %.)
 bool d128_tiles_pay(int B, int Hkv, int G, int64_t queries, int64_t S, int n_sink, int window, int block)
 {
     const int64_t rows = queries * G, big = (rows + 255) / 256, small = (rows + 127) / 128, heads = (int64_t)B * Hkv;

@@ -12,7 +12,7 @@
 //     forms exponentials or waits for LDS. (A wave of 64 items would read half as much from LDS per matrix instruction,
 //     but fill the register file alone, and overlap only what is interleaved by hand.)
 //   * LDS bounds it: every wave reads the streamed tile twice, by rows (104 B/clk and compute unit) and transposed
-//     (64 B/clk): 2280 cycles of reads against 1536 of matrix work for 8 waves and 32 keys (dQ), 3300 against 2048 (dK, dV).
+//     (64 B/clk): 2280 cycles of reads against 1536 of matrix work for 8 waves and 32 keys (dQ), 3300 against 2176 (dK, dV).
 // 32 heads of their own keys, 8,111 tokens of 128 + 4096: dQ 1008 -> 625 us, dK and dV 1168 -> 870 (LDS busy 76 and 86 % of
 // the cycles, matrix cores 57 and 59 %).
 // Tiles of 32 items travel global -> LDS by global_load_lds_dwordx4; rows of 256 bytes are unpadded, their 16-byte

@@ -14,7 +14,7 @@
 //     block of ones;
 //   * two waves per SIMD: one's matrix instructions run while the other forms exponentials or waits for LDS. What bounds
 //     a step of 32 keys then is the LDS: eight waves read keys by rows and values transposed, 1656 cycles at the rates
-//     it sustains (104 and 64 B/clk), for 1088 of matrix work a SIMD. (Four waves of 64 rows, one a SIMD, read half of that
+//     it sustains (104 and 64 B/clk), for 1152 of matrix work a SIMD. (Four waves of 64 rows, one a SIMD, read half of that
 //     but issue one instruction at a time: interleaved by hand, one matrix instruction per slot, a step took 2400 cycles.
 //     32 heads of their own keys, 32,768 tokens: 2450 us, now 2316.)
 // Keys travel in stages of 64, global -> LDS by global_load_lds_dwordx4 into a ring of four, one barrier per
