@@ -258,7 +258,8 @@ int loza_ssa_extend_paged_blocks(const void *q, const void *k_pages, const void 
  * new tokens against long windows otherwise leave most of the GPU idle): block_table == NULL is
  * loza_ssa_extend_blocks (num_pages, page_size, max_pages_per_seq unused), a table is
  * loza_ssa_extend_paged_blocks (S_max unused); block = 1 is the token-granular pattern. Results agree with
- * theirs to the order of the sums. `workspace` (16-byte aligned, device): loza_ssa_extend_workspace_bytes
+ * theirs to the order of the sums, and where tiles of 128 rows share keys all their weights have two bf16
+ * terms. `workspace` (16-byte aligned, device): loza_ssa_extend_workspace_bytes
  * (S_max = max_pages_per_seq * page_size of a paged cache; 0: these sizes need none, the pointer may be
  * NULL, and the call is the one without). It must stay untouched until the launches have run; its contents do
  * not matter before and mean nothing afterwards.

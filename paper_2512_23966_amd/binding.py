@@ -501,8 +501,9 @@ def _extend_call(fn_name, pointers, table, sizes, paging, S_max, q_len, d_qk, d_
 def _extend_common(fn_name, q, kcache, vcache, seqlens, out, lse, pattern, scale, workspace, stream):
     """bf16 SSA extend. q [B,q_len,Hq,d_qk], kcache [B,S_max,Hkv,d_qk], vcache [B,S_max,Hkv,d_v] or
     ``vcache is kcache``, seqlens [B] int32 on the GPU, out [B,q_len,Hq,d_v] bf16, lse [B,Hq,q_len] fp32.
-    workspace: uint8 GPU tensor of at least ``loza_ssa_extend_workspace_bytes`` bytes; without one, scratch memory
-    comes from torch's allocator (or, under capture, the call does without)."""
+    workspace: uint8 GPU tensor of at least ``loza_ssa_extend_workspace_bytes`` bytes, of its own for every call that may
+    overlap another in time; without one, scratch memory comes from torch's allocator (which may have to give its cache
+    back to find it) or, under capture and where there is none, the call does without: slower, and with other bits."""
     B, q_len, Hq, d_qk = q.shape
     _, S_max, Hkv, _ = kcache.shape
     d_v = out.shape[3]
