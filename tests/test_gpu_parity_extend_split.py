@@ -73,6 +73,18 @@ def test_split_extend(gpu_device, B, Hq, Hkv, d, S_max, q_len, lens, ns, win, bl
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hkv,S_max,q_len,ns,win", [(2, 8, 2, 4000, 5, 70, 3000), (4, 32, 8, 2304, 70, 64, 2000)])   # few rows; tiles
+def test_split_extend_d128_values_are_the_keys(gpu_device, B, Hq, Hkv, S_max, q_len, ns, win):
+    assert _plan(B, Hq, Hkv, S_max, q_len, 128, ns, win) > 1
+    lens, scale = [S_max, q_len - 2, 150, S_max - 77][:B], 128 ** -0.5
+    q, kc = _rand((B, q_len, Hq, 128), 69, torch.bfloat16, gpu_device), _rand((B, S_max, Hkv, 128), 70, torch.bfloat16, gpu_device)
+    for b, L in enumerate(lens):
+        kc[b, L:] = float("nan")
+    out, lse = _run(q, kc, kc, torch.tensor(lens, dtype=torch.int32, device=gpu_device), (ns, win), scale, 128)
+    _check(q, kc, kc, lens, out, lse, (ns, win), scale, f"split, d128 aliased: q{q_len}", None, 13)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("d", [576, 128])
 def test_large_results_do_not_come_from_split_tiles(gpu_device, d):
     """Rows whose weight sits on one key, in some groups of 16 rows and not in others."""
