@@ -355,7 +355,11 @@ size_t loza_ssa_calibration_alpha_grad_workspace_bytes(int64_t n);
  *        receives the gradient with respect to that tensor (dk with dv added to its first d_v
  *        columns) and dv is ignored (may be NULL).
  *   workspace: loza_ssa_backward_workspace_bytes(...) bytes of device memory, 16-byte aligned;
- *        contents on entry are ignored. Two calls that overlap in time need two workspaces.
+ *        contents on entry are ignored. Two calls that overlap in time need two workspaces. At d_qk = 576
+ *        most of it (up to 2 to 4 GiB) holds softmax weights on their way from one kernel to the next; a
+ *        smaller one that still holds the row statistics (8 bytes a query row, rows padded to 32 per key head)
+ *        and the partial sums of the sink keys (147,456 bytes per 64 of them and chunk of rows) is accepted, and
+ *        the call then takes about 1.5 times as long.
  * Supported: the (d_qk, d_v) pairs of loza_ssa_prefill, scale > 0, and Hq / Hkv a power of two up to
  * 32 or a multiple of 32 (else LOZA_ERR_UNSUPPORTED). Arithmetic: bf16 matrix-core operands (q, k,
  * v, dout, and p and ds rounded to bf16), fp32 accumulation, one rounding of each result to bf16.

@@ -141,6 +141,79 @@ def macro_bwd(ks: int, n_a: int, n_b: int, n_agpr: int, with_x: bool = True, n_v
     return text
 
 
+def macro_bwd_scores(ks: int, kt: int, n_copy: int, n_agpr: int) -> str:
+    """Scores pass of the wide backward: S[32 rows][32 keys] = Q K^T over ks steps of 16 features and, from the same
+    key fragments (the values are the key rows' prefix), T = dO V^T over kt, with this wave's n_copy copy instructions
+    (and one more that wave 0 alone issues) of a later key tile woven in, and between the matrix instructions the
+    elementwise step of the PREVIOUS tile: p = 2^(s scale log2e - lse log2e), ds = scale p (t - D), rounded to bf16 in
+    pairs. Nothing in it depends on the instruction before it: a pair's steps go into slots of their own, a slot
+    being a matrix instruction. Stationary fragments: ks of q, then kt of dO; the first n_agpr live in AGPRs."""
+    depth = min(DEPTH, ks)
+    slots = [("s", kk) if not t else ("t", kk) for kk in range(ks) for t in ((0, 1) if kk < kt else (0,))]
+    n = 0
+    names = {}
+
+    def op(name):
+        nonlocal n
+        names[name] = f"%{n}"
+        n += 1
+
+    outs, ins = [], []
+    for name, text in ([("S", '"=&v"(s_)'), ("T", '"=&v"(t_)')] + [(f"kf{d}", f'"=&v"(kf_[{d}])') for d in range(depth)] + [("tmp", '"=&v"(tmp_)')] +
+                       [(f"p{j}", f'"=&v"(p_[{j}])') for j in range(8)] + [(f"ds{j}", f'"=&v"(ds_[{j}])') for j in range(8)] +
+                       [(f"w{j}", f'"=&v"(w_[{j}])') for j in range(6)]):
+        op(name)
+        outs.append(text)
+    for name, text in ([("addr", '"v"(addr_)')] + [(f"x{i}", f'"{"a" if i < n_agpr else "v"}"(xf_[{i}])') for i in range(ks + kt)] +
+                       [(f"off{c}", f'"v"(voff_[{c}])') for c in range(n_copy + 1)] +
+                       [(f"{a}{e}", f'"v"({b}[{e}])') for a, b in (("s", "sp_"), ("t", "tp_"), ("l", "lse_"), ("d", "dd_")) for e in range(16)] +
+                       [(f"c{i}", f'"s"({v})') for i, v in enumerate(("tc_.max", "tc_.src", "tc_.dst", "tc_.dstx", "wave_", "sc_", "scale_"))]):
+        op(name)
+        ins.append(text)
+    o = names
+    lines = ["s_waitcnt lgkmcnt(0)"]
+    for d in range(depth):
+        lines.append(f"ds_read_b128 {o[f'kf{d}']}, {o['addr']} offset:{d * 32}")
+    at = {((2 * c + 1) * len(slots)) // (2 * (n_copy + 1)): c for c in range(n_copy + 1)}
+    work = {}
+    for j in range(8):                       # pair j: elements 2j, 2j + 1
+        a, b = 2 * j, 2 * j + 1
+        x0, x1, y0, y1, z0, z1 = (o[f"w{i}"] for i in range(6))
+        steps = [[f"v_fma_f32 {x0}, {o[f's{a}']}, {o['c5']}, -{o[f'l{a}']}", f"v_fma_f32 {x1}, {o[f's{b}']}, {o['c5']}, -{o[f'l{b}']}"],
+                 [f"v_exp_f32 {x0}, {x0}", f"v_sub_f32 {y0}, {o[f't{a}']}, {o[f'd{a}']}"],
+                 [f"v_exp_f32 {x1}, {x1}", f"v_sub_f32 {y1}, {o[f't{b}']}, {o[f'd{b}']}"],
+                 [f"v_mul_f32 {z0}, {o['c6']}, {x0}"],
+                 [f"v_mul_f32 {z1}, {o['c6']}, {x1}", f"v_mul_f32 {y0}, {z0}, {y0}"],
+                 [f"v_mul_f32 {y1}, {z1}, {y1}", f"v_cvt_pk_bf16_f32 {o[f'p{j}']}, {x0}, {x1}"],
+                 [f"v_cvt_pk_bf16_f32 {o[f'ds{j}']}, {y0}, {y1}"]]
+        for i, st in enumerate(steps):
+            work[2 + 8 * j + i] = st
+    assert max(work) < len(slots)
+    for m, (which, kk) in enumerate(slots):
+        if which == "s":
+            lines.append(f"s_waitcnt lgkmcnt({min(depth - 1, ks - 1 - kk)})")
+        acc, x = ("S", kk) if which == "s" else ("T", ks + kk)
+        lines.append(f"v_mfma_f32_32x32x16_bf16 {o[acc]}, {o[f'x{x}']}, {o[f'kf{kk % depth}']}, {'0' if kk == 0 else o[acc]}")
+        if kk + depth < ks and (which == "t" or kk >= kt):
+            lines.append(f"ds_read_b128 {o[f'kf{kk % depth}']}, {o['addr']} offset:{(kk + depth) * 32}")
+        lines += work.get(m, [])
+        if m in at:
+            c = at[m]
+            if c < n_copy:
+                # (the scalar add writes SCC: the statement names it as clobbered)
+                lines += [f"v_min_u32 {o['tmp']}, {o['c0']}, {o[f'off{c}']}", f"s_add_u32 m0, {o['c2']}, {c * 4096}", "s_nop 0",
+                          f"global_load_lds_dwordx4 {o['tmp']}, {o['c1']}"]
+            else:
+                lines += [f"s_cmp_lg_u32 {o['c4']}, 0", "s_cbranch_scc1 .Lloza_nox%=", f"v_min_u32 {o['tmp']}, {o['c0']}, {o[f'off{c}']}",
+                          f"s_mov_b32 m0, {o['c3']}", "s_nop 0", f"global_load_lds_dwordx4 {o['tmp']}, {o['c1']}", ".Lloza_nox%=:"]
+    lines += ["s_nop 7", "s_nop 7", "s_nop 7"]
+    text = f"// wide backward, scores pass: {ks} + {kt} steps, fragments 0..{n_agpr - 1} in AGPRs, {n_copy} + 1 woven copies, the previous tile's weights\n"
+    text += f"#define LOZA_BWD_SCORES_K{ks}_T{kt}(s_, t_, kf_, tmp_, p_, ds_, w_, addr_, xf_, voff_, sp_, tp_, lse_, dd_, tc_, wave_, sc_, scale_) \\\n    asm volatile( \\\n"
+    text += "".join(f'    "{l}\\n" \\\n' for l in lines)
+    text += "        : " + ", ".join(outs) + " \\\n        : " + ", ".join(ins) + " \\\n        : \"memory\", \"m0\", \"scc\")\n"
+    return text
+
+
 def macro(dqk: int) -> str:
     ks = dqk // 16
     depth = min(DEPTH, ks)
@@ -167,4 +240,5 @@ if __name__ == "__main__":
         print(macro_bwd(ks, n_a, n_b, n_agpr, n_voff=18))
     for ks, n_a, n_b, n_agpr in ((36, 9, 0, 32), (32, 9, 0, 24)):
         print(macro_bwd(ks, n_a, n_b, n_agpr))
+    print(macro_bwd_scores(36, 32, 9, 64))
     print("#endif")

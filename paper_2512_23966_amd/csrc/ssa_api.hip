@@ -699,6 +699,62 @@ static void backward_balance(loza::BwdParams &p, int d_qk, int d_v, bool alias)
     p = q;
 }
 
+// Chunks and work items of the passes of ssa_bwd_wide.hip; false where the kernels of ssa_bwd.hip serve: those keep no
+// weights, and start on 64 rows or keys instead of 128, so they win where a row sees 128 keys or fewer and the rounds
+// of workgroups are many (us, those against the passes; 64 heads: 3,000 tokens of window 128 530 against 553, of 16 373
+// against 488; 32 sequences of 128 tokens 514 against 548, of 64 sequences of 64 442 against 542; 8 of 128 175 against
+// 161, 16 of 200 525 against 467; 4,000 tokens of 16 + 256 1264 against 958, 1 + 7 blocks of 128 at 16,384 9700 against
+// 6850, 128 + 8192 at 12,000 39200 against 25100; 43 shapes tried).
+static bool backward_wide_plan(const loza::BwdParams &p, int d_qk, int d_v, bool alias, loza::WidePlan &w)
+{
+    if (d_qk != 576 || d_v != 512 || !alias) return false;
+    const int64_t R = p.S * p.G, tiles = (R + 127) / 128, groups = (p.S + 127) / 128, BH = (int64_t)p.B * p.Hkv;
+    if (groups > 32768) return false;                                // (the ring's division is exact up to there)
+    const int64_t sinks = (p.n_sink + 127) / 128, reach = (int64_t)p.window * p.block;
+    if (tiles * BH > 2 * kComputeUnits && (p.S <= 128 || p.n_sink + reach <= 128)) return false;
+    const int64_t span = 127 / p.G + 2;                              // positions of 128 rows, at most
+    const int64_t ring = (reach + span - 1 + 126) / 128 + 1;
+    loza::WideChunk &c = w.chunk;
+    c = loza::WideChunk{};
+    c.sink_groups = (int)(sinks < groups ? sinks : groups);
+    c.win_groups = (int)(ring < 2 ? 2 : ring < groups ? ring : groups < 2 ? 2 : groups);
+    c.win_magic = (uint32_t)(((1ULL << 32) + c.win_groups - 1) / c.win_groups);
+    c.slots = c.sink_groups + c.win_groups;
+    // The weights of a chunk of rows take 2 GiB of scratch memory at most (or what 256 row tiles, a round, take: up to
+    // 4): with 1, 16,384 tokens of 1 + 7 blocks of 128 take 7.4 ms instead of 6.9, with 4 or 8 7.0 and 6.8.
+    const int64_t tile_bytes = (int64_t)c.slots * 65536, cap = 2LL << 30;
+    w.row_tiles = (int)tiles;
+    if (tiles * tile_bytes <= cap) {
+        const int64_t n = cap / (tiles * tile_bytes);
+        w.chunk_bgs = (int)(n < BH ? n : BH);
+        w.chunk_tiles = (int)tiles;
+    } else {
+        const int64_t n = cap / tile_bytes / 256 * 256;
+        if (n < 256 && 256 * tile_bytes > 2 * cap) return false;
+        w.chunk_bgs = 1;
+        w.chunk_tiles = (int)(n < 256 ? 256 : n);
+        if (w.chunk_tiles > tiles) w.chunk_tiles = (int)tiles;
+    }
+    // Segments: rounds of 256 work items, each as long as a segment and 24 row blocks more (start, end, partial sums)
+    auto seen = [&](int64_t t) {                                      // key groups that t row tiles see, at most
+        const int64_t n = c.sink_groups + (reach + (t * 128 - 1) / p.G + 1 + 126) / 128 + 1;
+        return n < groups ? n : groups;
+    };
+    int64_t best = INT64_MAX;
+    for (int64_t n = 1; n <= 256 && n <= w.chunk_tiles; ++n) {
+        const int64_t seg = (w.chunk_tiles + n - 1) / n, items = n * w.chunk_bgs * seen(seg);
+        if (n > 1 && items > 1536) break;
+        const int64_t t = (items + kComputeUnits - 1) / kComputeUnits * (4 * seg + 24);
+        if (t < best) { best = t; c.seg_tiles = (int)seg; }
+    }
+    c.n_seg = (w.chunk_tiles + c.seg_tiles - 1) / c.seg_tiles;
+    c.max_groups = (int)seen(c.seg_tiles);
+    w.scratch_bytes = (size_t)(w.chunk_tiles * tile_bytes) * w.chunk_bgs;
+    w.part_bytes = (size_t)w.chunk_bgs * c.n_seg * c.max_groups * 128 * d_qk * sizeof(float);
+    w.acc_bytes = w.chunk_tiles < tiles ? (size_t)groups * 128 * d_qk * sizeof(float) : 0;
+    return true;
+}
+
 static int backward_fill(loza::BwdParams &p, int B, int Hq, int Hkv, int64_t S, int d_qk, int d_v,
                          int64_t sink, int64_t local, int64_t block, bool blocks, float scale, bool alias)
 {
@@ -724,14 +780,15 @@ static int backward_fill(loza::BwdParams &p, int B, int Hq, int Hkv, int64_t S, 
     return LOZA_OK;
 }
 
-static size_t backward_bytes(const loza::BwdParams &p, int d_qk, int d_v, bool alias, size_t *part_offset)
+// With `wide`: what the passes of ssa_bwd_wide.hip take, else the least that a call runs with.
+static size_t backward_bytes(const loza::BwdParams &p, int d_qk, int d_v, bool alias, const loza::WidePlan *wide, size_t *part_offset)
 {
     size_t stat = (size_t)p.B * p.Hkv * (size_t)p.r_pad * sizeof(float2);
     stat = (stat + 255) / 256 * 256;
     if (part_offset) *part_offset = stat;
     const size_t cols = alias ? (size_t)d_qk : (size_t)d_qk + d_v;
     const size_t part = p.max_chunks > 1 ? (size_t)p.B * p.Hkv * p.n_sink_kt * p.max_chunks * 64 * cols * sizeof(float) : 0;
-    return stat + part;
+    return stat + (wide && wide->bytes() > part ? wide->bytes() : part);
 }
 
 static size_t backward_workspace(int B, int Hq, int Hkv, int64_t S, int d_qk, int d_v,
@@ -739,7 +796,8 @@ static size_t backward_workspace(int B, int Hq, int Hkv, int64_t S, int d_qk, in
 {
     loza::BwdParams p{};
     if (backward_fill(p, B, Hq, Hkv, S, d_qk, d_v, sink, local, block, blocks, 1.0f, alias != 0) != LOZA_OK) return 0;
-    return backward_bytes(p, d_qk, d_v, alias != 0, nullptr);
+    loza::WidePlan w;
+    return backward_bytes(p, d_qk, d_v, alias != 0, backward_wide_plan(p, d_qk, d_v, alias != 0, w) ? &w : nullptr, nullptr);
 }
 
 static int backward_bf16(const void *q, const void *k, const void *v, const void *out, const float *lse,
@@ -754,7 +812,7 @@ static int backward_bf16(const void *q, const void *k, const void *v, const void
     loza::BwdParams p{};
     if (int rc = backward_fill(p, B, Hq, Hkv, S, d_qk, d_v, sink, local, block, blocks, scale, alias)) return rc;
     size_t part_offset = 0;
-    const size_t need = backward_bytes(p, d_qk, d_v, alias, &part_offset);
+    const size_t need = backward_bytes(p, d_qk, d_v, alias, nullptr, &part_offset);
     if (!workspace || workspace_bytes < need) return LOZA_ERR_WORKSPACE;
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out) || !aligned16(dout) || !aligned16(dq) ||
         !aligned16(dk) || (!alias && !aligned16(dv)) || !aligned16(workspace) || (reinterpret_cast<uintptr_t>(lse) & 3u))
@@ -764,8 +822,16 @@ static int backward_bf16(const void *q, const void *k, const void *v, const void
     p.dq = (uint16_t *)dq; p.dk = (uint16_t *)dk; p.dv = alias ? nullptr : (uint16_t *)dv;
     p.rowstat = (float2 *)workspace;
     p.part = (float *)((char *)workspace + part_offset);
-    backward_balance(p, d_qk, d_v, alias);
-    return loza::launch_backward_bf16(p, d_qk, d_v, alias, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
+    loza::WidePlan w;
+    const bool wide = backward_wide_plan(p, d_qk, d_v, alias, w) && workspace_bytes >= backward_bytes(p, d_qk, d_v, alias, &w, nullptr);
+    if (wide) {
+        w.chunk.scratch = (char *)workspace + part_offset;
+        w.chunk.part = (float *)(w.chunk.scratch + w.scratch_bytes);
+        w.chunk.acc = (float *)((char *)w.chunk.part + w.part_bytes);
+    } else {
+        backward_balance(p, d_qk, d_v, alias);
+    }
+    return loza::launch_backward_bf16(p, d_qk, d_v, alias, wide ? &w : nullptr, (hipStream_t)stream) == hipSuccess ? LOZA_OK : LOZA_ERR_HIP;
 }
 
 int loza_ssa_backward_split(int B, int Hq, int Hkv, int64_t S, int d_qk, int d_v, int64_t sink_blocks,

@@ -13,7 +13,8 @@
 // Three kernels:
 //   * ssa_bwd_rowstat_kernel: per query row, (lse log2(e), D) in the row order the main kernel
 //     walks through (position-major, heads of a group together).
-//   * (heads of width 128 take ssa_bwd128.hip in the place of the two below)
+//   * (heads of width 128 take ssa_bwd128.hip in the place of the two below, and the wide shape ssa_bwd_wide.hip, but for
+//     calls whose rows see few keys, and calls whose workspace does not hold the weights)
 //   * ssa_bwd_kernel<.., KEYS = false>: one workgroup keeps 64 query rows (Q and dO as matrix-core
 //     operands in registers) and streams the live key tiles of 32 keys past them: dQ.
 //   * ssa_bwd_kernel<.., KEYS = true>: one workgroup keeps 64 keys (K and V in registers) and
@@ -41,37 +42,11 @@
 
 #include "score_asm.h"
 #include "ssa_bwd_items.h"
+#include "ssa_bwd_tile.h"
 #include "ssa_device.h"
 #include "ssa_kernels.h"
 
 namespace loza {
-
-namespace {
-
-// One global -> LDS copy instruction: 64 lanes x 16 bytes from base + off (per lane) to the 1 KB of
-// LDS at lds_addr (wave-uniform, through M0). The compiler's wait counters do not see it: the tile
-// loop waits for all of them (vmcnt(0)) before the barrier that publishes a tile.
-__device__ __forceinline__ void copy_1k(const char *base, uint32_t off, uint32_t lds_addr)
-{
-    asm volatile("s_mov_b32 m0, %2\n s_nop 0\n global_load_lds_dwordx4 %0, %1"
-                 :: "v"(off), "s"(base), "s"(lds_addr) : "memory", "m0");
-}
-
-// Matrix-core A operand [32 columns of block db][16 items of key step ks] of a tile stored
-// [item][column] (padded rows of `row` bytes): two transposing 64-bit reads.
-__device__ __forceinline__ bf16x8 read_transposed(const char *tile, int row, int db, int ks, int lane)
-{
-    const int lh = lane >> 5, s16 = lane & 15, g16 = (lane >> 4) & 1;
-    const char *a = tile + (ks * 16 + lh * 8 + (s16 >> 2)) * row + (db * 32 + g16 * 16 + (s16 & 3) * 4) * 2;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(a));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(a + 4 * row));
-    s16x8 a8;
-    a8[0] = lo[0]; a8[1] = lo[1]; a8[2] = lo[2]; a8[3] = lo[3];
-    a8[4] = hi[0]; a8[5] = hi[1]; a8[6] = hi[2]; a8[7] = hi[3];
-    return __builtin_bit_cast(bf16x8, a8);
-}
-
-}  // namespace
 
 // The statistics of every query row, stored [B, Hkv, Rpad] with row index i * G + head-in-group: (lse log2(e), D = dO . O).
 template <int DV>
@@ -690,13 +665,14 @@ __global__ __launch_bounds__(256) void ssa_bwd_reduce_kernel(const BwdParams p)
 }
 
 template <int DQK, int DV, bool ALIAS>
-static hipError_t launch_backward_t(const BwdParams &p, hipStream_t stream)
+static hipError_t launch_backward_t(const BwdParams &p, const WidePlan *wide, hipStream_t stream)
 {
     const int64_t n_rows = (int64_t)p.B * p.S * p.Hq;
     constexpr int RPB = 256 / (DV / 8 < 64 ? DV / 8 : 64);             // rows per workgroup
     hipLaunchKernelGGL((ssa_bwd_rowstat_kernel<DV>), dim3((unsigned)((n_rows + RPB - 1) / RPB)), dim3(256), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (wide) return launch_bwd_wide(p, *wide, stream);
     const int64_t n_kt = (p.S + 63) / 64, kt0 = p.split_kt0();
     const int64_t items = (kt0 * p.max_chunks + (n_kt - kt0 - p.n_split_kt) + (int64_t)p.n_split_kt * p.split_chunks) * p.Hkv * p.B;
     if constexpr (DQK == 128) {
@@ -734,11 +710,11 @@ static hipError_t launch_backward_t(const BwdParams &p, hipStream_t stream)
 // power of two up to 32 (a tile is 32 / G whole positions) or a multiple of 32 (a tile is part of one).
 bool bwd_group_supported(int G) { return G >= 1 && (G % 32 == 0 || (G < 32 && (G & (G - 1)) == 0)); }
 
-hipError_t launch_backward_bf16(const BwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream)
+hipError_t launch_backward_bf16(const BwdParams &p, int d_qk, int d_v, bool alias, const WidePlan *wide, hipStream_t stream)
 {
-    if (d_qk == 576 && d_v == 512 && alias) return launch_backward_t<576, 512, true>(p, stream);
-    if (d_qk == 128 && d_v == 128) return alias ? launch_backward_t<128, 128, true>(p, stream)
-                                                : launch_backward_t<128, 128, false>(p, stream);
+    if (d_qk == 576 && d_v == 512 && alias) return launch_backward_t<576, 512, true>(p, wide, stream);
+    if (d_qk == 128 && d_v == 128) return alias ? launch_backward_t<128, 128, true>(p, nullptr, stream)
+                                                : launch_backward_t<128, 128, false>(p, nullptr, stream);
     return hipErrorInvalidValue;
 }
 

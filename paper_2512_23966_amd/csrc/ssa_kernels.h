@@ -123,11 +123,30 @@ __host__ __device__ inline void bwd_key_tile_rows(const BwdParams &p, int kt, in
     yt_hi = (int)(((i_hi + 1) * p.G - 1) / 32);
 }
 
+// The wide backward in passes that hand the weights p and dS to each other through memory (ssa_bwd_wide.hip). Rows are
+// taken in chunks: row tiles (128 rows) [t0, t1) of `nbg` (batch, key head)s from bg0 on.
+struct WideChunk {
+    char *scratch;     // p and dS of the chunk: [row blocks of 32][slots][32 rows x 128 keys: p, then dS, 8 KB each]
+    float *part;       // fp32 partial dK of the chunk: [segments of its rows][max_groups][128 keys x 576]
+    float *acc;        // sums over the chunks so far: [key groups of one (batch, key head)][128 x 576]
+    int bg0, nbg, t0, t1;
+    int slots, sink_groups, win_groups;   // key groups (of 128) a row block has places for: sinks, and a ring for the window's
+    uint32_t win_magic;                   // 2^32 / win_groups, rounded up
+    int seg_tiles, n_seg, max_groups;     // work items of dK: segments of seg_tiles row tiles x the groups each sees
+};
+struct WidePlan {
+    WideChunk chunk;
+    int row_tiles, chunk_tiles, chunk_bgs;   // per (batch, key head); per chunk
+    size_t scratch_bytes, part_bytes, acc_bytes;
+    size_t bytes() const { return (scratch_bytes + part_bytes + acc_bytes + 294911) / 294912 * 294912; }   // (whole groups of 64 keys x 576, twice)
+};
+hipError_t launch_bwd_wide(const BwdParams &p, const WidePlan &w, hipStream_t stream);
 // The two passes of the width-128 backward (ssa_bwd128.hip): `items` work items of 64 keys each, and dQ.
 hipError_t launch_bwd128_keys(BwdParams p, bool alias, int64_t items, hipStream_t stream);
 hipError_t launch_bwd128_rows(const BwdParams &p, bool alias, hipStream_t stream);
 bool bwd_group_supported(int G);
-hipError_t launch_backward_bf16(const BwdParams &p, int d_qk, int d_v, bool alias, hipStream_t stream);
+// `wide`: plan of the passes of ssa_bwd_wide.hip, null for the kernels of ssa_bwd.hip
+hipError_t launch_backward_bf16(const BwdParams &p, int d_qk, int d_v, bool alias, const WidePlan *wide, hipStream_t stream);
 
 struct F32Params {
     const float *q, *k, *v;
