@@ -147,12 +147,15 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
     return (sink_blocks < 0 || local_blocks < 1 || block < 1) ? LOZA_ERR_SHAPE : LOZA_OK;
 }
 
-// How many workgroups share the keys of a row in an extend that has scratch memory (of the kernel that takes the call
-// without it; 1: no sharing). Few
+// How many workgroups share the keys of a row in an extend that has scratch memory, and of which kernel (1: no sharing,
+// the kernel that takes the call without scratch memory). Few
 // new tokens leave most compute units idle: 2 tokens of one sequence are 8 groups of 16 rows of the absorbed-MLA
 // shape, and took the same 153 us (window 8192) as 128 tokens. Splits of the few-rows kernel are merged row by row
 // (2 tokens 22 us, 16 tokens 37 to 59); calls too large for that kernel split the tile kernel's keys, until its tiles
-// fill the chip by themselves. A split tile has two-term weights throughout (2.7 us a step, 1.45 with weights rounded
+// fill the chip by themselves, and so do calls of the few-rows kernel at the wide shape where the model says so (window
+// 8192: 8 sequences of 10 tokens 295 us, their tiles in 6 parts 154; 8 of 16 303 and in 4 217; 8 of 4 the rows in 2 parts
+// 103, the tiles in 16 90; 1 + 7 blocks, 8 of 16 49, tiles in 4 59: rows), but for those whose groups are one full
+// round, which would take 69 MB of scratch memory for a sixth of their time (16 of 4 tokens 167, in 8 parts 138). A split tile has two-term weights throughout (2.7 us a step, 1.45 with weights rounded
 // once): which rows have a large result is known only when the parts have been added, and a tile that has one may keep
 // none of its rows from once-rounded weights. 144 tokens of window 8192 386 -> 264 us; 256 tokens 400, in two 403: not
 // split. (d = 128, 8 key heads, window 4096: 280 tokens 152 -> 87, 600 tokens 153 -> 113.) Calls of the 256-row tiles of
@@ -161,10 +164,15 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
 // rounds, a round costs a start and a step per tile of keys, every row has a workgroup of the merge, and every set of
 // partial results of a row is written and read once; the host's part counts, since a short call waits for it (28
 // tokens of 1 + 7 blocks 25.6 us, in two parts 28.5 and 5 of the host; d = 128, 4 tokens 12.2, in 16 parts 8.5 and 5:
-// not split; 8 tokens 24.4 and 17.3 + 5). (Of a call that is not split, without tiles that are computed again for a large result; with 1 + 7 blocks
-// and N(0, 1) inputs nearly every call has one: 148 us instead of 61.) A split has to promise 7 %, which is what the
+// not split; 8 tokens 24.4 and 17.3 + 5). (With 1 + 7 blocks and N(0, 1) inputs nearly every unsplit call has a tile
+// that is computed again for a large result: 150 us instead of 61; 8 sequences of 32 tokens, in two parts 83.) A split has to promise 7 %, which is what the
 // model is worth. A chunk that (nearly) fills its cache is a prefill, and has its bits.
-int extend_splits(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk, const Pattern &pat)
+struct ExtendPlan {
+    bool rows;      // few-rows kernel, else tiles
+    int n_splits;
+};
+
+ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk, const Pattern &pat)
 {
     const bool wide = d_qk > 128;
     const int64_t rows = q_len * G, heads = (int64_t)B * Hkv, groups = (rows + 15) / 16 * heads;
@@ -184,17 +192,19 @@ int extend_splits(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk, con
         const double steps = (double)((live / 32 + 2 + n - 1) / n);
         const bool alone = tiles * n <= kComputeUnits;
         const double step = n > 1 ? (wide ? 2.7 : alone ? 1.4 : 2.0) : (wide ? 1.45 : alone ? 1.05 : 1.36);
-        return rounds(tiles * n, slots) * (12 + step * steps) + (n > 1 ? host + 6 + (wide ? 0.45e-3 : 0.11e-3) * rows * heads * n : 0);
+        // (one tile in twenty of 1,024 live N(0, 1) keys has a large result: where one round holds all, one more pass)
+        const double again = n == 1 && wide && live <= 1152 && tiles <= kComputeUnits ? 1.8 * (1 - pow(0.95, (double)tiles)) : 0;
+        return rounds(tiles * n, slots) * (12 + step * steps * (1 + again)) + (n > 1 ? host + 6 + (wide ? 0.45e-3 : 0.11e-3) * rows * heads * n : 0);
     };
     const bool few = loza::few_rows_bf16(B, Hkv, rows);
-    if (S * 8 <= q_len * 9) return 1;
-    if (!few && !wide && loza::d128_tiles_pay(B, Hkv, G, q_len, S, pat.n_sink, pat.window, pat.block)) return 1;
-    int best = 1;
+    ExtendPlan best{few, 1};
+    if (S * 8 <= q_len * 9) return best;
+    if (!few && !wide && loza::d128_tiles_pay(B, Hkv, G, q_len, S, pat.n_sink, pat.window, pat.block)) return best;
     double t = 0.93 * (few ? t_rows(1) : t_tile(1));
-    for (int n = 2; few && n <= kMaxSplits && groups * n <= kComputeUnits; ++n)
-        if (t_rows(n) < t) { t = t_rows(n); best = n; }
-    for (int n = 2; !few && n <= kMaxSplits && tiles * n <= 2 * slots; ++n)
-        if (t_tile(n) < t) { t = t_tile(n); best = n; }
+    auto offer = [&](bool by_rows, int n, double t_n) { if (t_n < t) { t = t_n; best = ExtendPlan{by_rows, n}; } };
+    for (int n = 2; few && n <= kMaxSplits && groups * n <= kComputeUnits; ++n) offer(true, n, t_rows(n));
+    const bool by_tiles = !few || (wide && (groups * 2 <= kComputeUnits || groups > kComputeUnits));
+    for (int n = 2; by_tiles && n <= kMaxSplits && tiles * n <= 2 * slots; ++n) offer(false, n, t_tile(n));
     return best;
 }
 
@@ -354,10 +364,12 @@ static int prefill_bf16(const void *q, const void *k, const void *v, void *out, 
     p.scale_log2 = scale * 1.44269504088896340736f;
     p.row_tiles = (int)row_tiles; p.n_splits = 1;
     set_rescale_policy(p);
-    const bool few_rows = loza::few_rows_bf16(B, Hkv, (extend ? q_len : S) * G);
+    bool few_rows = loza::few_rows_bf16(B, Hkv, (extend ? q_len : S) * G);
     if (extend) {
         if (scratch) {
-            p.n_splits = extend_splits(B, Hkv, G, q_len, S, d_qk, pat);
+            const ExtendPlan plan = extend_plan(B, Hkv, G, q_len, S, d_qk, pat);
+            few_rows = plan.rows;
+            p.n_splits = plan.n_splits;
             if (p.n_splits > 1) {
                 if (!workspace || workspace_bytes < split_bytes(B, Hq, q_len, d_v, p.n_splits)) return LOZA_ERR_WORKSPACE;
                 if (!aligned16(workspace)) return LOZA_ERR_ALIGN;
@@ -448,7 +460,7 @@ size_t loza_ssa_extend_workspace_bytes(int B, int Hq, int Hkv, int64_t S_max, in
     if (check_common(B, Hq, Hkv, S_max, d_qk, d_v, sink_blocks, local_blocks, 1.0f) != LOZA_OK) return 0;
     if (check_blocks(sink_blocks, local_blocks, block) != LOZA_OK || q_len < 1 || q_len > S_max) return 0;
     if (!loza::bf16_width_supported(d_qk)) return 0;
-    const int n = extend_splits(B, Hkv, Hq / Hkv, q_len, S_max, d_qk, block_pattern(sink_blocks, local_blocks, block, S_max));
+    const int n = extend_plan(B, Hkv, Hq / Hkv, q_len, S_max, d_qk, block_pattern(sink_blocks, local_blocks, block, S_max)).n_splits;
     return n > 1 ? split_bytes(B, Hq, q_len, d_v, n) : 0;
 }
 

@@ -22,6 +22,7 @@
 //   * each key row is read from LDS once for the scores and once (transposing) for the values per 16
 //     rows: LDS bandwidth bounds the loop (16 keys of the wide shape: 18 KB at 104 B/clk, 16 KB at 64
 //     B/clk and the incoming 18 KB: about 580 cycles per tile and compute unit).
+//   * (M = 32 rows a workgroup, two blocks of 16 that share every read, where width 128 has more than a round of groups)
 //   * workgroups that walk the same keys for other rows are placed on the same XCD, whose L2 then serves
 //     all but the first of them.
 // Tiles travel global -> LDS with global_load_lds_dwordx4 into a ring of NST stages per wave; the copy of
@@ -101,14 +102,15 @@ struct RowsCfg {
     static_assert(LDS_BYTES + 4096 <= 160 * 1024, "does not fit the 160 KB LDS");   // (and decode_row_direct's)
 };
 
-// One pass: rows 16 rt .. 16 rt + 15 of (batch b, key head g), tiles `split` of n_splits. EXACT: three-term weights
+// One pass: rows M rt .. M rt + M - 1 (M = 16 MB) of (batch b, key head g), tiles `split` of n_splits. EXACT: three-term weights
 // (decode). NT: the key rows are read by this workgroup only. All 256 threads call it together; the LDS it uses
 // (RowsCfg::LDS_BYTES) must not be in use when it starts.
-template <int DQK, int DV, bool ALIAS, bool NT, bool EXACT>
+template <int DQK, int DV, bool ALIAS, bool NT, bool EXACT, int MB>
 __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, const int b, const int g, const int rt, const int split, const int n_splits)
 {
     using C = RowsCfg<DQK, DV, ALIAS>;
-    constexpr int N = C::N, NST = C::NST, AHEAD = NST - 1, M = 16;
+    constexpr int N = C::N, NST = C::NST, AHEAD = NST - 1, M = 16 * MB;
+    static_assert(MB == 1 || !EXACT, "decodes take 16 rows");
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n16 = lane & 15, j4 = lane >> 4;
     const int G = p.G;
@@ -205,29 +207,37 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
 
     // ---- the queries: matrix-core B operands, row n16 of each block of 16 ------------------------------
     constexpr int KS = DQK / 32;
-    bf16x8 qf[KS];
-    int i_row, w_lo_row;
-    {
-        const int64_t row = r0 + n16, rc = row < R ? row : R - 1;
+    bf16x8 qf[MB][KS];
+    int i_row[MB], w_lo_row[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        const int64_t row = r0 + mb * 16 + n16, rc = row < R ? row : R - 1;
         const int64_t qi = row_position(rc, G);
         const int hh = (int)(rc - qi * G);
-        i_row = (int)(pos0 + qi);
-        w_lo_row = window_begin_of(i_row < 0 ? 0 : i_row, window, block);
+        i_row[mb] = (int)(pos0 + qi);
+        w_lo_row[mb] = window_begin_of(i_row[mb] < 0 ? 0 : i_row[mb], window, block);
         const uint16_t *qp = p.q + (((int64_t)b * Sq + qi) * p.Hq + (int64_t)g * G + hh) * DQK + j4 * 8;
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) qf[kk] = *(const bf16x8 *)(qp + kk * 32);
+        for (int kk = 0; kk < KS; ++kk) qf[mb][kk] = *(const bf16x8 *)(qp + kk * 32);
     }
     // (waited for here, with a wait the compiler sees: left to its own bookkeeping it would wait for the
     // queries inside the loop, with counts that also drain the tile copies it does not know about)
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(qf[kk]));
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+v"(qf[mb][kk]));
 
     constexpr int CB = DV / 16;   // column blocks
-    f32x4 o[CB];
-    float m_ref = LOZA_NEG_INF, l_run = 0.f;
+    f32x4 o[MB][CB];
+    float m_ref[MB], l_run[MB];
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) o[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int mb = 0; mb < MB; ++mb) {
+        m_ref[mb] = LOZA_NEG_INF;
+        l_run[mb] = 0.f;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) o[mb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 
     // per-lane LDS offsets of the reads, within a stage
     const uint32_t krd[2] = {(uint32_t)(n16 * C::CK * 16 + ((j4 ^ (n16 & 7)) * 16)),
@@ -254,66 +264,73 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
         pid = t + 1 + AHEAD < nt ? page_of(t + 1 + AHEAD) : 0;
 
         // scores: S^T[16 keys][16 rows], on two accumulators
-        f32x4 s2[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        f32x4 s2[MB][2];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) s2[mb][0] = s2[mb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
             const bf16x8 a = *(const bf16x8 *)(tile + krd[kk & 1] + (kk >> 1) * 128);
-            s2[kk & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[kk], s2[kk & 1], 0, 0, 0);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) s2[mb][kk & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[mb][kk], s2[mb][kk & 1], 0, 0, 0);
         }
         const int j0 = key_tile(t) * N;
         const bool interior = (j0 + N - 1 <= i_min) && ((j0 + N - 1 < n_sink) || (j0 >= w_lo_max));
-        f32x4 s = s2[0] + s2[1];
-        if (!interior) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int j = j0 + 4 * j4 + e;
-                const bool ok = (j <= i_row) & ((j < n_sink) | (j >= w_lo_row));
-                s[e] = ok ? s[e] : LOZA_NEG_INF;
-            }
-        }
-        float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])) * p.scale_log2;   // scale > 0
-        // the reference moves when some row exceeds it by 2^8 (or has none yet): then every row of the
-        // block takes its running maximum
-        if (__any(mx > m_ref + p.lazy_log2)) {
-            mx = max_over_groups(mx);
-            const float m_new = fmaxf(m_ref, mx);
-            const float a = m_new == LOZA_NEG_INF ? 1.0f : __builtin_amdgcn_exp2f(m_ref - m_new);
-            m_ref = m_new;
-            l_run *= a;
-            if (t > 0) {   // (not behind the first tile, whose accumulators are 0: 2,000 cycles; one sequence of window 8192 18.6 -> 17.4 us)
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-                // (the accumulators live in the AGPR half of the register file; pinned there on both
-                // sides of the multiply, four at a time pass through VGPRs, here and nowhere else)
-                f32x4 x = o[cb];
-                asm volatile("" : "+a"(x));
-                x *= a;
-                asm volatile("" : "+a"(x));
-                o[cb] = x;
-            }
-            }
-        }
-        const float m_use = m_ref == LOZA_NEG_INF ? 0.f : m_ref;   // a row with no live key so far
-        float e4[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) e4[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], p.scale_log2, -m_use));
-        l_run += (e4[0] + e4[1]) + (e4[2] + e4[3]);
-        u32x4 w;
-        w[0] = pack_bf16(e4[0], e4[1]);
-        w[1] = pack_bf16(e4[2], e4[3]);
-        auto lost = [](float x, uint32_t pair, int half) {        // what rounding x to that half of the pair lost
-            return x - __builtin_bit_cast(float, half ? pair & 0xffff0000u : pair << 16);
-        };
-        float r4[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) r4[e] = lost(e4[e], w[e >> 1], e & 1);
-        w[2] = pack_bf16(r4[0], r4[1]);
-        w[3] = pack_bf16(r4[2], r4[3]);
-        const bf16x8 pb = __builtin_bit_cast(bf16x8, w);
+        bf16x8 pb[MB];
         u32x4 w3 = {0, 0, 0, 0};
-        if constexpr (EXACT) {
-            w3[0] = pack_bf16(lost(r4[0], w[2], 0), lost(r4[1], w[2], 1));
-            w3[1] = pack_bf16(lost(r4[2], w[3], 0), lost(r4[3], w[3], 1));
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            f32x4 s = s2[mb][0] + s2[mb][1];
+            if (!interior) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int j = j0 + 4 * j4 + e;
+                    const bool ok = (j <= i_row[mb]) & ((j < n_sink) | (j >= w_lo_row[mb]));
+                    s[e] = ok ? s[e] : LOZA_NEG_INF;
+                }
+            }
+            float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])) * p.scale_log2;   // scale > 0
+            // the reference moves when some row exceeds it by 2^8 (or has none yet): then every row of the
+            // block takes its running maximum
+            if (__any(mx > m_ref[mb] + p.lazy_log2)) {
+                mx = max_over_groups(mx);
+                const float m_new = fmaxf(m_ref[mb], mx);
+                const float a = m_new == LOZA_NEG_INF ? 1.0f : __builtin_amdgcn_exp2f(m_ref[mb] - m_new);
+                m_ref[mb] = m_new;
+                l_run[mb] *= a;
+                if (t > 0) {   // (not behind the first tile, whose accumulators are 0: 2,000 cycles; one sequence of window 8192 18.6 -> 17.4 us)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) {
+                    // (the accumulators live in the AGPR half of the register file; pinned there on both
+                    // sides of the multiply, four at a time pass through VGPRs, here and nowhere else)
+                    f32x4 x = o[mb][cb];
+                    asm volatile("" : "+a"(x));
+                    x *= a;
+                    asm volatile("" : "+a"(x));
+                    o[mb][cb] = x;
+                }
+                }
+            }
+            const float m_use = m_ref[mb] == LOZA_NEG_INF ? 0.f : m_ref[mb];   // a row with no live key so far
+            float e4[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) e4[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], p.scale_log2, -m_use));
+            l_run[mb] += (e4[0] + e4[1]) + (e4[2] + e4[3]);
+            u32x4 w;
+            w[0] = pack_bf16(e4[0], e4[1]);
+            w[1] = pack_bf16(e4[2], e4[3]);
+            auto lost = [](float x, uint32_t pair, int half) {        // what rounding x to that half of the pair lost
+                return x - __builtin_bit_cast(float, half ? pair & 0xffff0000u : pair << 16);
+            };
+            float r4[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r4[e] = lost(e4[e], w[e >> 1], e & 1);
+            w[2] = pack_bf16(r4[0], r4[1]);
+            w[3] = pack_bf16(r4[2], r4[3]);
+            pb[mb] = __builtin_bit_cast(bf16x8, w);
+            if constexpr (EXACT) {
+                w3[0] = pack_bf16(lost(r4[0], w[2], 0), lost(r4[1], w[2], 1));
+                w3[1] = pack_bf16(lost(r4[2], w[3], 0), lost(r4[3], w[3], 1));
+            }
         }
 
         // values: O^T[16 columns][16 rows] += V^T P^T, two terms of the weights in one instruction
@@ -332,12 +349,14 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
                 a[x] = __builtin_bit_cast(bf16x8, a4);
             }
 #pragma unroll
-            for (int x = 0; x < GRP; ++x) o[c0 + x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], pb, o[c0 + x], 0, 0, 0);
+            for (int x = 0; x < GRP; ++x)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) o[mb][c0 + x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], pb[mb], o[mb][c0 + x], 0, 0, 0);
             // (half of this one's contraction is zeros; the shorter 16x16x16 must not follow on the same accumulators:
             // a gap of a few instructions between the two shapes lost results of the first)
             if constexpr (EXACT) {
 #pragma unroll
-                for (int x = 0; x < GRP; ++x) o[c0 + x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], __builtin_bit_cast(bf16x8, w3), o[c0 + x], 0, 0, 0);
+                for (int x = 0; x < GRP; ++x) o[0][c0 + x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], __builtin_bit_cast(bf16x8, w3), o[0][c0 + x], 0, 0, 0);
             }
         }
         // every LDS read of this stage is done before the next iteration's copies may land in it
@@ -347,22 +366,25 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
 
     // ---- the four waves' partial results meet in LDS ------------------------------------------------------
     float *ml = (float *)(smem + C::OFF_ML);
+    uint32_t *odd = (uint32_t *)(smem + C::OFF_ODD);
+    constexpr bool CHECK = EXACT && !ALIAS;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+    if (mb > 0) __syncthreads();                   // (the block before has been read)
     {
-        float l = l_run;
+        float l = l_run[mb];
         l += __shfl_xor(l, 16, 64);
         l += __shfl_xor(l, 32, 64);
         if (j4 == 0) {
-            ml[(wave * M + n16) * 2] = m_ref;
-            ml[(wave * M + n16) * 2 + 1] = l;
+            ml[(wave * 16 + n16) * 2] = m_ref[mb];
+            ml[(wave * 16 + n16) * 2 + 1] = l;
         }
     }
     {
         char *op = smem + wave * C::REGION + n16 * C::OROW + j4 * 16;
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) *(f32x4 *)(op + cb * 64) = o[cb];
+        for (int cb = 0; cb < CB; ++cb) *(f32x4 *)(op + cb * 64) = o[mb][cb];
     }
-    uint32_t *odd = (uint32_t *)(smem + C::OFF_ODD);
-    constexpr bool CHECK = EXACT && !ALIAS;
     if (CHECK && tid == 0) *odd = 0;
     __syncthreads();
     // wave w finishes rows 4 w .. 4 w + 3 of the block, 512 (or 4 x 128) columns at a time
@@ -371,19 +393,19 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
 #pragma unroll
     for (int step = 0; step < 4 / RPI; ++step) {
         const int rr = wave * 4 + step * RPI + lane / LPR, c = (lane % LPR) * 4;
-        const int64_t row = r0 + rr;
+        const int64_t row = r0 + mb * 16 + rr;
         if (row >= R) continue;
         float mw[C::NW], m_all = LOZA_NEG_INF, l_all = 0.f;
 #pragma unroll
         for (int w = 0; w < C::NW; ++w) {
-            mw[w] = ml[(w * M + rr) * 2];
+            mw[w] = ml[(w * 16 + rr) * 2];
             m_all = fmaxf(m_all, mw[w]);
         }
         f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
 #pragma unroll
         for (int w = 0; w < C::NW; ++w) {
             const float a = mw[w] == LOZA_NEG_INF ? 0.f : __builtin_amdgcn_exp2f(mw[w] - m_all);
-            l_all += a * ml[(w * M + rr) * 2 + 1];
+            l_all += a * ml[(w * 16 + rr) * 2 + 1];
             const char *op = smem + w * C::REGION + rr * C::OROW + c * 4;
             lo += a * *(const f32x4 *)op;
             hi += a * *(const f32x4 *)(op + HALF * 4);
@@ -424,6 +446,7 @@ __device__ __forceinline__ void ssa_rows_pass(const FwdParams &p, char *smem, co
             if (z != 0.f) atomicOr(odd, 1u << rr);
         }
         if (c == 0) p.lse[((int64_t)b * p.Hq + h) * Sq + qi] = (m_all + __builtin_amdgcn_logf(l_all)) * 0.69314718055994530942f;
+    }
     }
     if constexpr (CHECK) {
         // An infinite value at a live key gives an infinity, but the lower terms of its weight may be 0 or negative

@@ -10,7 +10,7 @@
 
 namespace loza {
 
-template <int DQK, int DV, bool ALIAS, bool NT, bool EXACT>
+template <int DQK, int DV, bool ALIAS, bool NT, bool EXACT, int MB>
 __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(256) void ssa_rows_kernel(const FwdParams p)
     const int split = unit % p.n_splits;
     unit /= p.n_splits;
     const int g = unit % p.Hkv, b = unit / p.Hkv;
-    ssa_rows_pass<DQK, DV, ALIAS, NT, EXACT>(p, smem, b, g, rt, split, p.n_splits);
+    ssa_rows_pass<DQK, DV, ALIAS, NT, EXACT, MB>(p, smem, b, g, rt, split, p.n_splits);
 }
 
 // Merge of the key splits of one query row that ssa_rows_kernel left (log-sum-exp rule, fixed order), of a decode
@@ -97,11 +97,11 @@ __global__ __launch_bounds__(256) void ssa_rows_merge_kernel(const FwdParams p)
     *(u32x2 *)(p.out + h * DV + col) = w2;
 }
 
-template <int DQK, int DV, bool ALIAS, bool NT, bool EXACT>
+template <int DQK, int DV, bool ALIAS, bool NT, bool EXACT, int MB = 1>
 static hipError_t launch_rows_t(const FwdParams &p, hipStream_t stream)
 {
     using C = RowsCfg<DQK, DV, ALIAS>;
-    constexpr auto kern = ssa_rows_kernel<DQK, DV, ALIAS, NT, EXACT>;
+    constexpr auto kern = ssa_rows_kernel<DQK, DV, ALIAS, NT, EXACT, MB>;
     hipError_t e = allow_lds<kern>(C::LDS_BYTES);
     if (e != hipSuccess) return e;
     const int64_t blocks = (int64_t)p.n_splits * p.row_tiles * p.Hkv * p.B;
@@ -120,6 +120,16 @@ static hipError_t launch_rows_d(FwdParams p, bool decode, hipStream_t stream)
 {
     const int64_t rows = (p.seqlens ? (int64_t)p.q_len : p.S) * p.G;
     p.row_tiles = (int)((rows + 15) / 16);
+    // More than one round of the chip, width 128: 32 rows a workgroup, whose every fragment from LDS feeds two matrix
+    // instructions (8 key heads, 200 tokens of window 4096 77.7 -> 55.3 us, 16 x 16 of 1 + 7 blocks 27.9 -> 19.9; up to one
+    // round 41 against 55). The wide shape gains nothing by it (256 groups 148 against 322 with half the workgroups):
+    // a wave's own instructions bound it there.
+    if constexpr (DQK == 128) {
+        if (!decode && (int64_t)p.row_tiles * p.Hkv * p.B > 256 && p.n_splits == 1) {
+            p.row_tiles = (int)((rows + 31) / 32);
+            return launch_rows_t<DQK, DV, ALIAS, false, false, 2>(p, stream);
+        }
+    }
     if (decode) return p.row_tiles == 1 ? launch_rows_t<DQK, DV, ALIAS, true, true>(p, stream) : launch_rows_t<DQK, DV, ALIAS, false, true>(p, stream);
     return p.row_tiles == 1 ? launch_rows_t<DQK, DV, ALIAS, true, false>(p, stream) : launch_rows_t<DQK, DV, ALIAS, false, false>(p, stream);
 }
