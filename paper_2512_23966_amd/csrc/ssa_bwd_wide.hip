@@ -16,7 +16,7 @@
 // scratch memory that the host sets aside; a chunk's dK is cut into work items (128 keys x a segment of its rows), whose
 // fp32 partial sums the reduction adds in order, onto those of the chunks before.
 // 16,384 tokens, 64 heads, 1 + 7 blocks of 128 (rocprofv3): dK and dV 6.12 ms and dQ 3.57 before; now scores 2.37, dK and
-// dV 2.6, dQ 1.4, reduction 0.2. Cycles: a scores tile 3050 for 2176 of matrix work (the stores 440), and 33 thousand of a
+// dV 2.6, dQ 1.4, reduction 0.1. Cycles: a scores tile 3050 for 2176 of matrix work (the stores 440), and 33 thousand of a
 // row tile's 131 before its first: its 272 KB of q and dO, which all workgroups ask memory for together; 32 rows x 128
 // keys of dK 3150 for 2240 (2490 without copies, 2650 where what they fetch is in L2: misses fill the memory pipeline's
 // queue and the copy instructions wait for it), 32 keys x 128 rows of dQ 1720 for 1152.
@@ -94,6 +94,17 @@ __device__ __forceinline__ uint32_t key_item(int item, uint32_t stride, uint32_t
 __device__ __forceinline__ uint32_t row_item(int item, uint32_t pos_stride, uint32_t head_stride, int s)
 {
     return (item >> s) * pos_stride + (item & ((1 << s) - 1)) * head_stride;
+}
+
+// Row tiles of [ta, tb) that see a key of group kg: [see0, see1).
+__device__ __forceinline__ void group_rows(const BwdParams &p, int kg, int ta, int tb, int &see0, int &see1)
+{
+    see0 = kg * p.G > ta ? kg * p.G : ta;
+    see1 = tb;
+    if (kg * 128 >= p.n_sink) {
+        const int64_t i_w = ((int64_t)(kg * 128 + 127) / p.block + p.window) * p.block - 1, t_w = (i_w * p.G + p.G - 1) / 128 + 1;
+        if (t_w < see1) see1 = (int)t_w;
+    }
 }
 
 }  // namespace
@@ -490,11 +501,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_wide_dk_kernel(const BwdParams p,
     if (j >= gA + gB) return;
     const int kg = j < gA ? j : wg0 + (j - gA);
     // row tiles of the segment that see a key of the group
-    if (kg * G > ta) ta = kg * G;
-    if (kg * 128 >= p.n_sink) {
-        const int64_t i_w = ((int64_t)(kg * 128 + 127) / p.block + p.window) * p.block - 1, t_w = (i_w * G + G - 1) / 128 + 1;
-        if (t_w < tb) tb = (int)t_w;
-    }
+    group_rows(p, kg, ta, tb, ta, tb);
     const int rb0 = ta * 4, rb_end = tb * 4 < (int)((R + 31) / 32) ? tb * 4 : (int)((R + 31) / 32), n_rb = rb_end - rb0;
 
     int g_shift = 5;
@@ -622,26 +629,24 @@ __global__ __launch_bounds__(256) void ssa_bwd_wide_reduce_kernel(const BwdParam
     float4 s = {0.f, 0.f, 0.f, 0.f};
     float4 *before = (float4 *)c.acc + (int64_t)kg * (128 * kDqk / 4) + at;
     if (c.t0 > kg * G) s = *before;
-    // (eight segments' loads in flight: one after the other, the sink group's many waited for memory each)
-    for (int s0 = 0; s0 < c.n_seg; s0 += 8) {
+    // The segments with rows that see the group follow each other. (Eight loads in flight: one after the other, the many
+    // segments of a sink group waited for memory each; 106 us a chunk of 455 partial sums while all segments were asked.)
+    int see0, see1;
+    group_rows(p, kg, c.t0, c.t1, see0, see1);
+    const int last = (see1 - 1 - c.t0) / c.seg_tiles;
+    for (int s0 = (see0 - c.t0) / c.seg_tiles; s0 <= last; s0 += 8) {
         float4 v[8];
-        bool sees[8];
 #pragma unroll
         for (int h = 0; h < 8; ++h) {
-            const int seg = s0 + h, ta = c.t0 + seg * c.seg_tiles, tb = ta + c.seg_tiles < c.t1 ? ta + c.seg_tiles : c.t1;
-            int j = -1;
-            if (ta < tb) {
-                int sA, sw0, sB;
-                RowTileKeys(p, R, (int64_t)ta * 128, (int64_t)tb * 128).pieces(7, sA, sw0, sB);
-                j = kg < sA ? kg : kg >= sw0 && kg < sw0 + sB ? sA + kg - sw0 : -1;
-            }
-            sees[h] = j >= 0;
-            v[h] = float4{0.f, 0.f, 0.f, 0.f};
-            if (sees[h]) v[h] = ((const float4 *)c.part)[((int64_t)(bgl * c.n_seg + seg) * c.max_groups + j) * (128 * kDqk / 4) + at];
+            const int seg = s0 + h < last ? s0 + h : last, ta = c.t0 + seg * c.seg_tiles, tb = ta + c.seg_tiles < c.t1 ? ta + c.seg_tiles : c.t1;
+            int sA, sw0, sB;
+            RowTileKeys(p, R, (int64_t)ta * 128, (int64_t)tb * 128).pieces(7, sA, sw0, sB);
+            const int j = kg < sA ? kg : sA + kg - sw0;
+            v[h] = ((const float4 *)c.part)[((int64_t)(bgl * c.n_seg + seg) * c.max_groups + j) * (128 * kDqk / 4) + at];
         }
 #pragma unroll
         for (int h = 0; h < 8; ++h) {
-            if (!sees[h]) continue;
+            if (s0 + h > last) break;
             s.x += v[h].x; s.y += v[h].y; s.z += v[h].z; s.w += v[h].w;
         }
     }
