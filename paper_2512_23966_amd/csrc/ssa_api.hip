@@ -153,9 +153,9 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
 // shape, and took the same 153 us (window 8192) as 128 tokens. Splits of the few-rows kernel are merged row by row
 // (2 tokens 22 us, 16 tokens 37 to 59); calls too large for that kernel split the tile kernel's keys, until its tiles
 // fill the chip by themselves, and so do calls of the few-rows kernel at the wide shape where the model says so (window
-// 8192: 8 sequences of 10 tokens 295 us, their tiles in 6 parts 154; 8 of 16 303 and in 4 217; 8 of 4 the rows in 2 parts
-// 103, the tiles in 16 90; 1 + 7 blocks, 8 of 16 49, tiles in 4 59: rows), but for those whose groups are one full
-// round, which would take 69 MB of scratch memory for a sixth of their time (16 of 4 tokens 167, in 8 parts 138). A split tile has two-term weights throughout (2.7 us a step, 1.45 with weights rounded
+// 8192: 8 sequences of 10 tokens 295 us, their tiles in 6 parts 146; 8 of 16 303 and in 4 198; 8 of 4 the rows in 2 parts
+// 103, the tiles in 16 84; 1 + 7 blocks, 8 of 16 49, tiles in 4 56: rows), but for those whose groups are one full
+// round, which would take 69 MB of scratch memory for a sixth of their time (16 of 4 tokens 167, in 8 parts 138). A split tile has two-term weights throughout (2.45 us a step, 1.45 with weights rounded
 // once): which rows have a large result is known only when the parts have been added, and a tile that has one may keep
 // none of its rows from once-rounded weights. 144 tokens of window 8192 386 -> 264 us; 256 tokens 400, in two 403: not
 // split. (d = 128, 8 key heads, window 4096: 280 tokens 152 -> 87, 600 tokens 153 -> 113.) Calls of the 256-row tiles of
@@ -165,7 +165,7 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
 // partial results of a row is written and read once; the host's part counts, since a short call waits for it (28
 // tokens of 1 + 7 blocks 25.6 us, in two parts 28.5 and 5 of the host; d = 128, 4 tokens 12.2, in 16 parts 8.5 and 5:
 // not split; 8 tokens 24.4 and 17.3 + 5). (With 1 + 7 blocks and N(0, 1) inputs nearly every unsplit call has a tile
-// that is computed again for a large result: 150 us instead of 61; 8 sequences of 32 tokens, in two parts 83.) A split has to promise 7 %, which is what the
+// that is computed again for a large result: 140 us instead of 61; 8 sequences of 32 tokens, in two parts 75.) A split has to promise 7 %, which is what the
 // model is worth. A chunk that (nearly) fills its cache is a prefill, and has its bits.
 struct ExtendPlan {
     bool rows;      // few-rows kernel, else tiles
@@ -191,9 +191,9 @@ ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk
     auto t_tile = [&](int64_t n) {
         const double steps = (double)((live / 32 + 2 + n - 1) / n);
         const bool alone = tiles * n <= kComputeUnits;
-        const double step = n > 1 ? (wide ? 2.7 : alone ? 1.4 : 2.0) : (wide ? 1.45 : alone ? 1.05 : 1.36);
+        const double step = n > 1 ? (wide ? 2.45 : alone ? 1.4 : 2.0) : (wide ? 1.45 : alone ? 1.05 : 1.36);
         // (one tile in twenty of 1,024 live N(0, 1) keys has a large result: where one round holds all, one more pass)
-        const double again = n == 1 && wide && live <= 1152 && tiles <= kComputeUnits ? 1.8 * (1 - pow(0.95, (double)tiles)) : 0;
+        const double again = n == 1 && wide && live <= 1152 && tiles <= kComputeUnits ? 1.6 * (1 - pow(0.95, (double)tiles)) : 0;
         return rounds(tiles * n, slots) * (12 + step * steps * (1 + again)) + (n > 1 ? host + 6 + (wide ? 0.45e-3 : 0.11e-3) * rows * heads * n : 0);
     };
     const bool few = loza::few_rows_bf16(B, Hkv, rows);

@@ -652,12 +652,22 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
         auto &pf = f.pf;
         auto &vlo = f.vlo;
         auto &vhi = f.vhi;
+        // (two terms: one key step's weights, each replaced by the next step's behind its last product. The second terms,
+        // read where they were used, had every product of one wait for LDS: an extend of split tiles, 8 sequences of 16 tokens,
+        // window 8192, 214 -> 198 us, a call of 1 + 7 blocks with a tile that is computed again 152 -> 140. Two
+        // pairs of buffers in the place of the second barrier, and sums without the dot product, changed nothing more.)
+        bf16x8 pl[PRECISE ? RB : 1];
+        auto load_pl = [&](int ks, int rb) { pl[PRECISE ? rb : 0] = *(const bf16x8 *)(pb_lo + rb * 32 * C::PROW + ks * 32); };
+        if constexpr (PRECISE) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) load_pl(0, rb);
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int step = 0; step < NSTEP; ++step) {
             const int ks = step / C::DVB, db = step % C::DVB;
             if (step + 2 < NSTEP) load_v(vp, step + 2, vlo[(step + 2) % 3], vhi[(step + 2) % 3]);
-            if (db == 0 && ks + 1 < KS) {
+            if (!PRECISE && db == 0 && ks + 1 < KS) {
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) pf[(ks + 1) & 1][rb] = *(const bf16x8 *)(pb + rb * 32 * C::PROW + (ks + 1) * 32);
             }
@@ -668,10 +678,13 @@ static __device__ __forceinline__ bool ssa_fwd_tile(const FwdParams &p, char *sm
             const bf16x8 a = __builtin_bit_cast(bf16x8, a8);
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-                o[db][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[ks & 1][rb], o[db][rb], 0, 0, 0);
+                o[db][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[PRECISE ? 0 : ks & 1][rb], o[db][rb], 0, 0, 0);
                 if (PRECISE) {
-                    const bf16x8 pl = *(const bf16x8 *)(pb_lo + rb * 32 * C::PROW + ks * 32);
-                    o[db][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pl, o[db][rb], 0, 0, 0);
+                    o[db][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pl[rb], o[db][rb], 0, 0, 0);
+                    if (db == C::DVB - 1 && ks + 1 < KS) {
+                        pf[0][rb] = *(const bf16x8 *)(pb + rb * 32 * C::PROW + (ks + 1) * 32);
+                        load_pl(ks + 1, rb);
+                    }
                 }
                 // the micro-jobs of the next tile's softmax that belong to this slot
                 constexpr int NSLOT = NSTEP * RB, JPS = (SM_JOBS + NSLOT - 1) / NSLOT;
