@@ -11,13 +11,13 @@
 //   * two waves per SIMD, of workgroups that do not wait for each other: one's matrix instructions run while the other
 //     forms exponentials or waits for LDS. (A wave of 64 items would read half as much from LDS per matrix instruction,
 //     but fill the register file alone, and overlap only what is interleaved by hand.)
-//   * LDS bounds it: every wave reads the streamed tile twice, by rows (104 B/clk and compute unit) and transposed
-//     (64 B/clk): 2280 cycles of reads against 1536 of matrix work for 8 waves and 32 keys (dQ), 3300 against 2176 (dK, dV).
-// 32 heads of their own keys, 8,111 tokens of 128 + 4096: dQ 1008 -> 625 us, dK and dV 1168 -> 870 (LDS busy 76 and 86 % of
-// the cycles, matrix cores 57 and 59 %).
+//   * every wave reads the streamed tile twice, by rows and transposed; matrix and vector work in turn bound it (LDS busy
+//     30 % of the cycles, matrix cores 59 and 59 %).
+// 32 heads of their own keys, 8,111 tokens of 128 + 4096: dQ 1008 -> 600 us, dK and dV 1168 -> 830.
 // Tiles of 32 items travel global -> LDS by global_load_lds_dwordx4; rows of 256 bytes are unpadded, their 16-byte
-// chunks permuted within groups of eight (chunk c of row r in slot c ^ (r & 7)): both kinds of reads are free of bank
-// conflicts.
+// chunks permuted (row_swizzle): both kinds of reads are free of bank conflicts. (By c ^ (r & 7) within groups of eight
+// two thirds of the LDS's cycles were conflicts, and it was busy 71 and 73 % of the time; forward and backward of
+// that case 1973 us, now 1891.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256, 2) void ssa_bwd128_kernel(const BwdParams p)
     // ---- copies: instruction n of a sub-tile's eight moves rows 4 n .. 4 n + 3 and belongs to wave n % NW --------
     const int n_y = (int)(KEYS ? R : S);
     const int c_row = wave * 4 + (lane >> 4);
-    const uint32_t c_chunk = (uint32_t)((lane & 8) | ((lane ^ c_row) & 7)) * 16u;   // (rows of a wave are equal mod 8 where NW is even)
+    const uint32_t c_chunk = ((uint32_t)(lane & 15) ^ row_swizzle(c_row)) * 16u;   // (a wave's rows are equal mod 16)
     // byte offset of row y of a tile from its first row
     auto item_offset = [&](int y) -> uint32_t {
         if (!KEYS) return (uint32_t)y * (uint32_t)p.Hkv * ROW;
@@ -252,16 +252,16 @@ __global__ __launch_bounds__(256, 2) void ssa_bwd128_kernel(const BwdParams p)
     // LDS offsets of this lane's reads within a tile (by rows: row ln; transposing: rows 4 lh + ...)
     // (of fragment 0; the permutation makes the others' a matter of single bits: tiles lie at multiples of 1 KB)
     const int s16 = lane & 15, v_row = lh * 4 + (s16 >> 2);
-    const uint32_t k_rd = (uint32_t)(ln * ROW + ((lh ^ (ln & 7)) * 16));
-    const uint32_t v_rd = (uint32_t)(v_row * ROW + (((((lane >> 4) & 1) * 2 + ((s16 & 3) >> 1)) ^ (v_row & 7)) * 16) + (s16 & 1) * 8);
+    const uint32_t k_rd = (uint32_t)(ln * ROW) + ((uint32_t)lh ^ row_swizzle(ln)) * 16u;
+    const uint32_t v_rd = (uint32_t)(v_row * ROW + (s16 & 1) * 8) + ((uint32_t)(((lane >> 4) & 1) * 2 + ((s16 & 3) >> 1)) ^ row_swizzle(v_row)) * 16u;
     typedef __attribute__((address_space(3))) const char *lds_ptr;
     auto read_rows = [&](uint32_t t, int kk) {
-        return *(__attribute__((address_space(3))) const bf16x8 *)(uintptr_t)((t ^ ((kk & 3) << 5)) + (kk >> 2) * 128);
+        return *(__attribute__((address_space(3))) const bf16x8 *)(uintptr_t)(t ^ (kk << 5));
     };
     auto read_cols = [&](uint32_t t, int ks, int db) {
-        const lds_ptr a = (lds_ptr)(uintptr_t)((t ^ ((db & 1) << 6)) + (db >> 1) * 128 + ks * 16 * ROW);
+        const lds_ptr a = (lds_ptr)(uintptr_t)((t ^ (db << 6)) + ks * 16 * ROW), c = (lds_ptr)(uintptr_t)((t ^ (db << 6 | 32)) + ks * 16 * ROW + 8 * ROW);   // (row r + 8: swizzled by 2 more)
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(a));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(a + 8 * ROW));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(c));
         s16x8 a8;
         a8[0] = lo[0]; a8[1] = lo[1]; a8[2] = lo[2]; a8[3] = lo[3];
         a8[4] = hi[0]; a8[5] = hi[1]; a8[6] = hi[2]; a8[7] = hi[3];

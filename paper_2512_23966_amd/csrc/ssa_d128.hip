@@ -12,14 +12,15 @@
 //     lane holds for 16 keys are its B operand, and the transposing value reads fetch the keys in that order;
 //   * the sum of the rounded weights (the normaliser of O) comes from the matrix core, too: one more column
 //     block of ones;
-//   * two waves per SIMD: one's matrix instructions run while the other forms exponentials or waits for LDS. What bounds
-//     a step of 32 keys then is the LDS: eight waves read keys by rows and values transposed, 1656 cycles at the rates
-//     it sustains (104 and 64 B/clk), for 1152 of matrix work a SIMD. (Four waves of 64 rows, one a SIMD, read half of that
-//     but issue one instruction at a time: interleaved by hand, one matrix instruction per slot, a step took 2400 cycles.
-//     32 heads of their own keys, 32,768 tokens: 2450 us, now 2316.)
+//   * two waves per SIMD: one's matrix instructions run while the other forms exponentials or waits for LDS: 1152 cycles of
+//     matrix work a step of 32 keys and SIMD in about 1900, and nearly as many of vector work; the LDS is busy for 20 % of
+//     them. (Four waves of 64 rows, one a SIMD, issue one instruction at a time: interleaved by hand, one matrix
+//     instruction per slot, a step took 2400 cycles.)
 // Keys travel in stages of 64, global -> LDS by global_load_lds_dwordx4 into a ring of four, one barrier per
-// stage. A stage holds unpadded rows of 256 bytes whose 16-byte chunks are permuted within groups of eight
-// (chunk c of row r in slot c ^ (r & 7)): both kinds of reads are free of bank conflicts.
+// stage. A stage holds unpadded rows of 256 bytes whose 16-byte chunks are permuted (row_swizzle) so that both kinds of
+// reads are free of bank conflicts. (Permuted within groups of eight, by c ^ (r & 7), the four rows of a transposing read lay
+// in the same 16 banks and rows r and r + 8 of the other kind in the same four: two thirds of the LDS's cycles were
+// conflicts, 59 % of all cycles LDS. 32 heads of their own keys, 32,768 tokens: 2262 us, now 2212.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -112,7 +113,7 @@ static __device__ __forceinline__ bool ssa_d128_tile(const FwdParams &p, char *s
     const uint32_t smem_lds = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char *)smem);
     const uint32_t stride = (uint32_t)p.Hkv * ROW;       // keys and values alike
     const int c_row = wave * 4 + (lane >> 4);
-    const uint32_t c_chunk = (uint32_t)((lane & 8) | ((lane ^ c_row) & 7)) * 16u;
+    const uint32_t c_chunk = ((uint32_t)(lane & 15) ^ row_swizzle(c_row)) * 16u;
     const bool paged = p.block_table != nullptr;
     const int64_t seq_row0 = paged ? 0 : (int64_t)b * p.S;
     const char *kbase = (const char *)p.k + (seq_row0 * p.Hkv + g) * (int64_t)ROW;
@@ -197,15 +198,15 @@ static __device__ __forceinline__ bool ssa_d128_tile(const FwdParams &p, char *s
     // LDS offsets of this lane's reads within 32 rows (keys: row ln; values: rows 4 lh + ..., transposing), of fragment
     // 0; the permutation makes the others' a matter of single bits
     const int s16 = lane & 15, v_row = lh * 4 + (s16 >> 2);
-    const uint32_t k_rd = (uint32_t)(ln * ROW + ((lh ^ (ln & 7)) * 16));
-    const uint32_t v_rd = (uint32_t)((ALIAS ? 0 : C::KBYTES) + v_row * ROW + (((((lane >> 4) & 1) * 2 + ((s16 & 3) >> 1)) ^ (v_row & 7)) * 16) + (s16 & 1) * 8);
+    const uint32_t k_rd = (uint32_t)(ln * ROW) + ((uint32_t)lh ^ row_swizzle(ln)) * 16u;
+    const uint32_t v_rd = (uint32_t)((ALIAS ? 0 : C::KBYTES) + v_row * ROW + (s16 & 1) * 8) + ((uint32_t)(((lane >> 4) & 1) * 2 + ((s16 & 3) >> 1)) ^ row_swizzle(v_row)) * 16u;
     auto read_k = [&](uint32_t a, int kk) {
-        return *(__attribute__((address_space(3))) const bf16x8 *)(uintptr_t)((a ^ ((kk & 3) << 5)) + (kk >> 2) * 128);
+        return *(__attribute__((address_space(3))) const bf16x8 *)(uintptr_t)(a ^ (kk << 5));
     };
     auto read_v = [&](uint32_t a, int f) {       // fragment f = ks * 4 + db
-        const uint32_t x = (a ^ ((f & 1) << 6)) + ((f >> 1) & 1) * 128 + (f >> 2) * 16 * ROW;
+        const uint32_t x = (a ^ ((f & 3) << 6)) + (f >> 2) * 16 * ROW, y = (a ^ ((f & 3) << 6 | 32)) + (f >> 2) * 16 * ROW + 8 * ROW;   // (row r + 8: swizzled by 2 more)
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(uintptr_t)x);
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(uintptr_t)(x + 8 * ROW));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(uintptr_t)y);
         s16x8 a8;
         a8[0] = lo[0]; a8[1] = lo[1]; a8[2] = lo[2]; a8[3] = lo[3];
         a8[4] = hi[0]; a8[5] = hi[1]; a8[6] = hi[2]; a8[7] = hi[3];

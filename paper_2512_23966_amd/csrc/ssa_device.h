@@ -81,6 +81,12 @@ static __device__ __forceinline__ float xor32(float x)
 // vmcnt[3:0] in bits 3:0 and vmcnt[5:4] in bits 15:14; expcnt and lgkmcnt fields left at "no wait")
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 
+// Tiles of 256-byte rows in LDS (64 banks of 4 bytes): the 16-byte chunk c of row r lies at place c ^ row_swizzle(r) of the
+// row. A ds_read_b128 serves 16 lanes at a time, four runs of four whose numbers differ in the two bits above (lanes 0 .. 3,
+// 12 .. 15, 20 .. 23, 24 .. 27, and so on); one chunk of as many rows then lies in 16 different places. A transposing
+// ds_read_b64_tr_b16 serves 32 lanes, here four chunks of each of four rows r .. r + 3: four different quarters.
+__device__ __forceinline__ uint32_t row_swizzle(int r) { return (uint32_t)((r & 3) << 2 | ((r >> 2) & 3)); }
+
 // First key of the window of query i: the window holds the `window` most recent blocks of `block`
 // tokens, the query's own block included (block = 1: the `window` most recent tokens).
 __host__ __device__ __forceinline__ int window_begin_of(int i, int window, int block)
