@@ -158,11 +158,12 @@ int loza_ssa_decode_num_splits(int B, int Hq, int Hkv, int64_t S_max, int64_t n_
  *   loza_ssa_decode_kernel    a loza_kernel; *n_splits (may be NULL): the key splits it takes
  *   loza_ssa_backward_split   how many key tiles of 64 (per sequence and key head) the dK/dV kernel cuts into
  *                             chunks of rows for balance; *n_chunks, *n_whole (may be NULL): the chunks of
- *                             each, and the work items of the launch that are not such chunks
+ *                             each, and the work items of the launch that are not such chunks (at d_qk = 576:
+ *                             where a call takes the kernels that keep no weights in its workspace)
  */
 typedef enum {
     LOZA_KERNEL_TILES = 1, /* tiles of 128 (decode: 64) query rows      */
-    LOZA_KERNEL_ROWS = 2,  /* few query rows: 16 a workgroup            */
+    LOZA_KERNEL_ROWS = 2,  /* few query rows: 16 or 32 a workgroup      */
     LOZA_KERNEL_D128 = 3   /* width 128: tiles of 256 query rows        */
 } loza_kernel;
 int loza_ssa_forward_kernel(int B, int Hq, int Hkv, int64_t n_queries, int64_t S, int d_qk,

@@ -737,8 +737,9 @@ static bool backward_wide_plan(const loza::BwdParams &p, int d_qk, int d_v, bool
     const int64_t tile_bytes = (int64_t)c.slots * 65536, cap = 2LL << 30;
     w.row_tiles = (int)tiles;
     if (tiles * tile_bytes <= cap) {
-        const int64_t n = cap / (tiles * tile_bytes);
-        w.chunk_bgs = (int)(n < BH ? n : BH);
+        // (with the partial sums, which outweigh the weights where a key head has few query heads)
+        const int64_t n = cap / (tiles * tile_bytes + groups * 128 * d_qk * (int64_t)sizeof(float));
+        w.chunk_bgs = (int)(n < 1 ? 1 : n < BH ? n : BH);
         w.chunk_tiles = (int)tiles;
     } else {
         const int64_t n = cap / tile_bytes / 256 * 256;
