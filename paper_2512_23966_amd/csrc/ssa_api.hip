@@ -716,7 +716,11 @@ static void backward_balance(loza::BwdParams &p, int d_qk, int d_v, bool alias)
 // of workgroups are many (us, those against the passes; 64 heads: 3,000 tokens of window 128 530 against 553, of 16 373
 // against 488; 32 sequences of 128 tokens 514 against 548, of 64 sequences of 64 442 against 542; 8 of 128 175 against
 // 161, 16 of 200 525 against 467; 4,000 tokens of 16 + 256 1264 against 958, 1 + 7 blocks of 128 at 16,384 9700 against
-// 6850, 128 + 8192 at 12,000 39200 against 25100; 43 shapes tried).
+// 6850, 128 + 8192 at 12,000 39200 against 25100; 43 shapes tried). So they do where key heads are many and have few query
+// heads each: then a group of 128 keys has few rows to share its 295 KB of partial sums. The line, four times their number above the
+// square of the heads a group, is the simplest that 100 shapes allow (1,000 tokens of 1 + 7 blocks, sequences x query heads a
+// group: 1 x 1 121 against 159, 16 x 1 134 against 238, 1 x 2 177 against 165, 4 x 2 182 against 185, 16 x 2 244 against 287, 4 x 4 297 against 199,
+// 16 x 4 438 against 480, 16 x 8 795 against 708, 64 x 8 2816 against 3229, 64 x 16 6065 against 5797).
 static bool backward_wide_plan(const loza::BwdParams &p, int d_qk, int d_v, bool alias, loza::WidePlan &w)
 {
     if (d_qk != 576 || d_v != 512 || !alias) return false;
@@ -724,6 +728,7 @@ static bool backward_wide_plan(const loza::BwdParams &p, int d_qk, int d_v, bool
     if (groups > 32768) return false;                                // (the ring's division is exact up to there)
     const int64_t sinks = (p.n_sink + 127) / 128, reach = (int64_t)p.window * p.block;
     if (tiles * BH > 2 * kComputeUnits && (p.S <= 128 || p.n_sink + reach <= 128)) return false;
+    if (4 * BH > (int64_t)p.G * p.G) return false;
     const int64_t span = 127 / p.G + 2;                              // positions of 128 rows, at most
     const int64_t ring = (reach + span - 1 + 126) / 128 + 1;
     loza::WideChunk &c = w.chunk;
@@ -739,7 +744,8 @@ static bool backward_wide_plan(const loza::BwdParams &p, int d_qk, int d_v, bool
     if (tiles * tile_bytes <= cap) {
         // (with the partial sums, which outweigh the weights where a key head has few query heads)
         const int64_t n = cap / (tiles * tile_bytes + groups * 128 * d_qk * (int64_t)sizeof(float));
-        w.chunk_bgs = (int)(n < 1 ? 1 : n < BH ? n : BH);
+        const int64_t chunks = n < 1 ? BH : (BH + n - 1) / n;         // (of equal size)
+        w.chunk_bgs = (int)((BH + chunks - 1) / chunks);
         w.chunk_tiles = (int)tiles;
     } else {
         const int64_t n = cap / tile_bytes / 256 * 256;

@@ -18,7 +18,7 @@ import paper_2512_23966_amd as loza
     (1, 513, 128, 1, 20, 200, 1),       # a row tile is one position
     (1, 500, 96, 1, 2, 3, 37),          # row tiles that straddle positions unevenly, blocks of no round size
     (1, 900, 8, 1, 128, 300, 1),        # a row tile is 16 positions
-    (1, 2000, 1, 1, 0, 500, 1),         # a row tile is 128 positions
+    (1, 2000, 2, 1, 0, 500, 1),         # a row tile is 64 positions
     (3, 700, 64, 1, 1, 3, 64),
     (1, 3000, 64, 1, 0, 3000, 1),       # two chunks of rows, every key seen by both
     (1, 7000, 64, 1, 1, 7, 128),        # three chunks, a window that leaves the first keys behind
@@ -53,4 +53,5 @@ def test_which_calls_keep_weights():
     def bytes_per_row(B, S, local, block=1, Hq=64):
         return loza.loza_ssa_backward_workspace_bytes_blocks(B, Hq, 1, S, 576, 512, 0, local, block, True) / (B * S * Hq)
     assert bytes_per_row(1, 1024, 128) > 100 and bytes_per_row(1, 1026, 128) == 8 and bytes_per_row(1, 1026, 129) > 100
+    assert bytes_per_row(4, 1000, 500, Hq=4) > 100 and bytes_per_row(5, 1000, 500, Hq=4) == 8   # key heads against query heads a group
     assert bytes_per_row(8, 128, 128) > 100 and bytes_per_row(9, 128, 128) == 8 and bytes_per_row(9, 129, 129) > 100

@@ -48,7 +48,7 @@ def test_tiles_of_few_rows(gpu_device, B, S_max, q_len, lens, ns, win, block, st
 ])
 def test_pairs_of_row_groups(gpu_device, B, Hq, Hkv, S_max, q_len, lens, ns, win, block):
     groups = (q_len * (Hq // Hkv) + 15) // 16 * Hkv * B
-    assert 256 < groups <= 512 and _plan(B, Hq, Hkv, S_max, q_len, 128, ns, win, block or 1) == 1
+    assert 256 < groups <= 512 and (q_len * (Hq // Hkv) + 31) // 32 * Hkv * B <= 256 and _plan(B, Hq, Hkv, S_max, q_len, 128, ns, win, block or 1) == 1
     _extend(gpu_device, B, Hq, Hkv, 128, S_max, q_len, lens, ns, win, block, f"pairs {Hq}/{Hkv} q{q_len}", 3)
 
 
