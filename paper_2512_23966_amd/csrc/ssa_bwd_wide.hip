@@ -35,8 +35,9 @@ namespace loza {
 namespace {
 
 constexpr int kDqk = 576, kDv = 512;
-// Padded LDS rows. Read by rows, 16 bytes a lane: an odd number of 16-byte chunks. Read transposed only, 8 bytes a lane,
-// 16 lanes covering 32 bytes of each of four rows: 32 bytes more than a multiple of 128 (no bank conflicts).
+// Padded LDS rows. Read by rows, 16 bytes a lane: an odd number of 16-byte chunks, no bank conflicts. Read transposed only: 32
+// bytes (a third to a half of the LDS's active cycles of the two products are conflicts; with 64 there are none, and the
+// time is the same, 9,180 and 9,200 us forward and backward of the case below: LDS does not bound them).
 constexpr int kPadT = 32;
 constexpr int kRow1 = kDqk * 2 + 16, kRow1T = kDqk * 2 + kPadT, kRow2T = kDv * 2 + kPadT;
 constexpr int kCopies1 = 37, kCopies1T = (32 * kRow1T + 1023) / 1024, kCopies2T = (32 * kRow2T + 1023) / 1024;   // 1 KB copies of a tile of 32 rows
@@ -321,8 +322,8 @@ __device__ __forceinline__ void copy_const(F &&f, int n)
 // transposed read of column block 0, its second one `second` bytes further), B four blocks of 32 x 32 weights; b_of(block,
 // ks): B fragment. copy(n): the n-th of 12 copy instructions, two products apart. Three quarters through, when all of
 // this tile has been read, ready() waits for the next one and for the other waves, first(frags) reads its first operands, and
-// plan() prepares the next copies: a wave has nothing else to do while it waits for a barrier, LDS or scalar arithmetic
-// (together 300 to 500 cycles of 1600 a tile when they stood between two tiles).
+// plan() prepares the next copies: what a wave waits for (a barrier, LDS, scalar arithmetic) then has matrix work behind it.
+// (The same cycles as with all of it between two tiles, while the copies are what a tile waits for.)
 template <bool ROPE, int ROW, typename B, typename Copy, typename Ready, typename First, typename Plan>
 __device__ __forceinline__ void wide_product(WideAcc &acc, WideFrags &fr, const char *y, const int second, const int wave, B &&b_of, Copy &&copy,
                                              Ready &&ready, First &&first, Plan &&plan)
