@@ -357,7 +357,8 @@ size_t loza_ssa_calibration_alpha_grad_workspace_bytes(int64_t n);
  *        columns) and dv is ignored (may be NULL).
  *   workspace: loza_ssa_backward_workspace_bytes(...) bytes of device memory, 16-byte aligned;
  *        contents on entry are ignored. Two calls that overlap in time need two workspaces. At d_qk = 576
- *        most of it (up to 2 to 4 GiB) holds softmax weights on their way from one kernel to the next; a
+ *        most of it holds softmax weights on their way from one kernel to the next and partial sums of dk (long
+        sequences: 2 to 2.5 GiB; up to 4.6 where windows are close to 32,000 tokens or a key head has two query heads); a
  *        smaller one that still holds the row statistics (8 bytes a query row, rows padded to 32 per key head)
  *        and the partial sums of the sink keys (147,456 bytes per 64 of them and chunk of rows) is accepted, and
  *        the call then takes about 1.5 times as long.

@@ -617,7 +617,11 @@ __global__ __launch_bounds__(256) void ssa_bwd_wide_dk_kernel(const BwdParams p,
 }
 
 // The chunk's partial sums of a key group, in the order of the segments, onto those of the chunks before; rounded
-// and written out where no later chunk sees the group. A workgroup is a 72nd of a group.
+// and written out where no later chunk sees the group. Sums that go on are those of sink groups and of
+// groups that rows on both sides of the chunk's end see: no two of them have the same place. But one that begins in
+// this chunk can have the place of one that ends in it, so sums are read from one buffer and written to another, which the next
+// chunk reads. (A group that goes on beyond two ends is seen by the rows between them, and so is written again.) A workgroup
+// is a 72nd of a group.
 __global__ __launch_bounds__(256) void ssa_bwd_wide_reduce_kernel(const BwdParams p, const WideChunk c)
 {
     const int G = p.G;
@@ -628,8 +632,8 @@ __global__ __launch_bounds__(256) void ssa_bwd_wide_reduce_kernel(const BwdParam
     if (bgl >= c.nbg) return;
     const int kg = x < gA ? x : wg0 + (x - gA);
     float4 s = {0.f, 0.f, 0.f, 0.f};
-    float4 *before = (float4 *)c.acc + (int64_t)kg * (128 * kDqk / 4) + at;
-    if (c.t0 > kg * G) s = *before;
+    const int64_t sum_at = (int64_t)group_slot(c, kg) * (128 * kDqk / 4) + at;
+    if (c.t0 > kg * G) s = ((const float4 *)c.acc_in)[sum_at];
     // The segments with rows that see the group follow each other. (Eight loads in flight: one after the other, the many
     // segments of a sink group waited for memory each; 106 us a chunk of 455 partial sums while all segments were asked.)
     int see0, see1;
@@ -657,7 +661,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_wide_reduce_kernel(const BwdParam
         later = (int64_t)c.t1 * 128 <= i_w * G + G - 1;
     }
     if (later) {
-        *before = s;
+        ((float4 *)c.acc_out)[sum_at] = s;
         return;
     }
     const int lane = at & 63, blk = at >> 6;                 // [column block][key block][run of four]
@@ -675,7 +679,7 @@ hipError_t launch_bwd_wide(const BwdParams &p, const WidePlan &w, hipStream_t st
     if ((e = allow_lds<ssa_bwd_wide_dq_kernel>(kLdsDq)) != hipSuccess) return e;
     if ((e = allow_lds<ssa_bwd_wide_dk_kernel>(kLdsProduct)) != hipSuccess) return e;
     const int BH = p.B * p.Hkv;
-    WideChunk c = w.chunk;
+    WideChunk c = w.chunk;   // (the first chunk of a (batch, key head) reads no sums)
     for (int bg = 0; bg < BH; bg += w.chunk_bgs) {
         for (int t = 0; t < w.row_tiles; t += w.chunk_tiles) {
             c.bg0 = bg;
@@ -697,6 +701,9 @@ hipError_t launch_bwd_wide(const BwdParams &p, const WidePlan &w, hipStream_t st
             const unsigned n_g = (unsigned)(w0 <= sinks ? i_max / 128 + 1 : sinks + i_max / 128 - w0 + 1);
             hipLaunchKernelGGL(ssa_bwd_wide_reduce_kernel, dim3(72 * n_g * c.nbg), dim3(256), 0, stream, p, c);
             if ((e = hipGetLastError()) != hipSuccess) return e;
+            float *sums = c.acc_in;
+            c.acc_in = c.acc_out;
+            c.acc_out = sums;
         }
     }
     return hipSuccess;

@@ -1,0 +1,20 @@
+"""What the workspace of the absorbed-MLA backward holds, on the host."""
+import pytest
+
+import paper_2512_23966_amd as loza
+
+GIB = 1 << 30
+
+
+def _bytes(B, S, Hq, Hkv, pattern):
+    """(all of it, the row statistics)"""
+    return loza.loza_ssa_backward_workspace_bytes_blocks(B, Hq, Hkv, S, 576, 512, *pattern, True), B * Hkv * ((S * Hq // Hkv + 31) // 32 * 32) * 8
+
+
+@pytest.mark.parametrize("Hq", [16, 64, 128])
+@pytest.mark.parametrize("pattern", [(1, 7, 128), (128, 8192, 1), (16, 256, 1)])
+def test_long_sequences_take_what_their_windows_need(Hq, pattern):
+    """Sums that go on from a chunk of rows to the next are those of the groups of keys that rows on both sides see."""
+    for S in (131072, 1 << 20, 1 << 22):
+        n, stat = _bytes(1, S, Hq, 1, pattern)
+        assert 0 < n - stat < 2.5 * GIB
