@@ -138,7 +138,7 @@ struct WidePlan {
     WideChunk chunk;
     int row_tiles, chunk_tiles, chunk_bgs;   // per (batch, key head); per chunk
     size_t scratch_bytes, part_bytes, acc_bytes;
-    size_t bytes() const { return (scratch_bytes + part_bytes + acc_bytes + 294911) / 294912 * 294912; }   // (whole groups of 64 keys x 576, twice)
+    size_t bytes() const { return scratch_bytes + part_bytes + acc_bytes; }
 };
 hipError_t launch_bwd_wide(const BwdParams &p, const WidePlan &w, hipStream_t stream);
 // The two passes of the width-128 backward (ssa_bwd128.hip): `items` work items of 64 keys each, and dQ.

@@ -18,3 +18,15 @@ def test_long_sequences_take_what_their_windows_need(Hq, pattern):
     for S in (131072, 1 << 20, 1 << 22):
         n, stat = _bytes(1, S, Hq, 1, pattern)
         assert 0 < n - stat < 2.5 * GIB
+
+
+@pytest.mark.parametrize("B,S,Hq,pattern,slots,chunk_tiles", [
+    (1, 2048, 64, (1, 7, 128), 10, 1024),            # a sink group, and nine that 1 + 7 blocks of 128 can touch
+    (2, 1000, 16, (0, 300, 1), 4, 125),              # two sequences in a chunk
+    (1, 131072, 64, (128, 8192, 1), 67, 256),        # chunks of 256 row tiles
+])
+def test_what_it_is_made_of(B, S, Hq, pattern, slots, chunk_tiles):
+    """4 bytes a pair of 128 rows x 128 keys, then whole partial results of 128 keys x 576 (and of the sums between chunks)."""
+    n, stat = _bytes(B, S, Hq, 1, pattern)
+    rest = n - stat - B * chunk_tiles * slots * 128 * 128 * 4
+    assert rest > 0 and rest % (128 * 576 * 4) == 0 and rest < 0.5 * GIB

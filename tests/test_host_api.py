@@ -284,9 +284,15 @@ def test_backward_rejects_bad_arguments_and_sizes_its_workspace():
     # the row statistics (8 bytes per query row, rows padded to 32 per kv head) ...
     assert B.loza_ssa_backward_workspace_bytes(2, 8, 2, 1000, 128, 128, 0, 100, False) == 2 * 2 * 4000 * 8
     # ... plus, with sink keys, fp32 partial sums of the sink key tiles: one per chunk of query rows
-    n = B.loza_ssa_backward_workspace_bytes(1, 64, 1, 131072, 576, 512, 128, 8192, True)
+    # (the least that a call takes at d_qk = 576; the size that is given out holds weights, too)
+    accepts = lambda n: call(S=131072, window=8192, ws_bytes=n, dout=FAKE + 8) != ERR_WORKSPACE
+    lo, hi = 0, B.loza_ssa_backward_workspace_bytes(1, 64, 1, 131072, 576, 512, 128, 8192, True)
+    assert accepts(hi)
+    while hi - lo > 1:
+        lo, hi = (lo, (lo + hi) // 2) if accepts((lo + hi) // 2) else ((lo + hi) // 2, hi)
     stat = 131072 * 64 * 8
-    assert n > stat and (n - stat) % (2 * 64 * 576 * 4) == 0       # two key tiles of 64 keys, 576 columns
+    chunks = (hi - stat) // (2 * 64 * 576 * 4)                      # of two key tiles of 64 keys, 576 columns
+    assert chunks > 1 and hi == stat + chunks * 2 * 64 * 576 * 4
     assert B.loza_ssa_backward_workspace_bytes(1, 3, 1, 1000, 128, 128, 0, 100, False) == 0
     assert B.loza_ssa_backward_workspace_bytes_blocks(1, 64, 1, 4096, 576, 512, 1, 7, 0, True) == 0
     assert B.loza_ssa_backward_workspace_bytes_blocks(1, 64, 1, 4096, 576, 512, 1, 7, 128, True) > 0
