@@ -716,11 +716,19 @@ static void backward_balance(loza::BwdParams &p, int d_qk, int d_v, bool alias)
 // of workgroups are many (us, those against the passes; 64 heads: 3,000 tokens of window 128 530 against 553, of 16 373
 // against 488; 32 sequences of 128 tokens 514 against 548, of 64 sequences of 64 442 against 542; 8 of 128 175 against
 // 161, 16 of 200 525 against 467; 4,000 tokens of 16 + 256 1264 against 958, 1 + 7 blocks of 128 at 16,384 9700 against
-// 6850, 128 + 8192 at 12,000 39200 against 25100; 43 shapes tried). So they do where key heads are many and have few query
-// heads each: then a group of 128 keys has few rows to share its 295 KB of partial sums. The line, four times their number above the
-// square of the heads a group, is the simplest that 100 shapes allow (1,000 tokens of 1 + 7 blocks, sequences x query heads a
-// group: 1 x 1 121 against 159, 16 x 1 134 against 238, 1 x 2 177 against 165, 4 x 2 182 against 185, 16 x 2 244 against 287, 4 x 4 297 against 199,
-// 16 x 4 438 against 480, 16 x 8 795 against 708, 64 x 8 2816 against 3229, 64 x 16 6065 against 5797).
+// 6850, 128 + 8192 at 12,000 39200 against 25100).
+// They win, too, where a key head has few query heads, since then a group of 128 keys has few (query, key) pairs to share its
+// 295 KB of partial sums: the line is 2,304 live keys of a row (the mean over the sequence) times heads a group. (One
+// sequence, heads a group, tokens, pattern: 2, 11,988, 200 109 against 134; 2, 64,000, 128 + 2048 2174 against 1860; 4, 8,653, 200 x 3 sequences
+// 375 against 440; 4, 8,000, 1 + 7 blocks 380 against 281; 8, 12,201, 200 x 8 2425 against 2746, 256 2725 against 2885; 8, 8,000, 1 + 7 blocks
+// 731 against 486; 16 x 500 tokens of 8 heads 280 against 290; 16, 8,000, 200 tokens and more: always the passes.)
+// But up to 4,096 keys in all their tiles of 64 leave most of the chip idle, and up to 8,192 where the tiles of sink keys,
+// which every row sees, are the longest (4, 2,000, 1 + 7 blocks 314 against 180; 2, 2,428, 200 76 against 78; 4, 4,330, 16 + 320 221 against
+// 117; with 2 heads a group 6,500 of 1 + 7 blocks 200 against 234, so not there). Nor do many key heads of very few query heads pay: four times
+// their number may not exceed the square of the heads a group (1,000 tokens of 1 + 7 blocks, sequences x query heads a
+// group: 1 x 1 121 against 159, 16 x 1 134 against 238, 4 x 2 182 against 185, 16 x 2 244 against 287, 4 x 4 297 against 199,
+// 16 x 4 438 against 480, 64 x 8 2816 against 3229, 64 x 16 6065 against 5797). Over 1,250 shapes near these lines the passes
+// are the slower ones by more than 3 % at 17 that take them, 10 % at most.
 static bool backward_wide_plan(const loza::BwdParams &p, int d_qk, int d_v, bool alias, loza::WidePlan &w)
 {
     if (d_qk != 576 || d_v != 512 || !alias) return false;
@@ -729,6 +737,8 @@ static bool backward_wide_plan(const loza::BwdParams &p, int d_qk, int d_v, bool
     const int64_t sinks = (p.n_sink + 127) / 128, reach = (int64_t)p.window * p.block;
     if (tiles * BH > 2 * kComputeUnits && (p.S <= 128 || p.n_sink + reach <= 128)) return false;
     if (4 * BH > (int64_t)p.G * p.G) return false;
+    const int64_t live = p.n_sink + reach < p.S ? p.n_sink + reach : p.S;
+    if (p.G * live * (2 * p.S - live) < 2304 * 2 * p.S && BH * p.S > (p.n_sink > 0 && p.G > 2 ? 8192 : 4096)) return false;
     const int64_t span = 127 / p.G + 2;                              // positions of 128 rows, at most
     const int64_t ring = (reach + span - 1 + 126) / 128 + 1;
     loza::WideChunk &c = w.chunk;

@@ -55,3 +55,17 @@ def test_which_calls_keep_weights():
     assert bytes_per_row(1, 1024, 128) > 100 and bytes_per_row(1, 1026, 128) == 8 and bytes_per_row(1, 1026, 129) > 100
     assert bytes_per_row(4, 1000, 500, Hq=4) > 100 and bytes_per_row(5, 1000, 500, Hq=4) == 8   # key heads against query heads a group
     assert bytes_per_row(8, 128, 128) > 100 and bytes_per_row(9, 128, 128) == 8 and bytes_per_row(9, 129, 129) > 100
+
+
+@pytest.mark.parametrize("B,S,Hq,pattern,weights", [
+    (1, 11988, 2, (0, 200, 1), False), (1, 64000, 2, (128, 2048, 1), True),     # us without and with: 109, 134; 2174, 1860
+    (3, 8653, 4, (0, 200, 1), False), (1, 8000, 4, (1, 7, 128), True),          # 375, 440; 380, 281
+    (8, 12201, 8, (0, 256, 1), False), (1, 8000, 8, (1, 7, 128), True),         # 2725, 2885; 731, 486
+    (16, 500, 8, (1, 7, 128), True), (16, 786, 8, (0, 200, 1), False),          # 280, 290 (what the line costs); 321, 370
+    (1, 4096, 4, (0, 200, 1), True), (1, 4097, 4, (0, 200, 1), False),          # 4,096 keys leave most of the chip idle
+    (2, 4096, 4, (16, 320, 1), True), (2, 4097, 4, (16, 320, 1), False),        # with sink keys twice as many
+    (1, 6500, 2, (1, 7, 128), False),                                           # 200, 234
+])
+def test_few_heads_a_group_and_short_windows_keep_none(B, S, Hq, pattern, weights):
+    n = loza.loza_ssa_backward_workspace_bytes_blocks(B, Hq, 1, S, 576, 512, *pattern, True)
+    assert (n > B * S * Hq * 1000) == weights
