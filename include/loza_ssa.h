@@ -263,7 +263,8 @@ int loza_ssa_extend_paged_blocks(const void *q, const void *k_pages, const void 
  * terms. `workspace` (16-byte aligned, device): loza_ssa_extend_workspace_bytes
  * (S_max = max_pages_per_seq * page_size of a paged cache; 0: these sizes need none, the pointer may be
  * NULL, and the call is the one without). It must stay untouched until the launches have run; its contents do
- * not matter before and mean nothing afterwards.
+ * not matter before and mean nothing afterwards. Where that size is for tiles of 128 rows in the place of the kernel for few
+ * query rows, a smaller one, or none, is accepted if that kernel can do with it; LOZA_ERR_WORKSPACE otherwise.
  */
 int loza_ssa_extend_with_workspace(const void *q, const void *k, const void *v, const int32_t *block_table, const int32_t *seqlens,
                                    void *out, float *lse, int B, int Hq, int Hkv, int64_t S_max, int64_t num_pages,

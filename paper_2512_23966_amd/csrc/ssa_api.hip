@@ -172,7 +172,10 @@ struct ExtendPlan {
     int n_splits;
 };
 
-ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk, const Pattern &pat)
+// least: the plan for a workspace that does not hold the other's partial results: calls are split by the kernel that takes
+// them without scratch memory alone (most of those the other gives to tiles are not split then and need none), and a
+// split tile counts 2.7 us a step, which is what the sizes that callers may have kept were given out by.
+ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk, const Pattern &pat, bool least = false)
 {
     const bool wide = d_qk > 128;
     const int64_t rows = q_len * G, heads = (int64_t)B * Hkv, groups = (rows + 15) / 16 * heads;
@@ -191,9 +194,9 @@ ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk
     auto t_tile = [&](int64_t n) {
         const double steps = (double)((live / 32 + 2 + n - 1) / n);
         const bool alone = tiles * n <= kComputeUnits;
-        const double step = n > 1 ? (wide ? 2.45 : alone ? 1.4 : 2.0) : (wide ? 1.45 : alone ? 1.05 : 1.36);
+        const double step = n > 1 ? (wide ? (least ? 2.7 : 2.45) : alone ? 1.4 : 2.0) : (wide ? 1.45 : alone ? 1.05 : 1.36);
         // (one tile in twenty of 1,024 live N(0, 1) keys has a large result: where one round holds all, one more pass)
-        const double again = n == 1 && wide && live <= 1152 && tiles <= kComputeUnits ? 1.6 * (1 - pow(0.95, (double)tiles)) : 0;
+        const double again = !least && n == 1 && wide && live <= 1152 && tiles <= kComputeUnits ? 1.6 * (1 - pow(0.95, (double)tiles)) : 0;
         return rounds(tiles * n, slots) * (12 + step * steps * (1 + again)) + (n > 1 ? host + 6 + (wide ? 0.45e-3 : 0.11e-3) * rows * heads * n : 0);
     };
     const bool few = loza::few_rows_bf16(B, Hkv, rows);
@@ -203,7 +206,7 @@ ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk
     double t = 0.93 * (few ? t_rows(1) : t_tile(1));
     auto offer = [&](bool by_rows, int n, double t_n) { if (t_n < t) { t = t_n; best = ExtendPlan{by_rows, n}; } };
     for (int n = 2; few && n <= kMaxSplits && groups * n <= kComputeUnits; ++n) offer(true, n, t_rows(n));
-    const bool by_tiles = !few || (wide && (groups * 2 <= kComputeUnits || groups > kComputeUnits));
+    const bool by_tiles = !few || (!least && wide && (groups * 2 <= kComputeUnits || groups > kComputeUnits));
     for (int n = 2; by_tiles && n <= kMaxSplits && tiles * n <= 2 * slots; ++n) offer(false, n, t_tile(n));
     return best;
 }
@@ -367,11 +370,13 @@ static int prefill_bf16(const void *q, const void *k, const void *v, void *out, 
     bool few_rows = loza::few_rows_bf16(B, Hkv, (extend ? q_len : S) * G);
     if (extend) {
         if (scratch) {
-            const ExtendPlan plan = extend_plan(B, Hkv, G, q_len, S, d_qk, pat);
+            auto held = [&](int n) { return n == 1 || (workspace && workspace_bytes >= split_bytes(B, Hq, q_len, d_v, n)); };
+            ExtendPlan plan = extend_plan(B, Hkv, G, q_len, S, d_qk, pat);
+            if (!held(plan.n_splits)) plan = extend_plan(B, Hkv, G, q_len, S, d_qk, pat, true);
+            if (!held(plan.n_splits)) return LOZA_ERR_WORKSPACE;
             few_rows = plan.rows;
             p.n_splits = plan.n_splits;
             if (p.n_splits > 1) {
-                if (!workspace || workspace_bytes < split_bytes(B, Hq, q_len, d_v, p.n_splits)) return LOZA_ERR_WORKSPACE;
                 if (!aligned16(workspace)) return LOZA_ERR_ALIGN;
                 p.part_o = (float *)workspace;
                 p.part_ml = (float *)workspace + (size_t)B * Hq * q_len * p.n_splits * d_v;

@@ -175,6 +175,41 @@ def test_what_splits_and_what_does_not():
                 assert 1 <= n <= 64 and (n == 1 or n * B * Hq * q_len <= 1024 * 128 + 128 * n * B * Hkv)
 
 
+# What these calls needed while their rows, not tiles, shared keys (4 bytes x (512 + 4) x rows x parts; none: one part)
+KEPT = [(8, 4, 65536, (128, 8192, 1), 2), (1, 32, 65536, (128, 8192, 1), 2), (2, 8, 65536, (128, 8192, 1), 4)]
+
+
+@pytest.mark.parametrize("B,q_len,S_max,pattern,parts", KEPT)
+def test_the_least_scratch_memory_of_few_rows(B, q_len, S_max, pattern, parts):
+    size = 4 * (512 + 4) * B * 64 * q_len * parts
+
+    def call(nbytes, ws=FAKE + 4):                                    # (misaligned: no call gets beyond its argument checks)
+        return B_.lib().loza_ssa_extend_with_workspace(FAKE, FAKE, FAKE, None, FAKE, FAKE, FAKE, B, 64, 1, S_max, 0, 0, 0, q_len, 576, 512, *pattern,
+                                                       0.07, ws, nbytes, None)
+    assert call(size) == -6 and call(size - 1) == -4 and call(0, None) == -4
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,q_len,lens,parts", [(2, 16, [6000, 5555], 2), (5, 15, [6000, 5600, 700, 9, 0], 1), (5, 13, [6000, 5999, 140, 18, 2222], 1)])
+def test_few_rows_with_little_scratch_memory(gpu_device, B, q_len, lens, parts):
+    """A workspace for the few-rows kernel alone, or none where that kernel does not split the call."""
+    S_max, pat, scale = 6000, (128, 5000), 192 ** -0.5
+    full = loza.loza_ssa_extend_workspace_bytes(B, 64, 1, S_max, q_len, 576, 512, *pat)
+    size = 4 * (512 + 4) * B * 64 * q_len * parts if parts > 1 else 0
+    assert full > size
+    q, kc = _rand((B, q_len, 64, 576), 71, torch.bfloat16, gpu_device), _rand((B, S_max, 1, 576), 72, torch.bfloat16, gpu_device)
+    seqlens = torch.tensor(lens, dtype=torch.int32, device=gpu_device)
+    ws = torch.full((size + 512,), 255, dtype=torch.uint8, device=gpu_device)
+    out = torch.full((B, q_len, 64, 512), float("nan"), dtype=torch.bfloat16, device=gpu_device)
+    lse = torch.full((B, 64, q_len), float("nan"), device=gpu_device)
+    rc = B_.lib().loza_ssa_extend_with_workspace(q.data_ptr(), kc.data_ptr(), kc.data_ptr(), None, seqlens.data_ptr(), out.data_ptr(), lse.data_ptr(),
+                                                 B, 64, 1, S_max, 0, 0, 0, q_len, 576, 512, *pat, 1, scale, ws.data_ptr() + 256 if size else None, size,
+                                                 torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0 and (ws[:256] == 255).all() and (ws[256 + size:] == 255).all()
+    _check(q, kc, kc, lens, out, lse, pat, scale, f"little scratch memory: {B} x {q_len}", None, 17)
+
+
 def test_bad_arguments_are_rejected_before_any_launch():
     def call(ws=FAKE, nbytes=1 << 40, table=None, seqlens=FAKE, q_len=4, page=64, block=1, scale=0.07):
         return B_.lib().loza_ssa_extend_with_workspace(FAKE, FAKE, FAKE, table, seqlens, FAKE, FAKE, 2, 64, 1, 8192, 256, page, 128, q_len, 576, 512, 128,
