@@ -164,9 +164,11 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
 // rounds, a round costs a start and a step per tile of keys, every row has a workgroup of the merge, and every set of
 // partial results of a row is written and read once; the host's part counts, since a short call waits for it (28
 // tokens of 1 + 7 blocks 25.6 us, in two parts 28.5 and 5 of the host; d = 128, 4 tokens 12.2, in 16 parts 8.5 and 5:
-// not split; 8 tokens 24.4 and 17.3 + 5). (With 1 + 7 blocks and N(0, 1) inputs nearly every unsplit call has a tile
-// that is computed again for a large result: 140 us instead of 61; 8 sequences of 32 tokens, in two parts 75.) A split has to promise 7 %, which is what the
-// model is worth. A chunk that (nearly) fills its cache is a prefill, and has its bits.
+// not split; 8 tokens 24.4 and 17.3 + 5). A split has to promise 7 %, which is what the
+// model is worth. But where one round holds all unsplit tiles of the wide shape, it may cost 7 %: an unsplit tile with a large result
+// is computed again behind all others, and how often that is depends on values (us unsplit where none is, where one is, and split; 72 tiles
+// of 1 + 7 blocks 65, 152, 62 in 3 parts; 100 of window 2048 116, 296, 113; 128 of window 4096 209, 536, 204; but 104 of 1 + 7 blocks
+// 65, 152 and 71 in two: not split). A chunk that (nearly) fills its cache is a prefill, and has its bits.
 struct ExtendPlan {
     bool rows;      // few-rows kernel, else tiles
     int n_splits;
@@ -195,15 +197,14 @@ ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk
         const double steps = (double)((live / 32 + 2 + n - 1) / n);
         const bool alone = tiles * n <= kComputeUnits;
         const double step = n > 1 ? (wide ? (least ? 2.7 : 2.45) : alone ? 1.4 : 2.0) : (wide ? 1.45 : alone ? 1.05 : 1.36);
-        // (one tile in twenty of 1,024 live N(0, 1) keys has a large result: where one round holds all, one more pass)
-        const double again = !least && n == 1 && wide && live <= 1152 && tiles <= kComputeUnits ? 1.6 * (1 - pow(0.95, (double)tiles)) : 0;
-        return rounds(tiles * n, slots) * (12 + step * steps * (1 + again)) + (n > 1 ? host + 6 + (wide ? 0.45e-3 : 0.11e-3) * rows * heads * n : 0);
+        return rounds(tiles * n, slots) * (12 + step * steps) + (n > 1 ? host + 6 + (wide ? 0.45e-3 : 0.11e-3) * rows * heads * n : 0);
     };
     const bool few = loza::few_rows_bf16(B, Hkv, rows);
     ExtendPlan best{few, 1};
     if (S * 8 <= q_len * 9) return best;
     if (!few && !wide && loza::d128_tiles_pay(B, Hkv, G, q_len, S, pat.n_sink, pat.window, pat.block)) return best;
     double t = 0.93 * (few ? t_rows(1) : t_tile(1));
+    if (!least && !few && wide && tiles <= kComputeUnits) t *= 1.07 / 0.93;
     auto offer = [&](bool by_rows, int n, double t_n) { if (t_n < t) { t = t_n; best = ExtendPlan{by_rows, n}; } };
     for (int n = 2; few && n <= kMaxSplits && groups * n <= kComputeUnits; ++n) offer(true, n, t_rows(n));
     const bool by_tiles = !few || (!least && wide && (groups * 2 <= kComputeUnits || groups > kComputeUnits));

@@ -165,6 +165,14 @@ def test_what_splits_and_what_does_not():
     assert _plan(9, 64, 1, 16384, 3, 576, 1, 7, 128) == 1             # 25.6 and 28.3
     assert _plan(1, 32, 8, 16384, 4, 128, 1, 7, 128) == 1             # 11.9, in 16 parts 8.6 and 5 of the host
     assert _plan(1, 64, 1, 16384, 2, 576, 1, 7, 128) > 1              # 25.1 and 14.1
+    # one round of tiles: where a split costs nothing it is taken, since an unsplit tile may be computed again; the plan
+    # does not hang on a single key (parts at 1,020 to 1,300 live keys)
+    assert _plan(24, 64, 1, 65536, 6, 576, 1, 7, 128) == 3            # 65 us, 152 with a large result, 62 split
+    assert _plan(16, 64, 1, 65536, 13, 576, 1, 7, 128) == 1           # 65, 152, in two parts 71
+    assert _plan(16, 64, 1, 65536, 13, 576, 0, 500) == 1              # 43, 99, in two parts 55
+    for B, q_len in ((8, 32), (1, 256), (4, 64), (24, 6)):
+        plans = [_plan(B, 64, 1, 65536, q_len, 576, 0, w) for w in range(1020, 1300)]
+        assert len(set(plans)) == 1
     for bad in ((0, 64, 1, 100, 2, 576, 512, 1, 9, 1), (1, 64, 1, 100, 101, 576, 512, 1, 9, 1), (1, 64, 1, 100, 2, 577, 512, 1, 9, 1),
                 (1, 64, 1, 100, 2, 576, 512, -1, 9, 1), (1, 64, 1, 100, 2, 576, 512, 1, 0, 1), (1, 64, 1, 100, 2, 576, 512, 1, 9, 0)):
         assert loza.loza_ssa_extend_workspace_bytes(*bad) == 0
