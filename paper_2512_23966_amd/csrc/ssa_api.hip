@@ -207,6 +207,7 @@ ExtendPlan extend_plan(int B, int Hkv, int G, int64_t q_len, int64_t S, int d_qk
     if (!least && !few && wide && tiles <= kComputeUnits) t *= 1.07 / 0.93;
     auto offer = [&](bool by_rows, int n, double t_n) { if (t_n < t) { t = t_n; best = ExtendPlan{by_rows, n}; } };
     for (int n = 2; few && n <= kMaxSplits && groups * n <= kComputeUnits; ++n) offer(true, n, t_rows(n));
+    if (best.n_splits > 1) t *= 0.93;                                  // (so has another kernel)
     const bool by_tiles = !few || (!least && wide && (groups * 2 <= kComputeUnits || groups > kComputeUnits));
     for (int n = 2; by_tiles && n <= kMaxSplits && tiles * n <= 2 * slots; ++n) offer(false, n, t_tile(n));
     return best;

@@ -173,6 +173,9 @@ def test_what_splits_and_what_does_not():
     for B, q_len in ((8, 32), (1, 256), (4, 64), (24, 6)):
         plans = [_plan(B, 64, 1, 65536, q_len, 576, 0, w) for w in range(1020, 1300)]
         assert len(set(plans)) == 1
+    # rows in two to four parts; tiles in 15 to 33 parts were no faster, and twice as slow where caches are short
+    assert _plan(8, 64, 1, 65536, 4, 576, 128, 4096) == 2             # 57 us, as tiles 59; caches of 200 to 400 rows 23 and 37
+    assert _plan(7, 64, 1, 65536, 2, 576, 128, 8192) == 4             # 51 and 63; 18 and 43
     for bad in ((0, 64, 1, 100, 2, 576, 512, 1, 9, 1), (1, 64, 1, 100, 101, 576, 512, 1, 9, 1), (1, 64, 1, 100, 2, 577, 512, 1, 9, 1),
                 (1, 64, 1, 100, 2, 576, 512, -1, 9, 1), (1, 64, 1, 100, 2, 576, 512, 1, 0, 1), (1, 64, 1, 100, 2, 576, 512, 1, 9, 0)):
         assert loza.loza_ssa_extend_workspace_bytes(*bad) == 0
