@@ -232,9 +232,28 @@ def compare_backward_f32(q, k, v, out, lse, dout, got, n_sink, window, scale, la
         assert over <= 0.0, f"{label}: {name} error exceeds its bound by {over} (max error {err.max()})"
 
 
-def run_backward(q, k, v, out, lse, dout, n_sink, window, scale, block=None):
+def least_backward_workspace(B, Hq, Hkv, S, d_qk, d_v, n_sink, window, block, alias):
+    """Bytes of the smallest workspace that a backward call accepts. At d_qk = 576 a call with it keeps no softmax weights in
+    memory, at 128 it is what the size function says. (Asked of calls whose dout is misaligned, which launch nothing.)"""
+    window = oracle.INT64_MAX if window is None else window
+    fake, err_workspace, err_align = 4096, -4, -6
+
+    def accepted(n):
+        rc = loza.binding.lib().loza_ssa_backward_blocks(fake, fake, fake if alias else 2 * fake, fake, fake, fake + 8, fake, fake, fake, B, Hq, Hkv, S,
+                                                         d_qk, d_v, n_sink, window, block or 1, 1.0, fake, n, None)
+        assert rc in (err_workspace, err_align)
+        return rc == err_align
+    lo, hi = 0, loza.loza_ssa_backward_workspace_bytes_blocks(B, Hq, Hkv, S, d_qk, d_v, n_sink, window, block or 1, alias)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if accepted(mid) else (mid, hi)
+    return hi
+
+
+def run_backward(q, k, v, out, lse, dout, n_sink, window, scale, block=None, least=False):
     """HIP backward through the C ABI. Returns (dq, dk, dv); with ``v is k`` dk is the gradient of the
-    shared tensor and dv is None. The outputs start as NaN: every element must be written."""
+    shared tensor and dv is None. The outputs start as NaN: every element must be written. ``least``: with the smallest
+    workspace, which at d_qk = 576 means the kernels that keep no weights."""
     B, S, Hq, d_qk = q.shape
     Hkv, d_v = k.shape[2], out.shape[3]
     alias = v is k
@@ -244,10 +263,12 @@ def run_backward(q, k, v, out, lse, dout, n_sink, window, scale, block=None):
     dv = None if alias else torch.full_like(v, nan)
     if block is None:
         nb = loza.loza_ssa_backward_workspace_bytes(B, Hq, Hkv, S, d_qk, d_v, n_sink, window, alias)
+        nb = least_backward_workspace(B, Hq, Hkv, S, d_qk, d_v, n_sink, window, block, alias) if least else nb
         ws = torch.empty(max(nb, 16), dtype=torch.uint8, device=q.device)
         loza.loza_ssa_backward(q, k, v, out, lse, dout, dq, dk, dv, n_sink, window, scale, ws)
     else:
         nb = loza.loza_ssa_backward_workspace_bytes_blocks(B, Hq, Hkv, S, d_qk, d_v, n_sink, window, block, alias)
+        nb = least_backward_workspace(B, Hq, Hkv, S, d_qk, d_v, n_sink, window, block, alias) if least else nb
         ws = torch.empty(max(nb, 16), dtype=torch.uint8, device=q.device)
         loza.loza_ssa_backward_blocks(q, k, v, out, lse, dout, dq, dk, dv, n_sink, window, block, scale, ws)
     torch.cuda.synchronize()

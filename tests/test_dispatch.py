@@ -44,6 +44,7 @@ def test_decode_plans_fit_their_workspace(d, Hq, Hkv, sink, local, block):
             assert 1 <= n <= loza.loza_ssa_decode_num_splits(B, Hq, Hkv, S, sink * block, None if local is None else local * block)
 
 
+# (at width 576: the kernels that keep no weights in memory, which take a call whose workspace does not hold them)
 @pytest.mark.parametrize("Hq,Hkv,d,S,sink,local,block,split", [
     (64, 1, 576, 16384, 1, 7, 128, (30, 8, 256)),           # backward 12.9 ms whole, 10.5 in chunks
     (64, 1, 576, 16384, 128, 8192, 1, (0, 1, 258)),         # 53.1 whole (the last items are short), 56.8 in chunks

@@ -10,6 +10,7 @@ import pytest
 import torch
 
 import paper_2512_23966_amd as loza
+from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
 
@@ -62,15 +63,16 @@ def test_prefill_and_backward_stay_inside_their_buffers(gpu_device, S, Hq, Hkv, 
     G.check(f"prefill S{S}")
     _all_written(out, "prefill out"); _all_written(lse, "prefill lse")
     dout = _rand(out.shape, 4, gpu_device)
-    dq, dk = G.tensor(q.shape, torch.bfloat16), G.tensor(k.shape, torch.bfloat16)
-    dv = None if alias else G.tensor(v.shape, torch.bfloat16)
-    nb = loza.loza_ssa_backward_workspace_bytes(1, Hq, Hkv, S, d_qk, d_v, ns, win, alias)
-    ws = G.tensor((max(nb, 16),), torch.uint8)
-    loza.loza_ssa_backward(q, k, v, out, lse, dout, dq, dk, dv, ns, win, scale, ws)
-    G.check(f"backward S{S}")
-    _all_written(dq, "dq"); _all_written(dk, "dk")
-    if dv is not None:
-        _all_written(dv, "dv")
+    for nb in {loza.loza_ssa_backward_workspace_bytes(1, Hq, Hkv, S, d_qk, d_v, ns, win, alias),
+               H.least_backward_workspace(1, Hq, Hkv, S, d_qk, d_v, ns, win, None, alias)}:
+        dq, dk = G.tensor(q.shape, torch.bfloat16), G.tensor(k.shape, torch.bfloat16)
+        dv = None if alias else G.tensor(v.shape, torch.bfloat16)
+        ws = G.tensor((max(nb, 16),), torch.uint8)
+        loza.loza_ssa_backward(q, k, v, out, lse, dout, dq, dk, dv, ns, win, scale, ws)
+        G.check(f"backward S{S}, workspace of {nb} bytes")
+        _all_written(dq, "dq"); _all_written(dk, "dk")
+        if dv is not None:
+            _all_written(dv, "dv")
 
 
 def test_prefill_f32_stays_inside_its_buffers(gpu_device):

@@ -26,6 +26,7 @@ def _case(device, B, S, Hq, Hkv, d_qk, d_v, alias, seed=0):
     return q, k, v, dout
 
 
+@pytest.mark.parametrize("least", [False, True])   # weights in memory, and the kernels that keep none
 @pytest.mark.parametrize("B,S,Hq,ns,win,block", [
     (1, 160, 64, 16, 40, None),     # the absorbed-MLA head layout: 64 heads on one latent
     (1, 200, 64, 8, 8, None),       # sink key tile seen by many row chunks (partial sums + reduce)
@@ -39,12 +40,12 @@ def _case(device, B, S, Hq, Hkv, d_qk, d_v, alias, seed=0):
     (1, 90, 96, 2, 30, None),       # 96 heads: a position is three row tiles
     (1, 300, 64, 2, 2, 64),         # two sink blocks = two key tiles with sink keys, each cut in chunks
 ])
-def test_mla_backward(gpu_device, B, S, Hq, ns, win, block):
+def test_mla_backward(gpu_device, B, S, Hq, ns, win, block, least):
     q, k, v, dout = _case(gpu_device, B, S, Hq, 1, 576, 512, alias=True)
     scale = 192 ** -0.5
     out, lse = H.oracle_forward_all(q, k, v, ns, win, scale, 512, block)
-    got = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, block)
-    H.compare_backward(q, k, v, out, lse, dout, got, ns, win, scale, f"mla bwd B{B} S{S} Hq{Hq} ns{ns} W{win} b{block}", block)
+    got = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, block, least)
+    H.compare_backward(q, k, v, out, lse, dout, got, ns, win, scale, f"mla bwd B{B} S{S} Hq{Hq} ns{ns} W{win} b{block} least{least}", block)
 
 
 @pytest.mark.parametrize("B,S,Hq,Hkv,alias,ns,win,block", [
@@ -66,29 +67,31 @@ def test_d128_backward(gpu_device, B, S, Hq, Hkv, alias, ns, win, block):
                        f"d128 bwd B{B} S{S} Hq{Hq} Hkv{Hkv} alias{alias} ns{ns} W{win} b{block}", block)
 
 
-def test_mla_backward_dense_gradient_over_several_sink_chunks(gpu_device):
+@pytest.mark.parametrize("least", [False, True])
+def test_mla_backward_dense_gradient_over_several_sink_chunks(gpu_device, least):
     """Every row contributes (dense dO) at a length where a key tile with sink keys is seen by several
     chunks of rows (their fp32 partial tiles are summed by the reduce kernel) and the key tiles of a
     window are many: S = 2048, 64 heads on one latent, 128 sink tokens, window 512."""
-    import paper_2512_23966_amd as loza
     B, S, Hq, ns, win = 1, 2048, 64, 128, 512
     q, k, v, dout = _case(gpu_device, B, S, Hq, 1, 576, 512, alias=True, seed=50)
     scale = 192 ** -0.5
-    # the schedule really has more than one chunk per sink tile: the workspace holds their partial tiles
-    stat_only = B * 1 * ((S * Hq + 31) // 32 * 32) * 8
-    assert loza.loza_ssa_backward_workspace_bytes(B, Hq, 1, S, 576, 512, ns, win, True) > stat_only + 2 * 64 * 576 * 4
+    # the schedule of the kernels that keep no weights really has more than one chunk per sink tile: two tiles, whose partial
+    # results their workspace holds
+    partial = H.least_backward_workspace(B, Hq, 1, S, 576, 512, ns, win, None, True) - S * Hq * 8
+    assert partial % (2 * 64 * 576 * 4) == 0 and partial // (2 * 64 * 576 * 4) > 1
     out, lse = H.oracle_forward_all(q, k, v, ns, win, scale, 512)
-    got = H.run_backward(q, k, v, out, lse, dout, ns, win, scale)
-    H.compare_backward(q, k, v, out, lse, dout, got, ns, win, scale, f"mla bwd dense S{S} ns{ns} W{win}")
+    got = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, least=least)
+    H.compare_backward(q, k, v, out, lse, dout, got, ns, win, scale, f"mla bwd dense S{S} ns{ns} W{win} least{least}")
 
 
-def test_mla_backward_two_latent_heads(gpu_device):
+@pytest.mark.parametrize("least", [False, True])
+def test_mla_backward_two_latent_heads(gpu_device, least):
     B, S, Hq, Hkv, ns, win = 2, 70, 128, 2, 4, 20
     q, k, v, dout = _case(gpu_device, B, S, Hq, Hkv, 576, 512, alias=True, seed=30)
     scale = 192 ** -0.5
     out, lse = H.oracle_forward_all(q, k, v, ns, win, scale, 512)
-    got = H.run_backward(q, k, v, out, lse, dout, ns, win, scale)
-    H.compare_backward(q, k, v, out, lse, dout, got, ns, win, scale, "mla bwd two latent heads")
+    got = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, least=least)
+    H.compare_backward(q, k, v, out, lse, dout, got, ns, win, scale, f"mla bwd two latent heads least{least}")
 
 
 def test_backward_after_the_hip_forward(gpu_device):
@@ -110,12 +113,13 @@ def test_backward_after_the_hip_forward(gpu_device):
         assert rel < 2.0 ** -7 and err.max() < 2.0 ** -6 * np.abs(r).max()
 
 
-def test_backward_is_deterministic(gpu_device):
+@pytest.mark.parametrize("least", [False, True])
+def test_backward_is_deterministic(gpu_device, least):
     q, k, v, dout = _case(gpu_device, 1, 200, 64, 1, 576, 512, alias=True, seed=20)
     ns, win, scale = 8, 8, 192 ** -0.5
     out, lse = H.run_prefill(q, k, v, ns, win, scale, d_v=512)
-    a = H.run_backward(q, k, v, out, lse, dout, ns, win, scale)
-    b = H.run_backward(q, k, v, out, lse, dout, ns, win, scale)
+    a = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, least=least)
+    b = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, least=least)
     assert torch.equal(a[0].view(torch.int16), b[0].view(torch.int16))
     assert torch.equal(a[1].view(torch.int16), b[1].view(torch.int16))
 
@@ -155,28 +159,29 @@ def test_backward_at_the_128k_prefill_shape(gpu_device):
     dout[idx] = dout_rows.to(gpu_device)
     out[idx] = out_rows.to(gpu_device)
     lse[idx[0], idx[2], idx[1]] = lse_rows.to(gpu_device)
-    dq, dk, _ = H.run_backward(q, k, v, out, lse, dout, cfg.n_sink, cfg.window, cfg.scale)
     rq, rk, rv = oracle.ssa_backward_rows(q_rows, k.cpu(), ("alias", cfg.d_v), dout_rows, rb, rh, ri, Hq=cfg.Hq,
                                           n_sink=cfg.n_sink, window=cfg.window, scale=cfg.scale,
                                           out_rows=out_rows, lse_rows=lse_rows)
     rk[..., :cfg.d_v] += rv
-    got_q = dq[idx].double().cpu().numpy()
-    got_k = dk.double().cpu().numpy()
-    assert np.isfinite(got_q).all() and np.isfinite(got_k).all()
-    for name, gg, r in (("dq (sampled rows)", got_q, rq), ("dk (all keys)", got_k, rk)):
-        err = np.abs(gg - r)
-        over = float((err - H.grad_tolerance(r)).max())
-        print(f"[parity] cfg3 backward, {n} rows with a gradient: {name} max|err|={err.max():.3e} "
-              f"max|ref|={np.abs(r).max():.3e}", flush=True)
-        assert over <= 0.0, f"{name}: error exceeds its bound by {over}"
-    # rows without an incoming gradient: exactly zero, and all of them written. (A sampled row whose
-    # true gradient is zero -- position 0 sees one key, so dP = D -- may come out as exact zeros too.)
-    nonzero = (dq != 0).any(dim=-1)
-    sampled = torch.zeros_like(nonzero)
-    sampled[idx] = True
-    must = torch.zeros_like(nonzero)
-    has_grad = torch.as_tensor((rq != 0).any(axis=-1), device=gpu_device)
-    must[idx[0][has_grad], idx[1][has_grad], idx[2][has_grad]] = True
-    assert not (nonzero & ~sampled).any(), "a row without an incoming gradient has a non-zero dq"
-    assert (nonzero | ~must).all(), "a row with a gradient came out as zeros"
-    assert torch.isfinite(dq.float().sum())
+    for least in (False, True):
+        dq, dk, _ = H.run_backward(q, k, v, out, lse, dout, cfg.n_sink, cfg.window, cfg.scale, least=least)
+        got_q = dq[idx].double().cpu().numpy()
+        got_k = dk.double().cpu().numpy()
+        assert np.isfinite(got_q).all() and np.isfinite(got_k).all()
+        for name, gg, r in (("dq (sampled rows)", got_q, rq), ("dk (all keys)", got_k, rk)):
+            err = np.abs(gg - r)
+            over = float((err - H.grad_tolerance(r)).max())
+            print(f"[parity] cfg3 backward, {n} rows with a gradient, least{least}: {name} max|err|={err.max():.3e} "
+                  f"max|ref|={np.abs(r).max():.3e}", flush=True)
+            assert over <= 0.0, f"{name}: error exceeds its bound by {over}"
+        # rows without an incoming gradient: exactly zero, and all of them written. (A sampled row whose
+        # true gradient is zero -- position 0 sees one key, so dP = D -- may come out as exact zeros too.)
+        nonzero = (dq != 0).any(dim=-1)
+        sampled = torch.zeros_like(nonzero)
+        sampled[idx] = True
+        must = torch.zeros_like(nonzero)
+        has_grad = torch.as_tensor((rq != 0).any(axis=-1), device=gpu_device)
+        must[idx[0][has_grad], idx[1][has_grad], idx[2][has_grad]] = True
+        assert not (nonzero & ~sampled).any(), "a row without an incoming gradient has a non-zero dq"
+        assert (nonzero | ~must).all(), "a row with a gradient came out as zeros"
+        assert torch.isfinite(dq.float().sum())

@@ -21,18 +21,20 @@ def _case(device, B, S, Hq, Hkv, d_qk, d_v, alias, seed=30):
     (1, 413, 32, 1, 128, False, 0, 150, None),    # no sink tile; the last key tile is ragged
     (1, 413, 32, 1, 128, False, 70, 100, None),   # sink tiles in chunks of their own, cut finer too
     (1, 413, 32, 1, 128, True, 70, None, None),   # every key live: one chunk per sink tile at the outset
-    (2, 200, 64, 1, 576, True, 20, 90, None),
+    (2, 200, 64, 1, 576, True, 20, 90, None),     # (of the kernels that keep no weights in memory)
     (1, 333, 64, 1, 576, True, 1, 2, 64),         # block-granular
     (1, 1100, 4, 1, 128, False, 16, 600, None),   # nothing to cut: a chunk would be fewer than 32 row tiles
 ])
 def test_backward_with_split_key_tiles(gpu_device, B, S, Hq, Hkv, d, alias, ns, win, block):
     d_v = 512 if d == 576 else 128
     q, k, v, dout = _case(gpu_device, B, S, Hq, Hkv, d, d_v, alias)
-    scale = d ** -0.5
+    scale, least = d ** -0.5, d == 576
+    if S < 1000:
+        assert loza.loza_ssa_backward_split(B, Hq, Hkv, S, d, d_v, ns, win, block or 1, alias)[0] >= 1
     out, lse = H.oracle_forward_all(q, k, v, ns, win, scale, d_v, block)
-    got = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, block)
+    got = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, block, least)
     H.compare_backward(q, k, v, out, lse, dout, got, ns, win, scale, f"split bwd S{S} Hq{Hq} d{d} ns{ns} W{win} b{block}", block)
-    again = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, block)
+    again = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, block, least)
     assert all(a is b or torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(got, again))
 
 

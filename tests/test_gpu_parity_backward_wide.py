@@ -1,5 +1,5 @@
 """Backward of the absorbed-MLA shape through weights in memory: against the kernels that keep none, which take a call
-whose workspace does not hold them (and which the oracle checks at these forms in the other backward tests). Edges: rows
+whose workspace does not hold them (the other backward tests compare both with the oracle, at forms of their own). Edges: rows
 and keys that end inside a tile, row tiles that straddle positions, groups of keys that only some rows of a segment
 see, sinks that end inside a group or meet the window, rows in several chunks, several (sequence, key head)s in one."""
 import pytest

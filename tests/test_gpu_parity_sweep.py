@@ -112,9 +112,10 @@ def test_backward_sweep(gpu_device, case):
     v = k if alias else _rand((1, S, Hkv, d_v), 9000 + case, gpu_device)
     dout = _rand((1, S, Hq, d_v), 9500 + case, gpu_device)
     out, lse = H.oracle_forward_all(q, k, v, ns, win, scale, d_v, block)
-    got = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, block)
-    H.compare_backward(q, k, v, out, lse, dout, got, ns, win, scale,
-                       f"sweep {case}: Hq{Hq}/{Hkv} d{d_qk} alias{alias} S{S} ns{ns} W{win} b{block}", block)
+    for least in (False, True) if mla else (False,):
+        got = H.run_backward(q, k, v, out, lse, dout, ns, win, scale, block, least)
+        H.compare_backward(q, k, v, out, lse, dout, got, ns, win, scale,
+                           f"sweep {case}: Hq{Hq}/{Hkv} d{d_qk} alias{alias} S{S} ns{ns} W{win} b{block} least{least}", block)
 
 
 @pytest.mark.parametrize("case", range(400, 412))
