@@ -154,7 +154,10 @@ int loza_ssa_decode_num_splits(int B, int Hq, int Hkv, int64_t S_max, int64_t n_
  * _blocks entry points take it; block = 1: n_sink and window in tokens. Negative (a loza_status) on sizes
  * that the call itself refuses.
  *   loza_ssa_forward_kernel   prefill (n_queries = S), calibration or extend (n_queries = q_len, S = S_max):
- *                             a loza_kernel (with scratch memory the workgroups of the same kernel share keys)
+ *                             a loza_kernel, of a call without scratch memory. An extend that has what
+ *                             loza_ssa_extend_workspace_bytes says, if that is more than 0, has workgroups that
+ *                             share keys: of the same kernel, or at d_qk = 576 of LOZA_KERNEL_TILES in the
+ *                             place of LOZA_KERNEL_ROWS where those are faster
  *   loza_ssa_decode_kernel    a loza_kernel; *n_splits (may be NULL): the key splits it takes
  *   loza_ssa_backward_split   how many key tiles of 64 (per sequence and key head) the dK/dV kernel cuts into
  *                             chunks of rows for balance; *n_chunks, *n_whole (may be NULL): the chunks of
@@ -359,10 +362,12 @@ size_t loza_ssa_calibration_alpha_grad_workspace_bytes(int64_t n);
  *   workspace: loza_ssa_backward_workspace_bytes(...) bytes of device memory, 16-byte aligned;
  *        contents on entry are ignored. Two calls that overlap in time need two workspaces. At d_qk = 576
  *        most of it holds softmax weights on their way from one kernel to the next and partial sums of dk (long
-        sequences: 2 to 2.5 GiB; up to 4.6 where windows are close to 32,000 tokens or a key head has two query heads); a
+        sequences: 2 to 2.5 GiB; up to 4.6 where windows are close to 32,000 tokens or a key head has two query heads;
+        0.5 for 2,048 tokens of 64 heads, 1 + 7 blocks of 128); a
  *        smaller one that still holds the row statistics (8 bytes a query row, rows padded to 32 per key head)
  *        and the partial sums of the sink keys (147,456 bytes per 64 of them and chunk of rows) is accepted, and
- *        the call then takes about 1.5 times as long.
+ *        the call then takes about 1.3 to 1.6 times as long. (Where the size that is given out is that small, no weights are kept: few
+        query heads on a key head with short windows, rows that see 128 keys or fewer, windows beyond about 32,000 tokens.)
  * Supported: the (d_qk, d_v) pairs of loza_ssa_prefill, scale > 0, and Hq / Hkv a power of two up to
  * 32 or a multiple of 32 (else LOZA_ERR_UNSUPPORTED). Arithmetic: bf16 matrix-core operands (q, k,
  * v, dout, and p and ds rounded to bf16), fp32 accumulation, one rounding of each result to bf16.

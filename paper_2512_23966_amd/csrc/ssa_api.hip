@@ -151,14 +151,16 @@ int check_blocks(int64_t sink_blocks, int64_t local_blocks, int64_t block)
 // the kernel that takes the call without scratch memory). Few
 // new tokens leave most compute units idle: 2 tokens of one sequence are 8 groups of 16 rows of the absorbed-MLA
 // shape, and took the same 153 us (window 8192) as 128 tokens. Splits of the few-rows kernel are merged row by row
-// (2 tokens 22 us, 16 tokens 37 to 59); calls too large for that kernel split the tile kernel's keys, until its tiles
+// (2 tokens 22 us, 16 tokens 57); calls too large for that kernel split the tile kernel's keys, until its tiles
 // fill the chip by themselves, and so do calls of the few-rows kernel at the wide shape where the model says so (window
-// 8192: 8 sequences of 10 tokens 295 us, their tiles in 6 parts 146; 8 of 16 303 and in 4 198; 8 of 4 the rows in 2 parts
-// 103, the tiles in 16 84; 1 + 7 blocks, 8 of 16 49, tiles in 4 56: rows), but for those whose groups are one full
-// round, which would take 69 MB of scratch memory for a sixth of their time (16 of 4 tokens 167, in 8 parts 138). A split tile has two-term weights throughout (2.45 us a step, 1.45 with weights rounded
+// 8192: 8 sequences of 10 tokens 294 us, their tiles in 6 parts 141; 8 of 16 302 and in 4 195; 8 of 4 the rows in 2 parts
+// 93, the tiles in 16 79; 1 + 7 blocks, 8 of 16 52, tiles in 4 56: rows). Those whose groups are one full round of the
+// few-rows kernel are left to it, and need no scratch memory, though tiles would be faster there, too (129 to 256 groups; 16 of 4
+// tokens 160, in 8 parts 138, and 17 of 4 in 7 parts 130). The host knows windows, not lengths: where caches are short, a
+// split costs 3 to 24 us (200 to 400 rows: 2 tokens 12 -> 15, 8 of 16 30 -> 44, 8 of 4 15 -> 39). A split tile has two-term weights throughout (2.45 us a step, 1.45 with weights rounded
 // once): which rows have a large result is known only when the parts have been added, and a tile that has one may keep
-// none of its rows from once-rounded weights. 144 tokens of window 8192 386 -> 264 us; 256 tokens 400, in two 403: not
-// split. (d = 128, 8 key heads, window 4096: 280 tokens 152 -> 87, 600 tokens 153 -> 113.) Calls of the 256-row tiles of
+// none of its rows from once-rounded weights. 144 tokens of window 8192 391 -> 259 us, 256 tokens 397 -> 361 in two
+// parts. (d = 128, 8 key heads, window 4096: 280 tokens 154 -> 71, 600 tokens 156 -> 120.) Calls of the 256-row tiles of
 // width 128 have enough workgroups, and tiles twice as fast (3 sequences of 385 tokens 130 us, as three parts of the
 // 128-row tiles 212). The line is a time model of both in microseconds, fitted to 260 sizes: workgroups go in
 // rounds, a round costs a start and a step per tile of keys, every row has a workgroup of the merge, and every set of

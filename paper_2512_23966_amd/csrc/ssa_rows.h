@@ -20,8 +20,9 @@
 //     bf16 terms hold all 24 bits of an fp32 weight (43 sequences of 1,024 live keys, wide shape: 33.0 us with
 //     it, 30.3 without; 8,192 live keys of one sequence 18.7 and 17.8; d = 128, 16 sequences: no difference).
 //   * each key row is read from LDS once for the scores and once (transposing) for the values per 16
-//     rows: LDS bandwidth bounds the loop (16 keys of the wide shape: 18 KB at 104 B/clk, 16 KB at 64
-//     B/clk and the incoming 18 KB: about 580 cycles per tile and compute unit).
+//     rows (16 keys of the wide shape: 18 KB at 104 B/clk, 16 KB at 64 B/clk and the incoming 18 KB: about 580 cycles
+//     per tile and compute unit; the LDS is busy 20 % of the time). With one wave a SIMD what bounds the loop is latency
+//     and issue of a wave's chain of scores, softmax and values (matrix cores busy 28 %, vector units 25 %).
 //   * (M = 32 rows a workgroup, two blocks of 16 that share every read, where width 128 has more than a round of groups)
 //   * workgroups that walk the same keys for other rows are placed on the same XCD, whose L2 then serves
 //     all but the first of them.
