@@ -790,8 +790,9 @@ static bool backward_wide_plan(const loza::BwdParams &p, int d_qk, int d_v, bool
     w.scratch_bytes = (size_t)(w.chunk_tiles * tile_bytes) * w.chunk_bgs;
     w.part_bytes = (size_t)w.chunk_bgs * c.n_seg * c.max_groups * 128 * d_qk * sizeof(float);
     // (Places as in a row block: the groups that rows on both sides of a chunk's end see are no more than one block's. Indexed
-    // by group it was 2.25 GiB of 4.77 at a million tokens, 64 heads, 1 + 7 blocks of 128; now 5 MB.)
-    w.acc_bytes = w.chunk_tiles < tiles ? 2 * (size_t)c.slots * 128 * d_qk * sizeof(float) : 0;
+    // by group, as it is where groups are few, it was 2.25 GiB of 4.77 at a million tokens, 64 heads, 1 + 7 blocks of 128; now 5 MB.)
+    w.acc_places = w.chunk_tiles == tiles ? 0 : 2 * c.slots < groups ? 2 * c.slots : (int)groups;
+    w.acc_bytes = (size_t)w.acc_places * 128 * d_qk * sizeof(float);
     return true;
 }
 
@@ -868,7 +869,7 @@ static int backward_bf16(const void *q, const void *k, const void *v, const void
         w.chunk.scratch = (char *)workspace + part_offset;
         w.chunk.part = (float *)(w.chunk.scratch + w.scratch_bytes);
         w.chunk.acc_in = (float *)((char *)w.chunk.part + w.part_bytes);
-        w.chunk.acc_out = (float *)((char *)w.chunk.acc_in + w.acc_bytes / 2);
+        w.chunk.acc_out = (float *)((char *)w.chunk.acc_in + (w.acc_places == 2 * w.chunk.slots ? w.acc_bytes / 2 : 0));
     } else {
         backward_balance(p, d_qk, d_v, alias);
     }

@@ -620,7 +620,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_wide_dk_kernel(const BwdParams p,
 // and written out where no later chunk sees the group. Sums that go on are those of sink groups and of
 // groups that rows on both sides of the chunk's end see: no two of them have the same place. But one that begins in
 // this chunk can have the place of one that ends in it, so sums are read from one buffer and written to another, which the next
-// chunk reads. (A group that goes on beyond two ends is seen by the rows between them, and so is written again.) A workgroup
+// chunk reads (one buffer where every group has a place). (A group that goes on beyond two ends is seen by the rows between them, and so is written again.) A workgroup
 // is a 72nd of a group.
 __global__ __launch_bounds__(256) void ssa_bwd_wide_reduce_kernel(const BwdParams p, const WideChunk c)
 {
@@ -632,7 +632,7 @@ __global__ __launch_bounds__(256) void ssa_bwd_wide_reduce_kernel(const BwdParam
     if (bgl >= c.nbg) return;
     const int kg = x < gA ? x : wg0 + (x - gA);
     float4 s = {0.f, 0.f, 0.f, 0.f};
-    const int64_t sum_at = (int64_t)group_slot(c, kg) * (128 * kDqk / 4) + at;
+    const int64_t sum_at = (int64_t)(c.acc_in == c.acc_out ? kg : group_slot(c, kg)) * (128 * kDqk / 4) + at;
     if (c.t0 > kg * G) s = ((const float4 *)c.acc_in)[sum_at];
     // The segments with rows that see the group follow each other. (Eight loads in flight: one after the other, the many
     // segments of a sink group waited for memory each; 106 us a chunk of 455 partial sums while all segments were asked.)

@@ -128,7 +128,9 @@ __host__ __device__ inline void bwd_key_tile_rows(const BwdParams &p, int kt, in
 struct WideChunk {
     char *scratch;     // p and dS of the chunk: [row blocks of 32][slots][32 rows x 128 keys: p, then dS, 8 KB each]
     float *part;       // fp32 partial dK of the chunk: [segments of its rows][max_groups][128 keys x 576]
-    float *acc_in, *acc_out;   // sums over the chunks before this one, and with it: [slots][128 x 576] of one (batch, key head)
+    // sums over the chunks before this one, and with it, of one (batch, key head): [slots][128 x 576] each; the same [key
+    // groups][128 x 576] where those are fewer
+    float *acc_in, *acc_out;
     int bg0, nbg, t0, t1;
     int slots, sink_groups, win_groups;   // key groups (of 128) a row block has places for: sinks, and a ring for the window's
     uint32_t win_magic;                   // 2^32 / win_groups, rounded up
@@ -137,6 +139,7 @@ struct WideChunk {
 struct WidePlan {
     WideChunk chunk;
     int row_tiles, chunk_tiles, chunk_bgs;   // per (batch, key head); per chunk
+    int acc_places;
     size_t scratch_bytes, part_bytes, acc_bytes;
     size_t bytes() const { return scratch_bytes + part_bytes + acc_bytes; }
 };

@@ -30,3 +30,13 @@ def test_what_it_is_made_of(B, S, Hq, pattern, slots, chunk_tiles):
     n, stat = _bytes(B, S, Hq, 1, pattern)
     rest = n - stat - B * chunk_tiles * slots * 128 * 128 * 4
     assert rest > 0 and rest % (128 * 576 * 4) == 0 and rest < 0.5 * GIB
+
+
+@pytest.mark.parametrize("B,S,Hq,pattern,given_out", [
+    (1, 3000, 64, (0, 3000, 1), 2092756992),
+    (1, 8000, 64, (128, 4096, 1), 1858797568),
+    (1, 16384, 64, (1, 7, 128), 2209906688),
+])
+def test_sizes_that_callers_may_have_kept_are_enough(B, S, Hq, pattern, given_out):
+    """(given out while every group of keys had a place for sums between chunks of rows)"""
+    assert _bytes(B, S, Hq, 1, pattern)[0] <= given_out
